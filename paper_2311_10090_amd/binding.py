@@ -1,4 +1,5 @@
-"""Thin ctypes binding of libmpe.so (include/mpe.h).  Argument marshalling only.
+"""Thin binding of libmpe.so (include/mpe.h).  Argument marshalling only: the calls of a training or stepping
+loop (reset, step, rollout, rollout_ac, set_*) go through the native extension _mpe_call, the rest through ctypes.
 
 PyTorch is used for device memory and the current HIP stream; every step of the rollout
 runs inside the library's kernels.  There is no CPU fallback: if the library is missing
@@ -75,11 +76,12 @@ class MpeConfig:
 
 
 _lib = None
+_call = None
 
 
 def load_library():
     """Load libmpe.so built in-tree (python -m paper_2311_10090_amd.build).  Raises if absent."""
-    global _lib
+    global _lib, _call
     if _lib is not None:
         return _lib
     if not os.path.exists(LIB_PATH):
@@ -108,6 +110,8 @@ def load_library():
     for n in EXPORTS:
         if n != "mpe_last_error":
             getattr(lib, n).restype = C.c_int
+    from . import _mpe_call   # the hot calls' native host path (built beside libmpe.so, linked against it)
+    _call = _mpe_call
     _lib = lib
     return lib
 
@@ -139,9 +143,12 @@ class MpeEnv:
         self.cfg = cfg
         self.device = torch.device(device)
         self.h = C.c_void_p()
+        self._h = self._dev = 0
         with torch.cuda.device(self.device):
             cc = cfg.to_c()
             _check(self.lib.mpe_create(C.byref(cc), C.byref(self.h)))
+            self._h = self.h.value                       # the handle and its device as the native calls take them
+            self._dev = torch.cuda.current_device()
         self.E, self.N, self.R, self.L = cfg.num_envs, cfg.num_agents, cfg.num_runs, cfg.num_landmarks
         self.TE = self.E * self.R
         self.D = _check(self.lib.mpe_obs_dim(self.h))
@@ -153,6 +160,7 @@ class MpeEnv:
         if getattr(self, "h", None) is not None and self.h.value:
             self.lib.mpe_destroy(self.h)
             self.h = C.c_void_p()
+            self._h = 0
 
     def __del__(self):
         try:
@@ -174,32 +182,24 @@ class MpeEnv:
 
     # -- entry points
     def reset(self, seed: int, obs=None):
-        with torch.cuda.device(self.device):
-            _check(self.lib.mpe_reset(self.h, seed, _ptr(obs, torch.float32), _stream()))
+        _check(_call.reset(self._h, self._dev, seed, obs))
         return obs
 
     def step(self, actions, obs=None, reward=None, done=None):
-        with torch.cuda.device(self.device):
-            _check(self.lib.mpe_step(self.h, _ptr(actions, torch.uint8), _ptr(obs, torch.float32),
-                                     _ptr(reward, torch.float32), _ptr(done, torch.uint8), _stream()))
+        rc = _call.step(self._h, self._dev, actions, obs, reward, done)
+        if rc < 0:
+            _check(rc)
         return obs, reward, done
 
     def set_policy(self, W1=None, b1=None, W2=None, b2=None, W3=None, b3=None):
-        args = [_ptr(a, torch.float32) for a in (W1, b1, W2, b2, W3, b3)]
-        with torch.cuda.device(self.device):
-            _check(self.lib.mpe_set_policy(self.h, *args, _stream()))
+        _check(_call.set_policy(self._h, self._dev, W1, b1, W2, b2, W3, b3))
 
     def rollout(self, T: int, obs_traj=None, act_traj=None, rew_traj=None, done_traj=None, last_obs=None):
-        with torch.cuda.device(self.device):
-            _check(self.lib.mpe_rollout(self.h, T, _ptr(obs_traj, torch.float32), _ptr(act_traj, torch.uint8),
-                                        _ptr(rew_traj, torch.float32), _ptr(done_traj, torch.uint8),
-                                        _ptr(last_obs, torch.float32), _stream()))
+        _check(_call.rollout(self._h, self._dev, T, obs_traj, act_traj, rew_traj, done_traj, last_obs))
         return obs_traj, act_traj, rew_traj, done_traj, last_obs
 
     def set_critic(self, V1=None, c1=None, V2=None, c2=None, V3=None, c3=None):
-        args = [_ptr(a, torch.float32) for a in (V1, c1, V2, c2, V3, c3)]
-        with torch.cuda.device(self.device):
-            _check(self.lib.mpe_set_critic(self.h, *args, _stream()))
+        _check(_call.set_critic(self._h, self._dev, V1, c1, V2, c2, V3, c3))
 
     def empty_traj_ac(self, T):
         """obs, act, logp, value, rew, done, last_obs, last_value buffers of mpe_rollout_ac."""
@@ -209,26 +209,21 @@ class MpeEnv:
 
     def rollout_ac(self, T: int, obs_traj=None, act_traj=None, logp_traj=None, value_traj=None, rew_traj=None,
                    done_traj=None, last_obs=None, last_value=None):
-        with torch.cuda.device(self.device):
-            _check(self.lib.mpe_rollout_ac(self.h, T, _ptr(obs_traj, torch.float32), _ptr(act_traj, torch.uint8),
-                                           _ptr(logp_traj, torch.float32), _ptr(value_traj, torch.float32),
-                                           _ptr(rew_traj, torch.float32), _ptr(done_traj, torch.uint8),
-                                           _ptr(last_obs, torch.float32), _ptr(last_value, torch.float32), _stream()))
+        _check(_call.rollout_ac(self._h, self._dev, T, obs_traj, act_traj, logp_traj, value_traj, rew_traj, done_traj, last_obs,
+                                last_value))
         return obs_traj, act_traj, logp_traj, value_traj, rew_traj, done_traj, last_obs, last_value
 
     def set_gru_policy(self, *arrays):
         """We, be, Wi, bi, Wh, bh, Wf, bf, Wo, bo device tensors (or nothing to remove the policy)."""
         arrays = arrays if arrays else (None,) * 10
         assert len(arrays) == 10
-        with torch.cuda.device(self.device):
-            _check(self.lib.mpe_set_gru_policy(self.h, *[_ptr(a, torch.float32) for a in arrays], _stream()))
+        _check(_call.set_gru_policy(self._h, self._dev, *arrays))
 
     def set_gru_critic(self, *arrays):
         """Wc, bc, wv, bv device tensors (or nothing to remove the head)."""
         arrays = arrays if arrays else (None,) * 4
         assert len(arrays) == 4
-        with torch.cuda.device(self.device):
-            _check(self.lib.mpe_set_gru_critic(self.h, *[_ptr(a, torch.float32) for a in arrays], _stream()))
+        _check(_call.set_gru_critic(self._h, self._dev, *arrays))
 
     def get_hidden(self):
         h = torch.empty((self.TE, self.N, GRU_HIDDEN), dtype=torch.float32, device=self.device)
