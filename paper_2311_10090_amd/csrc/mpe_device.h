@@ -50,8 +50,12 @@ __device__ __forceinline__ uint4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
   for (int r = 0; r < 10; ++r) {
     const uint64_t p0 = uint64_t(0xD2511F53u) * c0;
     const uint64_t p1 = uint64_t(0xCD9E8D57u) * c2;
-    const uint32_t n0 = uint32_t(p1 >> 32) ^ c1 ^ k0;
-    const uint32_t n2 = uint32_t(p0 >> 32) ^ c3 ^ k1;
+    // From the second round on all three terms are per-lane values or keys: one three-input v_bitop3 (0x96 =
+    // a ^ b ^ c) instead of two v_xor.  In the first round c1 (step), c3 (tag) and the keys are uniform and
+    // their xor is scalar work.
+    const uint32_t h1 = uint32_t(p1 >> 32), h0 = uint32_t(p0 >> 32);
+    const uint32_t n0 = r == 0 ? h1 ^ (c1 ^ k0) : uint32_t(__builtin_amdgcn_bitop3_b32(h1, c1, k0, 0x96));
+    const uint32_t n2 = r == 0 ? h0 ^ (c3 ^ k1) : uint32_t(__builtin_amdgcn_bitop3_b32(h0, c3, k1, 0x96));
     c1 = uint32_t(p1);
     c3 = uint32_t(p0);
     c0 = n0;
