@@ -156,6 +156,16 @@ hipError_t launch_rollout_gru(bool tag, int N, int L, int G, const TagArgs& A, c
 // Critic head of the recurrent actor-critic: Wc [R][128][128], bc [R][128], wv [R][128], bv [R]
 hipError_t pack_gru_critic(PolicyBuffers& pb, int R, const float* Wc, const float* bc, const float* wv, const float* bv,
                            hipStream_t s);
+// Small batches and small runs (mpe_small.h): *taken = true and the rollout launched where that kernel is the faster
+// one for the batch, else nothing done.  A.tg is read by the predator-prey shapes only.
+// run_block: the envs that a run is a multiple of where the other kernels have a block shape for it.
+hipError_t launch_small_spread(int N, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed, hipStream_t s, bool* taken);
+hipError_t launch_small_spread_ac(int N, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed, const void* critic,
+                                  hipStream_t s, bool* taken);
+hipError_t launch_small_tag(int N, int L, int G, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed, hipStream_t s,
+                            bool* taken);
+hipError_t launch_small_tag_ac(int N, int L, int G, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed,
+                               const void* critic, hipStream_t s, bool* taken);
 void launch_fill_zero(float* p, size_t n, hipStream_t s);
 
 }  // namespace mpe

@@ -46,20 +46,16 @@ using SpreadNet = NetShape<6 * N, 4 * N + 2>;
 // Plain rollout: W1A + W2A and the biases of the policy (its W3A lives in registers).
 // Actor-critic rollout (AC): the whole packed image of the policy and of the critic (W1A, W2A,
 // W3A, biases each), a value per row, and one arrival counter per 64-env sync group.
-// ROWS = the block's agent rows, rounded up to whole wavefronts of RW rows (only 16-env blocks of
-// 3 agents have such padding rows: 48 -> 64; no env owns them and nothing of them leaves the block).
+// ROWS = the block's agent rows, rounded up to whole wavefronts of RW rows (7 and 9 agents in 32-env or 16-env
+// blocks have such padding rows; no env owns them and nothing of them leaves the block).
 template <int N, int EB, bool AC = false, bool BF = false, int RW = 64>
 struct SmemF32 {
   using P = PkT<BF, SpreadNet<N>::kWideIn, SpreadNet<N>::kSlices1>;
   static constexpr int D = 6 * N;
   static constexpr int ROWS = (EB * N + RW - 1) / RW * RW;
-  // LEAN (actor-critic in 16-env blocks, i.e. many small runs): W3A of both networks stays in global memory
-  // (re-read every step, 64 bytes per lane), so that two blocks fit a CU instead of one.
-  static constexpr bool LEAN = AC && EB == 16;
-  static constexpr size_t OFF_BIAS = (AC && !LEAN) ? P::OFF_BIAS : P::LDS_BYTES;
+  static constexpr size_t OFF_BIAS = AC ? P::OFF_BIAS : P::LDS_BYTES;
   static constexpr size_t OFF_CRITIC = OFF_BIAS + P::BIAS_BYTES;     // AC: the critic's packed image
-  static constexpr size_t CRITIC_BIAS = LEAN ? P::LDS_BYTES : P::OFF_BIAS;   // offset of its biases inside it
-  static constexpr size_t OFF_OBS = OFF_CRITIC + (AC ? (LEAN ? P::LDS_BYTES + P::BIAS_BYTES : P::RUN_BYTES) : 0);
+  static constexpr size_t OFF_OBS = OFF_CRITIC + (AC ? P::RUN_BYTES : 0);
   static constexpr size_t OBS = size_t(ROWS) * D * 4 + 64;           // + zeroed tail: layer 1 reads 16 cols
   static constexpr size_t OFF_NEWPOS = OFF_OBS + OBS;                // [2][ROWS] float2, by step parity
   static constexpr size_t OFF_VALUE = OFF_NEWPOS + size_t(2) * ROWS * 8;   // AC: [ROWS] float
@@ -74,8 +70,8 @@ struct SmemF32 {
 // recorded (paper Sec. 3.2: IPPO / MAPPO; App. G: two tanh layers of width 64).  A block is then
 // EB / 64 independent 64-env sync groups that share the two staged networks.
 //
-// RW = rows per wavefront.  64: one lane per row.  32 (64-env blocks only, for batches that leave CUs
-// empty): twice the wavefronts, each with ONE pair of 16-row tiles; lanes 32..63 are exact clones of
+// RW = rows per wavefront.  64: one lane per row.  32 (blocks of one sync group, for batches that leave SIMDs
+// empty and for runs of 32 envs): twice the wavefronts, each with ONE pair of 16-row tiles; lanes 32..63 are exact clones of
 // lanes 0..31 (same row, same inputs, same arithmetic, so their LDS writes repeat the same values)
 // that store nothing to global memory.  The step latency of a block, which is all that matters when
 // every block has a CU to itself, is then one pair of tiles plus the env step instead of two pairs.
@@ -97,7 +93,7 @@ __global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_pol
   float* tile = reinterpret_cast<float*>(smem + M::OFF_OBS);
   float2* newpos = reinterpret_cast<float2*>(smem + M::OFF_NEWPOS);
   const uint8_t* csm = smem + M::OFF_CRITIC;                                         // AC only
-  const float* cbias = reinterpret_cast<const float*>(smem + M::OFF_CRITIC + M::CRITIC_BIAS);
+  const float* cbias = reinterpret_cast<const float*>(smem + M::OFF_CRITIC + P::OFF_BIAS);
   float* values = reinterpret_cast<float*>(smem + M::OFF_VALUE);
 
   // Wavefront -> rows.  With several sync groups per block (EB > 64) the N wavefronts of group g are
@@ -137,9 +133,6 @@ __global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_pol
   const uint8_t* run_weights = packed + (per_run_weights ? size_t(uint32_t(g0) / A.E) * P::RUN_BYTES : 0);
   [[maybe_unused]] const uint8_t* critic_weights =
       AC ? packed_critic + (per_run_weights ? size_t(uint32_t(g0) / A.E) * P::RUN_BYTES : 0) : nullptr;
-  // where the layer-3 operands are re-read from in the actor-critic rollout
-  [[maybe_unused]] const uint8_t* w3_policy = M::LEAN ? run_weights : smem;
-  [[maybe_unused]] const uint8_t* w3_critic = M::LEAN ? critic_weights : smem + M::OFF_CRITIC;
   // A operands of layer 3 from a packed image (global memory or LDS)
   auto load_w3 = [&](const uint8_t* image) {
     W3Terms w;
@@ -162,23 +155,7 @@ __global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_pol
     // the packed image is W1A, W2A, W3A, biases; plain rollouts skip W3A (it is in registers)
     const uint4* src = reinterpret_cast<const uint4*>(run_weights);
     uint4* dst = reinterpret_cast<uint4*>(wsm);
-    if constexpr (M::LEAN) {
-      // W1A + W2A and the biases of both networks
-      const uint4* csrc = reinterpret_cast<const uint4*>(critic_weights);
-      uint4* cdst = reinterpret_cast<uint4*>(smem + M::OFF_CRITIC);
-      for (int k = threadIdx.x; k < int(P::LDS_BYTES / 16); k += THREADS) {
-        dst[k] = src[k];
-        cdst[k] = csrc[k];
-      }
-      const uint4* bsrc = reinterpret_cast<const uint4*>(run_weights + P::OFF_BIAS);
-      const uint4* cbsrc = reinterpret_cast<const uint4*>(critic_weights + P::OFF_BIAS);
-      uint4* bdst = reinterpret_cast<uint4*>(bias);
-      uint4* cbdst = reinterpret_cast<uint4*>(smem + M::OFF_CRITIC + M::CRITIC_BIAS);
-      for (int k = threadIdx.x; k < int(P::BIAS_BYTES / 16); k += THREADS) {
-        bdst[k] = bsrc[k];
-        cbdst[k] = cbsrc[k];
-      }
-    } else if constexpr (AC) {
+    if constexpr (AC) {
       for (int k = threadIdx.x; k < int(P::RUN_BYTES / 16); k += THREADS) dst[k] = src[k];
       const uint4* csrc = reinterpret_cast<const uint4*>(critic_weights);
       uint4* cdst = reinterpret_cast<uint4*>(smem + M::OFF_CRITIC);
@@ -258,7 +235,7 @@ __global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_pol
     for (int pr = 0; pr < RW / 32; ++pr) {
       float* rows = tile + (wave * RW + pr * 32) * D;
       float* vals = values + wave * RW + pr * 32;
-      const W3Terms wc = load_w3(w3_critic);
+      const W3Terms wc = load_w3(csm);
       if constexpr (BF) policy_pair_bf<SpreadNet<N>, true>(csm, cbias, wc, rows, rows + 16 * D, lane, vals, vals + 16);
       else policy_pair<SpreadNet<N>, true>(csm, cbias, wc, rows, rows + 16 * D, lane, vals, vals + 16);
     }
@@ -283,7 +260,7 @@ __global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_pol
 #pragma unroll 1
     for (int pr = 0; pr < RW / 32; ++pr) {
       float* rows = tile + (wave * RW + pr * 32) * D;
-      if constexpr (AC) w3 = load_w3(w3_policy);
+      if constexpr (AC) w3 = load_w3(wsm);
       if constexpr (BF) policy_pair_bf<SpreadNet<N>>(wsm, bias, w3, rows, rows + 16 * D, lane);
       else policy_pair<SpreadNet<N>>(wsm, bias, w3, rows, rows + 16 * D, lane);
     }
@@ -691,33 +668,23 @@ hipError_t pack_impl(PolicyBuffers& pb, int R, const float* W1, const float* b1,
   return hipGetLastError();
 }
 
-// Small batches: when every block has a CU (nearly) to itself, the time of a rollout is the step latency of
-// one block (one wavefront per SIMD running its matrix and vector instructions back to back), so the rows
-// are spread over more wavefronts of 32 rows = one pair of 16-row tiles each, one wavefront per SIMD where
-// that works out.  Measured per 128-step rollout, against N wavefronts of 64 rows:
-//   64 envs x 1 or 2 agents = 2 or 4 wavefronts: 0.48 / 0.50 ms against 0.76 / 0.77 ms up to one block per
-//     CU, still 1.07x / 1.18x at three blocks per CU (the most that are resident);
-//   32 envs x 3 agents = 3 wavefronts, while such blocks have a CU each (8,192 envs): 0.51 against 0.81 ms
-//     (actor-critic 0.85 against 1.51 ms);
-//   64 envs x 3 agents = 6 wavefronts, two SIMDs with two: 0.73 against 0.82 ms up to one block per CU,
-//     slower beyond.
-enum SmallShape { kRegular = 0, kHalf64 = 1, kHalf32 = 2 };
-template <int N>
-SmallShape small_shape(const RolloutArgs& A) {
-  const uint32_t cus = compute_units();
-  if (N == 3 && (A.TE + 31) / 32 <= cus) return kHalf32;
-  if ((A.TE + 63) / 64 <= (N == 3 ? cus : 4 * cus)) return kHalf64;
-  return kRegular;
-}
-
+// Batches of 1 or 2 agents that are too large for the small-batch kernel (mpe_small.h) and still leave SIMDs short of
+// wavefronts: the rows of a 64-env block spread over wavefronts of 32 rows = one pair of 16-row tiles each, one per
+// SIMD.  Measured per 128-step rollout, against N wavefronts of 64 rows: 0.48 / 0.50 ms against 0.76 / 0.77 ms up to
+// one block per CU, still 1.07x / 1.18x at three blocks per CU (the most that are resident).
 template <int N, bool PER_AGENT, bool AC, bool BF>
 hipError_t launch_blocks64(const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s, const void* critic) {
-  const SmallShape shape = small_shape<N>(A);
-  if constexpr (N == 3) {
-    if (shape == kHalf32) return rollout_impl<N, 32, 1, PER_AGENT, AC, BF, 32>(A, pb, s, critic);
+  if constexpr (N <= 2) {
+    if ((A.TE + 63) / 64 <= 4 * compute_units()) return rollout_impl<N, 64, 1, PER_AGENT, AC, BF, 32>(A, pb, s, critic);
   }
-  if (shape == kHalf64) return rollout_impl<N, 64, 1, PER_AGENT, AC, BF, 32>(A, pb, s, critic);
   return rollout_impl<N, 64, 3, PER_AGENT, AC, BF>(A, pb, s, critic);
+}
+
+// The arguments in the form that the small-batch kernel takes for both scenarios.
+TagArgs small_args(const RolloutArgs& A) {
+  TagArgs t{};
+  t.r = A;
+  return t;
 }
 
 // Envs per block.  64 (N wavefronts, one block barrier per step) is the general shape: three
@@ -739,8 +706,17 @@ hipError_t launch_n(const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s
       *why = "with several runs and 4 or more agents, num_envs per run must be a multiple of 64 (of 32 with 8 to 10 agents)";
       return hipSuccess;
     }
+    if (bool taken = false; true) {
+      const hipError_t e = launch_small_spread(N, BF, small_args(A), 1, pb.packed, s, &taken);
+      if (taken || e != hipSuccess) return e;
+    }
     return per_agent ? rollout_impl<N, kEnvs, 1, true, false, false>(A, pb, s) : rollout_impl<N, kEnvs, 1, false, false, false>(A, pb, s);
   } else {
+  if (one_run || A.E % 16 == 0) {
+    bool taken = false;
+    const hipError_t e = launch_small_spread(N, BF, small_args(A), 32, pb.packed, s, &taken);
+    if (taken || e != hipSuccess) return e;
+  }
   if (one_run && A.TE / 256 >= compute_units())
     return per_agent ? rollout_impl<N, 256, 3, true, false, BF>(A, pb, s) : rollout_impl<N, 256, 3, false, false, BF>(A, pb, s);
   if constexpr (!BF && N >= 2) {
@@ -757,11 +733,9 @@ hipError_t launch_n(const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s
   if (one_run || A.E % 64 == 0)
     return per_agent ? launch_blocks64<N, true, false, BF>(A, pb, s, nullptr)
                      : launch_blocks64<N, false, false, BF>(A, pb, s, nullptr);
-  // small runs (the paper's IPPO setting is 16 envs per run): blocks of 32 or 16 envs inside a run
+  // runs of 32 envs; smaller ones (the paper's IPPO setting is 16 envs per run) are the small-batch kernel's
   if (A.E % 32 == 0)
     return per_agent ? rollout_impl<N, 32, 1, true, false, BF, 32>(A, pb, s) : rollout_impl<N, 32, 1, false, false, BF, 32>(A, pb, s);
-  if (A.E % 16 == 0)
-    return per_agent ? rollout_impl<N, 16, 1, true, false, BF, 32>(A, pb, s) : rollout_impl<N, 16, 1, false, false, BF, 32>(A, pb, s);
   *why = "with several runs, num_envs per run must be a multiple of 16";
   return hipSuccess;
   }
@@ -784,21 +758,24 @@ hipError_t launch_ac_n(const RolloutArgs& A, const PolicyBuffers& pb, const Poli
       *why = "with several runs and 4 or more agents, num_envs per run must be a multiple of 64 (of 32 with 7 agents, of 16 with 8 to 10)";
       return hipSuccess;
     }
+    if (bool taken = false; true) {
+      const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), 1, pb.packed, critic.packed, s, &taken);
+      if (taken || e != hipSuccess) return e;
+    }
     return per_agent ? rollout_impl<N, kEnvs, 1, true, true, false>(A, pb, s, critic.packed)
                      : rollout_impl<N, kEnvs, 1, false, true, false>(A, pb, s, critic.packed);
   } else {
+  if (one_run || A.E % 16 == 0) {
+    bool taken = false;
+    const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), 64, pb.packed, critic.packed, s, &taken);
+    if (taken || e != hipSuccess) return e;
+  }
   if (one_run ? A.TE / 256 >= compute_units() / 2 : A.E % 256 == 0)
     return per_agent ? rollout_impl<N, 256, 3, true, true, BF>(A, pb, s, critic.packed)
                      : rollout_impl<N, 256, 3, false, true, BF>(A, pb, s, critic.packed);
   if (one_run || A.E % 64 == 0)
     return per_agent ? launch_blocks64<N, true, true, BF>(A, pb, s, critic.packed)
                      : launch_blocks64<N, false, true, BF>(A, pb, s, critic.packed);
-  if (A.E % 32 == 0)
-    return per_agent ? rollout_impl<N, 32, 1, true, true, BF, 32>(A, pb, s, critic.packed)
-                     : rollout_impl<N, 32, 1, false, true, BF, 32>(A, pb, s, critic.packed);
-  if (A.E % 16 == 0)
-    return per_agent ? rollout_impl<N, 16, 1, true, true, BF, 32>(A, pb, s, critic.packed)
-                     : rollout_impl<N, 16, 1, false, true, BF, 32>(A, pb, s, critic.packed);
   *why = "with several runs, num_envs per run must be a multiple of 16";
   return hipSuccess;
   }

@@ -24,11 +24,11 @@ constexpr bool mode_is_bf(int mode) { return mode == kPolicyBf || mode == kPolic
 
 // EB = envs per block.  Plain rollouts: 64.  Actor-critic: both packed images (79 KB) are staged per block,
 // so a block is 8 wavefronts where the shape allows it (wavefront-local shapes need no block barrier).
-// ROWS = the block's agent rows, rounded up to whole wavefronts of RW rows (only 16-env blocks of 3 agents
-// have such padding rows: 48 -> 64; no env owns them and nothing of them leaves the block).
+// ROWS = the block's agent rows: whole wavefronts of RW rows.
 template <typename S, int MODE, int EB = 64, int RW = 64>
 struct TagSmem {
-  static constexpr int ROWS = (EB * S::N + RW - 1) / RW * RW;
+  static constexpr int ROWS = EB * S::N;
+  static_assert(ROWS % RW == 0, "whole wavefronts");
   static constexpr bool kAc = mode_is_ac(MODE);
   static constexpr bool kHasPolicy = MODE == kPolicy || MODE == kPolicyBf || kAc;
   using P = PkT<mode_is_bf(MODE), (S::D > 16)>;
@@ -100,7 +100,7 @@ struct TagOccupancy {
 };
 
 template <typename S, int MODE, int EB = 64, int RW = 64>
-__global__ __launch_bounds__((EB * S::N + RW - 1) / RW * 64, (TagOccupancy<S, MODE, EB, RW>::kWavesPerSimd)) void tag_rollout_kernel(
+__global__ __launch_bounds__(EB * S::N / RW * 64, (TagOccupancy<S, MODE, EB, RW>::kWavesPerSimd)) void tag_rollout_kernel(
     TagArgs TA, const uint8_t* __restrict__ packed, const uint8_t* __restrict__ packed_critic, int per_run_weights,
     uint32_t groups, uint32_t groups_per_xcd) {
   using M = TagSmem<S, MODE, EB, RW>;
@@ -109,7 +109,6 @@ __global__ __launch_bounds__((EB * S::N + RW - 1) / RW * 64, (TagOccupancy<S, MO
   static_assert(RW == 64 || (RW == 32 && (!S::kWaveLocal || 32 % S::N == 0)), "rows per wavefront");
   using Net = NetShape<S::D, S::D <= 32 ? S::D : 32>;
   constexpr int N = S::N, L = S::L, G = S::G, NA = S::A, D = S::D, ROWS = M::ROWS, THREADS = ROWS * (64 / RW);
-  constexpr bool kPadded = ROWS != EB * N;
   static_assert(THREADS % 64 == 0, "block must be whole wavefronts");
   const RolloutArgs& A = TA.r;
   const TagPhys& tg = TA.tg;
@@ -120,16 +119,14 @@ __global__ __launch_bounds__((EB * S::N + RW - 1) / RW * 64, (TagOccupancy<S, MO
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int tid = wave * RW + (lane & (RW - 1));     // this lane's row
-  const int el_row = tid / N, i = tid - el_row * N;  // env within block, agent
-  const bool in_block = !kPadded || el_row < EB;     // false for padding rows: they shadow env 0 of the block
-  const int el = in_block ? el_row : 0;
+  const int el = tid / N, i = tid - el * N;          // env within block, agent
   const size_t TE = A.TE;
   // block b runs on XCD b % 8: give each XCD one contiguous range of env groups
   const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
   if (grp >= groups) return;  // whole block, before any barrier
   const size_t g0 = size_t(grp) * EB;
   const size_t g = g0 + el;
-  const bool in_range = in_block && g < TE;
+  const bool in_range = g < TE;
   const bool valid = in_range && lane < RW;          // the lane that stores this row's outputs
   const uint32_t gc = in_range ? uint32_t(g) : uint32_t(g0);
   const uint32_t run = gc / A.E;
@@ -423,25 +420,27 @@ hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void
     constexpr int kAcEnvs = S::kWaveLocal ? 512 / S::N : (S::N <= 6 ? 64 : 32);
     const bool ac = mode_is_ac(mode);
     const uint32_t per_block = ac ? uint32_t(kAcEnvs) : 64u;
-    if (A.r.TE != A.r.E && A.r.E % per_block != 0) {
-      // small runs (the paper's IPPO setting is 16 envs per run): blocks of 16 envs inside a run
-      if (A.r.E % 16 == 0)
-        return ac ? tag_policy_impl<S, 16, 32, true>(mode, A, packed, packed_critic, s)
-                  : tag_policy_impl<S, 16, 32, false>(mode, A, packed, nullptr, s);
+    if (A.r.TE == A.r.E || A.r.E % 16 == 0) {
+      bool taken = false;
+      const hipError_t e = ac ? launch_small_tag_ac(S::N, S::L, S::G, mode_is_bf(mode), A, per_block, packed, packed_critic, s, &taken)
+                              : launch_small_tag(S::N, S::L, S::G, mode_is_bf(mode), A, per_block, packed, s, &taken);
+      if (taken || e != hipSuccess) return e;
+    }
+    if (A.r.TE != A.r.E && A.r.E % per_block != 0) {   // (multiples of 16: launched above)
       *why = "with several runs, num_envs per run must be a multiple of 16";
       return hipSuccess;
     }
-    if constexpr (S::D <= 16) {
-      // Small batches (every block has a CU to itself, so the step latency of one block is the time): the
-      // rows spread over wavefronts of 32 rows, one per SIMD: 64 envs x 2 agents, 32 envs x 3 or 4 agents.
-      // Measured per 128-step rollout up to 8,192 envs of 4 agents: 0.54 against 0.84 ms, bf16 0.36 against
-      // 0.59 ms, actor-critic 0.88 against 2.41 ms; two such blocks per CU still win with 2 agents (1.55x)
-      // and for the actor-critic rollout of 4 agents (1.4x).
+    if constexpr (S::N == 2 || S::N == 4) {
+      // Batches just beyond the small-batch kernel's, while such blocks leave SIMDs short of wavefronts: the rows of
+      // 64 envs x 2 agents or 32 envs x 4 agents over wavefronts of 32 rows, one per SIMD, up to two blocks per CU
+      // (1.55x with 2 agents, 1.4x for the actor-critic rollout of 4 agents; one of its plain rollout is no match
+      // for the small-batch kernel).
       constexpr int kSmallEnvs = S::N == 2 ? 64 : 32;
-      const uint32_t per_cu = (S::N == 2 || (S::N == 4 && ac)) ? 2u : 1u;
-      if ((A.r.TE + kSmallEnvs - 1) / kSmallEnvs <= per_cu * compute_units())
-        return ac ? tag_policy_impl<S, kSmallEnvs, 32, true>(mode, A, packed, packed_critic, s)
-                  : tag_policy_impl<S, kSmallEnvs, 32, false>(mode, A, packed, nullptr, s);
+      const bool fits = (A.r.TE + kSmallEnvs - 1) / kSmallEnvs <= 2 * compute_units();
+      if (ac && fits) return tag_policy_impl<S, kSmallEnvs, 32, true>(mode, A, packed, packed_critic, s);
+      if constexpr (S::N == 2) {
+        if (fits) return tag_policy_impl<S, kSmallEnvs, 32, false>(mode, A, packed, nullptr, s);
+      }
     }
     if (ac) return tag_policy_impl<S, kAcEnvs, 64, true>(mode, A, packed, packed_critic, s);
     return tag_policy_impl<S, 64, 64, false>(mode, A, packed, nullptr, s);
