@@ -277,10 +277,7 @@ int mpe_step(mpe_env* e, const uint8_t* actions, float* obs, float* reward, uint
     A.r.fault = e->fault_dev;
     A.tg = e->tg;
     A.actions_in = actions;
-    const char* why = nullptr;
-    hipError_t err = launch_tag_rollout(e->N, e->L, e->G, 0, A, nullptr, nullptr, static_cast<hipStream_t>(stream), &why);
-    if (why) return fail(MPE_EINVAL, "mpe_step: %s", why);
-    if (err != hipSuccess) return fail(MPE_EHIP, "mpe_step: %s", hipGetErrorString(err));
+    launch_env_agents(true, e->N, e->L, e->G, A, static_cast<hipStream_t>(stream));
   } else {
     launch_step(e->N, e->st, e->ph, e->TE, e->E, e->seed, e->abs_step, actions, obs, reward, done,
                 static_cast<hipStream_t>(stream));

@@ -74,7 +74,7 @@ struct TagPhys {
 struct TagArgs {
   RolloutArgs r;                 // state, sizes, seed, step, outputs (r.ph is unused)
   TagPhys tg;
-  const uint8_t* actions_in;     // [TE][N], single step with given actions only
+  const uint8_t* actions_in;     // [TE][N], single step with given actions only (launch_env_agents)
 };
 
 // (N, L, G) = agents, landmarks, good agents
@@ -82,8 +82,7 @@ bool tag_supported(int N, int L, int G);
 bool tag_policy_supported(int N, int L, int G, int H, int weight_dtype);
 void launch_tag_reset(int N, int L, int G, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
                       hipStream_t s);
-// mode 0: one step under A.actions_in (r.T must be 1; obs after the step -> r.last_obs, reward ->
-// r.rew_traj, done -> r.done_traj); mode 1: uniform random actions; mode 2: the packed fp32 policy;
+// mode 1: uniform random actions; mode 2: the packed fp32 policy;
 // mode 3: the packed bf16 policy; mode 4 / 5: the packed fp32 / bf16 policy and critic (actor-critic outputs in r)
 hipError_t launch_tag_rollout(int N, int L, int G, int mode, const TagArgs& A, const void* packed,
                               const void* packed_critic, hipStream_t s, const char** why);
@@ -128,7 +127,6 @@ hipError_t launch_rollout_ac_wide(int N, int H, const RolloutArgs& A, const Poli
                                   const PolicyBuffers& critic, hipStream_t s, const char** why);
 hipError_t launch_rollout_policy_wide(int N, int H, const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s,
                                       const char** why);
-bool uniform_wide_supported(int N);                      // env-only rollout with the wide kernel's mapping
 hipError_t launch_rollout_uniform_wide(int N, const RolloutArgs& A, hipStream_t s);
 bool f32_supported(int N, int H, bool bf16);             // headline kernel (H = 64; N <= 3, with fp32 weights N <= 10)
 size_t packed_run_bytes_f32(int N, bool bf16);
@@ -156,6 +154,11 @@ hipError_t launch_rollout_gru(bool tag, int N, int L, int G, const TagArgs& A, c
 // Critic head of the recurrent actor-critic: Wc [R][128][128], bc [R][128], wv [R][128], bv [R]
 hipError_t pack_gru_critic(PolicyBuffers& pb, int R, const float* Wc, const float* bc, const float* wv, const float* bv,
                            hipStream_t s);
+// One lane per agent (mpe_env_agents.hip), both scenarios: one step under A.actions_in (reward, done and obs after the
+// step through A.r.rew_traj, done_traj, last_obs), or, with A.actions_in null, a rollout with uniform actions.
+// Whether its rollout is the faster one for this batch.
+bool env_agents_faster(bool tag, int N, uint32_t TE);
+void launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s);
 // Small batches and small runs (mpe_small.h): *taken = true and the rollout launched where that kernel is the faster
 // one for the batch, else nothing done.  A.tg is read by the predator-prey shapes only.
 // run_block: the envs that a run is a multiple of where the other kernels have a block shape for it.

@@ -713,9 +713,8 @@ hipError_t rollout_impl(const RolloutArgs& A, const PolicyBuffers& pb, hipStream
 #define MPE_WIDE_POLICY_CASES(X) \
   X(10, 128, 64, 3) X(10, 64, 64, 3) X(9, 128, 64, 3) X(9, 64, 64, 3) X(8, 128, 32, 3) X(8, 64, 32, 3) X(7, 128, 64, 3) \
   X(7, 64, 64, 3) X(6, 128, 64, 3) X(6, 64, 64, 3) X(5, 128, 64, 3) X(5, 64, 64, 3) X(4, 128, 64, 3) X(4, 64, 64, 3)
-// Env-only rollouts that use this kernel's lane-per-agent mapping: 4 and more agents (measured 4.6-5.3 TB/s
-// of trajectory writes against 1.8-4.2 TB/s of the env-per-lane kernel, whose lanes each own 6 N^2 floats
-// per step); the width is not used there.
+// Env-only rollouts of large batches that use this kernel's lane-per-agent mapping: 4 and more agents (4.6-5.3 TB/s
+// of trajectory writes; smaller batches: mpe_env_agents.hip); the width is not used there.
 #define MPE_WIDE_CASES(X) \
   X(10, 128, 64, 3) X(9, 64, 64, 3) X(8, 64, 32, 3) X(7, 64, 64, 3) X(6, 64, 64, 3) X(5, 64, 64, 3) X(4, 64, 64, 3)
 
@@ -742,14 +741,7 @@ hipError_t pack_policy_wide(PolicyBuffers& pb, int N, int H, int R, const float*
   return hipErrorInvalidValue;
 }
 
-// Env-only rollout (seeded uniform actions) with the lane-per-agent mapping of the wide kernel.
-bool uniform_wide_supported(int N) {
-#define X(N_, H_, EB_, MW_) if (N == N_) return true;
-  MPE_WIDE_CASES(X)
-#undef X
-  return false;
-}
-
+// Env-only rollout (seeded uniform actions) of large batches with the lane-per-agent mapping of the wide kernel.
 hipError_t launch_rollout_uniform_wide(int N, const RolloutArgs& A, hipStream_t s) {
   const PolicyBuffers none{};
 #define X(N_, H_, EB_, MW_)                                                                      \

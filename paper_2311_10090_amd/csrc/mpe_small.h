@@ -19,26 +19,19 @@
 #pragma once
 
 #include "mpe_mlp64.h"
-#include "mpe_tag_device.h"
+#include "mpe_scenario.h"
 
 namespace mpe {
 
 namespace {
 
-// The scenario of an instance: simple spread with N agents, or a predator-prey shape.
 template <int N_>
-struct SmallSpread {
-  static constexpr int N = N_, D = 6 * N_, L = N_;
-  static constexpr bool kTag = false;
-  using Shape = TagShape<2, 1, 1>;             // unused
+struct SmallSpread : SpreadScn<N_> {
   using Net = NetShape<6 * N_, 4 * N_ + 2>;
 };
 template <int N_, int L_, int G_>
-struct SmallTag {
-  using Shape = TagShape<N_, L_, G_>;
-  static constexpr int N = N_, D = Shape::D, L = L_;
-  static constexpr bool kTag = true;
-  using Net = NetShape<D, D>;
+struct SmallTag : TagScn<N_, L_, G_> {
+  using Net = NetShape<TagScn<N_, L_, G_>::D, TagScn<N_, L_, G_>::D>;
 };
 
 // ------------------------------------------------------------------------------ network of one 16-row tile
@@ -347,19 +340,7 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
       float o[OW];
 #pragma unroll
       for (int c = 0; c < OW; ++c) o[c] = 0.0f;
-      if constexpr (kTag) {
-        tag_obs_regs<TS>(o, i, px, py, vx, vy, qx, qy, lx, ly, gvx, gvy);
-      } else {
-        o[0] = vx; o[1] = vy; o[2] = px; o[3] = py;
-#pragma unroll
-        for (int l = 0; l < N; ++l) { o[4 + 2 * l] = lx[l] - px; o[5 + 2 * l] = ly[l] - py; }
-#pragma unroll
-        for (int k = 0; k < N - 1; ++k) {
-          const bool up = k >= i;
-          o[4 + 2 * N + 2 * k] = (up ? qx[k + 1] : qx[k]) - px;
-          o[5 + 2 * N + 2 * k] = (up ? qy[k + 1] : qy[k]) - py;
-        }
-      }
+      agent_obs<Scn>(o, i, px, py, vx, vy, qx, qy, lx, ly, gvx, gvy);
       float* rows = obs_tile + size_t(parity) * B * D;
       if (gq == 0) {
         float2* dst = reinterpret_cast<float2*>(rows + row * D);

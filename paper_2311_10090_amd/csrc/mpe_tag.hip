@@ -1,5 +1,5 @@
 // Predator-prey ("simple tag") scenario of the MPE family (paper App. B.7: every scenario of the
-// family is implemented; Sec. 3.1 "MPE"): reset, single step, and the persistent T-step rollout
+// family is implemented; Sec. 3.1 "MPE"): reset and the persistent T-step rollout
 // with uniform actions or with the fused policy, fp32 (three-term fp16 operand split) or bf16 (App. G: two tanh layers of width 64).
 //
 // Mapping: one lane per agent row, a block is 64 envs = N wavefronts (as in the fused simple-spread
@@ -18,7 +18,7 @@ namespace {
 
 // kPolicy / kPolicyBf: fp32 (split-operand) / bf16 policy.  kPolicyAc / kPolicyAcBf: the policy plus a critic
 // of the same shape with one output: log-probability of the sampled action and value per agent and step.
-enum TagMode : int { kGiven = 0, kUniform = 1, kPolicy = 2, kPolicyBf = 3, kPolicyAc = 4, kPolicyAcBf = 5 };
+enum TagMode : int { kUniform = 1, kPolicy = 2, kPolicyBf = 3, kPolicyAc = 4, kPolicyAcBf = 5 };
 constexpr bool mode_is_ac(int mode) { return mode == kPolicyAc || mode == kPolicyAcBf; }
 constexpr bool mode_is_bf(int mode) { return mode == kPolicyBf || mode == kPolicyAcBf; }
 
@@ -256,10 +256,7 @@ __global__ __launch_bounds__(EB * S::N / RW * 64, (TagOccupancy<S, MODE, EB, RW>
     }
     // ---- action
     uint32_t act;
-    if constexpr (MODE == kGiven) {
-      const uint32_t v = in_range ? TA.actions_in[row_off] : 0u;
-      act = v < uint32_t(kNumActions) ? v : 0u;
-    } else if constexpr (MODE == kUniform) {
+    if constexpr (MODE == kUniform) {
       act = word_to_action(philox4x32_10(env, step, uint32_t(i), kTagUniformAction, A.seed, run).x);
     } else {
       const float* bias = reinterpret_cast<const float*>(smem + M::OFF_BIAS);
@@ -412,8 +409,13 @@ hipError_t tag_policy_impl(int mode, const TagArgs& A, const void* packed, const
 template <typename S>
 hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void* packed_critic, hipStream_t s,
                       const char** why) {
-  if (mode == kGiven) return tag_rollout_impl<S, kGiven>(A, nullptr, nullptr, s);
-  if (mode == kUniform) return tag_rollout_impl<S, kUniform>(A, nullptr, nullptr, s);
+  if (mode == kUniform) {
+    if constexpr (S::N != 4 && S::N != 10) {
+      if (!env_agents_faster(true, S::N, A.r.TE)) return tag_rollout_impl<S, kUniform>(A, nullptr, nullptr, s);
+    }
+    launch_env_agents(true, S::N, S::L, S::G, A, s);
+    return hipGetLastError();
+  }
   if constexpr (S::D <= 32) {
     // actor-critic: both images are staged per block; 8 wavefronts share them where wavefronts never exchange
     // data, otherwise the largest of 64 and 32 envs whose rows fit beside the two images
