@@ -159,6 +159,9 @@ hipError_t pack_gru_critic(PolicyBuffers& pb, int R, const float* Wc, const floa
 // Whether its rollout is the faster one for this batch.
 bool env_agents_faster(bool tag, int N, uint32_t TE);
 void launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s);
+// Full batches, independent wavefronts (mpe_waves.h).  critic: the packed critic of the actor-critic rollout, or null.
+hipError_t launch_waves_spread(int N, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s);
+hipError_t launch_waves_tag(int N, int L, int G, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s);
 // Small batches and small runs (mpe_small.h): *taken = true and the rollout launched where that kernel is the faster
 // one for the batch, else nothing done.  A.tg is read by the predator-prey shapes only.
 // run_block: the envs that a run is a multiple of where the other kernels have a block shape for it.

@@ -636,15 +636,13 @@ __device__ __forceinline__ bf16x8 tanh_pack_bf(const f32x4& a0, const f32x4& a1)
   return __builtin_bit_cast(bf16x8, p);
 }
 
-// bf16 policy forward of two 16-row tiles X and Y (same interface as policy_pair): weights and
-// layer inputs bf16, fp32 accumulation and tanh.  Logits of row j go to cols 0..4 of that row.
-template <typename S, bool VALUE = false>
-__device__ __forceinline__ void policy_pair_bf(const uint8_t* __restrict__ wsm, const float* __restrict__ bias,
-                                               const W3Terms& w3, float* __restrict__ rowsX,
-                                               float* __restrict__ rowsY, int lane,
-                                               float* __restrict__ valX = nullptr, float* __restrict__ valY = nullptr) {
-  constexpr int D = S::D;
-  const int j = lane & 15, gq = lane >> 4;
+// bf16 network of two 16-row tiles, registers in and out (as policy_core): weights and layer inputs bf16, fp32
+// accumulation and tanh.
+template <typename S>
+__device__ __forceinline__ void policy_core_bf(const uint8_t* __restrict__ wsm, const float* __restrict__ bias,
+                                               const W3Terms& w3, const float (&vx)[S::kSlices1][8],
+                                               const float (&vy)[S::kSlices1][8], f32x4& zX, f32x4& zY, int lane) {
+  const int gq = lane >> 4;
   __builtin_amdgcn_s_setprio(2);   // see policy_core
   {
     uint32_t zero = 0;   // see policy_pair: keeps the LDS weight reads inside the step loop
@@ -661,14 +659,11 @@ __device__ __forceinline__ void policy_pair_bf(const uint8_t* __restrict__ wsm, 
   bf16x8 bx[KS1], by[KS1];
 #pragma unroll
   for (int s = 0; s < KS1; ++s) {
-    float vx[8], vy[8];
-    load_row_inputs<S>(rowsX, j, gq, s, vx);
-    load_row_inputs<S>(rowsY, j, gq, s, vy);
     u32x4 px, py;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      px[q] = pack_bf16_rne(vx[2 * q], vx[2 * q + 1]);
-      py[q] = pack_bf16_rne(vy[2 * q], vy[2 * q + 1]);
+      px[q] = pack_bf16_rne(vx[s][2 * q], vx[s][2 * q + 1]);
+      py[q] = pack_bf16_rne(vy[s][2 * q], vy[s][2 * q + 1]);
     }
     bx[s] = __builtin_bit_cast(bf16x8, px);
     by[s] = __builtin_bit_cast(bf16x8, py);
@@ -708,14 +703,32 @@ __device__ __forceinline__ void policy_pair_bf(const uint8_t* __restrict__ wsm, 
       accY[m] = MPE_MFMA_BF(a, hy[s], accY[m]);
     }
   }
-  f32x4 zX = *reinterpret_cast<const f32x4*>(bias + 2 * kH + 4 * gq);
-  f32x4 zY = zX;
+  zX = *reinterpret_cast<const f32x4*>(bias + 2 * kH + 4 * gq);
+  zY = zX;
 #pragma unroll
   for (int s = 0; s < 2; ++s) {
     zX = MPE_MFMA_BF(w3.s[s].h, tanh_pack_bf(accX[2 * s], accX[2 * s + 1]), zX);
     zY = MPE_MFMA_BF(w3.s[s].h, tanh_pack_bf(accY[2 * s], accY[2 * s + 1]), zY);
   }
   __builtin_amdgcn_s_setprio(0);
+}
+
+// The same on rows in LDS (interface of policy_pair): logits of row j go to cols 0..4 of that row.
+template <typename S, bool VALUE = false>
+__device__ __forceinline__ void policy_pair_bf(const uint8_t* __restrict__ wsm, const float* __restrict__ bias,
+                                               const W3Terms& w3, float* __restrict__ rowsX,
+                                               float* __restrict__ rowsY, int lane,
+                                               float* __restrict__ valX = nullptr, float* __restrict__ valY = nullptr) {
+  constexpr int D = S::D;
+  const int j = lane & 15, gq = lane >> 4;
+  float vx[S::kSlices1][8], vy[S::kSlices1][8];
+#pragma unroll
+  for (int s = 0; s < S::kSlices1; ++s) {
+    load_row_inputs<S>(rowsX, j, gq, s, vx[s]);
+    load_row_inputs<S>(rowsY, j, gq, s, vy[s]);
+  }
+  f32x4 zX, zY;
+  policy_core_bf<S>(wsm, bias, w3, vx, vy, zX, zY, lane);
   // lane (j, gq) holds outputs 4gq + r of row j: outputs 0..3 in group 0, output 4 in group 1
   if constexpr (VALUE) {
     if (gq == 0) {

@@ -1,8 +1,7 @@
-// Fused rollout kernel for the headline shape: fp32 policy 6N -> 64 -> 64 -> 5 (N <= 3 agents; with fp32 weights
-// also 4 to 10 agents, whose 4N + 2 live inputs fill one K slice of layer 1 (up to 7 agents, 64-env blocks) or two
-// (8 to 10 agents, 32-env blocks)),
-// shared by all agents or one set of weights per run (paper: App. G IPPO table, two tanh layers
-// of width 64; Sec. 3.2 parameter sharing; Sec. 5.2 and App. E: whole training runs vectorised on one device).
+// Fused rollout kernel for the headline shape: policy 6N -> 64 -> 64 -> 5, N <= 3 agents, shared by all agents or one
+// set of weights per run (paper: App. G IPPO table, two tanh layers of width 64; Sec. 3.2 parameter sharing; Sec. 5.2
+// and App. E: whole training runs vectorised on one device).  The choice among this file's kernels, the small-batch
+// kernel (mpe_small.h) and the independent wavefronts (mpe_waves.h, always with 4 and more agents) is made here too.
 //
 // Where the contraction runs.  On gfx950 the fp32 MFMA shares the vector datapath: fp32 matrix
 // and fp32 vector peaks are the same number, and measured MFMA-f32 and VALU time add up instead
@@ -46,13 +45,13 @@ using SpreadNet = NetShape<6 * N, 4 * N + 2>;
 // Plain rollout: W1A + W2A and the biases of the policy (its W3A lives in registers).
 // Actor-critic rollout (AC): the whole packed image of the policy and of the critic (W1A, W2A,
 // W3A, biases each), a value per row, and one arrival counter per 64-env sync group.
-// ROWS = the block's agent rows, rounded up to whole wavefronts of RW rows (7 and 9 agents in 32-env or 16-env
-// blocks have such padding rows; no env owns them and nothing of them leaves the block).
+// ROWS = the block's agent rows: whole wavefronts of RW rows.
 template <int N, int EB, bool AC = false, bool BF = false, int RW = 64>
 struct SmemF32 {
   using P = PkT<BF, SpreadNet<N>::kWideIn, SpreadNet<N>::kSlices1>;
   static constexpr int D = 6 * N;
-  static constexpr int ROWS = (EB * N + RW - 1) / RW * RW;
+  static constexpr int ROWS = EB * N;
+  static_assert(N <= 3 && ROWS % RW == 0, "whole wavefronts");
   static constexpr size_t OFF_BIAS = AC ? P::OFF_BIAS : P::LDS_BYTES;
   static constexpr size_t OFF_CRITIC = OFF_BIAS + P::BIAS_BYTES;     // AC: the critic's packed image
   static constexpr size_t OFF_OBS = OFF_CRITIC + (AC ? P::RUN_BYTES : 0);
@@ -76,7 +75,7 @@ struct SmemF32 {
 // that store nothing to global memory.  The step latency of a block, which is all that matters when
 // every block has a CU to itself, is then one pair of tiles plus the env step instead of two pairs.
 template <int N, int EB, int MINW, bool PER_AGENT, bool AC, bool BF, int RW = 64>
-__global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_policy_f32_kernel(RolloutArgs A, const uint8_t* __restrict__ packed,
+__global__ __launch_bounds__(EB * N / RW * 64, MINW) void rollout_policy_f32_kernel(RolloutArgs A, const uint8_t* __restrict__ packed,
                                                                           const uint8_t* __restrict__ packed_critic,
                                                                           int per_run_weights, uint32_t groups,
                                                                           uint32_t groups_per_xcd) {
@@ -84,7 +83,6 @@ __global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_pol
   using P = typename M::P;
 
   constexpr int D = 6 * N, ROWS = M::ROWS, THREADS = ROWS * (64 / RW);
-  constexpr bool kPadded = ROWS != EB * N;
   static_assert(THREADS % 64 == 0, "block must be whole wavefronts");
   static_assert(RW == 64 || (RW == 32 && EB <= 64), "half-filled wavefronts only in blocks of one sync group");
   extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
@@ -108,9 +106,7 @@ __global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_pol
   constexpr int kGroups = EB > 64 ? EB / 64 : 1;
   const int wave = kGroups > 1 ? (hw_wave % kGroups) * N + hw_wave / kGroups : hw_wave;
   const int tid = wave * RW + (lane & (RW - 1));     // this lane's row
-  const int el_row = tid / N, i = tid - el_row * N;  // env within block, agent
-  const bool in_block = !kPadded || el_row < EB;     // false for padding rows: they shadow env 0 of the block
-  const int el = in_block ? el_row : 0;
+  const int el = tid / N, i = tid - el * N;          // env within block, agent
   const size_t TE = A.TE;
   // XCD-aware mapping: the hardware deals block b to XCD b % 8; giving each XCD one contiguous
   // range of env groups lets the partial cache lines that neighbouring groups write per step
@@ -119,7 +115,7 @@ __global__ __launch_bounds__((EB * N + RW - 1) / RW * 64, MINW) void rollout_pol
   if (grp >= groups) return;  // whole block, before any barrier
   const size_t g0 = size_t(grp) * EB;
   const size_t g = g0 + el;
-  const bool in_range = in_block && g < TE;
+  const bool in_range = g < TE;
   const bool valid = in_range && lane < RW;          // the lane that stores this row's outputs
   const uint32_t gc = in_range ? uint32_t(g) : uint32_t(g0);
   const uint32_t run = gc / A.E;
@@ -698,24 +694,25 @@ hipError_t launch_n(const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s
   const bool one_run = A.TE == A.E;
   const bool per_agent = A.ph.reward_mode == 1;
   if constexpr (N > 3) {
-    // 4 to 10 agents (fp32 weights; bf16 ones run the lane-per-agent bf16 kernel): blocks of 64 envs (N wavefronts,
-    // one or two per CU by their LDS) up to 7 agents, of 32 envs beyond (the rows are 6 N floats wide)
     static_assert(!BF, "bf16 weights with 4 and more agents are another kernel's");
-    constexpr int kEnvs = N <= 7 ? 64 : 32;
+    constexpr uint32_t kEnvs = N <= 7 ? 64 : 32;
     if (!one_run && A.E % kEnvs != 0) {
       *why = "with several runs and 4 or more agents, num_envs per run must be a multiple of 64 (of 32 with 8 to 10 agents)";
       return hipSuccess;
     }
-    if (bool taken = false; true) {
-      const hipError_t e = launch_small_spread(N, BF, small_args(A), 1, pb.packed, s, &taken);
-      if (taken || e != hipSuccess) return e;
-    }
-    return per_agent ? rollout_impl<N, kEnvs, 1, true, false, false>(A, pb, s) : rollout_impl<N, kEnvs, 1, false, false, false>(A, pb, s);
+    bool taken = false;
+    const hipError_t e = launch_small_spread(N, BF, small_args(A), 0, pb.packed, s, &taken);
+    return taken || e != hipSuccess ? e : launch_waves_spread(N, BF, small_args(A), pb.packed, nullptr, s);
   } else {
   if (one_run || A.E % 16 == 0) {
     bool taken = false;
     const hipError_t e = launch_small_spread(N, BF, small_args(A), 32, pb.packed, s, &taken);
     if (taken || e != hipSuccess) return e;
+  }
+  // 3 agents, one run, beyond the small-batch kernel's range: while one block of eight independent wavefronts (168 envs)
+  // per CU holds the batch, that is faster than 64-env blocks (40,960 envs: 0.96 against 1.2 ms)
+  if constexpr (N == 3 && !BF) {
+    if (one_run && A.TE <= 168 * compute_units()) return launch_waves_spread(N, BF, small_args(A), pb.packed, nullptr, s);
   }
   if (one_run && A.TE / 256 >= compute_units())
     return per_agent ? rollout_impl<N, 256, 3, true, false, BF>(A, pb, s) : rollout_impl<N, 256, 3, false, false, BF>(A, pb, s);
@@ -751,24 +748,23 @@ hipError_t launch_ac_n(const RolloutArgs& A, const PolicyBuffers& pb, const Poli
   const bool one_run = A.TE == A.E;
   const bool per_agent = A.ph.reward_mode == 1;
   if constexpr (N > 3) {
-    // both staged images and the block's observation rows: 64 envs up to 6 agents, 32 envs with 7, 16 envs beyond
     static_assert(!BF, "bf16 weights with 4 and more agents are another kernel's");
-    constexpr int kEnvs = N <= 6 ? 64 : (N == 7 ? 32 : 16);
+    constexpr uint32_t kEnvs = N <= 6 ? 64 : (N == 7 ? 32 : 16);
     if (!one_run && A.E % kEnvs != 0) {
       *why = "with several runs and 4 or more agents, num_envs per run must be a multiple of 64 (of 32 with 7 agents, of 16 with 8 to 10)";
       return hipSuccess;
     }
-    if (bool taken = false; true) {
-      const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), 1, pb.packed, critic.packed, s, &taken);
-      if (taken || e != hipSuccess) return e;
-    }
-    return per_agent ? rollout_impl<N, kEnvs, 1, true, true, false>(A, pb, s, critic.packed)
-                     : rollout_impl<N, kEnvs, 1, false, true, false>(A, pb, s, critic.packed);
+    bool taken = false;
+    const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), 0, pb.packed, critic.packed, s, &taken);
+    return taken || e != hipSuccess ? e : launch_waves_spread(N, BF, small_args(A), pb.packed, critic.packed, s);
   } else {
   if (one_run || A.E % 16 == 0) {
     bool taken = false;
     const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), 64, pb.packed, critic.packed, s, &taken);
     if (taken || e != hipSuccess) return e;
+  }
+  if constexpr (N == 3 && !BF) {   // as in the plain rollout (32,768 envs: 1.72 against 1.98 ms)
+    if (one_run && A.TE <= 168 * compute_units()) return launch_waves_spread(N, BF, small_args(A), pb.packed, critic.packed, s);
   }
   if (one_run ? A.TE / 256 >= compute_units() / 2 : A.E % 256 == 0)
     return per_agent ? rollout_impl<N, 256, 3, true, true, BF>(A, pb, s, critic.packed)

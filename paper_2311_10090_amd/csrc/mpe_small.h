@@ -13,7 +13,8 @@
 //  * everything that the next step does not wait for is done by SERVICE wavefronts, one lane per row and one step
 //    behind: trajectory stores, rewards, log-probabilities; and by them one step AHEAD: the sampling noise and the
 //    positions of an episode that is about to start (both are functions of the counter-based generator alone);
-//  * in the actor-critic rollout, CRITIC wavefronts (one per tile) evaluate the critic one step behind.
+//  * in the actor-critic rollout, CRITIC wavefronts (one per tile, or fewer that take several tiles in turn where a block
+//    would have more than 16 wavefronts) evaluate the critic one step behind.
 // All wavefronts of a block meet at one block barrier per step; everything they exchange is double-buffered by
 // step parity.
 #pragma once
@@ -214,7 +215,10 @@ struct SmallSmem {
   using Net = typename Scn::Net;
   using P = PkT<BF, Net::kWideIn, Net::kSlices1>;
   static constexpr int N = Scn::N, D = Scn::D, L = Scn::L, B = EB * N;
-  static constexpr int TILES = B / 16, SERVICE = (B + 63) / 64, WAVES = TILES * (AC ? 2 : 1) + SERVICE;
+  static constexpr int TILES = B / 16, SERVICE = (B + 63) / 64;
+  // critic wavefronts: one per tile where the block's 16 wavefronts allow it, else each takes several in turn
+  static constexpr int CRITICS = !AC ? 0 : (2 * TILES + SERVICE <= 16 ? TILES : 16 - TILES - SERVICE);
+  static constexpr int WAVES = TILES + CRITICS + SERVICE;
   static_assert(B % 16 == 0 && WAVES <= 16, "whole 16-row tiles");
   static constexpr size_t W = REGW ? 0 : P::LDS_BYTES;             // staged W1A + W2A of one network
   static constexpr size_t OFF_CRITIC = W;
@@ -224,8 +228,8 @@ struct SmallSmem {
   static constexpr size_t OBS = size_t(B) * D * 4;
   static constexpr size_t OFF_XCH = OFF_OBS + 2 * OBS + 64;                         // [2][B] float4: new position (and velocity)
   static constexpr size_t OFF_NOISE = OFF_XCH + size_t(2) * B * 16;                 // [2][5][B]
-  static constexpr size_t OFF_LOGITS = OFF_NOISE + size_t(2) * kNumActions * B * 4; // [2][5][B], AC only
-  static constexpr size_t OFF_ACT = OFF_LOGITS + (AC ? size_t(2) * kNumActions * B * 4 : 0);   // [2][B]
+  // AC: the logits of a step go to the service wavefront in the place of its noise, which has been read by then
+  static constexpr size_t OFF_ACT = OFF_NOISE + size_t(2) * kNumActions * B * 4;    // [2][B]
   static constexpr int ENT = N + L;                                                 // entities of an env
   static constexpr size_t OFF_RESET = OFF_ACT + size_t(2) * B * 4;                  // [2][EB][N + L] float2
   static constexpr size_t TOTAL = OFF_RESET + size_t(2) * EB * ENT * 8;
@@ -250,7 +254,7 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
   float* obs_tile = reinterpret_cast<float*>(smem + M::OFF_OBS);
   float4* xch = reinterpret_cast<float4*>(smem + M::OFF_XCH);
   float* noise = reinterpret_cast<float*>(smem + M::OFF_NOISE);
-  [[maybe_unused]] float* logits = reinterpret_cast<float*>(smem + M::OFF_LOGITS);
+  [[maybe_unused]] float* logits = noise;
   uint32_t* acts = reinterpret_cast<uint32_t*>(smem + M::OFF_ACT);
   float2* fresh = reinterpret_cast<float2*>(smem + M::OFF_RESET);
 
@@ -437,41 +441,37 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
       }
       if (i == 0) A.st.ep_step[g] = ep;
     }
-  } else if (AC && wave < 2 * TILES) {
-    // ================================================================ critic wavefront: tile `wave - TILES`
+  } else if (AC && wave < TILES + M::CRITICS) {
+    // ================================================================ critic wavefront: tiles wave - TILES, + CRITICS, ...
     if constexpr (AC) {
-      const int c0 = (wave - TILES) * 16, j = lane & 15, gq = lane >> 4;
+      const int j = lane & 15, gq = lane >> 4;
       TileNet<S, BF, REGW> net;
       net.init(packed_critic + run_off, smem + M::OFF_CRITIC, reinterpret_cast<const float*>(smem + M::OFF_CBIAS), lane);
-      const int row = c0 + j;
-      const bool store = gq == 0 && row < nvalid * N;
-      const size_t row_off = g0 * N + row;
-      auto value = [&](int parity) {
-        float v[KS1][8];
+      // values of the observations in the tiles of this wavefront -> dst [TE][N]
+      auto values = [&](int parity, float* dst) {
+        for (int c0 = (wave - TILES) * 16; c0 < B; c0 += M::CRITICS * 16) {
+          float v[KS1][8];
 #pragma unroll
-        for (int s = 0; s < KS1; ++s) load_row_inputs<S>(obs_tile + (size_t(parity) * B + c0) * D, j, gq, s, v[s]);
-        const f32x4 z = net.forward(v);
-        return (!BF && S::kRowTerms) ? (z[0] + z[1]) + z[2] : z[0];
+          for (int s = 0; s < KS1; ++s) load_row_inputs<S>(obs_tile + (size_t(parity) * B + c0) * D, j, gq, s, v[s]);
+          const f32x4 z = net.forward(v);
+          if (gq == 0 && c0 + j < nvalid * N) dst[g0 * N + c0 + j] = (!BF && S::kRowTerms) ? (z[0] + z[1]) + z[2] : z[0];
+        }
       };
       __syncthreads();
       float* value_p = A.value_traj;
       for (int t = 0; t < A.T; ++t) {
         __syncthreads();
         if (value_p) {   // of the observation that step t acted on
-          const float v = value(t & 1);
-          if (store) value_p[row_off] = v;
+          values(t & 1, value_p);
           value_p += TE * N;
         }
       }
       __syncthreads();
-      if (A.last_value) {
-        const float v = value(A.T & 1);
-        if (store) A.last_value[row_off] = v;
-      }
+      if (A.last_value) values(A.T & 1, A.last_value);
     }
   } else {
     // ================================================================ service wavefront: rows 64 w .. of the block
-    const int w = wave - TILES * (AC ? 2 : 1);
+    const int w = wave - TILES - M::CRITICS;
     const int r0 = w * 64;
     constexpr int kLastRows = B - (M::SERVICE - 1) * 64;                 // rows of the last service wavefront
     const bool has_row = M::SERVICE * 64 == B || r0 + lane < B;
@@ -639,70 +639,81 @@ hipError_t launch_small_impl(const TagArgs& A, const void* packed, const void* c
   return hipGetLastError();
 }
 
-// Envs per block: 16 (the paper's run size; 16 envs x N agents are N whole tiles), 8 where the actor-critic rollout of
-// many agents would need more than the 16 wavefronts of a block; 0: no such block.
-template <typename Scn, bool AC>
-constexpr int small_envs() {
-  constexpr int N = Scn::N;
-  return !AC || N <= 7 ? 16 : (N % 2 == 0 ? 8 : 0);
-}
-
-// Up to how many blocks of 16 envs per CU this kernel is the faster one for a batch of whole runs (or of runs whose
-// size suits the kernels for full batches).  Its time grows with every round of resident blocks, theirs in steps of
-// one large block per CU; the lines below are where the two measured curves cross, per shape (128-step rollouts, us,
-// this kernel against the others at 16 x 256 x {1, 2, 3, 4, 6, 8, 12} envs; fp32 unless stated):
-//   3 agents         193/418 295/419 411/531 493/537 727/958 953/978 1438/1339     (bf16 148/314 .. 537/675 744/681)
-//   3 agents, critic 274/699 466/706 690/961 907/965 1549/1803 1975/2509 2812/2522
+// Up to how many envs this kernel is the faster one for a batch of whole runs (or of runs whose size suits the kernels
+// for full batches), in tenths of 16-env blocks per CU.  Its time grows with every round of resident blocks, that of the
+// others in steps; the lines are where the two measured curves cross, per shape.  128-step rollouts, us, this kernel
+// against the others, at 16 x 256 x {1, 2, 3, 4, 6, 8, 12} envs (fp32 unless stated):
+//   3 agents         193/418 295/419 411/531 493/537 727/958 953/945 1438/1339     (bf16 148/314 .. 537/675 744/681)
+//   3 agents, critic 274/699 466/706 690/961 907/965 1549/1803 1975/1717 2812/2522
 //   2 agents         176/390 281/388 296/393 322/394 543/527                       (critic 218/689 324/692 487/697 753/696)
 //   1 agent          170/383 188/385 190/383 196/382 404/532 494/533 699/548
-//   tag (4,2,1)      221/433 356/433 545/732 852/734                               (critic 324/705 604/720 888/1044 1178/1105)
-// With 2 agents and a critic the large kernels fall behind once more between 6 and 8 (half of the CUs idle).
+//   6 agents         364/661 674/670 942/1032 1248/1107                            (critic 537/1136 1039/1153 1523/1830 2011/1910)
+//   tag (4,2,1)      221/626 356/644 545/640 852/638                               (critic 324/1109 604/1112 888/1119 1178/1124)
+//   tag (10,3,2)     719/769 1381/1164
+// `past`: where those kernels' first round of blocks (4 wavefronts of whole envs per CU) is just full, a second range.
+struct SmallRange {
+  uint32_t upto, past;
+};
 template <typename Scn, bool AC, bool BF>
-bool small_is_faster(uint32_t blocks16, uint32_t cus) {
+constexpr SmallRange small_range() {
   constexpr int N = Scn::N;
-  auto upto = [&](uint32_t k) { return blocks16 <= k * cus; };
   if constexpr (!Scn::kTag) {
-    if constexpr (N == 1) return upto(8);
-    if constexpr (N == 2) return AC ? upto(3) || (!upto(6) && upto(8)) : upto(4);
-    if constexpr (N == 3) return upto(AC || !BF ? 8 : 6);
-    if constexpr (N <= 6) return upto(AC && N < 6 ? 4 : 3);
-    if constexpr (AC) return upto(4) || N >= 8;
-    return upto(N == 7 ? 2 : 1);
+    if constexpr (N == 1) return {80, 0};
+    if constexpr (N == 2) return {AC ? 30 : 40, 0};
+    if constexpr (N == 3) return {AC || BF ? 60 : 80, 0};
+    constexpr SmallRange plain[7] = {{32, 0}, {23, 0}, {20, 30}, {17, 0}, {15, 0}, {12, 0}, {10, 0}};
+    constexpr SmallRange critic[7] = {{35, 0}, {26, 40}, {22, 35}, {20, 32}, {16, 0}, {14, 21}, {12, 0}};
+    return AC ? critic[N - 4] : plain[N - 4];
   } else {
-    if constexpr (N == 2) return upto(AC ? 3 : 4);
-    if constexpr (N == 3) return upto(6);
-    if constexpr (N == 4) return upto(AC && BF ? 1 : 3);
-    if constexpr (N == 5) return upto(AC ? (BF ? 3 : 4) : (BF ? 2 : 3));
-    if constexpr (N == 6) return upto(!AC && BF ? 2 : 3);
-    return upto(2);
+    if constexpr (N == 2) return {AC ? 30 : 40, 0};
+    if constexpr (N == 3) return {60, 0};
+    if constexpr (N == 4) return {AC && BF ? 28 : 31, 0};
+    if constexpr (N == 5) return AC && !BF ? SmallRange{24, 40} : SmallRange{22, 0};
+    if constexpr (N == 6) return AC && !BF ? SmallRange{22, 35} : SmallRange{19, 30};
+    if constexpr (N == 8) return {15, 0};
+    return {AC ? 11 : 10, 0};
   }
+}
+
+template <typename Scn, int EB, bool AC, bool BF>
+hipError_t launch_small_eb(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
+  // Stationary operands while a block has a CU to itself (6-10 % faster there); they take 100 to 170 registers per
+  // wavefront, so beyond that, and with more than 8 wavefronts per block, the operands are read from LDS.
+  constexpr int W = SmallSmem<Scn, EB, AC, BF, true>::WAVES, kMin = (W + 3) / 4;
+  if constexpr (kMin <= 2) {
+    if ((A.r.TE + EB - 1) / EB <= compute_units()) return launch_small_impl<Scn, EB, AC, BF, true, 2>(A, packed, critic, s);
+  }
+  return launch_small_impl<Scn, EB, AC, BF, false, (kMin < 4 ? 4 : kMin)>(A, packed, critic, s);
 }
 
 // *taken: whether the rollout was launched here.  run_block: the envs that a run must be a multiple of for the other
-// kernels to run it in blocks of their own shapes; smaller or odd runs always come here (measured with the blocks
-// that those kernels then used: 1,024 runs x 16 envs x 3 agents 491 against 682 us, actor-critic 886 against 2,094).
+// kernels to run it in blocks of their own shapes (0: any run, in blocks of 4 wavefronts of 64 / N envs of its own); runs
+// that do not suit them, or that would fill less than half of such a block, always come here (measured with the blocks
+// that the other kernels then used: 1,024 runs x 16 envs x 3 agents 491 against 682 us, actor-critic 886 against 2,094).
 template <typename Scn, bool AC, bool BF>
 hipError_t launch_small(const TagArgs& A, uint32_t run_block, const void* packed, const void* critic, hipStream_t s, bool* taken) {
-  constexpr int EB = small_envs<Scn, AC>();
-  if constexpr (EB == 0) return hipSuccess;
-  else {
-    const bool runs = A.r.TE != A.r.E;
-    if (runs && A.r.E % EB != 0) return hipSuccess;
-    const uint32_t cus = compute_units(), blocks16 = (A.r.TE + 15) / 16, blocks = (A.r.TE + EB - 1) / EB;
-    if (!(runs && A.r.E % run_block != 0)) {
-      if (!small_is_faster<Scn, AC, BF>(blocks16, cus)) return hipSuccess;
-      // runs of 32 envs (not 64) have a dense block shape of their own in the plain rollout of 1 to 3 agents
-      if (runs && run_block == 32 && A.r.E % 64 != 0 && blocks16 > 4 * cus) return hipSuccess;
-    }
-    *taken = true;
-    // Stationary operands while a block has a CU to itself (6-10 % faster there); they take 100 to 170 registers per
-    // wavefront, so beyond that, and with more than 8 wavefronts per block, the operands are read from LDS.
-    constexpr int W = SmallSmem<Scn, EB, AC, BF, true>::WAVES, kMin = (W + 3) / 4;
-    if constexpr (kMin <= 2) {
-      if (blocks <= cus) return launch_small_impl<Scn, EB, AC, BF, true, 2>(A, packed, critic, s);
-    }
-    return launch_small_impl<Scn, EB, AC, BF, false, (kMin < 4 ? 4 : kMin)>(A, packed, critic, s);
+  constexpr int N = Scn::N;
+  constexpr uint32_t kWavesBlock = 4 * (64 / N);
+  // Blocks are 16 envs, the paper's run size (16 envs x N agents are N whole tiles); 8 envs with 6, 8 and 10 agents while
+  // such blocks have a CU each (actor-critic, 2,048 envs: 8 agents 507 against 817 us, predator-prey with 10 agents 600
+  // against 1,044), and where the rows and both networks of 16 envs x 10 agents pass the LDS.
+  constexpr bool kEight = N == 6 || N == 8 || N == 10, kOnlyEight = AC && N == 10 && Scn::D > 32;
+  const bool runs = A.r.TE != A.r.E;
+  if (runs && A.r.E % 16 != 0) return hipSuccess;
+  const uint32_t cus = compute_units(), blocks16 = (A.r.TE + 15) / 16;
+  const bool odd_runs = runs && (run_block ? A.r.E % run_block != 0 : A.r.E * 2 < kWavesBlock);
+  if (!odd_runs) {
+    constexpr SmallRange range = small_range<Scn, AC, BF>();
+    const bool first_round_full = A.r.TE > kWavesBlock * cus;
+    if (blocks16 * 10 > cus * (first_round_full && range.past ? range.past : range.upto)) return hipSuccess;
+    // runs of 32 envs (not 64) have a dense block shape of their own in the plain rollout of 1 to 3 agents
+    if (runs && run_block == 32 && A.r.E % 64 != 0 && blocks16 > 4 * cus) return hipSuccess;
   }
+  *taken = true;
+  if constexpr (kEight) {
+    if (kOnlyEight || (A.r.TE + 7) / 8 <= cus) return launch_small_eb<Scn, 8, AC, BF>(A, packed, critic, s);
+  }
+  if constexpr (!kOnlyEight) return launch_small_eb<Scn, 16, AC, BF>(A, packed, critic, s);
 }
 
 }  // namespace

@@ -416,40 +416,40 @@ hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void
     launch_env_agents(true, S::N, S::L, S::G, A, s);
     return hipGetLastError();
   }
-  if constexpr (S::D <= 32) {
-    // actor-critic: both images are staged per block; 8 wavefronts share them where wavefronts never exchange
-    // data, otherwise the largest of 64 and 32 envs whose rows fit beside the two images
-    constexpr int kAcEnvs = S::kWaveLocal ? 512 / S::N : (S::N <= 6 ? 64 : 32);
-    const bool ac = mode_is_ac(mode);
-    const uint32_t per_block = ac ? uint32_t(kAcEnvs) : 64u;
-    if (A.r.TE == A.r.E || A.r.E % 16 == 0) {
-      bool taken = false;
-      const hipError_t e = ac ? launch_small_tag_ac(S::N, S::L, S::G, mode_is_bf(mode), A, per_block, packed, packed_critic, s, &taken)
-                              : launch_small_tag(S::N, S::L, S::G, mode_is_bf(mode), A, per_block, packed, s, &taken);
-      if (taken || e != hipSuccess) return e;
-    }
-    if (A.r.TE != A.r.E && A.r.E % per_block != 0) {   // (multiples of 16: launched above)
-      *why = "with several runs, num_envs per run must be a multiple of 16";
-      return hipSuccess;
-    }
-    if constexpr (S::N == 2 || S::N == 4) {
-      // Batches just beyond the small-batch kernel's, while such blocks leave SIMDs short of wavefronts: the rows of
-      // 64 envs x 2 agents or 32 envs x 4 agents over wavefronts of 32 rows, one per SIMD, up to two blocks per CU
-      // (1.55x with 2 agents, 1.4x for the actor-critic rollout of 4 agents; one of its plain rollout is no match
-      // for the small-batch kernel).
-      constexpr int kSmallEnvs = S::N == 2 ? 64 : 32;
-      const bool fits = (A.r.TE + kSmallEnvs - 1) / kSmallEnvs <= 2 * compute_units();
-      if (ac && fits) return tag_policy_impl<S, kSmallEnvs, 32, true>(mode, A, packed, packed_critic, s);
-      if constexpr (S::N == 2) {
-        if (fits) return tag_policy_impl<S, kSmallEnvs, 32, false>(mode, A, packed, nullptr, s);
-      }
-    }
-    if (ac) return tag_policy_impl<S, kAcEnvs, 64, true>(mode, A, packed, packed_critic, s);
-    return tag_policy_impl<S, 64, 64, false>(mode, A, packed, nullptr, s);
-  } else {
-    *why = "no policy kernel for this shape (observation rows longer than 32)";
+  if (A.r.TE != A.r.E && A.r.E % 16 != 0) {
+    *why = "with several runs, num_envs per run must be a multiple of 16";
     return hipSuccess;
   }
+  const bool ac = mode_is_ac(mode), bf = mode_is_bf(mode);
+  // Which kernel beyond the small-batch range.  This file's, with the rows of a block in LDS: 2 agents; the plain
+  // rollout of 3 agents, and of 4 once three wavefronts per SIMD are there (65,536 envs 2.14 ms either way, 49,152 envs
+  // 1.57 against 1.62 ms).  Independent wavefronts of whole envs (mpe_waves.h) otherwise (6 agents at 24,576 envs 1.61
+  // against 2.25 ms, 10 agents 2.73 against 4.30, actor-critic of 4 agents at 49,152 / 65,536 envs 2.82 / 3.64 against
+  // 3.79 / 3.78).
+  constexpr bool kRows = S::N == 2 || S::N == 3 || S::N == 4, kRowsAc = S::N == 2;
+  constexpr int kAcEnvs = 512 / S::N;                 // 8 wavefronts around both images (2 agents)
+  const bool rows = ac ? kRowsAc : kRows && (S::N != 4 || A.r.TE > 128 * compute_units());
+  const uint32_t per_block = !rows ? 0u : (ac ? uint32_t(kAcEnvs) : 64u);
+  {
+    bool taken = false;
+    const hipError_t e = ac ? launch_small_tag_ac(S::N, S::L, S::G, bf, A, per_block, packed, packed_critic, s, &taken)
+                            : launch_small_tag(S::N, S::L, S::G, bf, A, per_block, packed, s, &taken);
+    if (taken || e != hipSuccess) return e;
+  }
+  if constexpr (kRows) {
+    if (rows) {
+      if constexpr (kRowsAc) {
+        // Batches just beyond the small-batch kernel's: the rows of 64-env blocks over wavefronts of 32 rows, one per
+        // SIMD, up to two blocks per CU (1.55x)
+        if ((A.r.TE + 63) / 64 <= 2 * compute_units())
+          return ac ? tag_policy_impl<S, 64, 32, true>(mode, A, packed, packed_critic, s)
+                    : tag_policy_impl<S, 64, 32, false>(mode, A, packed, nullptr, s);
+        if (ac) return tag_policy_impl<S, kAcEnvs, 64, true>(mode, A, packed, packed_critic, s);
+      }
+      if (!ac) return tag_policy_impl<S, 64, 64, false>(mode, A, packed, nullptr, s);
+    }
+  }
+  return launch_waves_tag(S::N, S::L, S::G, bf, A, packed, ac ? packed_critic : nullptr, s);
 }
 
 template <typename S>

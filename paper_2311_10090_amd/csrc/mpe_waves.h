@@ -1,0 +1,474 @@
+// Fused rollout with independent wavefronts, for full batches: a wavefront owns WHOLE environments, as many as fit its
+// 64 lanes (one lane per agent row; 60 to 64 of the lanes have a row), so the agents of an env never live in two
+// wavefronts and nothing in the step loop waits for another wavefront.  A block is W such wavefronts around one staged
+// copy of the weights.  Both scenarios; fp32 (split-operand) or bf16 networks of width 64; actor-critic (AC).
+//
+// A lane keeps its observation row in registers and stores it to the trajectory itself; the layer-1 operands and the
+// logits travel between the row's lane and the matrix layout by 4 x 4 transposes between register index and 16-lane
+// group (no memory).  LDS holds the weights and, per wavefront, the positions its agents exchange and the landmarks:
+// 10 KB per wavefront less than with rows in LDS, which is what lets twelve wavefronts (three per SIMD, 168 registers
+// each) share a CU in blocks of a size that suits the batch.
+// What bounds it: vector issue and matrix time, as in mpe_policy_f32.hip: one wavefront per SIMD issues at the latency of
+// its own chain, two or three overlap to about 55 % matrix-pipe occupancy.  Blocks of 64 envs with the rows in LDS, which
+// these shapes used before, put 4 to 6 wavefronts on a CU and met at a block barrier every step: 20,011 envs x 6 agents,
+// fp32, 128 steps 2,304 -> 1,310 us; predator-prey of 5 agents at 24,576 envs 2,124 -> 1,250 us.  (Looping over the pairs
+// of tiles instead of unrolling them halves the code and changes nothing measurable.)  The arithmetic is that of the other
+// kernels in the same order, and so are the results, bit for bit.
+#pragma once
+
+#include <type_traits>
+
+#include "mpe_mlp64.h"
+#include "mpe_scenario.h"
+
+namespace mpe {
+
+namespace {
+
+template <int N_>
+struct WaveSpread : SpreadScn<N_> {
+  using Net = NetShape<6 * N_, 4 * N_ + 2>;
+};
+template <int N_, int L_, int G_>
+struct WaveTag : TagScn<N_, L_, G_> {
+  using Net = NetShape<TagScn<N_, L_, G_>::D, TagScn<N_, L_, G_>::D>;
+};
+
+// LDS of one wavefront: positions by step parity (the current one holds a new episode's after a reset), landmarks.
+template <typename Scn>
+struct WaveLds {
+  static constexpr int N = Scn::N, EW = 64 / N, ROWS = EW * N;
+  float4 xch[2][Scn::kTag ? ROWS : (ROWS + 1) / 2];    // predator-prey: position and velocity; else position (float2)
+  float2 lm[EW * (Scn::L + 1)];
+  float dmin[ROWS];
+};
+
+template <typename Scn, int W, bool AC, bool BF>
+struct WavesSmem {
+  using P = PkT<BF, Scn::Net::kWideIn, Scn::Net::kSlices1>;
+  // staged image of a network: W1A, W2A, the part of W3A that is used, biases
+  static constexpr size_t W3_BYTES = size_t(BF || Scn::Net::kRowTerms ? 2 : 6) * 64 * 16;
+  static constexpr size_t OFF_BIAS = P::OFF_W3A + W3_BYTES, IMAGE = OFF_BIAS + P::BIAS_BYTES;
+  static constexpr size_t OFF_CRITIC = IMAGE;
+  static constexpr size_t OFF_WAVE = IMAGE * (AC ? 2 : 1);
+  static constexpr size_t WAVE = (sizeof(WaveLds<Scn>) + 15) / 16 * 16;
+  static constexpr size_t TOTAL = OFF_WAVE + W * WAVE;
+  static_assert(IMAGE % 16 == 0 && TOTAL <= 160 * 1024, "LDS");
+};
+
+template <typename Scn, int W, bool AC, bool BF, int MINW>
+__global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA, const uint8_t* __restrict__ packed,
+                                                                     const uint8_t* __restrict__ packed_critic, uint32_t blocks,
+                                                                     uint32_t blocks_per_xcd) {
+  using M = WavesSmem<Scn, W, AC, BF>;
+  using P = typename M::P;
+  using Net = typename Scn::Net;
+  using TS = typename Scn::Shape;
+  constexpr bool kTag = Scn::kTag;
+  constexpr int N = Scn::N, L = Scn::L, D = Scn::D, KIN = Net::KIN, KS1 = Net::kSlices1;
+  constexpr int EW = 64 / N, EB = W * EW, ROWS = EW * N;
+  constexpr int G = kTag ? TS::G : 1, NA = kTag ? TS::A : 0;
+  constexpr bool kSpare = ROWS != 64;
+  const RolloutArgs& A = TA.r;
+  [[maybe_unused]] const TagPhys& tg = TA.tg;
+  extern __shared__ __attribute__((aligned(16))) uint8_t smem[];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
+  WaveLds<Scn>& sm = *reinterpret_cast<WaveLds<Scn>*>(smem + M::OFF_WAVE + size_t(wave) * M::WAVE);
+  const size_t TE = A.TE;
+  const uint32_t blk = (blockIdx.x & 7u) * blocks_per_xcd + (blockIdx.x >> 3);   // XCD-aware, as in the other kernels
+  if (blk >= blocks) return;                          // whole block, before any barrier
+  // the blocks of a run are its own; its last one may be partly filled
+  const uint32_t per_run = (A.E + EB - 1) / EB, run = blk / per_run;
+  const uint32_t env0 = (blk - run * per_run) * EB + wave * EW;        // first env of this wavefront inside its run
+  const int nvalid = env0 < A.E ? min(int(A.E - env0), EW) : 0;
+  const bool active = !kSpare || lane < ROWS;         // spare lanes shadow the wavefront's first row and store nothing
+  const int row = active ? lane : 0, el = row / N, i = row - el * N;
+  const bool in_range = el < nvalid, valid = active && in_range;
+  const uint32_t env = env0 + (in_range ? el : 0);
+  const size_t g = size_t(run) * A.E + (nvalid ? env : 0u);
+  const int32_t max_ep = kTag ? tg.max_ep : A.ph.max_ep;
+
+  // ---- weights of each network
+  {
+    auto stage = [&](const uint8_t* image, uint8_t* to) {
+      const uint4* src = reinterpret_cast<const uint4*>(image + size_t(run) * P::RUN_BYTES);
+      uint4* dst = reinterpret_cast<uint4*>(to);
+      for (int k = threadIdx.x; k < int(M::OFF_BIAS / 16); k += W * 64) dst[k] = src[k];
+      for (int k = threadIdx.x; k < int(P::BIAS_BYTES / 16); k += W * 64) dst[M::OFF_BIAS / 16 + k] = src[P::OFF_BIAS / 16 + k];
+    };
+    stage(packed, smem);
+    if constexpr (AC) stage(packed_critic, smem + M::OFF_CRITIC);
+  }
+  const float* bias = reinterpret_cast<const float*>(smem + M::OFF_BIAS);
+  [[maybe_unused]] const uint8_t* csm = smem + M::OFF_CRITIC;
+  [[maybe_unused]] const float* cbias = reinterpret_cast<const float*>(csm + M::OFF_BIAS);
+
+  // ---- this lane's agent; everything about the others is read from LDS where it is needed
+  float px = 0.0f, py = 0.0f, vx = 0.0f, vy = 0.0f;
+  int32_t ep = 0;
+  if (in_range) {
+    px = A.st.pos_a[(0 * N + i) * TE + g];
+    py = A.st.pos_a[(1 * N + i) * TE + g];
+    vx = A.st.vel_a[(0 * N + i) * TE + g];
+    vy = A.st.vel_a[(1 * N + i) * TE + g];
+    ep = A.st.ep_step[g];
+  }
+#pragma unroll
+  for (int k = 0; k < (L + N - 1) / N; ++k) {         // landmarks i, i + N, ...
+    const int l = i + k * N;
+    if (l < L && active)
+      sm.lm[el * (L + 1) + l] = in_range ? make_float2(A.st.pos_l[(0 * L + l) * TE + g], A.st.pos_l[(1 * L + l) * TE + g]) : make_float2(0.0f, 0.0f);
+  }
+  // what the lanes of an env read of each other, by step parity
+  auto put = [&](int parity) {
+    if (active) {
+      if constexpr (kTag) sm.xch[parity][row] = make_float4(px, py, vx, vy);
+      else reinterpret_cast<float2*>(sm.xch[parity])[row] = make_float2(px, py);
+    }
+  };
+  auto pos = [&](int parity, int a) {                 // agent a of this lane's env
+    if constexpr (kTag) {
+      const float4 p = sm.xch[parity][el * N + a];
+      return make_float2(p.x, p.y);
+    } else {
+      return reinterpret_cast<const float2*>(sm.xch[parity])[el * N + a];
+    }
+  };
+  put(1);
+  __syncthreads();   // weights staged; the only block-wide barrier
+  [[maybe_unused]] TagRole me{};
+  if constexpr (kTag) me = tag_role<TS>(i, tg);
+
+  // The live entries of this lane's observation row; `cur`: where its env's positions are.
+  auto build = [&](float (&o)[KIN], int cur) {
+    float qx[N], qy[N], lx[L + 1], ly[L + 1], gvx[G], gvy[G];
+    lx[L] = ly[L] = 0.0f;
+    gvx[0] = gvy[0] = 0.0f;
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+      if constexpr (kTag) {
+        const float4 p = sm.xch[cur][el * N + a];
+        qx[a] = p.x;
+        qy[a] = p.y;
+        if (a >= NA) {
+          gvx[a - NA] = p.z;
+          gvy[a - NA] = p.w;
+        }
+      } else {
+        const float2 p = pos(cur, a);
+        qx[a] = p.x;
+        qy[a] = p.y;
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < L; ++k) {
+      const float2 p = sm.lm[el * (L + 1) + k];
+      lx[k] = p.x;
+      ly[k] = p.y;
+    }
+    agent_obs<Scn>(o, i, px, py, vx, vy, qx, qy, lx, ly, gvx, gvy);
+  };
+  auto store_row = [&](const float (&o)[KIN], float* dst) {
+    if (!valid) return;
+    constexpr int CW = D % 4 == 0 ? 4 : 2;            // rows start on 16 bytes, or on 8
+    typedef float vC __attribute__((ext_vector_type(CW)));
+#pragma unroll
+    for (int q = 0; q < D / CW; ++q) {
+      vC v;
+#pragma unroll
+      for (int e = 0; e < CW; ++e) v[e] = CW * q + e < KIN ? o[CW * q + e < KIN ? CW * q + e : 0] : 0.0f;
+      reinterpret_cast<vC*>(dst)[q] = v;
+    }
+  };
+  // The networks on the wavefront's four tiles, two at a time.  z: the five logits of the lane's row; value: the critic's
+  // output.  The critic runs on a pair of tiles just before the policy, so that both read one split of its inputs.
+  auto forward = [&](const float (&o)[KIN], float (&z)[kNumActions], float& value, auto with_policy) {
+    constexpr bool kPolicy = decltype(with_policy)::value;
+    auto load_w3 = [&](const uint8_t* image) {
+      W3Terms w;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const bf16x8* src = reinterpret_cast<const bf16x8*>(image + P::OFF_W3A) + lane;
+        if constexpr (BF || Net::kRowTerms) {
+          w.s[s].h = src[s * 64];
+        } else {
+          w.s[s].h = src[(s * 3 + 0) * 64];
+          w.s[s].m = src[(s * 3 + 1) * 64];
+          w.s[s].l = src[(s * 3 + 2) * 64];
+        }
+      }
+      return w;
+    };
+    auto net = [&](const uint8_t* image, const float* b, const float (&tx)[KS1][8], const float (&ty)[KS1][8], f32x4& x, f32x4& y) {
+      if constexpr (BF) policy_core_bf<Net>(image, b, load_w3(image), tx, ty, x, y, lane);
+      else policy_core<Net>(image, b, load_w3(image), tx, ty, x, y, lane);
+    };
+    constexpr bool kTerms = !BF && Net::kRowTerms;    // output layout of layer 3, see tile_logits in mpe_small.h
+    uint32_t zs[4][4], cs[4];                         // [register][tile]
+#pragma unroll
+    for (int pr = 0; pr < 2; ++pr) {
+      float tx[KS1][8], ty[KS1][8];
+#pragma unroll
+      for (int s = 0; s < KS1; ++s)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          uint32_t v[4];
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const int c = 32 * s + (Net::kWideIn ? 8 * q : 8 * (q & 1)) + e;
+            v[q] = c < KIN ? __float_as_uint(o[c < KIN ? c : KIN - 1]) : 0u;
+          }
+          transpose_groups(v);
+          tx[s][e] = __uint_as_float(v[2 * pr]);
+          ty[s][e] = __uint_as_float(v[2 * pr + 1]);
+        }
+      f32x4 x, y;
+      if constexpr (AC) {
+        net(csm, cbias, tx, ty, x, y);
+        cs[2 * pr] = __float_as_uint(kTerms ? (x[0] + x[1]) + x[2] : x[0]);
+        cs[2 * pr + 1] = __float_as_uint(kTerms ? (y[0] + y[1]) + y[2] : y[0]);
+      }
+      if constexpr (kPolicy) {
+        net(smem, bias, tx, ty, x, y);
+        if constexpr (kTerms) {
+          zs[0][2 * pr] = __float_as_uint((x[0] + x[1]) + x[2]);
+          zs[0][2 * pr + 1] = __float_as_uint((y[0] + y[1]) + y[2]);
+          zs[1][2 * pr] = __float_as_uint(x[3]);
+          zs[1][2 * pr + 1] = __float_as_uint(y[3]);
+        } else {
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            zs[r][2 * pr] = __float_as_uint(x[r]);
+            zs[r][2 * pr + 1] = __float_as_uint(y[r]);
+          }
+        }
+      }
+    }
+    if constexpr (kPolicy) {
+      transpose_groups(zs[0]);
+      transpose_groups(zs[1]);
+      if constexpr (kTerms) {
+#pragma unroll
+        for (int k = 0; k < 4; ++k) z[k] = __uint_as_float(zs[0][k]);
+        z[4] = (__uint_as_float(zs[1][0]) + __uint_as_float(zs[1][1])) + __uint_as_float(zs[1][2]);
+      } else {
+        transpose_groups(zs[2]);
+        transpose_groups(zs[3]);
+#pragma unroll
+        for (int k = 0; k < 4; ++k) z[k] = __uint_as_float(zs[k][0]);
+        z[4] = __uint_as_float(zs[0][1]);
+      }
+    }
+    if constexpr (AC) {
+      transpose_groups(cs);
+      value = __uint_as_float(cs[0]);
+    }
+  };
+
+  float* obs_p = A.obs_traj;
+  uint8_t* act_p = A.act_traj;
+  float* rew_p = A.rew_traj;
+  uint8_t* done_p = A.done_traj;
+  [[maybe_unused]] float* logp_p = A.logp_traj;
+  [[maybe_unused]] float* value_p = A.value_traj;
+  const size_t row_off = g * N + i;
+  const bool env_writer = valid && i == 0;
+  const bool per_agent = kTag || A.ph.reward_mode == 1;
+  uint32_t step = A.abs_step;
+  float o[KIN];
+#pragma unroll
+  for (int c = 0; c < KIN; ++c) o[c] = 0.0f;
+  wave_sync();
+  build(o, 1);
+  for (int t = 0; t < A.T; ++t, ++step) {
+    const int par = t & 1;
+    if (obs_p) {
+      store_row(o, obs_p + row_off * D);
+      obs_p += TE * (N * D);
+    }
+    float z[kNumActions], value = 0.0f;
+    forward(o, z, value, std::true_type{});
+    const uint32_t act = gumbel_argmax(z, A.seed, run, env, step, uint32_t(i));
+    if (act_p) {
+      if (valid) act_p[row_off] = uint8_t(act);
+      act_p += TE * N;
+    }
+    if constexpr (AC) {
+      // log pi(act | obs) = z_act - max - ln sum exp(z - max)
+      float zmax = z[0], zact = z[0];
+#pragma unroll
+      for (int k = 1; k < kNumActions; ++k) {
+        zmax = fmaxf(zmax, z[k]);
+        zact = act == uint32_t(k) ? z[k] : zact;
+      }
+      float sum = 0.0f;
+#pragma unroll
+      for (int k = 0; k < kNumActions; ++k) sum += hw_exp2((z[k] - zmax) * kLog2e);
+      if (logp_p) {
+        if (valid) logp_p[row_off] = (zact - zmax) - kLn2 * hw_log2(sum);
+        logp_p += TE * N;
+      }
+      if (value_p) {
+        if (valid) value_p[row_off] = value;
+        value_p += TE * N;
+      }
+    }
+
+    // ---- transition on the positions of the step before (buffer par ^ 1)
+    float qx[N], qy[N];
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+      const float2 p = pos(par ^ 1, a);
+      qx[a] = p.x;
+      qy[a] = p.y;
+    }
+    if constexpr (kTag) {
+      float lx[L + 1], ly[L + 1];
+      lx[L] = ly[L] = 0.0f;
+#pragma unroll
+      for (int k = 0; k < L; ++k) {
+        const float2 p = sm.lm[el * (L + 1) + k];
+        lx[k] = p.x;
+        ly[k] = p.y;
+      }
+      tag_move<TS>(act, i, me, tg, px, py, vx, vy, qx, qy, lx, ly);
+    } else {
+      agent_move<N>(act, i, A.ph, px, py, vx, vy, qx, qy);
+    }
+    put(par);
+    wave_sync();
+    if (rew_p) {
+#pragma unroll
+      for (int a = 0; a < N; ++a) {
+        const float2 p = pos(par, a);
+        qx[a] = p.x;
+        qy[a] = p.y;
+      }
+      if constexpr (kTag) {
+        const float r = tag_reward<TS>(i, me, tg, px, py, qx, qy);
+        if (valid) rew_p[row_off] = r;
+      } else {
+        // coverage: this lane finds the distance of landmark i to the nearest agent; summed in landmark order
+        const float2 mine = sm.lm[el * (L + 1) + i];
+        float best2 = INFINITY;
+#pragma unroll
+        for (int a = 0; a < N; ++a) {
+          const float dx = qx[a] - mine.x, dy = qy[a] - mine.y;
+          best2 = fminf(best2, fmaf(dx, dx, dy * dy));
+        }
+        if (active) sm.dmin[row] = hw_sqrt(best2);
+        wave_sync();
+        float r = 0.0f;
+#pragma unroll
+        for (int a = 0; a < N; ++a) r -= sm.dmin[el * N + a];
+        if (per_agent) {
+          const float m = mixed_reward(r, overlap_count<N>(i, px, py, qx, qy, A.ph), A.ph);
+          if (valid) rew_p[row_off] = m;
+        } else if (env_writer) {
+          rew_p[g] = r;
+        }
+      }
+      rew_p += per_agent ? TE * N : TE;
+    }
+    ep += 1;
+    const bool done = ep >= max_ep;
+    if (done_p) {
+      if (env_writer) done_p[g] = done ? 1 : 0;
+      done_p += TE;
+    }
+    if (done) {
+      // new episode keyed by step + 1: every lane draws its own agent and landmarks i, i + N, ... of its env
+      uint32_t env_r = env;
+      asm volatile("" : "+v"(env_r));
+      const uint4 d = philox4x32_10(env_r, step + 1u, uint32_t(i), kTagResetPos, A.seed, run);
+      px = word_to_position(d.x);
+      py = word_to_position(d.y);
+      vx = vy = 0.0f;
+      ep = 0;
+#pragma unroll
+      for (int k = 0; k < (L + N - 1) / N; ++k) {
+        const int l = i + k * N;
+        if (l < L) {
+          const uint4 w = philox4x32_10(env_r, step + 1u, uint32_t(N + l), kTagResetPos, A.seed, run);
+          float2 p = make_float2(word_to_position(w.x), word_to_position(w.y));
+          if (kTag) { p.x *= 0.9f; p.y *= 0.9f; }      // obstacles start inside [-0.9, 0.9)
+          if (active) sm.lm[el * (L + 1) + l] = p;
+        }
+      }
+    }
+    wave_sync();               // the positions before a reset have been read
+    if (done) put(par);
+    wave_sync();
+    build(o, par);
+  }
+  if (A.last_obs) store_row(o, A.last_obs + row_off * D);
+  if constexpr (AC) {
+    if (A.last_value) {        // value of the observation after the last step
+      float z[kNumActions], value = 0.0f;
+      forward(o, z, value, std::false_type{});
+      if (valid) A.last_value[row_off] = value;
+    }
+  }
+  if (valid) {
+    A.st.pos_a[(0 * N + i) * TE + g] = px;
+    A.st.pos_a[(1 * N + i) * TE + g] = py;
+    A.st.vel_a[(0 * N + i) * TE + g] = vx;
+    A.st.vel_a[(1 * N + i) * TE + g] = vy;
+#pragma unroll
+    for (int k = 0; k < (L + N - 1) / N; ++k) {
+      const int l = i + k * N;
+      if (l < L) {
+        const float2 p = sm.lm[el * (L + 1) + l];
+        A.st.pos_l[(0 * L + l) * TE + g] = p.x;
+        A.st.pos_l[(1 * L + l) * TE + g] = p.y;
+      }
+    }
+    if (i == 0) A.st.ep_step[g] = ep;
+  }
+}
+
+// Blocks of W wavefronts that share a CU: by LDS, and by registers (168 per wavefront up to 12 wavefronts, 256 up to 8).
+template <typename Scn, int W, bool AC, bool BF>
+struct WavesBlocks {
+  static constexpr int EB = W * (64 / Scn::N);
+  static constexpr size_t LDS = WavesSmem<Scn, W, AC, BF>::TOTAL;
+  static constexpr int kResident = W != 4 || 2 * LDS > 160 * 1024 ? 1 : (3 * LDS > 160 * 1024 ? 2 : 3);
+  static constexpr int kMinWaves = W * kResident > 8 ? 3 : 2;      // per SIMD, for the register budget
+  static uint32_t count(const RolloutArgs& A) { return A.TE / A.E * ((A.E + EB - 1) / EB); }
+};
+
+template <typename Scn, int W, bool AC, bool BF>
+hipError_t launch_waves_impl(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
+  using B = WavesBlocks<Scn, W, AC, BF>;
+  auto kern = rollout_waves_kernel<Scn, W, AC, BF, B::kMinWaves>;
+  static std::atomic<uint64_t> lds_allowed{0};
+  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), B::LDS, lds_allowed); e != hipSuccess) return e;
+  const uint32_t blocks = B::count(A.r), per_xcd = (blocks + 7) / 8;
+  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(W * 64), B::LDS, s, A, static_cast<const uint8_t*>(packed),
+                     static_cast<const uint8_t*>(critic), blocks, per_xcd);
+  return hipGetLastError();
+}
+
+// Estimated time of a batch in blocks of W wavefronts, in units of a CU's time with 12 resident wavefronts: full rounds
+// of resident blocks, then a last one with as many blocks per CU as are left.  4, 8 and 12 wavefronts per CU take 0.42,
+// 0.75 and 1 (measured with 6 agents, fp32, 128 steps: 661-698, 1,030-1,210 and 1,412-1,660 us).
+template <typename Scn, int W, bool AC, bool BF>
+float waves_cost(const RolloutArgs& A) {
+  using B = WavesBlocks<Scn, W, AC, BF>;
+  const uint32_t cus = compute_units(), blocks = B::count(A), round = cus * B::kResident, rest = blocks % round;
+  auto time_of = [](uint32_t waves) { return waves == 0 ? 0.0f : (waves <= 4 ? 0.42f : (waves <= 8 ? 0.75f : 1.0f)); };
+  return float(blocks / round) * time_of(W * B::kResident) + time_of(W * ((rest + cus - 1) / cus));
+}
+
+template <typename Scn, bool AC, bool BF>
+hipError_t launch_waves(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
+  const float c4 = waves_cost<Scn, 4, AC, BF>(A.r), c8 = waves_cost<Scn, 8, AC, BF>(A.r), c12 = waves_cost<Scn, 12, AC, BF>(A.r);
+  if (c4 <= c8 && c4 <= c12) return launch_waves_impl<Scn, 4, AC, BF>(A, packed, critic, s);
+  if (c8 <= c12) return launch_waves_impl<Scn, 8, AC, BF>(A, packed, critic, s);
+  return launch_waves_impl<Scn, 12, AC, BF>(A, packed, critic, s);
+}
+
+}  // namespace
+
+}  // namespace mpe

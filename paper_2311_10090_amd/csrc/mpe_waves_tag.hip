@@ -1,0 +1,20 @@
+// Full-batch fused rollout with independent wavefronts, predator-prey.
+#include "mpe_waves.h"
+
+namespace mpe {
+
+hipError_t launch_waves_tag(int N, int L, int G, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
+#define X(n, l, g)                                                                                                  \
+  if (N == n && L == l && G == g) {                                                                                 \
+    if (bf16)                                                                                                       \
+      return critic ? launch_waves<WaveTag<n, l, g>, true, true>(A, packed, critic, s)                              \
+                    : launch_waves<WaveTag<n, l, g>, false, true>(A, packed, nullptr, s);                           \
+    return critic ? launch_waves<WaveTag<n, l, g>, true, false>(A, packed, critic, s)                               \
+                  : launch_waves<WaveTag<n, l, g>, false, false>(A, packed, nullptr, s);                            \
+  }
+  X(4, 2, 1) X(3, 0, 1) X(6, 2, 2) X(5, 2, 1) X(8, 2, 2) X(10, 3, 2)
+#undef X
+  return hipErrorInvalidValue;
+}
+
+}  // namespace mpe
