@@ -128,21 +128,30 @@ __device__ __forceinline__ void transpose_groups(uint32_t (&v)[4]) {
 // Gumbel-max over 5 logits: g = -ln(-ln u), u odd multiples of 2^-24 from two Philox blocks.
 // ln = ln2 * log2 on the hardware unit (u >= 2^-24 is a normal number; -ln u is in
 // [6e-8, 16.7], also normal), so v_k = z_k - ln2 * log2(-ln2 * log2(u_k)).
-__device__ __forceinline__ uint32_t gumbel_argmax(const float (&z)[kNumActions], uint32_t seed,
-                                                  uint32_t run, uint32_t env, uint32_t step, uint32_t agent) {
+// gumbel_noise: log2(-ln2 * log2(u_k)), which needs no logits; gumbel_pick: the argmax over v_k.
+__device__ __forceinline__ void gumbel_noise(float (&nz)[kNumActions], uint32_t seed, uint32_t run, uint32_t env, uint32_t step,
+                                             uint32_t agent) {
   const uint4 w0 = philox4x32_10(env, step, agent, kTagGumbel0, seed, run);
   const uint4 w1 = philox4x32_10(env, step, agent, kTagGumbel1, seed, run);
   const uint32_t w[kNumActions] = {w0.x, w0.y, w0.z, w0.w, w1.x};
+#pragma unroll
+  for (int k = 0; k < kNumActions; ++k) nz[k] = hw_log2(-kLn2 * hw_log2(word_to_open_uniform(w[k])));
+}
+__device__ __forceinline__ uint32_t gumbel_pick(const float (&z)[kNumActions], const float (&nz)[kNumActions]) {
   uint32_t best = 0;
   float best_v = -INFINITY;
 #pragma unroll
   for (int k = 0; k < kNumActions; ++k) {
-    const float u = word_to_open_uniform(w[k]);
-    const float e = -kLn2 * hw_log2(u);               // -ln u  > 0
-    const float v = fmaf(-kLn2, hw_log2(e), z[k]);     // z - ln(-ln u)
+    const float v = fmaf(-kLn2, nz[k], z[k]);
     if (v > best_v) { best_v = v; best = uint32_t(k); }
   }
   return best;
+}
+__device__ __forceinline__ uint32_t gumbel_argmax(const float (&z)[kNumActions], uint32_t seed,
+                                                  uint32_t run, uint32_t env, uint32_t step, uint32_t agent) {
+  float nz[kNumActions];
+  gumbel_noise(nz, seed, run, env, step, agent);
+  return gumbel_pick(z, nz);
 }
 
 }  // namespace mpe

@@ -199,16 +199,6 @@ __device__ __forceinline__ void tile_logits(const f32x4& a, float (&z)[kNumActio
   }
 }
 
-// The sampling noise of gumbel_argmax: v_k = fmaf(-ln 2, noise_k, z_k).
-__device__ __forceinline__ void gumbel_noise(float (&nz)[kNumActions], uint32_t seed, uint32_t run, uint32_t env, uint32_t step,
-                                             uint32_t agent) {
-  const uint4 w0 = philox4x32_10(env, step, agent, kTagGumbel0, seed, run);
-  const uint4 w1 = philox4x32_10(env, step, agent, kTagGumbel1, seed, run);
-  const uint32_t w[kNumActions] = {w0.x, w0.y, w0.z, w0.w, w1.x};
-#pragma unroll
-  for (int k = 0; k < kNumActions; ++k) nz[k] = hw_log2(-kLn2 * hw_log2(word_to_open_uniform(w[k])));
-}
-
 // ------------------------------------------------------------------------------ LDS plan of a block
 template <typename Scn, int EB, bool AC, bool BF, bool REGW>
 struct SmallSmem {
