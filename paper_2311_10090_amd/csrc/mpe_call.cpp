@@ -14,6 +14,7 @@
 
 #include <c10/core/DeviceGuard.h>
 #include <c10/hip/HIPStream.h>
+#include <torch/csrc/Exceptions.h>
 #include <torch/csrc/autograd/python_variable.h>
 
 #include "../../include/mpe.h"
@@ -44,18 +45,22 @@ struct Args {
       ok = false;
       return nullptr;
     }
-    const at::Tensor& t = THPVariable_Unpack(o);
-    if (!t.is_cuda() || !t.is_contiguous()) {
-      PyErr_SetString(PyExc_AssertionError, "device-resident contiguous tensor required");
-      ok = false;
-      return nullptr;
+    // A tensor without storage (the arguments inside a function transform) throws when it is asked for its address:
+    // raised as Python's own accessors raise it, never let through the interpreter's C frames.
+    try {
+      const at::Tensor& t = THPVariable_Unpack(o);
+      if (!t.is_cuda() || !t.is_contiguous()) {
+        PyErr_SetString(PyExc_AssertionError, "device-resident contiguous tensor required");
+      } else if (t.scalar_type() != type) {
+        PyErr_Format(PyExc_AssertionError, "expected %s, got %s", c10::toString(type), c10::toString(t.scalar_type()));
+      } else {
+        return t.data_ptr();
+      }
+    } catch (...) {
+      torch::translate_exception_to_python(std::current_exception());
     }
-    if (t.scalar_type() != type) {
-      PyErr_Format(PyExc_AssertionError, "expected %s, got %s", c10::toString(type), c10::toString(t.scalar_type()));
-      ok = false;
-      return nullptr;
-    }
-    return t.data_ptr();
+    ok = false;
+    return nullptr;
   }
   float* f32() { return static_cast<float*>(pointer(at::kFloat)); }
   uint8_t* u8() { return static_cast<uint8_t*>(pointer(at::kByte)); }
@@ -72,8 +77,8 @@ PyObject* run(const Args& a, int device, F call) {
     Py_BEGIN_ALLOW_THREADS
     rc = call(stream);
     Py_END_ALLOW_THREADS
-  } catch (const std::exception& e) {
-    PyErr_SetString(PyExc_RuntimeError, e.what());
+  } catch (...) {
+    torch::translate_exception_to_python(std::current_exception());
     return nullptr;
   }
   // the library's message belongs to this thread: the caller fetches it through mpe_last_error
