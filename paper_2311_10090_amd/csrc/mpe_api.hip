@@ -245,10 +245,10 @@ int mpe_obs_dim(const mpe_env* e) {
 int mpe_reset(mpe_env* e, uint32_t seed, float* obs, void* stream) {
   if (!e) return fail(MPE_EINVAL, "mpe_reset: NULL handle");
   if (obs && !aligned16(obs)) return fail(MPE_EINVAL, "mpe_reset: obs must be 16-byte aligned");
-  if (e->tag) launch_tag_reset(e->N, e->L, e->G, e->st, e->TE, e->E, seed, obs, static_cast<hipStream_t>(stream));
-  else launch_reset(e->N, e->st, e->TE, e->E, seed, obs, static_cast<hipStream_t>(stream));
-  if (e->hidden) launch_fill_zero(e->hidden, size_t(e->TE) * e->N * 128, static_cast<hipStream_t>(stream));
-  MPE_HIP(hipGetLastError());
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  if (e->tag) MPE_HIP(launch_tag_reset(e->N, e->L, e->G, e->st, e->TE, e->E, seed, obs, s));
+  else MPE_HIP(launch_reset(e->N, e->st, e->TE, e->E, seed, obs, s));
+  if (e->hidden) MPE_HIP(launch_fill_zero(e->hidden, size_t(e->TE) * e->N * 128, s));
   e->seed = seed;
   e->abs_step = 0;
   e->ready = true;
@@ -277,12 +277,11 @@ int mpe_step(mpe_env* e, const uint8_t* actions, float* obs, float* reward, uint
     A.r.fault = e->fault_dev;
     A.tg = e->tg;
     A.actions_in = actions;
-    launch_env_agents(true, e->N, e->L, e->G, A, static_cast<hipStream_t>(stream));
+    MPE_HIP(launch_env_agents(true, e->N, e->L, e->G, A, static_cast<hipStream_t>(stream)));
   } else {
-    launch_step(e->N, e->st, e->ph, e->TE, e->E, e->seed, e->abs_step, actions, obs, reward, done,
-                static_cast<hipStream_t>(stream));
+    MPE_HIP(launch_step(e->N, e->st, e->ph, e->TE, e->E, e->seed, e->abs_step, actions, obs, reward, done,
+                        static_cast<hipStream_t>(stream)));
   }
-  MPE_HIP(hipGetLastError());
   e->abs_step += 1;
   return MPE_OK;
 }
@@ -358,7 +357,7 @@ int mpe_rollout(mpe_env* e, int32_t T, float* obs_traj, uint8_t* act_traj, float
     if (why) return fail(MPE_EINVAL, "mpe_rollout: %s", why);
     if (err != hipSuccess) return fail(MPE_EHIP, "mpe_rollout: %s", hipGetErrorString(err));
   } else {
-    launch_rollout_uniform(e->N, A, static_cast<hipStream_t>(stream));
+    MPE_HIP(launch_rollout_uniform(e->N, A, static_cast<hipStream_t>(stream)));
   }
   MPE_HIP(hipGetLastError());
   e->abs_step += uint32_t(T);
@@ -383,8 +382,7 @@ int mpe_set_gru_policy(mpe_env* e, const float* We, const float* be, const float
   if (!e->hidden) {
     const size_t n = size_t(e->TE) * e->N * 128;
     MPE_HIP(hipMalloc(&e->hidden, n * sizeof(float)));
-    launch_fill_zero(e->hidden, n, s);
-    MPE_HIP(hipGetLastError());
+    MPE_HIP(launch_fill_zero(e->hidden, n, s));
   }
   // until the new image is packed the handle has no recurrent policy: a failure below must not leave an
   // earlier one installed on a partly rewritten buffer
@@ -428,8 +426,7 @@ int mpe_set_hidden(mpe_env* e, const float* hidden, void* stream) {
     MPE_HIP(hipMemcpyAsync(e->hidden, hidden, n * sizeof(float), hipMemcpyDeviceToDevice,
                            static_cast<hipStream_t>(stream)));
   } else {
-    launch_fill_zero(e->hidden, n, static_cast<hipStream_t>(stream));
-    MPE_HIP(hipGetLastError());
+    MPE_HIP(launch_fill_zero(e->hidden, n, static_cast<hipStream_t>(stream)));
   }
   return MPE_OK;
 }
@@ -640,9 +637,8 @@ int mpe_rollout_noalloc(const mpe_config* cfg, uint32_t seed, const float* W1, c
   // The array keeps the last call's contents.  Cleared here: the fault word (a fill kernel, not a memset node, so
   // that the call can be captured into a graph).  Overwritten in full before use: the state (reset kernel) and
   // the packed image (the pack kernel writes every byte of it that a rollout kernel reads).
-  launch_fill_zero(reinterpret_cast<float*>(base), 1, s);
-  launch_reset(e.N, e.st, e.TE, e.E, seed, nullptr, s);
-  MPE_HIP(hipGetLastError());
+  MPE_HIP(launch_fill_zero(reinterpret_cast<float*>(base), 1, s));
+  MPE_HIP(launch_reset(e.N, e.st, e.TE, e.E, seed, nullptr, s));
   e.seed = seed;
   e.abs_step = 0;
   const RolloutArgs A = rollout_args(&e, T, obs_traj, act_traj, rew_traj, done_traj, last_obs);
@@ -658,7 +654,7 @@ int mpe_rollout_noalloc(const mpe_config* cfg, uint32_t seed, const float* W1, c
     if (why) return fail(MPE_EINVAL, "mpe_rollout_noalloc: %s", why);
     if (err != hipSuccess) return fail(MPE_EHIP, "mpe_rollout_noalloc: %s", hipGetErrorString(err));
   } else {
-    launch_rollout_uniform(e.N, A, s);
+    MPE_HIP(launch_rollout_uniform(e.N, A, s));
   }
   MPE_HIP(hipGetLastError());
   return MPE_OK;

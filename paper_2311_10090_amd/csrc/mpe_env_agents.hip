@@ -479,7 +479,7 @@ __global__ __launch_bounds__(kStepWaves * 64) void step_agents_kernel(TagArgs TA
 }
 
 template <typename Scn>
-void launch_agents(const TagArgs& A, hipStream_t s) {
+hipError_t launch_agents(const TagArgs& A, hipStream_t s) {
   constexpr int EB = wave_envs<Scn>();
   if (A.actions_in) {
     const uint32_t waves = (A.r.TE + EB - 1) / EB;
@@ -488,6 +488,7 @@ void launch_agents(const TagArgs& A, hipStream_t s) {
     const uint32_t groups = (A.r.TE + EB - 1) / EB, per_xcd = (groups + 7) / 8;
     hipLaunchKernelGGL(rollout_agents_kernel<Scn>, dim3(per_xcd * 8), dim3(128), 0, s, A, groups, per_xcd);
   }
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -521,12 +522,12 @@ bool env_agents_faster(bool tag, int N, uint32_t TE) {
   return per_cu <= (N <= 7 ? 96 : 52);
 }
 
-void launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s) {
+hipError_t launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s) {
   if (tag) {
 #define X(n, l, g) if (N == n && L == l && G == g) return launch_agents<TagScn<n, l, g>>(A, s);
-    X(4, 2, 1) X(2, 1, 1) X(3, 0, 1) X(6, 2, 2) X(5, 2, 1) X(8, 2, 2) X(10, 3, 2)
+    MPE_TAG_SHAPES(X)
 #undef X
-    return;
+    return hipErrorInvalidValue;
   }
   switch (N) {
     case 1: return launch_agents<SpreadScn<1>>(A, s);
@@ -539,7 +540,7 @@ void launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStrea
     case 8: return launch_agents<SpreadScn<8>>(A, s);
     case 9: return launch_agents<SpreadScn<9>>(A, s);
     case 10: return launch_agents<SpreadScn<10>>(A, s);
-    default: return;
+    default: return hipErrorInvalidValue;
   }
 }
 

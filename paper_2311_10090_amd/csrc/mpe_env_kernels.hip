@@ -320,16 +320,18 @@ inline bool ws_aligned(const RolloutArgs& A) {
 
 template <int N>
 struct EnvLaunch {
-  static void reset(const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs, hipStream_t s) {
+  static hipError_t reset(const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs, hipStream_t s) {
     hipLaunchKernelGGL(reset_kernel<N>, env_grid(TE), dim3(kWave), 0, s, st, TE, E, seed, obs);
+    return hipGetLastError();
   }
-  static void step(const StatePtrs& st, const Phys& ph, uint32_t TE, uint32_t E, uint32_t seed,
-                   uint32_t abs_step, const uint8_t* actions, float* obs, float* reward, uint8_t* done,
-                   hipStream_t s) {
+  static hipError_t step(const StatePtrs& st, const Phys& ph, uint32_t TE, uint32_t E, uint32_t seed,
+                         uint32_t abs_step, const uint8_t* actions, float* obs, float* reward, uint8_t* done,
+                         hipStream_t s) {
     hipLaunchKernelGGL(step_kernel<N>, env_grid(TE), dim3(kWave), 0, s, st, ph, TE, E, seed, abs_step,
                        actions, obs, reward, done);
+    return hipGetLastError();
   }
-  static void rollout(const RolloutArgs& A, hipStream_t s) {
+  static hipError_t rollout(const RolloutArgs& A, hipStream_t s) {
     const uint32_t groups = (A.TE + kWave - 1) / kWave;
     const uint32_t per_xcd = (groups + 7) / 8;
     const dim3 grid(per_xcd * 8), block(2 * kWave);
@@ -341,49 +343,35 @@ struct EnvLaunch {
       if (mixed) hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, true, true>), grid, block, 0, s, A, groups, per_xcd);
       else hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, true, false>), grid, block, 0, s, A, groups, per_xcd);
     }
+    return hipGetLastError();
   }
 };
 
 }  // namespace
 
-#define MPE_DISPATCH_N(N_, CALL)                 \
-  switch (N_) {                                  \
-    case 1: { constexpr int kN = 1; CALL; } break;   \
-    case 2: { constexpr int kN = 2; CALL; } break;   \
-    case 3: { constexpr int kN = 3; CALL; } break;   \
-    case 4: { constexpr int kN = 4; CALL; } break;   \
-    case 5: { constexpr int kN = 5; CALL; } break;   \
-    case 6: { constexpr int kN = 6; CALL; } break;   \
-    case 7: { constexpr int kN = 7; CALL; } break;   \
-    case 8: { constexpr int kN = 8; CALL; } break;   \
-    case 9: { constexpr int kN = 9; CALL; } break;   \
-    case 10: { constexpr int kN = 10; CALL; } break; \
-    default: break;                              \
-  }
-
+// `return CALL;` for the agent count; hipErrorInvalidValue for one that the kernel is not built for
+#define MPE_CASE(N_, CALL) case N_: { constexpr int kN = N_; return CALL; }
 // step and rollout of the lane-per-env kernels: up to 3 agents
-#define MPE_DISPATCH_FEW(N_, CALL)               \
-  switch (N_) {                                  \
-    case 1: { constexpr int kN = 1; CALL; } break;   \
-    case 2: { constexpr int kN = 2; CALL; } break;   \
-    case 3: { constexpr int kN = 3; CALL; } break;   \
-    default: break;                              \
+#define MPE_DISPATCH_FEW(N_, CALL) \
+  switch (N_) { MPE_CASE(1, CALL) MPE_CASE(2, CALL) MPE_CASE(3, CALL) default: return hipErrorInvalidValue; }
+#define MPE_DISPATCH_N(N_, CALL)                                                               \
+  switch (N_) {                                                                                \
+    MPE_CASE(1, CALL) MPE_CASE(2, CALL) MPE_CASE(3, CALL) MPE_CASE(4, CALL) MPE_CASE(5, CALL)  \
+    MPE_CASE(6, CALL) MPE_CASE(7, CALL) MPE_CASE(8, CALL) MPE_CASE(9, CALL) MPE_CASE(10, CALL) \
+    default: return hipErrorInvalidValue;                                                      \
   }
 
-void launch_reset(int N, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
-                  hipStream_t s) {
+hipError_t launch_reset(int N, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
+                        hipStream_t s) {
   MPE_DISPATCH_N(N, EnvLaunch<kN>::reset(st, TE, E, seed, obs, s));
 }
 
-void launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, uint32_t E, uint32_t seed,
-                 uint32_t abs_step, const uint8_t* actions, float* obs, float* reward, uint8_t* done,
-                 hipStream_t s) {
+hipError_t launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, uint32_t E, uint32_t seed,
+                       uint32_t abs_step, const uint8_t* actions, float* obs, float* reward, uint8_t* done,
+                       hipStream_t s) {
   // One lane per env up to 3 agents (65,536 envs x 3 agents 5.4 us, 6.7 us with one lane per agent); for more agents
   // one lane per agent (4 / 7 / 10 agents at 8,192 envs: 4.3 -> 3.8, 15.3 -> 5.2, 14.3 -> 8.2 us).
-  if (N <= 3) {
-    MPE_DISPATCH_FEW(N, EnvLaunch<kN>::step(st, ph, TE, E, seed, abs_step, actions, obs, reward, done, s));
-    return;
-  }
+  if (N <= 3) MPE_DISPATCH_FEW(N, EnvLaunch<kN>::step(st, ph, TE, E, seed, abs_step, actions, obs, reward, done, s));
   TagArgs A{};
   A.r.st = st;
   A.r.ph = ph;
@@ -396,20 +384,19 @@ void launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, uint32
   A.r.done_traj = done;
   A.r.last_obs = obs;
   A.actions_in = actions;
-  launch_env_agents(false, N, N, 0, A, s);
+  return launch_env_agents(false, N, N, 0, A, s);
 }
 
-void launch_rollout_uniform(int N, const RolloutArgs& A, hipStream_t s) {
+hipError_t launch_rollout_uniform(int N, const RolloutArgs& A, hipStream_t s) {
   if (env_agents_faster(false, N, A.TE)) {
     TagArgs TA{};
     TA.r = A;
-    launch_env_agents(false, N, N, 0, TA, s);
-    return;
+    return launch_env_agents(false, N, N, 0, TA, s);
   }
   // many agents: one lane per agent (the wide fused kernel without its policy) writes contiguous pieces of the
   // trajectory
-  if (N > 3) (void)launch_rollout_uniform_wide(N, A, s);
-  else MPE_DISPATCH_FEW(N, EnvLaunch<kN>::rollout(A, s));
+  if (N > 3) return launch_rollout_uniform_wide(N, A, s);
+  MPE_DISPATCH_FEW(N, EnvLaunch<kN>::rollout(A, s));
 }
 
 }  // namespace mpe

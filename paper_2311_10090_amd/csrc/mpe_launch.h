@@ -77,11 +77,17 @@ struct TagArgs {
   const uint8_t* actions_in;     // [TE][N], single step with given actions only (launch_env_agents)
 };
 
+// Every launch function returns what the runtime said of the launch, and hipErrorInvalidValue (nothing launched) for a
+// shape that it is not built for.
+
+// The predator-prey shapes that are built: (agents, landmarks, good agents).
+#define MPE_TAG_SHAPES(X) X(4, 2, 1) X(2, 1, 1) X(3, 0, 1) X(6, 2, 2) X(5, 2, 1) X(8, 2, 2) X(10, 3, 2)
+
 // (N, L, G) = agents, landmarks, good agents
 bool tag_supported(int N, int L, int G);
 bool tag_policy_supported(int N, int L, int G, int H, int weight_dtype);
-void launch_tag_reset(int N, int L, int G, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
-                      hipStream_t s);
+hipError_t launch_tag_reset(int N, int L, int G, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
+                            hipStream_t s);
 // mode 1: uniform random actions; mode 2: the packed fp32 policy;
 // mode 3: the packed bf16 policy; mode 4 / 5: the packed fp32 / bf16 policy and critic (actor-critic outputs in r)
 hipError_t launch_tag_rollout(int N, int L, int G, int mode, const TagArgs& A, const void* packed,
@@ -92,12 +98,12 @@ hipError_t pack_policy_tag(PolicyBuffers& pb, int N, int L, int G, int R, bool b
                            const float* b1, const float* W2, const float* b2, const float* W3, const float* b3,
                            hipStream_t s);
 
-void launch_reset(int N, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
-                  hipStream_t s);
-void launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, uint32_t E, uint32_t seed,
-                 uint32_t abs_step, const uint8_t* actions, float* obs, float* reward, uint8_t* done,
-                 hipStream_t s);
-void launch_rollout_uniform(int N, const RolloutArgs& A, hipStream_t s);
+hipError_t launch_reset(int N, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
+                        hipStream_t s);
+hipError_t launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, uint32_t E, uint32_t seed,
+                       uint32_t abs_step, const uint8_t* actions, float* obs, float* reward, uint8_t* done,
+                       hipStream_t s);
+hipError_t launch_rollout_uniform(int N, const RolloutArgs& A, hipStream_t s);
 
 // Policy weights re-packed into MFMA A-operand order (device memory owned by the handle, or, `borrowed`,
 // a piece of memory of `bytes` bytes that is never freed or grown here).
@@ -158,7 +164,7 @@ hipError_t pack_gru_critic(PolicyBuffers& pb, int R, const float* Wc, const floa
 // step through A.r.rew_traj, done_traj, last_obs), or, with A.actions_in null, a rollout with uniform actions.
 // Whether its rollout is the faster one for this batch.
 bool env_agents_faster(bool tag, int N, uint32_t TE);
-void launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s);
+hipError_t launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s);
 // Full batches, independent wavefronts (mpe_waves.h).  critic: the packed critic of the actor-critic rollout, or null.
 hipError_t launch_waves_spread(int N, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s);
 hipError_t launch_waves_tag(int N, int L, int G, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s);
@@ -172,6 +178,6 @@ hipError_t launch_small_tag(int N, int L, int G, bool bf16, const TagArgs& A, ui
                             bool* taken);
 hipError_t launch_small_tag_ac(int N, int L, int G, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed,
                                const void* critic, hipStream_t s, bool* taken);
-void launch_fill_zero(float* p, size_t n, hipStream_t s);
+hipError_t launch_fill_zero(float* p, size_t n, hipStream_t s);
 
 }  // namespace mpe

@@ -815,20 +815,19 @@ __global__ void fill_zero_kernel(float* __restrict__ p, size_t n) {
 
 }  // namespace
 
-void launch_fill_zero(float* p, size_t n, hipStream_t s) {
-  if (n == 0) return;
+hipError_t launch_fill_zero(float* p, size_t n, hipStream_t s) {
+  if (n == 0) return hipSuccess;
   const size_t blocks = (n + 255) / 256;
   hipLaunchKernelGGL(fill_zero_kernel, dim3(uint32_t(blocks < 4096 ? blocks : 4096)), dim3(256), 0, s, p, n);
+  return hipGetLastError();
 }
 
 // Simple spread with 1..10 agents and every predator-prey shape that is built; hidden 128, bf16 weights.
-#define MPE_GRU_TAG_SHAPES(X) X(4, 2, 1) X(2, 1, 1) X(3, 0, 1) X(6, 2, 2) X(5, 2, 1) X(8, 2, 2) X(10, 3, 2)
-
 bool gru_supported(bool tag, int N, int L, int G, int H, int weight_dtype) {
   if (H != kG || weight_dtype != 1) return false;
   if (!tag) return N >= 1 && N <= 10;
 #define X(n, l, g) if (N == n && L == l && G == g) return true;
-  MPE_GRU_TAG_SHAPES(X)
+  MPE_TAG_SHAPES(X)
 #undef X
   return false;
 }
@@ -856,7 +855,7 @@ hipError_t launch_rollout_gru(bool tag, int N, int L, int G, const TagArgs& A, c
   if (tag) {
 #define X(n, l, g) \
     if (N == n && L == l && G == g) return rollout_gru_impl<GruTag<n, l, g>>(A, pb, critic, hidden, s, why);
-    MPE_GRU_TAG_SHAPES(X)
+    MPE_TAG_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;
   }

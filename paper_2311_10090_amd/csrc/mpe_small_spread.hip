@@ -18,9 +18,8 @@ hipError_t launch_small_spread(int N, bool bf16, const TagArgs& A, uint32_t run_
     case 8: return launch_small<SmallSpread<8>, false, false>(A, run_block, packed, nullptr, s, taken);
     case 9: return launch_small<SmallSpread<9>, false, false>(A, run_block, packed, nullptr, s, taken);
     case 10: return launch_small<SmallSpread<10>, false, false>(A, run_block, packed, nullptr, s, taken);
-    default: return hipSuccess;
+    default: return hipErrorInvalidValue;
   }
 }
-
 
 }  // namespace mpe

@@ -18,9 +18,8 @@ hipError_t launch_small_spread_ac(int N, bool bf16, const TagArgs& A, uint32_t r
     case 8: return launch_small<SmallSpread<8>, true, false>(A, run_block, packed, critic, s, taken);
     case 9: return launch_small<SmallSpread<9>, true, false>(A, run_block, packed, critic, s, taken);
     case 10: return launch_small<SmallSpread<10>, true, false>(A, run_block, packed, critic, s, taken);
-    default: return hipSuccess;
+    default: return hipErrorInvalidValue;
   }
 }
-
 
 }  // namespace mpe

@@ -413,8 +413,7 @@ hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void
     if constexpr (S::N != 4 && S::N != 10) {
       if (!env_agents_faster(true, S::N, A.r.TE)) return tag_rollout_impl<S, kUniform>(A, nullptr, nullptr, s);
     }
-    launch_env_agents(true, S::N, S::L, S::G, A, s);
-    return hipGetLastError();
+    return launch_env_agents(true, S::N, S::L, S::G, A, s);
   }
   if (A.r.TE != A.r.E && A.r.E % 16 != 0) {
     *why = "with several runs, num_envs per run must be a multiple of 16";
@@ -475,9 +474,6 @@ hipError_t tag_pack(PolicyBuffers& pb, int R, bool bf16, int nout, const float* 
 
 }  // namespace
 
-// The shapes that are built: (agents, landmarks, good agents).
-#define MPE_TAG_SHAPES(X) X(4, 2, 1) X(2, 1, 1) X(3, 0, 1) X(6, 2, 2) X(5, 2, 1) X(8, 2, 2) X(10, 3, 2)
-
 bool tag_supported(int N, int L, int G) {
 #define X(n, l, g) if (N == n && L == l && G == g) return true;
   MPE_TAG_SHAPES(X)
@@ -490,16 +486,17 @@ bool tag_policy_supported(int N, int L, int G, int H, int weight_dtype) {
          4 + 2 * L + 2 * (N - 1) + 2 * G <= 32;
 }
 
-void launch_tag_reset(int N, int L, int G, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
-                      hipStream_t s) {
+hipError_t launch_tag_reset(int N, int L, int G, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
+                            hipStream_t s) {
 #define X(n, l, g)                                                                                      \
   if (N == n && L == l && G == g) {                                                                     \
     hipLaunchKernelGGL((tag_reset_kernel<TagShape<n, l, g>>), dim3((TE + 63) / 64), dim3(64 * n), 0, s, st, TE, E, \
                        seed, obs);                                                                      \
-    return;                                                                                             \
+    return hipGetLastError();                                                                           \
   }
   MPE_TAG_SHAPES(X)
 #undef X
+  return hipErrorInvalidValue;
 }
 
 hipError_t launch_tag_rollout(int N, int L, int G, int mode, const TagArgs& A, const void* packed,

@@ -244,3 +244,22 @@ def test_bench_source_hash_ignores_comments_and_layout_but_not_code():
     assert bench._code_only(a) == bench._code_only(b)
     assert bench._code_only(a) != bench._code_only(c) and bench._code_only(a) != bench._code_only(d)
     assert len(bench.kernel_source_hash()) == 64
+
+
+@pytest.mark.parametrize("symbol,arguments", [
+    # (agents, ...) of a shape that no kernel is built for; nothing is launched, so the other arguments are not read
+    ("_ZN3mpe11launch_stepEiRKNS_9StatePtrsERKNS_4PhysEjjjjPKhPfS8_PhP12ihipStream_t", (11, "z", "z", 1, 1, 0, 0, None, None, None, None, None)),
+    ("_ZN3mpe12launch_resetEiRKNS_9StatePtrsEjjjPfP12ihipStream_t", (11, "z", 1, 1, 0, None, None)),
+    ("_ZN3mpe22launch_rollout_uniformEiRKNS_11RolloutArgsEP12ihipStream_t", (11, "z", None)),
+    ("_ZN3mpe17launch_env_agentsEbiiiRKNS_7TagArgsEP12ihipStream_t", (0, 11, 11, 0, "z", None)),
+    ("_ZN3mpe17launch_env_agentsEbiiiRKNS_7TagArgsEP12ihipStream_t", (1, 4, 3, 1, "z", None)),
+    ("_ZN3mpe16launch_tag_resetEiiiRKNS_9StatePtrsEjjjPfP12ihipStream_t", (4, 3, 1, "z", 1, 1, 0, None, None)),
+])
+def test_a_shape_without_a_kernel_is_an_error_of_the_launch(lib, symbol, arguments):
+    """The launch functions behind mpe_reset, mpe_step and mpe_rollout answer hipErrorInvalidValue (1) where they launch
+    nothing, so that no call can return MPE_OK without its work."""
+    zeros = C.create_string_buffer(1024)
+    fn = getattr(lib, symbol)
+    fn.restype = C.c_int
+    fn.argtypes = [C.c_void_p if a is None or a == "z" else C.c_int for a in arguments]
+    assert fn(*[zeros if a == "z" else a for a in arguments]) == 1
