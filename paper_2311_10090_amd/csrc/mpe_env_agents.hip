@@ -77,7 +77,7 @@ __device__ __forceinline__ void draw_fresh(float2* fresh, int el, int i, bool st
 }
 
 template <typename Scn>
-__global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, uint32_t groups, uint32_t groups_per_xcd) {
+__global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, GridPiece piece) {
   using M = AgentsSmem<Scn>;
   using TS = typename Scn::Shape;
   constexpr bool kTag = Scn::kTag;
@@ -89,8 +89,8 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, uint32_
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const size_t TE = A.TE;
-  const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);   // XCD-aware, as in the other kernels
-  if (grp >= groups) return;
+  const uint32_t grp = xcd_group(piece);
+  if (grp >= piece.end) return;
   const size_t g0 = size_t(grp) * EB;
   const int nvalid = TE - g0 < size_t(EB) ? int(TE - g0) : EB;
   const bool has_row = B == 64 || lane < B;                 // spare lanes shadow row 0 and store nothing
@@ -325,7 +325,7 @@ struct StepSmem {
 constexpr int kStepWaves = 4;
 
 template <typename Scn>
-__global__ __launch_bounds__(kStepWaves * 64) void step_agents_kernel(TagArgs TA) {
+__global__ __launch_bounds__(kStepWaves * 64) void step_agents_kernel(TagArgs TA, uint32_t first) {
   using M = StepSmem<Scn>;
   using TS = typename Scn::Shape;
   constexpr bool kTag = Scn::kTag;
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(kStepWaves * 64) void step_agents_kernel(TagArgs TA
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   M& sm = all[wave];
   const size_t TE = A.TE;
-  const size_t g0 = (size_t(blockIdx.x) * kStepWaves + wave) * EB;
+  const size_t g0 = ((size_t(first) + blockIdx.x) * kStepWaves + wave) * EB;
   if (g0 >= TE) return;                                     // whole wavefront; there is no block barrier
   const int nvalid = TE - g0 < size_t(EB) ? int(TE - g0) : EB;
   const bool has_row = B == 64 || lane < B;
@@ -481,14 +481,16 @@ __global__ __launch_bounds__(kStepWaves * 64) void step_agents_kernel(TagArgs TA
 template <typename Scn>
 hipError_t launch_agents(const TagArgs& A, hipStream_t s) {
   constexpr int EB = wave_envs<Scn>();
+  const uint32_t waves = (A.r.TE + EB - 1) / EB;
   if (A.actions_in) {
-    const uint32_t waves = (A.r.TE + EB - 1) / EB;
-    hipLaunchKernelGGL(step_agents_kernel<Scn>, dim3((waves + kStepWaves - 1) / kStepWaves), dim3(kStepWaves * 64), 0, s, A);
-  } else {
-    const uint32_t groups = (A.r.TE + EB - 1) / EB, per_xcd = (groups + 7) / 8;
-    hipLaunchKernelGGL(rollout_agents_kernel<Scn>, dim3(per_xcd * 8), dim3(128), 0, s, A, groups, per_xcd);
+    constexpr int kThreads = kStepWaves * 64;
+    return launch_groups<kThreads>((waves + kStepWaves - 1) / kStepWaves, [&](dim3, const GridPiece& p) {
+      hipLaunchKernelGGL(step_agents_kernel<Scn>, dim3(p.end - p.first), dim3(kThreads), 0, s, A, p.first);
+    });
   }
-  return hipGetLastError();
+  return launch_groups<128>(waves, [&](dim3 grid, const GridPiece& p) {
+    hipLaunchKernelGGL(rollout_agents_kernel<Scn>, grid, dim3(128), 0, s, A, p);
+  });
 }
 
 }  // namespace

@@ -35,6 +35,28 @@ inline uint32_t compute_units() {
   return uint32_t(n);
 }
 
+// Blocks of the kernels with one or more lanes per agent, each of which steps one group of envs.
+// The hardware deals block b to XCD b % 8; each XCD gets one contiguous range of groups, so that the partial cache lines
+// which neighbouring groups write per step meet in one L2.
+// A grid dimension holds fewer than 2^32 threads, which these kernels need at 2.0e8 to 1.1e9 envs (the two wavefronts of 6
+// envs x 10 agents: 21 threads per env): groups beyond 2^31 threads go to further launches.
+struct GridPiece {
+  uint32_t first, end, per_xcd;   // groups [first, end)
+};
+__device__ __forceinline__ uint32_t xcd_group(const GridPiece& p) {   // not below p.end for a block that is left over
+  return p.first + (blockIdx.x & 7u) * p.per_xcd + (blockIdx.x >> 3);
+}
+template <int THREADS, typename Launch>
+hipError_t launch_groups(uint32_t groups, Launch launch) {
+  constexpr uint32_t kPiece = (1u << 31) / uint32_t(THREADS) / 8u * 8u;
+  for (uint32_t first = 0; first < groups; first += kPiece) {
+    const uint32_t n = groups - first < kPiece ? groups - first : kPiece, per_xcd = (n + 7) / 8;
+    launch(dim3(per_xcd * 8), GridPiece{first, first + n, per_xcd});
+    if (hipError_t e = hipGetLastError(); e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 struct RolloutArgs {
   StatePtrs st;
   Phys ph;

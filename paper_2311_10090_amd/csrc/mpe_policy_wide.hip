@@ -280,8 +280,7 @@ __device__ __forceinline__ void policy_tile(const uint8_t* __restrict__ wsm, con
 template <int N, int H, int EB, int MINW, bool PER_AGENT, bool UNIFORM, bool AC = false>
 __global__ __launch_bounds__((RowMap<N, EB, UNIFORM>::WAVES * 64), MINW) void rollout_policy_kernel(RolloutArgs A, const uint8_t* __restrict__ packed,
                                                                       const uint8_t* __restrict__ packed_critic,
-                                                                      int per_run_weights, uint32_t groups,
-                                                                      uint32_t groups_per_xcd) {
+                                                                      int per_run_weights, GridPiece piece) {
   using S = Shape<N, H>;
   using M = Smem<N, H, EB, UNIFORM, AC>;
   using RM = RowMap<N, EB, UNIFORM>;
@@ -317,10 +316,8 @@ __global__ __launch_bounds__((RowMap<N, EB, UNIFORM>::WAVES * 64), MINW) void ro
   float* stage = reinterpret_cast<float*>(smem + M::OFF_STAGE + size_t(wave) * M::STAGE_WAVE);
   uint32_t* arrived = reinterpret_cast<uint32_t*>(smem + M::OFF_ARRIVED) + wave / GW;
   const size_t TE = A.TE;
-  // XCD-aware mapping: the hardware deals block b to XCD b % 8; each XCD gets one contiguous range
-  // of env groups, so the partial cache lines of neighbouring groups meet in one L2.
-  const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
-  if (grp >= groups) return;  // whole block, before any barrier
+  const uint32_t grp = xcd_group(piece);
+  if (grp >= piece.end) return;  // whole block, before any barrier
   const size_t g0 = size_t(grp) * EB;
   const size_t g = g0 + el;
   const bool valid = active && g < TE;
@@ -697,11 +694,11 @@ hipError_t rollout_impl(const RolloutArgs& A, const PolicyBuffers& pb, hipStream
   auto kern = rollout_policy_kernel<N, H, EB, MINW, PER_AGENT, UNIFORM, AC>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed); e != hipSuccess) return e;
-  const uint32_t groups = (A.TE + EB - 1) / EB;
-  const uint32_t per_xcd = (groups + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(RowMap<N, EB, UNIFORM>::WAVES * 64), M::TOTAL, s, A, static_cast<const uint8_t*>(pb.packed),
-                     static_cast<const uint8_t*>(critic), int(A.TE != A.E), groups, per_xcd);
-  return hipGetLastError();
+  constexpr int kThreads = RowMap<N, EB, UNIFORM>::WAVES * 64;
+  return launch_groups<kThreads>((A.TE + EB - 1) / EB, [&](dim3 grid, const GridPiece& p) {
+    hipLaunchKernelGGL(kern, grid, dim3(kThreads), M::TOTAL, s, A, static_cast<const uint8_t*>(pb.packed),
+                       static_cast<const uint8_t*>(critic), int(A.TE != A.E), p);
+  });
 }
 
 }  // namespace

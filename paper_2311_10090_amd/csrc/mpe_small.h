@@ -229,8 +229,7 @@ struct SmallSmem {
 // MINW: wavefronts per SIMD the register budget is set for.
 template <typename Scn, int EB, bool AC, bool BF, bool REGW, int MINW>
 __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MINW) void rollout_small_kernel(
-    TagArgs TA, const uint8_t* __restrict__ packed, const uint8_t* __restrict__ packed_critic, int per_run_weights, uint32_t groups,
-    uint32_t groups_per_xcd) {
+    TagArgs TA, const uint8_t* __restrict__ packed, const uint8_t* __restrict__ packed_critic, int per_run_weights, GridPiece piece) {
   using M = SmallSmem<Scn, EB, AC, BF, REGW>;
   using P = typename M::P;
   using S = typename Scn::Net;
@@ -251,8 +250,8 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const size_t TE = A.TE;
-  const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);   // XCD-aware, as in the other kernels
-  if (grp >= groups) return;                           // whole block, before any barrier
+  const uint32_t grp = xcd_group(piece);
+  if (grp >= piece.end) return;                           // whole block, before any barrier
   const size_t g0 = size_t(grp) * EB;
   const int nvalid = TE - g0 < size_t(EB) ? int(TE - g0) : EB;
   const size_t run_off = per_run_weights ? size_t(uint32_t(g0) / A.E) * P::RUN_BYTES : 0;
@@ -622,11 +621,10 @@ hipError_t launch_small_impl(const TagArgs& A, const void* packed, const void* c
   auto kern = rollout_small_kernel<Scn, EB, AC, BF, REGW, MINW>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed); e != hipSuccess) return e;
-  const uint32_t groups = (A.r.TE + EB - 1) / EB;
-  const uint32_t per_xcd = (groups + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(M::WAVES * 64), M::TOTAL, s, A, static_cast<const uint8_t*>(packed),
-                     static_cast<const uint8_t*>(critic), int(A.r.TE != A.r.E), groups, per_xcd);
-  return hipGetLastError();
+  return launch_groups<M::WAVES * 64>((A.r.TE + EB - 1) / EB, [&](dim3 grid, const GridPiece& p) {
+    hipLaunchKernelGGL(kern, grid, dim3(M::WAVES * 64), M::TOTAL, s, A, static_cast<const uint8_t*>(packed),
+                       static_cast<const uint8_t*>(critic), int(A.r.TE != A.r.E), p);
+  });
 }
 
 // Up to how many envs this kernel is the faster one for a batch of whole runs (or of runs whose size suits the kernels

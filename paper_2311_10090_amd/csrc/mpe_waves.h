@@ -58,8 +58,7 @@ struct WavesSmem {
 
 template <typename Scn, int W, bool AC, bool BF, int MINW>
 __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA, const uint8_t* __restrict__ packed,
-                                                                     const uint8_t* __restrict__ packed_critic, uint32_t blocks,
-                                                                     uint32_t blocks_per_xcd) {
+                                                                     const uint8_t* __restrict__ packed_critic, GridPiece piece) {
   using M = WavesSmem<Scn, W, AC, BF>;
   using P = typename M::P;
   using Net = typename Scn::Net;
@@ -76,8 +75,8 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   WaveLds<Scn>& sm = *reinterpret_cast<WaveLds<Scn>*>(smem + M::OFF_WAVE + size_t(wave) * M::WAVE);
   const size_t TE = A.TE;
-  const uint32_t blk = (blockIdx.x & 7u) * blocks_per_xcd + (blockIdx.x >> 3);   // XCD-aware, as in the other kernels
-  if (blk >= blocks) return;                          // whole block, before any barrier
+  const uint32_t blk = xcd_group(piece);
+  if (blk >= piece.end) return;                          // whole block, before any barrier
   // the blocks of a run are its own; its last one may be partly filled
   const uint32_t per_run = (A.E + EB - 1) / EB, run = blk / per_run;
   const uint32_t env0 = (blk - run * per_run) * EB + wave * EW;        // first env of this wavefront inside its run
@@ -444,10 +443,10 @@ hipError_t launch_waves_impl(const TagArgs& A, const void* packed, const void* c
   auto kern = rollout_waves_kernel<Scn, W, AC, BF, B::kMinWaves>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), B::LDS, lds_allowed); e != hipSuccess) return e;
-  const uint32_t blocks = B::count(A.r), per_xcd = (blocks + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(W * 64), B::LDS, s, A, static_cast<const uint8_t*>(packed),
-                     static_cast<const uint8_t*>(critic), blocks, per_xcd);
-  return hipGetLastError();
+  return launch_groups<W * 64>(B::count(A.r), [&](dim3 grid, const GridPiece& p) {
+    hipLaunchKernelGGL(kern, grid, dim3(W * 64), B::LDS, s, A, static_cast<const uint8_t*>(packed),
+                       static_cast<const uint8_t*>(critic), p);
+  });
 }
 
 // Estimated time of a batch in blocks of W wavefronts, in units of a CU's time with 12 resident wavefronts: full rounds

@@ -156,3 +156,59 @@ def test_recurrent_state_beyond_2_to_32(mods):
     env.close()
     del outs, hid
     torch.cuda.empty_cache()
+
+
+def test_more_threads_than_one_grid_dimension_holds(mods):
+    """With 10 agents a lane per agent is 10.7 threads per env (21.3 in the env-only rollout of predator-prey, two
+    wavefronts per 6 envs), so the calls need more than the 2^32 threads of one grid dimension from 4.03e8, 4.29e8 (the
+    full-batch env-only rollout) and 2.01e8 envs on, and are launched in pieces of 2^31 threads.  One-step calls without
+    observations: actions, rewards and flags of envs at the start, around those places, around the ends of the pieces and at
+    the end against the oracle, of an env-only rollout, a step and a policy rollout."""
+    MpeEnv, Oracle = mods
+    N, n = 10, 64
+    for tag, E in ((True, 215_000_011), (False, 431_000_011)):
+        say("%s, %d envs" % ("tag" if tag else "spread", E))
+        if tag:
+            env, cfg = MpeEnv(Hp.tag_gpu_config(E, 10, 3, 8, 1, 0)), lambda off: Hp.tag_oracle_config(n, 10, 3, 8, 1, 0, env_offset=off)
+        else:
+            env, cfg = MpeEnv(Hp.gpu_config(E, N, 1, 64, 0)), lambda off: Hp.oracle_config(n, N, 1, 64, 0, env_offset=off)
+        w = synth.policy_weights_with_bias(4, 1, 6 * N, 64)
+        act = torch.empty((1, E, N), dtype=torch.uint8, device="cuda")
+        rew = torch.empty((1,) + env.rew_shape, dtype=torch.float32, device="cuda")
+        done = torch.empty((1, E), dtype=torch.uint8, device="cuda")
+        given = torch.randint(0, 5, (E, N), dtype=torch.uint8, device="cuda")
+        pieces = (100_663_260, 201_326_560) if tag else (201_326_560, 214_748_340, 402_653_120, 429_496_700)
+        offsets = (0,) + pieces + (E - n,)
+
+        def keep():
+            torch.cuda.synchronize()
+            return [[x[0, off:off + n].cpu().numpy() for x in (act, rew, done)] for off in offsets]
+
+        env.reset(3)
+        env.rollout(1, None, act, rew, done, None)
+        got = [keep()]
+        env.step(given, None, rew[0], done[0])
+        got.append(keep())
+        if not tag:
+            env.set_policy(*Hp.to_dev(w))
+            env.rollout(1, None, act, rew, done, None)
+            got.append(keep())
+        steps = [given[off:off + n].cpu().numpy() for off in offsets]
+        env.close()
+        del act, rew, done, given
+        torch.cuda.empty_cache()
+        for k, off in enumerate(offsets):
+            orc = Oracle(cfg(off), threads=4)
+            orc.reset(3)
+            _, ract, rrew, rdone, _ = orc.rollout(1)
+            want = [(ract[0], rrew[0], rdone[0])]
+            _, srew, sdone = orc.step(steps[k])
+            want.append((None, srew, sdone))
+            if not tag:
+                orc.set_policy(*w)
+                _, ract, rrew, rdone, _ = orc.rollout(1)
+                want.append((ract[0], rrew[0], rdone[0]))
+            for call, (a, r, d) in enumerate(want):
+                ga, gr, gd = got[call][k]
+                assert np.array_equal(gd, d) and (a is None or np.array_equal(ga, a)), (tag, off, call)
+                assert np.abs(gr - r).max() <= 1e-3, (tag, off, call)
