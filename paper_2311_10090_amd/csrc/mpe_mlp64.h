@@ -636,12 +636,11 @@ __device__ __forceinline__ bf16x8 tanh_pack_bf(const f32x4& a0, const f32x4& a1)
   return __builtin_bit_cast(bf16x8, p);
 }
 
-// bf16 network of two 16-row tiles, registers in and out (as policy_core): weights and layer inputs bf16, fp32
-// accumulation and tanh.
-template <typename S>
+// bf16 network of two 16-row tiles: weights and layer inputs bf16, fp32 accumulation and tanh.  load(s, vx, vy): this
+// lane's layer-1 inputs of K slice s (see policy_core), called where they are packed.
+template <typename S, typename Load>
 __device__ __forceinline__ void policy_core_bf(const uint8_t* __restrict__ wsm, const float* __restrict__ bias,
-                                               const W3Terms& w3, const float (&vx)[S::kSlices1][8],
-                                               const float (&vy)[S::kSlices1][8], f32x4& zX, f32x4& zY, int lane) {
+                                               const W3Terms& w3, Load load, f32x4& zX, f32x4& zY, int lane) {
   const int gq = lane >> 4;
   __builtin_amdgcn_s_setprio(2);   // see policy_core
   {
@@ -659,11 +658,13 @@ __device__ __forceinline__ void policy_core_bf(const uint8_t* __restrict__ wsm, 
   bf16x8 bx[KS1], by[KS1];
 #pragma unroll
   for (int s = 0; s < KS1; ++s) {
+    float vx[8], vy[8];
+    load(s, vx, vy);
     u32x4 px, py;
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      px[q] = pack_bf16_rne(vx[s][2 * q], vx[s][2 * q + 1]);
-      py[q] = pack_bf16_rne(vy[s][2 * q], vy[s][2 * q + 1]);
+      px[q] = pack_bf16_rne(vx[2 * q], vx[2 * q + 1]);
+      py[q] = pack_bf16_rne(vy[2 * q], vy[2 * q + 1]);
     }
     bx[s] = __builtin_bit_cast(bf16x8, px);
     by[s] = __builtin_bit_cast(bf16x8, py);
@@ -714,21 +715,40 @@ __device__ __forceinline__ void policy_core_bf(const uint8_t* __restrict__ wsm, 
 }
 
 // The same on rows in LDS (interface of policy_pair): logits of row j go to cols 0..4 of that row.
-template <typename S, bool VALUE = false>
+// EARLY: whether the inputs are read before the network starts or where they are packed.  Wavefronts of 64 rows are up to
+// 5 % faster with the former (128 steps, 2 agents, 65,536 envs 674 against 708 us); of the lone ones of 32 rows the plain
+// rollout of 1 agent (runs of 64, 65,536 envs 367 against 389 us), the actor-critic one of more (2 agents, 24,576 envs 688
+// against 722 us; plain 392 against 377) and predator-prey (actor-critic, 2 agents, 24,576 envs 681 against 715) with the latter.
+template <typename S, bool VALUE = false, bool EARLY = true>
 __device__ __forceinline__ void policy_pair_bf(const uint8_t* __restrict__ wsm, const float* __restrict__ bias,
                                                const W3Terms& w3, float* __restrict__ rowsX,
                                                float* __restrict__ rowsY, int lane,
                                                float* __restrict__ valX = nullptr, float* __restrict__ valY = nullptr) {
   constexpr int D = S::D;
   const int j = lane & 15, gq = lane >> 4;
-  float vx[S::kSlices1][8], vy[S::kSlices1][8];
-#pragma unroll
-  for (int s = 0; s < S::kSlices1; ++s) {
-    load_row_inputs<S>(rowsX, j, gq, s, vx[s]);
-    load_row_inputs<S>(rowsY, j, gq, s, vy[s]);
-  }
   f32x4 zX, zY;
-  policy_core_bf<S>(wsm, bias, w3, vx, vy, zX, zY, lane);
+  if constexpr (EARLY) {
+    float inX[S::kSlices1][8], inY[S::kSlices1][8];
+#pragma unroll
+    for (int s = 0; s < S::kSlices1; ++s) {
+      load_row_inputs<S>(rowsX, j, gq, s, inX[s]);
+      load_row_inputs<S>(rowsY, j, gq, s, inY[s]);
+    }
+    auto load = [&](int s, float (&vx)[8], float (&vy)[8]) {
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        vx[e] = inX[s][e];
+        vy[e] = inY[s][e];
+      }
+    };
+    policy_core_bf<S>(wsm, bias, w3, load, zX, zY, lane);
+  } else {
+    auto load = [&](int s, float (&vx)[8], float (&vy)[8]) {
+      load_row_inputs<S>(rowsX, j, gq, s, vx);
+      load_row_inputs<S>(rowsY, j, gq, s, vy);
+    };
+    policy_core_bf<S>(wsm, bias, w3, load, zX, zY, lane);
+  }
   // lane (j, gq) holds outputs 4gq + r of row j: outputs 0..3 in group 0, output 4 in group 1
   if constexpr (VALUE) {
     if (gq == 0) {

@@ -225,6 +225,7 @@ __global__ __launch_bounds__(EB * N / RW * 64, MINW) void rollout_policy_f32_ker
   const float* wtile = tile + wave * (RW * D);        // this wavefront's rows
   uint32_t* arrived = reinterpret_cast<uint32_t*>(smem + M::OFF_ARRIVED) + wave / N;   // EB > 64 only
 
+  constexpr bool kEarly = RW == 64 || (N == 2 && !AC);   // see policy_pair_bf
   // Critic forward of this wavefront's rows: values[row] (wave-local rows).
   auto critic_rows = [&]() {
 #pragma unroll 1
@@ -232,7 +233,7 @@ __global__ __launch_bounds__(EB * N / RW * 64, MINW) void rollout_policy_f32_ker
       float* rows = tile + (wave * RW + pr * 32) * D;
       float* vals = values + wave * RW + pr * 32;
       const W3Terms wc = load_w3(csm);
-      if constexpr (BF) policy_pair_bf<SpreadNet<N>, true>(csm, cbias, wc, rows, rows + 16 * D, lane, vals, vals + 16);
+      if constexpr (BF) policy_pair_bf<SpreadNet<N>, true, kEarly>(csm, cbias, wc, rows, rows + 16 * D, lane, vals, vals + 16);
       else policy_pair<SpreadNet<N>, true>(csm, cbias, wc, rows, rows + 16 * D, lane, vals, vals + 16);
     }
   };
@@ -257,7 +258,7 @@ __global__ __launch_bounds__(EB * N / RW * 64, MINW) void rollout_policy_f32_ker
     for (int pr = 0; pr < RW / 32; ++pr) {
       float* rows = tile + (wave * RW + pr * 32) * D;
       if constexpr (AC) w3 = load_w3(wsm);
-      if constexpr (BF) policy_pair_bf<SpreadNet<N>>(wsm, bias, w3, rows, rows + 16 * D, lane);
+      if constexpr (BF) policy_pair_bf<SpreadNet<N>, false, kEarly>(wsm, bias, w3, rows, rows + 16 * D, lane);
       else policy_pair<SpreadNet<N>>(wsm, bias, w3, rows, rows + 16 * D, lane);
     }
     wave_sync();

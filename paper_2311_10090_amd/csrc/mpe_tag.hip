@@ -236,7 +236,7 @@ __global__ __launch_bounds__(EB * S::N / RW * 64, (TagOccupancy<S, MODE, EB, RW>
         float* rows = tile + (wave * RW + pr * 32) * D;
         float* vals = values + wave * RW + pr * 32;
         const W3Terms wc = load_w3(csm);
-        if constexpr (BF) policy_pair_bf<Net, true>(csm, cbias, wc, rows, rows + 16 * D, lane, vals, vals + 16);
+        if constexpr (BF) policy_pair_bf<Net, true, RW == 64>(csm, cbias, wc, rows, rows + 16 * D, lane, vals, vals + 16);
         else policy_pair<Net, true>(csm, cbias, wc, rows, rows + 16 * D, lane, vals, vals + 16);
       }
     }
@@ -267,7 +267,7 @@ __global__ __launch_bounds__(EB * S::N / RW * 64, (TagOccupancy<S, MODE, EB, RW>
       for (int pr = 0; pr < RW / 32; ++pr) {
         float* rows = tile + (wave * RW + pr * 32) * D;
         if constexpr (AC) w3 = load_w3(smem);
-        if constexpr (BF) policy_pair_bf<Net>(smem, bias, w3, rows, rows + 16 * D, lane);
+        if constexpr (BF) policy_pair_bf<Net, false, RW == 64>(smem, bias, w3, rows, rows + 16 * D, lane);
         else policy_pair<Net>(smem, bias, w3, rows, rows + 16 * D, lane);
       }
       wave_sync();

@@ -200,7 +200,14 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
       return w;
     };
     auto net = [&](const uint8_t* image, const float* b, const float (&tx)[KS1][8], const float (&ty)[KS1][8], f32x4& x, f32x4& y) {
-      if constexpr (BF) policy_core_bf<Net>(image, b, load_w3(image), tx, ty, x, y, lane);
+      auto load = [&](int s, float (&vx)[8], float (&vy)[8]) {
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+          vx[e] = tx[s][e];
+          vy[e] = ty[s][e];
+        }
+      };
+      if constexpr (BF) policy_core_bf<Net>(image, b, load_w3(image), load, x, y, lane);
       else policy_core<Net>(image, b, load_w3(image), tx, ty, x, y, lane);
     };
     constexpr bool kTerms = !BF && Net::kRowTerms;    // output layout of layer 3, see tile_logits in mpe_small.h
