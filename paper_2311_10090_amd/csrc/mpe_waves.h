@@ -136,6 +136,9 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
   };
   put(1);
   __syncthreads();   // weights staged; the only block-wide barrier
+  // A wavefront past its run's last env ends here.  In this form, and not as a return, the rest of the kernel compiles as it
+  // does without: the branch around the loop cost full batches 2 to 5 % (actor-critic, 32,768 envs x 6 agents 4.18 -> 4.40 ms).
+  asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 1f\n\ts_endpgm\n1:" : : "s"(nvalid) : "scc", "memory");
   [[maybe_unused]] TagRole me{};
   if constexpr (kTag) me = tag_role<TS>(i, tg);
 
@@ -458,7 +461,10 @@ hipError_t launch_waves_impl(const TagArgs& A, const void* packed, const void* c
 
 // Estimated time of a batch in blocks of W wavefronts, in units of a CU's time with 12 resident wavefronts: full rounds
 // of resident blocks, then a last one with as many blocks per CU as are left.  4, 8 and 12 wavefronts per CU take 0.42,
-// 0.75 and 1 (measured with 6 agents, fp32, 128 steps: 661-698, 1,030-1,210 and 1,412-1,660 us).
+// 0.75 and 1 (measured with 6 agents, fp32, 128 steps: 661-698, 1,030-1,210 and 1,412-1,660 us).  Where blocks of 4 and of
+// 8 come out the same, 8 are faster by up to 14 % with fp32 weights: half the copies of them to stage, and no CU with one
+// block of 4 beside one with two (8,192 / 24,576 envs x 10 agents 1,374 / 3,426 us against 1,580 / 3,820); with bf16 ones, a
+// third of the bytes, 4 are (predator-prey, actor-critic, 12,288 envs x 6 agents 1,242 us against 1,280).
 template <typename Scn, int W, bool AC, bool BF>
 float waves_cost(const RolloutArgs& A) {
   using B = WavesBlocks<Scn, W, AC, BF>;
@@ -470,7 +476,7 @@ float waves_cost(const RolloutArgs& A) {
 template <typename Scn, bool AC, bool BF>
 hipError_t launch_waves(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
   const float c4 = waves_cost<Scn, 4, AC, BF>(A.r), c8 = waves_cost<Scn, 8, AC, BF>(A.r), c12 = waves_cost<Scn, 12, AC, BF>(A.r);
-  if (c4 <= c8 && c4 <= c12) return launch_waves_impl<Scn, 4, AC, BF>(A, packed, critic, s);
+  if ((BF ? c4 <= c8 : c4 < c8) && c4 <= c12) return launch_waves_impl<Scn, 4, AC, BF>(A, packed, critic, s);
   if (c8 <= c12) return launch_waves_impl<Scn, 8, AC, BF>(A, packed, critic, s);
   return launch_waves_impl<Scn, 12, AC, BF>(A, packed, critic, s);
 }
