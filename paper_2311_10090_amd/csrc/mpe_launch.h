@@ -187,18 +187,24 @@ hipError_t pack_gru_critic(PolicyBuffers& pb, int R, const float* Wc, const floa
 // Whether its rollout is the faster one for this batch.
 bool env_agents_faster(bool tag, int N, uint32_t TE);
 hipError_t launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s);
+// Blocks of half-filled wavefronts are up to 16 threads per env and launched whole: for up to this many envs, 2^31 threads.
+constexpr uint32_t kWholeLaunchEnvs = 1u << 27;
+// Envs in the smallest block of the independent wavefronts: 4 of them, each of as many whole envs as fit its 64 lanes.
+constexpr uint32_t waves_block_envs(uint32_t N) { return 4 * (64 / N); }
+// Several runs that would fill less than half of such a block.
+inline bool half_empty_waves(const RolloutArgs& A, uint32_t N) { return A.TE != A.E && A.E * 2 < waves_block_envs(N); }
 // Full batches, independent wavefronts (mpe_waves.h).  critic: the packed critic of the actor-critic rollout, or null.
 hipError_t launch_waves_spread(int N, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s);
 hipError_t launch_waves_tag(int N, int L, int G, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s);
 // Small batches and small runs (mpe_small.h): *taken = true and the rollout launched where that kernel is the faster
 // one for the batch, else nothing done.  A.tg is read by the predator-prey shapes only.
-// run_block: the envs that a run is a multiple of where the other kernels have a block shape for it.
-hipError_t launch_small_spread(int N, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed, hipStream_t s, bool* taken);
-hipError_t launch_small_spread_ac(int N, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed, const void* critic,
+// unfit: the runs suit no block of the other kernels.
+hipError_t launch_small_spread(int N, bool bf16, const TagArgs& A, bool unfit, const void* packed, hipStream_t s, bool* taken);
+hipError_t launch_small_spread_ac(int N, bool bf16, const TagArgs& A, bool unfit, const void* packed, const void* critic,
                                   hipStream_t s, bool* taken);
-hipError_t launch_small_tag(int N, int L, int G, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed, hipStream_t s,
+hipError_t launch_small_tag(int N, int L, int G, bool bf16, const TagArgs& A, bool unfit, const void* packed, hipStream_t s,
                             bool* taken);
-hipError_t launch_small_tag_ac(int N, int L, int G, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed,
+hipError_t launch_small_tag_ac(int N, int L, int G, bool bf16, const TagArgs& A, bool unfit, const void* packed,
                                const void* critic, hipStream_t s, bool* taken);
 hipError_t launch_fill_zero(float* p, size_t n, hipStream_t s);
 

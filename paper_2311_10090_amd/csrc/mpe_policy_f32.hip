@@ -702,18 +702,21 @@ hipError_t launch_n(const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s
       return hipSuccess;
     }
     bool taken = false;
-    const hipError_t e = launch_small_spread(N, BF, small_args(A), 0, pb.packed, s, &taken);
+    const hipError_t e = launch_small_spread(N, BF, small_args(A), half_empty_waves(A, N), pb.packed, s, &taken);
     return taken || e != hipSuccess ? e : launch_waves_spread(N, BF, small_args(A), pb.packed, nullptr, s);
   } else {
-  if (one_run || A.E % 16 == 0) {
+  const uint32_t cus = compute_units();
+  // runs of 32 envs (not 64) have a dense block shape of their own below, the faster one beyond 4 16-env blocks per CU
+  const bool runs32 = !one_run && A.E % 32 == 0 && A.E % 64 != 0;
+  if ((one_run || A.E % 16 == 0) && !(runs32 && A.TE > 64 * cus)) {
     bool taken = false;
-    const hipError_t e = launch_small_spread(N, BF, small_args(A), 32, pb.packed, s, &taken);
+    const hipError_t e = launch_small_spread(N, BF, small_args(A), A.E % 32 != 0, pb.packed, s, &taken);
     if (taken || e != hipSuccess) return e;
   }
   // 3 agents, one run, beyond the small-batch kernel's range: while one block of eight independent wavefronts (168 envs)
   // per CU holds the batch, that is faster than 64-env blocks (40,960 envs: 0.96 against 1.2 ms)
   if constexpr (N == 3 && !BF) {
-    if (one_run && A.TE <= 168 * compute_units()) return launch_waves_spread(N, BF, small_args(A), pb.packed, nullptr, s);
+    if (one_run && A.TE <= 168 * cus) return launch_waves_spread(N, BF, small_args(A), pb.packed, nullptr, s);
   }
   if (one_run && A.TE / 256 >= compute_units())
     return per_agent ? rollout_impl<N, 256, 3, true, false, BF>(A, pb, s) : rollout_impl<N, 256, 3, false, false, BF>(A, pb, s);
@@ -756,12 +759,12 @@ hipError_t launch_ac_n(const RolloutArgs& A, const PolicyBuffers& pb, const Poli
       return hipSuccess;
     }
     bool taken = false;
-    const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), 0, pb.packed, critic.packed, s, &taken);
+    const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), half_empty_waves(A, N), pb.packed, critic.packed, s, &taken);
     return taken || e != hipSuccess ? e : launch_waves_spread(N, BF, small_args(A), pb.packed, critic.packed, s);
   } else {
   if (one_run || A.E % 16 == 0) {
     bool taken = false;
-    const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), 64, pb.packed, critic.packed, s, &taken);
+    const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), A.E % 64 != 0, pb.packed, critic.packed, s, &taken);
     if (taken || e != hipSuccess) return e;
   }
   if constexpr (N == 3 && !BF) {   // as in the plain rollout (32,768 envs: 1.72 against 1.98 ms)

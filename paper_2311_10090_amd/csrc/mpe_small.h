@@ -655,7 +655,7 @@ constexpr SmallRange small_range() {
   } else {
     if constexpr (N == 2) return {AC ? 30 : 40, 0};
     if constexpr (N == 3) return {60, 0};
-    if constexpr (N == 4) return {AC && BF ? 28 : 31, 0};
+    if constexpr (N == 4) return {AC && BF ? 20 : 31, 0};
     if constexpr (N == 5) return AC && !BF ? SmallRange{24, 40} : SmallRange{22, 0};
     if constexpr (N == 6) return AC && !BF ? SmallRange{22, 35} : SmallRange{19, 30};
     if constexpr (N == 8) return {15, 0};
@@ -674,14 +674,13 @@ hipError_t launch_small_eb(const TagArgs& A, const void* packed, const void* cri
   return launch_small_impl<Scn, EB, AC, BF, false, (kMin < 4 ? 4 : kMin)>(A, packed, critic, s);
 }
 
-// *taken: whether the rollout was launched here.  run_block: the envs that a run must be a multiple of for the other
-// kernels to run it in blocks of their own shapes (0: any run, in blocks of 4 wavefronts of 64 / N envs of its own); runs
-// that do not suit them, or that would fill less than half of such a block, always come here (measured with the blocks
-// that the other kernels then used: 1,024 runs x 16 envs x 3 agents 491 against 682 us, actor-critic 886 against 2,094).
+// *taken: whether the rollout was launched here.  unfit: runs that suit no block of the other kernels, which the caller
+// knows; they always come here (1,024 runs x 16 envs x 3 agents 491 us against 682 in the 16-env blocks of half-filled
+// wavefronts that such runs used before, actor-critic 886 against 2,094; predator-prey: see run_blocks16 in mpe_tag.hip).
 template <typename Scn, bool AC, bool BF>
-hipError_t launch_small(const TagArgs& A, uint32_t run_block, const void* packed, const void* critic, hipStream_t s, bool* taken) {
+hipError_t launch_small(const TagArgs& A, bool unfit, const void* packed, const void* critic, hipStream_t s, bool* taken) {
   constexpr int N = Scn::N;
-  constexpr uint32_t kWavesBlock = 4 * (64 / N);
+  constexpr uint32_t kWavesBlock = waves_block_envs(N);
   // Blocks are 16 envs, the paper's run size (16 envs x N agents are N whole tiles); 8 envs with 6, 8 and 10 agents while
   // such blocks have a CU each (actor-critic, 2,048 envs: 8 agents 507 against 817 us, predator-prey with 10 agents 600
   // against 1,044), and where the rows and both networks of 16 envs x 10 agents pass the LDS.
@@ -689,13 +688,10 @@ hipError_t launch_small(const TagArgs& A, uint32_t run_block, const void* packed
   const bool runs = A.r.TE != A.r.E;
   if (runs && A.r.E % 16 != 0) return hipSuccess;
   const uint32_t cus = compute_units(), blocks16 = (A.r.TE + 15) / 16;
-  const bool odd_runs = runs && (run_block ? A.r.E % run_block != 0 : A.r.E * 2 < kWavesBlock);
-  if (!odd_runs) {
+  if (!(runs && unfit)) {
     constexpr SmallRange range = small_range<Scn, AC, BF>();
     const bool first_round_full = A.r.TE > kWavesBlock * cus;
     if (blocks16 * 10 > cus * (first_round_full && range.past ? range.past : range.upto)) return hipSuccess;
-    // runs of 32 envs (not 64) have a dense block shape of their own in the plain rollout of 1 to 3 agents
-    if (runs && run_block == 32 && A.r.E % 64 != 0 && blocks16 > 4 * cus) return hipSuccess;
   }
   *taken = true;
   if constexpr (kEight) {

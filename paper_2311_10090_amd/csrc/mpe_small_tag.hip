@@ -3,11 +3,11 @@
 
 namespace mpe {
 
-hipError_t launch_small_tag(int N, int L, int G, bool bf16, const TagArgs& A, uint32_t run_block, const void* packed, hipStream_t s, bool* taken) {
+hipError_t launch_small_tag(int N, int L, int G, bool bf16, const TagArgs& A, bool unfit, const void* packed, hipStream_t s, bool* taken) {
 #define X(n, l, g)                                                                             \
   if (N == n && L == l && G == g)                                                              \
-    return bf16 ? launch_small<SmallTag<n, l, g>, false, true>(A, run_block, packed, nullptr, s, taken)     \
-                : launch_small<SmallTag<n, l, g>, false, false>(A, run_block, packed, nullptr, s, taken);
+    return bf16 ? launch_small<SmallTag<n, l, g>, false, true>(A, unfit, packed, nullptr, s, taken)     \
+                : launch_small<SmallTag<n, l, g>, false, false>(A, unfit, packed, nullptr, s, taken);
   MPE_TAG_SHAPES(X)
 #undef X
   return hipErrorInvalidValue;

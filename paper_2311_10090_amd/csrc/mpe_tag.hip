@@ -24,11 +24,11 @@ constexpr bool mode_is_bf(int mode) { return mode == kPolicyBf || mode == kPolic
 
 // EB = envs per block.  Plain rollouts: 64.  Actor-critic: both packed images (79 KB) are staged per block,
 // so a block is 8 wavefronts where the shape allows it (wavefront-local shapes need no block barrier).
-// ROWS = the block's agent rows: whole wavefronts of RW rows.
+// ROWS = the block's agent rows, rounded up to whole wavefronts of RW rows (only 16-env blocks of 5 agents
+// have such padding rows: 80 -> 96; no env owns them and nothing of them leaves the block).
 template <typename S, int MODE, int EB = 64, int RW = 64>
 struct TagSmem {
-  static constexpr int ROWS = EB * S::N;
-  static_assert(ROWS % RW == 0, "whole wavefronts");
+  static constexpr int ROWS = (EB * S::N + RW - 1) / RW * RW;
   static constexpr bool kAc = mode_is_ac(MODE);
   static constexpr bool kHasPolicy = MODE == kPolicy || MODE == kPolicyBf || kAc;
   using P = PkT<mode_is_bf(MODE), (S::D > 16)>;
@@ -100,7 +100,7 @@ struct TagOccupancy {
 };
 
 template <typename S, int MODE, int EB = 64, int RW = 64>
-__global__ __launch_bounds__(EB * S::N / RW * 64, (TagOccupancy<S, MODE, EB, RW>::kWavesPerSimd)) void tag_rollout_kernel(
+__global__ __launch_bounds__((EB * S::N + RW - 1) / RW * 64, (TagOccupancy<S, MODE, EB, RW>::kWavesPerSimd)) void tag_rollout_kernel(
     TagArgs TA, const uint8_t* __restrict__ packed, const uint8_t* __restrict__ packed_critic, int per_run_weights,
     uint32_t groups, uint32_t groups_per_xcd) {
   using M = TagSmem<S, MODE, EB, RW>;
@@ -109,6 +109,7 @@ __global__ __launch_bounds__(EB * S::N / RW * 64, (TagOccupancy<S, MODE, EB, RW>
   static_assert(RW == 64 || (RW == 32 && (!S::kWaveLocal || 32 % S::N == 0)), "rows per wavefront");
   using Net = NetShape<S::D, S::D <= 32 ? S::D : 32>;
   constexpr int N = S::N, L = S::L, G = S::G, NA = S::A, D = S::D, ROWS = M::ROWS, THREADS = ROWS * (64 / RW);
+  constexpr bool kPadded = ROWS != EB * N;
   static_assert(THREADS % 64 == 0, "block must be whole wavefronts");
   const RolloutArgs& A = TA.r;
   const TagPhys& tg = TA.tg;
@@ -119,14 +120,16 @@ __global__ __launch_bounds__(EB * S::N / RW * 64, (TagOccupancy<S, MODE, EB, RW>
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const int tid = wave * RW + (lane & (RW - 1));     // this lane's row
-  const int el = tid / N, i = tid - el * N;          // env within block, agent
+  const int el_row = tid / N, i = tid - el_row * N;  // env within block, agent
+  const bool in_block = !kPadded || el_row < EB;     // false for padding rows: they shadow env 0 of the block
+  const int el = in_block ? el_row : 0;
   const size_t TE = A.TE;
   // block b runs on XCD b % 8: give each XCD one contiguous range of env groups
   const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
   if (grp >= groups) return;  // whole block, before any barrier
   const size_t g0 = size_t(grp) * EB;
   const size_t g = g0 + el;
-  const bool in_range = g < TE;
+  const bool in_range = in_block && g < TE;
   const bool valid = in_range && lane < RW;          // the lane that stores this row's outputs
   const uint32_t gc = in_range ? uint32_t(g) : uint32_t(g0);
   const uint32_t run = gc / A.E;
@@ -406,6 +409,70 @@ hipError_t tag_policy_impl(int mode, const TagArgs& A, const void* packed, const
   return hipErrorInvalidValue;
 }
 
+// Several runs that are no whole number of the blocks that their kernel would use (every run has blocks of its own):
+// of per_block envs in this file's kernels; of the independent wavefronts where most of a block would be empty (4 agents,
+// plain: a tenth of it), or any of it in a batch of up to 48 envs per CU that passes one such block per CU.
+template <typename S>
+bool unfit_runs(bool ac, bool rows, uint32_t per_block, const RolloutArgs& A) {
+  constexpr uint32_t N = S::N, kWaves = waves_block_envs(N);
+  if (rows) return A.E % per_block != 0;
+  if (N == 3 || N == 10) return half_empty_waves(A, N);
+  const uint64_t room = uint64_t((A.E + kWaves - 1) / kWaves) * kWaves, used = A.E;
+  return used * 5 <= room * 3 || (N == 4 && !ac && used * 10 < room * 9) ||
+         (used < room && A.TE <= 48 * compute_units() && A.TE / A.E * (room / kWaves) > compute_units());
+}
+
+// From how many 16-env blocks per CU on (in tenths; up to four blocks per CU, and past them) such runs are faster in
+// blocks of 16 envs of this file's kernel, with wavefronts of 32 rows, than in the small-batch kernel.  Four of the
+// former share a CU, and a first round of them that is not full takes nearly as long as a full one.  64-step rollouts of
+// runs x 16 envs, us, this kernel against the small-batch kernel, at 16 x 256 x {1, 2, 3, 4, 6, 8, 16} envs:
+//   4 agents fp32           207/105 273/173 284/264 312/432 504/586 618/750 1222/1486
+//   4 agents bf16           154/87 204/142 209/223 223/358 324/481 495/615 849/1220
+//   4 agents bf16, critic   245/133 357/263 366/393 372/523 873/782 973/1041 1827/2105
+//   5 agents bf16           178/140 229/201 341/404 373/431 643/732 811/921 1480/1746
+//   6 agents bf16           185/151 237/263 355/387 386/504 645/741 816/980 1529/1924
+//   6 agents bf16, critic   286/220 394/436 580/648 792/861 1131/1286 1484/1712 2924/3424
+//   8 agents fp32           260/224 370/448 604/671 750/892 1133/1335 1508/1786
+//   8 agents bf16           199/181 275/358 401/535 540/714 785/1067 1035/1421
+//   8 agents bf16, critic   297/265 422/525 704/787 839/1051 1258/1565 1676/2097
+//   2 agents bf16           139/69 143/111 142/112 142/127 193/207 195/331 484/575    (critic 227/91 232/125 237/174 240/265 572/393)
+constexpr uint32_t kNever = 1u << 20;
+struct Blocks16 {
+  uint32_t from, past;
+};
+template <typename S>
+constexpr Blocks16 run_blocks16(int mode) {
+  constexpr int N = S::N;
+  switch (mode) {
+    case kPolicy: return N == 4 ? Blocks16{35, 35} : (N == 8 ? Blocks16{15, 15} : Blocks16{kNever, kNever});
+    case kPolicyBf:
+      if (N == 2) return {kNever, 45};
+      if (N == 4) return {28, 28};
+      if (N == 5) return {25, 25};
+      if (N == 6) return {15, 15};
+      return N == 8 ? Blocks16{12, 12} : Blocks16{kNever, kNever};
+    case kPolicyAcBf:
+      if (N == 2) return {35, kNever};
+      if (N == 4) return {25, 70};
+      return N == 6 || N == 8 ? Blocks16{15, 15} : Blocks16{kNever, kNever};
+    default: return {kNever, kNever};
+  }
+}
+
+template <typename S>
+hipError_t tag_blocks16(int mode, const TagArgs& A, const void* packed, const void* packed_critic, hipStream_t s) {
+  if constexpr (S::N == 4 || S::N == 8) {
+    if (mode == kPolicy) return tag_rollout_impl<S, kPolicy, 16, 32>(A, packed, nullptr, s);
+  }
+  if constexpr (S::N != 3 && S::N != 10) {
+    if (mode == kPolicyBf) return tag_rollout_impl<S, kPolicyBf, 16, 32>(A, packed, nullptr, s);
+  }
+  if constexpr (S::N == 2 || S::N == 4 || S::N == 6 || S::N == 8) {
+    if (mode == kPolicyAcBf) return tag_rollout_impl<S, kPolicyAcBf, 16, 32>(A, packed, packed_critic, s);
+  }
+  return hipErrorInvalidValue;
+}
+
 template <typename S>
 hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void* packed_critic, hipStream_t s,
                       const char** why) {
@@ -427,20 +494,42 @@ hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void
   // 3.79 / 3.78).
   constexpr bool kRows = S::N == 2 || S::N == 3 || S::N == 4, kRowsAc = S::N == 2;
   constexpr int kAcEnvs = 512 / S::N;                 // 8 wavefronts around both images (2 agents)
-  const bool rows = ac ? kRowsAc : kRows && (S::N != 4 || A.r.TE > 128 * compute_units());
-  const uint32_t per_block = !rows ? 0u : (ac ? uint32_t(kAcEnvs) : 64u);
+  const uint32_t cus = compute_units();
+  const bool runs = A.r.TE != A.r.E;
+  const bool rows = ac ? kRowsAc : kRows && (S::N != 4 || A.r.TE > 128 * cus);
+  const bool unfit = runs && unfit_runs<S>(ac, rows, rows ? (ac ? uint32_t(kAcEnvs) : 64u) : 0u, A.r);
+  if (unfit && A.r.TE <= kWholeLaunchEnvs) {
+    const uint32_t blocks = A.r.TE / 16, line = blocks > 4 * cus ? run_blocks16<S>(mode).past : run_blocks16<S>(mode).from;
+    if (blocks * 10 > cus * line) return tag_blocks16<S>(mode, A, packed, packed_critic, s);
+  }
   {
     bool taken = false;
-    const hipError_t e = ac ? launch_small_tag_ac(S::N, S::L, S::G, bf, A, per_block, packed, packed_critic, s, &taken)
-                            : launch_small_tag(S::N, S::L, S::G, bf, A, per_block, packed, s, &taken);
+    const hipError_t e = ac ? launch_small_tag_ac(S::N, S::L, S::G, bf, A, unfit, packed, packed_critic, s, &taken)
+                            : launch_small_tag(S::N, S::L, S::G, bf, A, unfit, packed, s, &taken);
     if (taken || e != hipSuccess) return e;
+  }
+  // bf16, actor-critic, 4 agents, up to 96 envs per CU: 32-env blocks of 32-row wavefronts (12,288 / 16,384 / 24,576 envs
+  // 717 / 722 / 1,065 us; independent wavefronts 793 / 793 / 1,257; 32,768 envs 1,449 against 1,264)
+  if constexpr (S::N == 4) {
+    if (mode == kPolicyAcBf && (!runs || A.r.E % 32 == 0) && A.r.TE <= 96 * cus)
+      return tag_rollout_impl<S, kPolicyAcBf, 32, 32>(A, packed, packed_critic, s);
+  }
+  // bf16, plain, 8 agents, more than one block of 4 independent wavefronts per CU: 64-env blocks, one per CU, while the
+  // last round of them is (nearly) full or the only one
+  // (12,288 / 16,384 / 32,768 / 49,152 envs 762 / 799 / 1,603 / 2,443 us; independent wavefronts 795 / 861 / 1,725 / 2,503;
+  // 24,576 envs 1,523 against 1,329)
+  if constexpr (S::N == 8) {
+    const uint32_t blocks = (A.r.TE + 63) / 64;
+    if (mode == kPolicyBf && (!runs || A.r.E % 64 == 0) && (blocks <= cus || (blocks - 1) % cus * 10 >= cus * 9) && A.r.TE <= kWholeLaunchEnvs &&
+        A.r.TE > waves_block_envs(8) * cus)
+      return tag_rollout_impl<S, kPolicyBf>(A, packed, nullptr, s);
   }
   if constexpr (kRows) {
     if (rows) {
       if constexpr (kRowsAc) {
         // Batches just beyond the small-batch kernel's: the rows of 64-env blocks over wavefronts of 32 rows, one per
         // SIMD, up to two blocks per CU (1.55x)
-        if ((A.r.TE + 63) / 64 <= 2 * compute_units())
+        if ((A.r.TE + 63) / 64 <= 2 * cus)
           return ac ? tag_policy_impl<S, 64, 32, true>(mode, A, packed, packed_critic, s)
                     : tag_policy_impl<S, 64, 32, false>(mode, A, packed, nullptr, s);
         if (ac) return tag_policy_impl<S, kAcEnvs, 64, true>(mode, A, packed, packed_critic, s);
