@@ -706,6 +706,12 @@ hipError_t launch_n(const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s
     return taken || e != hipSuccess ? e : launch_waves_spread(N, BF, small_args(A), pb.packed, nullptr, s);
   } else {
   const uint32_t cus = compute_units();
+  // Runs that are a multiple of 16 envs but not of 32 suit the small-batch kernel only, but for bf16 weights and 2 agents
+  // beyond 6 blocks of 16 envs per CU: such blocks here (2,048 / 4,096 runs x 16 envs x 64 steps 207 / 441 us against 306 / 527).
+  if constexpr (N == 2 && BF) {
+    if (!one_run && A.E % 16 == 0 && A.E % 32 != 0 && A.TE > 96 * cus && A.TE <= kWholeLaunchEnvs)
+      return per_agent ? rollout_impl<N, 16, 1, true, false, BF, 32>(A, pb, s) : rollout_impl<N, 16, 1, false, false, BF, 32>(A, pb, s);
+  }
   // runs of 32 envs (not 64) have a dense block shape of their own below, the faster one beyond 4 16-env blocks per CU
   const bool runs32 = !one_run && A.E % 32 == 0 && A.E % 64 != 0;
   if ((one_run || A.E % 16 == 0) && !(runs32 && A.TE > 64 * cus)) {
@@ -717,6 +723,12 @@ hipError_t launch_n(const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s
   // per CU holds the batch, that is faster than 64-env blocks (40,960 envs: 0.96 against 1.2 ms)
   if constexpr (N == 3 && !BF) {
     if (one_run && A.TE <= 168 * cus) return launch_waves_spread(N, BF, small_args(A), pb.packed, nullptr, s);
+  }
+  // The same gap with bf16 weights: 32-env blocks of 32-row wavefronts while four per CU hold the batch (32,768 envs 629
+  // us, 64-env blocks 679; 49,152 envs 1,038 against 911).
+  if constexpr (N == 3 && BF) {
+    if ((one_run || A.E % 32 == 0) && A.TE <= 128 * cus)
+      return per_agent ? rollout_impl<N, 32, 1, true, false, BF, 32>(A, pb, s) : rollout_impl<N, 32, 1, false, false, BF, 32>(A, pb, s);
   }
   if (one_run && A.TE / 256 >= compute_units())
     return per_agent ? rollout_impl<N, 256, 3, true, false, BF>(A, pb, s) : rollout_impl<N, 256, 3, false, false, BF>(A, pb, s);
@@ -762,6 +774,16 @@ hipError_t launch_ac_n(const RolloutArgs& A, const PolicyBuffers& pb, const Poli
     const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), half_empty_waves(A, N), pb.packed, critic.packed, s, &taken);
     return taken || e != hipSuccess ? e : launch_waves_spread(N, BF, small_args(A), pb.packed, critic.packed, s);
   } else {
+  // Runs that are no multiple of 64 envs suit the small-batch kernel only, but for bf16 weights and runs of a multiple of
+  // 32: blocks of 32 envs here with 2 agents between 5 and 8 16-env blocks per CU (24,576 envs 703 against 743 us; 65,536
+  // envs 1,830 against 1,770) and with 3 agents between 6 and 8, one full round of them, and beyond 12 (24,576 envs 984
+  // against 961, 32,768 envs 1,138 against 1,288, 65,536 envs 2,374 against 2,508).
+  if constexpr (N >= 2 && BF) {
+    const uint32_t cus = compute_units();
+    if (!one_run && A.E % 32 == 0 && A.E % 64 != 0 && ((A.TE > (N == 2 ? 80 : 96) * cus && A.TE <= 128 * cus) || (N == 3 && A.TE > 192 * cus && A.TE <= kWholeLaunchEnvs)))
+      return per_agent ? rollout_impl<N, 32, 1, true, true, BF, 32>(A, pb, s, critic.packed)
+                       : rollout_impl<N, 32, 1, false, true, BF, 32>(A, pb, s, critic.packed);
+  }
   if (one_run || A.E % 16 == 0) {
     bool taken = false;
     const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), A.E % 64 != 0, pb.packed, critic.packed, s, &taken);

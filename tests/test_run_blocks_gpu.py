@@ -15,10 +15,11 @@ TAG_RUNS = [(4, 0, 0, 16, 3.4, 3.7), (4, 0, 0, 160, 3.0, 9.0), (4, 1, 0, 16, 2.7
             (8, 1, 0, 48, 1.1, 1.5), (8, 1, 1, 16, 1.4, 1.7), (2, 1, 0, 16, 4.4, 4.8), (2, 1, 1, 48, 3.4, 3.7),
             # runs that stay with the small-batch kernel or end inside a block of independent wavefronts
             (5, 0, 1, 32, 1.2, 2.9), (6, 0, 0, 48, 1.2, 3.2), (10, 0, 0, 32, 1.0, 3.0)]
-SPREAD_RUNS = [(6, 0, 0, 64, 1.8, 7.0), (9, 0, 0, 32, 1.0, 5.0), (10, 0, 1, 32, 1.0, 5.0)]
+SPREAD_RUNS = [(2, 1, 0, 16, 5.8, 6.3), (2, 1, 0, 48, 5.8, 6.3), (2, 1, 1, 32, 4.8, 5.3), (2, 1, 1, 96, 7.7, 8.3), (3, 1, 1, 32, 5.8, 6.3),
+               (3, 1, 1, 32, 8.2, 12.3), (3, 1, 0, 64, 5.8, 6.3), (6, 0, 0, 64, 1.8, 7.0), (9, 0, 0, 32, 1.0, 5.0), (10, 0, 1, 32, 1.0, 5.0)]
 # one run, ragged: scenario, agents, bf16, actor-critic, 16-env blocks per CU on either side
 ONE_RUN = [("tag", 4, 1, 1, 1.9, 2.3), ("tag", 4, 1, 1, 5.9, 6.1), ("tag", 8, 1, 0, 1.9, 3.9), ("tag", 8, 1, 0, 3.9, 4.2),
-           ("spread", 10, 0, 0, 1.0, 2.0)]
+           ("spread", 3, 1, 0, 5.9, 7.9), ("spread", 3, 1, 0, 7.9, 8.2), ("spread", 10, 0, 0, 1.0, 2.0)]
 CASES = [("tag",) + c for c in TAG_RUNS] + [("spread",) + c for c in SPREAD_RUNS] + [c[:4] + (0,) + c[4:] for c in ONE_RUN]
 
 
