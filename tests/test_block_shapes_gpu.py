@@ -1,5 +1,5 @@
-"""The fused feed-forward rollout picks its block shape by batch size (32- or 64-env blocks with 32-row
-wavefronts for small batches, 64-env blocks with 64-row wavefronts, 256-env blocks of four sync groups).
+"""The fused feed-forward rollout picks its kernel and block shape by batch size (the small-batch kernel's 16-env blocks,
+independent wavefronts of whole envs, 32- or 64-env blocks, 256-env blocks of four sync groups).
 All shapes run the same arithmetic in the same order and an env's trajectory depends only on (seed, run,
 env index), so jobs of different sizes must agree bit for bit on the envs they share; sampled ranges of
 every job, including its ragged tail, are also compared with the oracle."""
@@ -42,8 +42,9 @@ def _job(mods, E, N, wd, mixed, ac, w, cw, seed):
     return out, state
 
 
-# sizes: N = 3: 32-env blocks up to 8,192 envs, 64-env blocks of six wavefronts up to 16,384, of three up to
-# 65,535, 256-env blocks from 65,536; N <= 2: 64-env blocks of 2N wavefronts below 65,536
+# sizes (256 CUs): the small-batch kernel up to 32,768 envs (24,576 with bf16 weights or a critic, for 2 agents 16,384 and
+# with a critic 12,288); then 3 agents fp32: independent wavefronts up to 43,008, bf16: 32-env blocks up to 32,768; 64-env
+# blocks (1 and 2 agents: 32-row wavefronts) up to 65,535 (with a critic 32,767), 256-env blocks beyond
 @pytest.mark.parametrize("N,wd,mixed,ac,sizes", [
     (3, 0, False, False, (8192, 8200, 16384, 20001, 65600)),
     (3, 0, True, False, (5000, 12000, 30000)),
@@ -103,8 +104,9 @@ def _tag_job(mods, E, shape, wd, ac, w, cw, seed):
     return out, state
 
 
-# predator-prey: 32-env blocks of 32-row wavefronts up to 8,192 envs (64-env blocks up to 32,768 envs with
-# 2 agents; up to 16,384 envs for the actor-critic rollout of 4 agents), the regular blocks beyond
+# predator-prey (256 CUs): the small-batch kernel up to 12,697 envs with 4 agents (8,192 bf16 with a critic), 24,576 with 3,
+# 16,384 with 2 (12,288 with a critic); then 2 agents 64-env blocks of 32-row wavefronts up to 32,768, 4 agents independent
+# wavefronts up to 32,768 (any size with a critic), the regular blocks beyond
 @pytest.mark.parametrize("shape,wd,ac,sizes", [
     ((4, 2, 3), 0, False, (8192, 8200, 20001)),
     ((4, 2, 3), 1, False, (8000, 9000)),
@@ -190,9 +192,8 @@ def test_recurrent_block_shapes_agree_bit_for_bit_and_with_the_oracle(mods, N, s
         assert (err * prior).max() <= Hp.EPISODE_ATOL, "envs %d.. of the %d-env job" % (off, E)
 
 
-# several runs of 16 k envs each (the paper's IPPO setting on MPE is 16 envs per run, App. G): blocks of 32
-# or 16 envs inside one run, with its weights; 16 envs x 3 agents: 48 rows + 16 padding rows in two
-# wavefronts of 32
+# several runs of 16 k envs each (the paper's IPPO setting on MPE is 16 envs per run, App. G): the small-batch kernel's
+# blocks of 16 envs inside one run, with its weights (many runs: test_run_blocks_gpu.py)
 @pytest.mark.parametrize("N,E,R,wd,mixed,ac", [
     (3, 16, 40, 0, False, False), (3, 48, 5, 0, False, False), (3, 80, 3, 0, True, False), (3, 16, 9, 0, False, True),
     (3, 16, 12, 1, False, False), (1, 16, 7, 0, False, False), (2, 32, 9, 0, False, False), (2, 16, 5, 0, True, True),

@@ -1,7 +1,13 @@
 """Environment-only kernels with one lane per agent, and the ragged variant of the lane-per-env rollout: an environment's
-trajectory depends on its index alone, so a small batch repeats the first environments of a large one (another kernel)
-bit for bit, and so do single steps fed with the recorded actions."""
+trajectory depends on its index alone, so a small batch repeats the first environments of a large one bit for bit, and so
+do single steps fed with the recorded actions.  The large batch runs another kernel for 3 to 10 agents of simple spread and
+for predator-prey with 2, 3, 5, 6 and 8 agents.  Predator-prey with 4 and 10 agents has no other rollout kernel: those two
+are compared with the oracle below.  1 and 2 agents of simple spread run the writer kernel at every size (its ragged
+variant throughout, as the large batch is odd); its aligned variant with 3 agents is one more size."""
+import numpy as np
 import pytest
+
+from tests import helpers as Hp
 
 pytestmark = pytest.mark.gpu
 
@@ -29,6 +35,13 @@ def test_small_ragged_and_stepped_batches_repeat_the_large_one(scenario, agents,
     ref = [x[:, :128].clone() for x in env.rollout(T, *env.empty_traj(T))[:4]]
     last = env.rollout(1, None, None, None, None, env.empty_obs())[4][:128].clone()
     env.close()
+    if scenario == "spread" and agents == 3:            # past the lane-per-agent range, whole waves, aligned slices
+        E = 65 * torch.cuda.get_device_properties(0).multi_processor_count // 64 * 64 + 64
+        env = make(E)
+        out = env.rollout(T, *env.empty_traj(T))
+        for k in range(4):
+            assert torch.equal(out[k][:, :128], ref[k]), (E, k)
+        env.close()
     for E in (1, 21, 64, 127):
         env = make(E)
         out = env.rollout(T, *env.empty_traj(T))
@@ -43,3 +56,26 @@ def test_small_ragged_and_stepped_batches_repeat_the_large_one(scenario, agents,
             if t + 1 < T:
                 assert torch.equal(obs, ref[0][t + 1, :E]), (E, t)
         env.close()
+
+
+@pytest.mark.parametrize("shape", [(4, 2, 3), (10, 3, 8)])
+def test_predator_prey_without_another_kernel_against_the_oracle(shape):
+    """Many blocks, the last one ragged: the first envs and the last ones.  Actions, flags and episode starts as the oracle
+    has them, positions of the first steps within the episode tolerance of the parity tests."""
+    import torch
+    from oracle import Oracle
+    from paper_2311_10090_amd.binding import MpeEnv
+    T, E, n = 30, 1003, 40
+    env = MpeEnv(Hp.tag_gpu_config(E, *shape, 1, 0))
+    env.reset(9)
+    out = [o.cpu().numpy() for o in env.rollout(T, *env.empty_traj(T))]
+    torch.cuda.synchronize()
+    env.close()
+    for off in (0, E - n):
+        orc = Oracle(Hp.tag_oracle_config(n, *shape, 1, 0, env_offset=off), threads=4)
+        orc.reset(9)
+        ref = orc.rollout(T)
+        obs, act, rew, done = [o[:, off:off + n] for o in out[:4]]
+        assert np.array_equal(act, ref[1]) and np.array_equal(done, ref[3]), off
+        assert np.abs(obs[0] - ref[0][0]).max() <= 1e-6 and np.abs(obs[25] - ref[0][25]).max() <= 1e-6, off
+        assert np.abs(obs[:5] - ref[0][:5]).max() <= Hp.EPISODE_ATOL, off

@@ -1,6 +1,8 @@
 """The small-batch kernel (one 16-row tile per wavefront, service and critic wavefronts) against the kernels for full
 batches: an environment's trajectory depends on its index alone, so the first environments of a batch of any size are
-the same bit for bit.  Sizes: one env, a ragged block, two blocks; episodes of 5 steps so that resets are frequent."""
+the same bit for bit.  Sizes: one env, a ragged block, two blocks; just past one 8-env and one 16-env block per CU, both
+ragged, where other instantiations take over (16-env blocks with 6, 8 and 10 agents; operands read from LDS), as far as a
+shape's range goes; episodes of 5 steps so that resets are frequent."""
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -16,7 +18,8 @@ def test_first_envs_do_not_depend_on_the_batch(scenario, agents, landmarks, adve
     import torch
     from paper_2311_10090_amd import synth
     from paper_2311_10090_amd.binding import MpeConfig, MpeEnv
-    T, big, small = 12, 40961 if agents > 3 else 57345, (1, 21, 32)
+    cus = torch.cuda.get_device_properties(0).multi_processor_count
+    T, big, small = 12, 40961 if agents > 3 else 57345, (1, 21, 32, 8 * cus + 5, 16 * cus + 5)
     D = synth.tag_obs_dim(agents, landmarks, adversaries) if scenario == "tag" else 6 * agents
     dev = lambda arrs: [torch.from_numpy(a).cuda() for a in arrs]
     policy, critic = dev(synth.policy_weights_with_bias(3, 1, D, 64)), dev(synth.critic_weights(3, 1, D, 64))
