@@ -16,7 +16,7 @@ namespace mpe {
 
 namespace {
 
-// Envs per wavefront: the largest even number whose agents fit 64 lanes (1 agent: 64 envs).
+// Envs per wavefront: the largest even number whose agents fit 64 lanes.
 template <typename Scn>
 constexpr int wave_envs() { return 64 / Scn::N / 2 * 2; }
 
@@ -478,15 +478,20 @@ __global__ __launch_bounds__(kStepWaves * 64) void step_agents_kernel(TagArgs TA
   }
 }
 
+// Single steps: predator-prey, and simple spread from 4 agents (launch_step).
 template <typename Scn>
 hipError_t launch_agents(const TagArgs& A, hipStream_t s) {
   constexpr int EB = wave_envs<Scn>();
   const uint32_t waves = (A.r.TE + EB - 1) / EB;
   if (A.actions_in) {
-    constexpr int kThreads = kStepWaves * 64;
-    return launch_groups<kThreads>((waves + kStepWaves - 1) / kStepWaves, [&](dim3, const GridPiece& p) {
-      hipLaunchKernelGGL(step_agents_kernel<Scn>, dim3(p.end - p.first), dim3(kThreads), 0, s, A, p.first);
-    });
+    if constexpr (Scn::kTag || Scn::N > 3) {
+      constexpr int kThreads = kStepWaves * 64;
+      return launch_groups<kThreads>((waves + kStepWaves - 1) / kStepWaves, [&](dim3, const GridPiece& p) {
+        hipLaunchKernelGGL(step_agents_kernel<Scn>, dim3(p.end - p.first), dim3(kThreads), 0, s, A, p.first);
+      });
+    } else {
+      return hipErrorInvalidValue;
+    }
   }
   return launch_groups<128>(waves, [&](dim3 grid, const GridPiece& p) {
     hipLaunchKernelGGL(rollout_agents_kernel<Scn>, grid, dim3(128), 0, s, A, p);
@@ -532,8 +537,6 @@ hipError_t launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hi
     return hipErrorInvalidValue;
   }
   switch (N) {
-    case 1: return launch_agents<SpreadScn<1>>(A, s);
-    case 2: return launch_agents<SpreadScn<2>>(A, s);
     case 3: return launch_agents<SpreadScn<3>>(A, s);
     case 4: return launch_agents<SpreadScn<4>>(A, s);
     case 5: return launch_agents<SpreadScn<5>>(A, s);

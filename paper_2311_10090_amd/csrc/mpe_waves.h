@@ -475,6 +475,8 @@ float waves_cost(const RolloutArgs& A) {
 
 template <typename Scn, bool AC, bool BF>
 hipError_t launch_waves(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
+  // 3 agents of simple spread come here up to 168 envs per CU: one block of 8 always (see waves_cost)
+  if constexpr (!Scn::kTag && Scn::N == 3) return launch_waves_impl<Scn, 8, AC, BF>(A, packed, critic, s);
   const float c4 = waves_cost<Scn, 4, AC, BF>(A.r), c8 = waves_cost<Scn, 8, AC, BF>(A.r), c12 = waves_cost<Scn, 12, AC, BF>(A.r);
   if ((BF ? c4 <= c8 : c4 < c8) && c4 <= c12) return launch_waves_impl<Scn, 4, AC, BF>(A, packed, critic, s);
   if (c8 <= c12) return launch_waves_impl<Scn, 8, AC, BF>(A, packed, critic, s);

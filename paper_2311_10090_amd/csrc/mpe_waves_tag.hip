@@ -4,6 +4,12 @@
 namespace mpe {
 
 hipError_t launch_waves_tag(int N, int L, int G, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
+  // 3 agents: the actor-critic rollout only (the plain one is mpe_tag.hip's at every size)
+  if (N == 3 && L == 0 && G == 1) {
+    if (!critic) return hipErrorInvalidValue;
+    return bf16 ? launch_waves<WaveTag<3, 0, 1>, true, true>(A, packed, critic, s)
+                : launch_waves<WaveTag<3, 0, 1>, true, false>(A, packed, critic, s);
+  }
 #define X(n, l, g)                                                                                                  \
   if (N == n && L == l && G == g) {                                                                                 \
     if (bf16)                                                                                                       \
@@ -12,7 +18,7 @@ hipError_t launch_waves_tag(int N, int L, int G, bool bf16, const TagArgs& A, co
     return critic ? launch_waves<WaveTag<n, l, g>, true, false>(A, packed, critic, s)                               \
                   : launch_waves<WaveTag<n, l, g>, false, false>(A, packed, nullptr, s);                            \
   }
-  X(4, 2, 1) X(3, 0, 1) X(6, 2, 2) X(5, 2, 1) X(8, 2, 2) X(10, 3, 2)
+  X(4, 2, 1) X(6, 2, 2) X(5, 2, 1) X(8, 2, 2) X(10, 3, 2)
 #undef X
   return hipErrorInvalidValue;
 }
