@@ -234,8 +234,9 @@ struct GruSmem {
   static constexpr size_t OFF_CTAIL = OFF_DONE + 64;                                         // AC: bc, wv, bv
   // [5][B] sampling noise of the next step, where the LDS has the room (else the agent lanes draw it themselves)
   static constexpr size_t OFF_NOISE = OFF_CTAIL + (AC ? size_t(GruCriticPk::TAIL_FLOATS) * 4 : 0);
-  // (simple spread with 2 agents, actor-critic, blocks of 16 or 32 envs: 3 to 4 % slower with it)
-  static constexpr bool kAhead = OFF_NOISE + LOGIT_BYTES <= 160 * 1024 && !(AC && !Scn::kTag && N == 2 && EB < 64);
+  // (simple spread with 2 agents, actor-critic, blocks of 16 envs: 3 to 4 % slower with it, 1,024 / 4,096 envs x 64 steps 265 / 268
+  // us against 274 / 277; in blocks of 32, 8,192 envs, 452 against 445)
+  static constexpr bool kAhead = OFF_NOISE + LOGIT_BYTES <= 160 * 1024 && !(AC && !Scn::kTag && N == 2 && EB == 16);
   static constexpr size_t TOTAL = OFF_NOISE + (kAhead ? LOGIT_BYTES : 0);
   // AC: the partial values, [8][B] floats, live behind the logits in the dead observation tile (written in the
   // second-layer phase, read by the agent lanes before they write the next observation)
