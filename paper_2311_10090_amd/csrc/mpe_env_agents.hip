@@ -76,8 +76,16 @@ __device__ __forceinline__ void draw_fresh(float2* fresh, int el, int i, bool st
   }
 }
 
-template <typename Scn>
-__global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, GridPiece piece) {
+// The groups of a launch that is not in pieces.  A form of its own, because the time of the step loops hangs on where
+// their code lies: with a GridPiece for all, which moves it by 12 bytes, 8,192 envs x 6 agents of
+// predator-prey took 134 instead of 117 us, 1,000 envs x 10 agents 138 instead of 129, 10,000 x 3 66.4 instead of 65.6.
+struct WholeGrid {
+  uint32_t end, per_xcd;
+};
+__device__ __forceinline__ uint32_t xcd_group(const WholeGrid& p) { return (blockIdx.x & 7u) * p.per_xcd + (blockIdx.x >> 3); }
+
+template <typename Scn, typename Piece>
+__global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece piece) {
   using M = AgentsSmem<Scn>;
   using TS = typename Scn::Shape;
   constexpr bool kTag = Scn::kTag;
@@ -494,7 +502,8 @@ hipError_t launch_agents(const TagArgs& A, hipStream_t s) {
     }
   }
   return launch_groups<128>(waves, [&](dim3 grid, const GridPiece& p) {
-    hipLaunchKernelGGL(rollout_agents_kernel<Scn>, grid, dim3(128), 0, s, A, p);
+    if (p.first == 0 && p.end == waves) hipLaunchKernelGGL((rollout_agents_kernel<Scn, WholeGrid>), grid, dim3(128), 0, s, A, WholeGrid{p.end, p.per_xcd});
+    else hipLaunchKernelGGL((rollout_agents_kernel<Scn, GridPiece>), grid, dim3(128), 0, s, A, p);
   });
 }
 
