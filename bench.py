@@ -232,7 +232,7 @@ def main():
         mixed = {"fused_agent_steps_per_s": agent_steps / (w3 / k), "fused_kernel_ms_avg": float(np.mean(k3)),
                  "env_only_agent_steps_per_s": agent_steps / (w4 / k), "env_only_kernel_ms_avg": float(np.mean(k4)),
                  "bytes_per_env_step": bytes_per_env_step(N, D) + 4 * (N - 1),
-                 "note": "MPE_REWARD_MIXED, local_ratio 0.5; env-only at N <= 3 uses the general one-wave-per-64-envs kernel"}
+                 "note": "MPE_REWARD_MIXED, local_ratio 0.5; env-only kernels as in the shared mode, with one more round of stores"}
         env3.close()
         del b3
 
@@ -291,8 +291,8 @@ def main():
                 "agent_steps_per_s": nruns * per_run * N * T / (w7 / k), "kernel_ms_avg": float(np.mean(k7))}
             env7.close()
             del b7
-        runs16["note"] = ("one set of weights per run; runs of 16 envs x 3 agents are blocks of 48 rows + 16 padding rows "
-                          "in two wavefronts; multiples of 64 envs per run (cfg4) are the fast shape")
+        runs16["note"] = ("one set of weights per run; runs of 16 envs run in the small-batch kernel's 16-env blocks, runs of 32 in "
+                          "32-env blocks of 32-row wavefronts; multiples of 64 envs per run (cfg4) are the fast shape")
 
     # second scenario (predator-prey, 3 adversaries + 1 good agent + 2 obstacles) at the same number of
     # envs and steps: fused fp32 policy 16 -> 64 -> 64 -> 5 and env-only with uniform actions
@@ -338,12 +338,12 @@ def main():
         tag["actor_critic"] = {"agent_steps_per_s": t_steps / dt6, "ms_per_rollout": dt6 * 1e3,
                                "flop_per_agent_step": ac_flop, "fp32_equivalent_TFLOPs": ac_flop * t_steps / dt6 / 1e12,
                                "frac_of_fp32_matrix_peak": ac_flop * t_steps / dt6 / 1e12 / MFMA_FP32_PEAK_TFLOPS,
-                               "note": "mpe_rollout_ac, wall time per call; 128-env blocks of 8 wavefronts around both staged networks"}
+                               "note": "mpe_rollout_ac, wall time per call; independent wavefronts of 16 whole envs (rollout_waves_kernel), 8 around both staged networks"}
         env6.close()
         del b6
         tag["config"] = {"scenario": "MPE_SCENARIO_TAG", "envs": wl.num_envs, "agents": tN, "adversaries": tA,
                          "landmarks": tL, "obs_dim": tD, "T": T, "bytes_per_env_step": t_bytes,
-                         "kernel": "tag_rollout_kernel (lane per agent; policy / uniform variants)"}
+                         "kernel": "tag_rollout_kernel (plain policies), rollout_waves_kernel (actor-critic), rollout_agents_kernel (uniform actions)"}
 
     # recurrent policy (GRU 128, bf16) on the headline env shape
     gru = {}
@@ -433,7 +433,7 @@ def main():
         "value_by_seed": by_seed,
         "roofline": {
             "kernel": (("rollout_policy_f32_reg_kernel" if wl.num_runs > 1 and wl.num_envs % 64 == 0 and TE >= 65536
-                        else "rollout_policy_f32_kernel") if wl.weight_dtype == 0 else "rollout_policy_kernel")
+                        else "rollout_small_kernel" if TE <= 16384 else "rollout_policy_f32_kernel") if wl.weight_dtype == 0 else "rollout_policy_kernel")
                       + " (fused, one launch per step)",
             # What binds the kernel is vector-instruction issue (operand split, tanh, Philox, env step; the
             # SQ counters below), not the matrix cores and not HBM.  `achieved` is the algorithmic work, the
@@ -462,8 +462,8 @@ def main():
             })(192 if (wl.weight_dtype == 0 and N >= 2) else 216 if wl.weight_dtype == 0 else 208 if H == 128 else 56),
         },
         "env_only": {
-            "kernel": ("rollout_uniform_ws_kernel" if N <= 3 else
-                       "rollout_policy_kernel<..., UNIFORM> (lane per agent)" if N == 10 else "rollout_uniform_kernel")
+            "kernel": ("rollout_agents_kernel (lane per agent)" if N == 3 and TE <= 16384 else "rollout_uniform_ws_kernel" if N <= 3 else
+                       "rollout_policy_kernel<..., UNIFORM> (lane per agent)")
                       + " (seeded uniform actions, one launch per step)",
             "agent_steps_per_s": agent_steps / (wall2 / args.steps),
             "env_steps_per_s": TE * T / (wall2 / args.steps),

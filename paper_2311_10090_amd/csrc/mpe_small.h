@@ -675,8 +675,8 @@ hipError_t launch_small_eb(const TagArgs& A, const void* packed, const void* cri
 }
 
 // *taken: whether the rollout was launched here.  unfit: runs that suit no block of the other kernels, which the caller
-// knows; they always come here (1,024 runs x 16 envs x 3 agents 491 us against 682 in the 16-env blocks of half-filled
-// wavefronts that such runs used before, actor-critic 886 against 2,094; predator-prey: see run_blocks16 in mpe_tag.hip).
+// knows; they always come here (1,024 runs x 16 envs x 3 agents 473 us against 596 in the 16-env blocks of half-filled
+// wavefronts that such runs used before, actor-critic 883 against 2,044; predator-prey: see run_blocks16 in mpe_tag.hip).
 template <typename Scn, bool AC, bool BF>
 hipError_t launch_small(const TagArgs& A, bool unfit, const void* packed, const void* critic, hipStream_t s, bool* taken) {
   constexpr int N = Scn::N;
