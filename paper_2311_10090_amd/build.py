@@ -11,7 +11,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmpe.so")
 CALL = os.path.join(HERE, "_mpe_call.so")
-SOURCES = ["mpe_api.hip", "mpe_env_kernels.hip", "mpe_env_agents.hip", "mpe_policy_wide.hip", "mpe_policy_f32.hip", "mpe_policy_dispatch.hip", "mpe_tag.hip", "mpe_policy_gru.hip", 
+SOURCES = ["mpe_api.hip", "mpe_env_kernels.hip", "mpe_env_agents.hip", "mpe_policy_wide.hip", "mpe_policy_f32.hip", "mpe_policy_dispatch.hip", "mpe_tag.hip", "mpe_policy_gru.hip", "mpe_gru_waves.hip",
            "mpe_small_spread.hip", "mpe_small_spread_ac.hip", "mpe_small_tag.hip", "mpe_small_tag_ac.hip", "mpe_waves_spread.hip",
            "mpe_waves_tag.hip"]
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-fno-gpu-rdc",

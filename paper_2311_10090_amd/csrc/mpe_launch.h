@@ -169,8 +169,8 @@ hipError_t ensure_policy_bytes(PolicyBuffers& pb, size_t bytes);
 // Recurrent policy (hidden 128, bf16): simple spread with 1..3 agents.
 // tag: the predator-prey scenario with (N, L, G) agents, landmarks, good agents; otherwise simple spread (L, G unused)
 bool gru_supported(bool tag, int N, int L, int G, int H, int weight_dtype);
-// D = observation width of the scenario
-hipError_t pack_policy_gru(PolicyBuffers& pb, int D, int R, const float* We, const float* be, const float* Wi,
+// D = observation width of the scenario, TE, E = all envs, envs per run
+hipError_t pack_policy_gru(PolicyBuffers& pb, bool tag, int N, int D, uint32_t TE, uint32_t E, const float* We, const float* be, const float* Wi,
                            const float* bi, const float* Wh, const float* bh, const float* Wf, const float* bf,
                            const float* Wo, const float* bo, hipStream_t s);
 // hidden: [TE][N][128] fp32, read at the start and written at the end of the rollout; A.tg is read by the
@@ -180,8 +180,8 @@ hipError_t pack_policy_gru(PolicyBuffers& pb, int D, int R, const float* We, con
 hipError_t launch_rollout_gru(bool tag, int N, int L, int G, const TagArgs& A, const PolicyBuffers& pb, const void* critic,
                               float* hidden, hipStream_t s, const char** why);
 // Critic head of the recurrent actor-critic: Wc [R][128][128], bc [R][128], wv [R][128], bv [R]
-hipError_t pack_gru_critic(PolicyBuffers& pb, int R, const float* Wc, const float* bc, const float* wv, const float* bv,
-                           hipStream_t s);
+hipError_t pack_gru_critic(PolicyBuffers& pb, int N, int D, uint32_t TE, uint32_t E, const float* Wc, const float* bc, const float* wv,
+                           const float* bv, hipStream_t s);
 // One lane per agent (mpe_env_agents.hip), both scenarios: one step under A.actions_in (reward, done and obs after the
 // step through A.r.rew_traj, done_traj, last_obs), or, with A.actions_in null, a rollout with uniform actions.
 // Whether its rollout is the faster one for this batch.

@@ -32,12 +32,45 @@
 // predator-prey shape; the network phases see only rows, the two agent phases hold the scenario's own
 // transition, rewards, reset and observation.  Observations wider than 32 entries (6 and more agents of
 // simple spread) enter the embedding as two K slices.
+#include "mpe_gru_waves.h"
 #include "mpe_mlp64.h"
 #include "mpe_tag_device.h"
 
 namespace mpe {
 
 namespace {
+
+// The largest block (in envs) whose activations fit the LDS: 64 envs for up to 3 agents, 32 envs for up to 6
+// agents whose observation fits one K slice, 16 envs otherwise.
+constexpr int gru_max_envs(int N, int D) { return N <= 3 ? 64 : ((N <= 6 && D <= 32) ? 32 : 16); }
+
+// Envs in a block for a batch of one run: smaller ones while each still gets a CU to itself.
+inline uint32_t gru_block_envs(int N, int D, uint32_t envs) {
+  const uint32_t kmax = uint32_t(gru_max_envs(N, D)), cus = compute_units();
+  if (kmax == 16 || (envs + 15) / 16 <= cus) return 16;
+  return kmax == 32 || (envs + 31) / 32 <= cus ? 32 : 64;
+}
+
+// Envs of a batch, from the first on, that run in independent wavefronts (mpe_gru_waves.hip); the rest runs in blocks.
+// Three choices: all in blocks, whole rounds of independent wavefronts (a block of them per CU) and the rest in blocks, or
+// everything in independent wavefronts; the shortest by this estimate, in units of such a round, which takes the same
+// time whatever its last block holds.  A round of blocks costs what its envs are of that round, times 1.1 to 1.2 (1.17 to 1.37,
+// and 1.65 for 8 and more agents of simple spread, with a critic) by the block's size.  Measured, 64 steps, plain / critic, us: 3 agents, a round of
+// 20,480 envs 1,066 / 1,298, blocks for 4,096, 8,192 and 16,384 envs 272 / 367, 469 / 641, 920 / 1,200; 6 agents, a round of 10,240
+// envs 1,137 / 1,373, blocks for 4,096 522 / 733; 10 agents, 6,144 envs 1,258 / 1,499, blocks for 4,096 1,040 / 1,808; 1 agent, 65,536 envs
+// 1,034 / 1,250, blocks for 16,384 306 / 413.  Several runs stay in blocks, which stage a run's weights once for all their steps.
+uint32_t gru_waves_envs(int N, int D, bool ac, uint32_t TE, uint32_t E) {
+  if (TE != E) return 0;
+  const uint32_t cus = compute_units(), round = cus * gru_waves_block_envs(N), full = TE / round, rest = TE % round;
+  auto blocks = [&](uint32_t envs) {
+    const uint32_t eb = gru_block_envs(N, D, envs), n = cus * eb;
+    const float each = ac ? (eb == 16 ? (N >= 8 && D > 32 ? 1.65f : 1.37f) : (eb == 32 ? 1.24f : 1.17f)) : (eb == 16 ? 1.2f : (eb == 32 ? 1.12f : 1.1f));
+    return float((envs + n - 1) / n) * float(n) / float(round) * each;
+  };
+  const float all = blocks(TE), some = float(full) + blocks(rest), none = float(full + (rest != 0));
+  if (all <= some && all <= none) return 0;
+  return some <= none ? TE - rest : TE;
+}
 
 constexpr int kG = 128;    // hidden width of every layer
 constexpr int kAS = 272;   // bytes per activation row in LDS: 128 bf16 + 16 bytes of padding
@@ -97,6 +130,7 @@ struct GruPk {
   static constexpr int BIAS_FLOATS = 6 * kG + 16;
   static constexpr size_t BYTES = OFF_BIAS + size_t(BIAS_FLOATS) * 4;   // one run; runs follow each other
   static_assert(BYTES % 16 == 0, "images of consecutive runs stay 16-byte aligned");
+  static_assert(BYTES == kGruImageBytes);
   static constexpr int N_EMB = 8 * 2 * 64 * 8, N_GRU = 8 * 24 * 64 * 8, N_FC = 8 * 4 * 64 * 8, N_OUT = 4 * 64 * 8;
   static constexpr int THREADS = N_EMB + N_GRU + N_FC + N_OUT + BIAS_FLOATS;
 };
@@ -177,6 +211,7 @@ struct GruCriticPk {
   static constexpr int TAIL_FLOATS = 2 * kG + 4;
   static constexpr size_t BYTES = OFF_TAIL + size_t(TAIL_FLOATS) * 4;
   static_assert(BYTES % 16 == 0, "images of consecutive runs stay 16-byte aligned");
+  static_assert(BYTES == kGruCriticImageBytes);
   static constexpr int N_FC = 8 * 4 * 64 * 8;
   static constexpr int THREADS = N_FC + TAIL_FLOATS;
 };
@@ -261,7 +296,7 @@ template <typename Scn, int EB, bool AC>
 __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint8_t* __restrict__ packed,
                                                           const uint8_t* __restrict__ packed_critic,
                                                           float* __restrict__ hidden, int per_run_weights,
-                                                          uint32_t groups, uint32_t groups_per_xcd) {
+                                                          uint32_t first_env, uint32_t groups, uint32_t groups_per_xcd) {
   using M = GruSmem<Scn, EB, AC>;
   using TS = typename Scn::Shape;                      // predator-prey only
   constexpr bool kTag = Scn::kTag;
@@ -298,7 +333,7 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   const size_t TE = A.TE;
   const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
   if (grp >= groups) return;  // whole block, before any barrier
-  const size_t g0 = size_t(grp) * EB;
+  const size_t g0 = first_env + size_t(grp) * EB;
   const size_t left = TE - g0;
   const int nvalid = left < size_t(EB) ? int(left) : EB;   // valid envs of this block
   const int vrows = nvalid * N;                            // valid agent rows
@@ -758,43 +793,40 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   }
 }
 
+// The envs from `first` on.
 template <typename Scn, int EB, bool AC>
-hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, hipStream_t s) {
+hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, uint32_t first, hipStream_t s) {
   using M = GruSmem<Scn, EB, AC>;
   auto kern = rollout_gru_kernel<Scn, EB, AC>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed); e != hipSuccess) return e;
-  const uint32_t groups = (A.r.TE + EB - 1) / EB;
+  const uint32_t groups = (A.r.TE - first + EB - 1) / EB;
   const uint32_t per_xcd = (groups + 7) / 8;
   hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(512), M::TOTAL, s, A, static_cast<const uint8_t*>(pb.packed),
-                     static_cast<const uint8_t*>(critic), hidden, int(A.r.TE != A.r.E), groups, per_xcd);
+                     static_cast<const uint8_t*>(critic), hidden, int(A.r.TE != A.r.E), first, groups, per_xcd);
   return hipGetLastError();
-}
-
-// The largest block (in envs) whose activations fit the LDS: 64 envs for up to 3 agents, 32 envs for up to 6
-// agents whose observation fits one K slice, 16 envs otherwise.
-template <typename Scn>
-constexpr int gru_max_envs() {
-  return Scn::N <= 3 ? 64 : ((Scn::N <= 6 && Scn::D <= 32) ? 32 : 16);
 }
 
 template <typename Scn, bool AC>
 hipError_t rollout_gru_sized(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, hipStream_t s) {
+  constexpr int kMax = gru_max_envs(Scn::N, Scn::D);
+  const bool runs = A.r.TE != A.r.E;
+  const uint32_t first = gru_waves_envs(Scn::N, Scn::D, AC, A.r.TE, A.r.E), rest = A.r.TE - first;
+  if (first) {
+    hipError_t e = launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, A, pb.packed, critic, hidden, first, s);
+    if (e != hipSuccess || rest == 0) return e;
+  }
   // Smaller blocks while each still gets a CU to itself (measured per 128-step rollout, 3 agents: 16-env
   // blocks 0.57-0.60 ms up to 4,096 envs and 32-env blocks 0.96-1.01 ms up to 8,192 envs against 1.9 ms with
   // 64-env blocks; with more blocks than CUs the largest blocks are the fastest).
   // With one set of weights per run a block must lie inside a run: the largest of 64, 32, 16 that divides
   // the run size bounds the choice.
-  constexpr int kMax = gru_max_envs<Scn>();
-  const uint32_t cus = compute_units();
-  const bool runs = A.r.TE != A.r.E;
-  if (kMax == 16 || (A.r.TE + 15) / 16 <= cus || (runs && A.r.E % 32 != 0))
-    return rollout_gru_blocks<Scn, 16, AC>(A, pb, critic, hidden, s);
+  const uint32_t eb = gru_block_envs(Scn::N, Scn::D, rest);
+  if (eb == 16 || (runs && A.r.E % 32 != 0)) return rollout_gru_blocks<Scn, 16, AC>(A, pb, critic, hidden, first, s);
   if constexpr (kMax >= 32) {
-    if (kMax == 32 || (A.r.TE + 31) / 32 <= cus || (runs && A.r.E % 64 != 0))
-      return rollout_gru_blocks<Scn, 32, AC>(A, pb, critic, hidden, s);
+    if (eb == 32 || (runs && A.r.E % 64 != 0)) return rollout_gru_blocks<Scn, 32, AC>(A, pb, critic, hidden, first, s);
   }
-  if constexpr (kMax >= 64) return rollout_gru_blocks<Scn, 64, AC>(A, pb, critic, hidden, s);
+  if constexpr (kMax >= 64) return rollout_gru_blocks<Scn, 64, AC>(A, pb, critic, hidden, first, s);
   return hipErrorInvalidValue;
 }
 
@@ -834,19 +866,34 @@ bool gru_supported(bool tag, int N, int L, int G, int H, int weight_dtype) {
   return false;
 }
 
-hipError_t pack_policy_gru(PolicyBuffers& pb, int D, int R, const float* We, const float* be, const float* Wi,
+hipError_t pack_policy_gru(PolicyBuffers& pb, bool tag, int N, int D, uint32_t TE, uint32_t E, const float* We, const float* be, const float* Wi,
                            const float* bi, const float* Wh, const float* bh, const float* Wf, const float* bf,
                            const float* Wo, const float* bo, hipStream_t s) {
   if (D < 1 || D > 64) return hipErrorInvalidValue;
-  if (hipError_t e = ensure_policy_bytes(pb, size_t(R) * GruPk::BYTES); e != hipSuccess) return e;
+  const uint32_t R = TE / E;
+  const int live = tag ? D : 4 * N + 2;
+  const bool waves = gru_waves_envs(N, D, false, TE, E) || gru_waves_envs(N, D, true, TE, E);
+  const size_t bytes = size_t(R) * GruPk::BYTES + (waves ? GruWavePk::bytes((live + 31) / 32) : 0);
+  if (hipError_t e = ensure_policy_bytes(pb, bytes); e != hipSuccess) return e;
+  if (waves) {
+    hipError_t e = pack_gru_waves(static_cast<uint8_t*>(pb.packed) + GruWavePk::base(), D, live, We, be, Wi, bi, Wh, bh, Wf, bf, Wo, bo, s);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(pack_gru_kernel, dim3((GruPk::THREADS + 255) / 256, R), dim3(256), 0, s,
                      static_cast<uint8_t*>(pb.packed), D, We, be, Wi, bi, Wh, bh, Wf, bf, Wo, bo);
   return hipGetLastError();
 }
 
-hipError_t pack_gru_critic(PolicyBuffers& pb, int R, const float* Wc, const float* bc, const float* wv, const float* bv,
-                           hipStream_t s) {
-  if (hipError_t e = ensure_policy_bytes(pb, size_t(R) * GruCriticPk::BYTES); e != hipSuccess) return e;
+hipError_t pack_gru_critic(PolicyBuffers& pb, int N, int D, uint32_t TE, uint32_t E, const float* Wc, const float* bc, const float* wv,
+                           const float* bv, hipStream_t s) {
+  const uint32_t R = TE / E;
+  const bool waves = gru_waves_envs(N, D, true, TE, E);
+  const size_t bytes = size_t(R) * GruCriticPk::BYTES + (waves ? GruWaveCriticPk::BYTES : 0);
+  if (hipError_t e = ensure_policy_bytes(pb, bytes); e != hipSuccess) return e;
+  if (waves) {
+    hipError_t e = pack_gru_waves_critic(static_cast<uint8_t*>(pb.packed) + GruWaveCriticPk::base(), Wc, bc, wv, bv, s);
+    if (e != hipSuccess) return e;
+  }
   hipLaunchKernelGGL(pack_gru_critic_kernel, dim3((GruCriticPk::THREADS + 255) / 256, R), dim3(256), 0, s,
                      static_cast<uint8_t*>(pb.packed), Wc, bc, wv, bv);
   return hipGetLastError();
