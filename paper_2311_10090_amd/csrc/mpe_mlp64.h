@@ -6,7 +6,7 @@
 //   S::KIN       leading inputs of a row that the first layer reads (<= 64; the rest of the row is
 //                zero in every observation); up to 16 inputs ride in half of an instruction's K
 //                positions and the other half carries a second term (S::kWideIn false), 17..32 inputs
-//                fill the K slice and layer 1 takes five instructions per product,
+//                fill the K slice and layer 1 takes the six instructions of any other product,
 //                33..64 inputs are two such slices (S::kSlices1)
 //   S::kRowTerms layer 3 with the weight terms along the output rows (needs 7 scratch floats per row)
 #pragma once
@@ -31,7 +31,6 @@ typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kH = 64;                    // hidden width
 constexpr float kPre = 2.0f * kLog2e;     // both tanh layers get pre-activations already times 2*log2(e)
-constexpr double kPreExact = 2.8853900817779268;   // the same in double, for the weights
 
 // ------------------------------------------------------------------------------ operand splits
 // fp32 products on the 16-bit matrix cores: an operand is a sum of fp16 terms, a product the sum of the cross
@@ -45,19 +44,13 @@ constexpr double kPreExact = 2.8853900817779268;   // the same in double, for th
 // precision fma that reads the fp16 half in place (v_fma_mix_f32): 7 instructions per PAIR of values, and
 // the packed pairs are the matrix operands as they are.  (An fp32 = 3 x bf16 split, 8 + 8 + 8 bits, is exact
 // everywhere but costs 11 instructions per pair: and, sub, and, sub per value and three byte-permutes.)
-// Used for the observations.
+// Used for the observations and the weights of layers 1 and 3.
 // Two terms, each rounded to NEAREST (split2_pair below): 4 instructions per pair, |x - h - m| <= 2^-23 |x|,
 // one unit in the last place of fp32.  Used where the operand already carries an error of that size: the
-// hidden activations (outputs of the hardware tanh, ~1e-7 absolute).
-// Weights are split once, by the pack kernel (split_weight), from the exact double product with 2 log2(e), every term
-// rounded to nearest: three terms for layers 1 and 3, two for layer 2.
-// Error and cost: a matrix instruction takes 16 cycles of its pipe and 8 of the SIMD's issue, during which no vector
-// instruction issues (measured: 16 tanh and 16 of them, four wavefronts per SIMD, 24 cycles per tanh alone and 36 with one
-// matrix instruction each), and these kernels run at the issue rate, so an instruction that adds nothing costs its 8 cycles and
-// its energy.  Leaving the m m product out and splitting exact weights: 65,536 envs x 3 agents x 128 steps 1,491 -> 1,403
-// us, predator-prey actor-critic 3,748 -> 3,529 us; rms error against the float64 networks over 36 shapes and sizes
-// 0.74 to 0.90 (values) and 0.81 to 0.97 (log-probabilities) of what rounded fp32 products and m m gave (a plain float32
-// evaluation with a correctly rounded tanh has about half of it: it is set by the hardware tanh, not by the split).
+// hidden activations (outputs of the hardware tanh, ~1e-7 absolute) and the weights of layer 2 (stored
+// pre-scaled by 2 log2(e), a product that is itself rounded to fp32).  Measured against the float64
+// networks on 6e5 recorded rows, the outputs' mean error is 1.4e-7 with either split (a plain float32
+// evaluation with a correctly rounded tanh: 0.7e-7): it is set by the tanh, not by the split.
 typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
@@ -91,17 +84,13 @@ __device__ __forceinline__ void split2_pair(float x0, float x1, uint32_t& ph, ui
   const f32x2_ r = {sub_half<false>(ph, x0), sub_half<true>(ph, x1)};
   pm = __builtin_bit_cast(uint32_t, __builtin_convertvector(r, f16x2));
 }
-// Weights, split once by the pack kernel: the 16-bit patterns of N terms of a double, each rounded to nearest (finite
-// values beyond fp16's range give its largest one and leave the rest to the next term).
-template <int N>
-__device__ __forceinline__ void split_weight(double x, uint32_t (&t)[N]) {
-#pragma unroll
-  for (int k = 0; k < N; ++k) {
-    const bool beyond = fabs(x) > 65504.0 && fabs(x) < double(INFINITY);
-    const _Float16 h = _Float16(float(beyond ? copysign(65504.0, x) : x));
-    t[k] = __builtin_bit_cast(uint16_t, h);
-    x -= double(float(h));
-  }
+// One value: the 16-bit patterns of its three terms.
+__device__ __forceinline__ void split3(float x, uint32_t& h, uint32_t& m, uint32_t& l) {
+  uint32_t ph, pm, pl;
+  split3_pair(x, 0.0f, ph, pm, pl);
+  h = ph & 0xFFFFu;
+  m = pm & 0xFFFFu;
+  l = pl & 0xFFFFu;
 }
 
 // Packed per-run layout (bytes).  A operands of v_mfma_f32_16x16x32_f16 (fp16 terms of the split): lane (i = lane%16,
@@ -113,7 +102,7 @@ __device__ __forceinline__ void split_weight(double x, uint32_t (&t)[N]) {
 //                                 combo 0 = (h | m), combo 1 = (h | l)
 //   W1A [m 4][s][term 3][lane 64]  shapes with 17..64 inputs (kWideIn; s = K slice, one or two): k = 32 s + 8 gq + e,
 //                                 all three terms
-//   W2A [m 4][s 2][term 2][lane 64]  two terms of the pre-scaled weights
+//   W2A [m 4][s 2][term 2][lane 64]  the two-term split (split2_pair) of the pre-scaled weights
 //   W3A [s 2][term 3][lane 64]   (5 outputs padded to 16), shapes without kRowTerms only
 //   W3A [s 2][lane 64]           kRowTerms: the 16 output rows of the instruction carry the three
 //                                 terms of the 5 outputs (l3_row_* below), so ONE A operand meets
@@ -173,41 +162,41 @@ __global__ void pack_split_kernel(uint8_t* __restrict__ packed, const float* __r
   b3 += size_t(run) * nout;
   constexpr int n1 = 4 * KS1 * 64 * 8, n2 = 4 * 2 * 64 * 8, n3 = 2 * 64 * 8, nb = 2 * kH + 16;
   int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  auto put3 = [&](size_t off, int blk, int lanes, int lane, int e, double v) {
+  auto put3 = [&](size_t off, int blk, int lanes, int lane, int e, float v) {
     // blk = index of the [term][lane] group; terms are `lanes` * 16 bytes apart
-    uint32_t t[3];
-    split_weight(v, t);
+    uint32_t h, m, l;
+    split3(v, h, m, l);
     uint16_t* base = reinterpret_cast<uint16_t*>(out + off) + size_t(blk) * 3 * lanes * 8 + lane * 8 + e;
-    base[0] = uint16_t(t[0]);
-    base[size_t(lanes) * 8] = uint16_t(t[1]);
-    base[size_t(2) * lanes * 8] = uint16_t(t[2]);
+    base[0] = uint16_t(h);
+    base[size_t(lanes) * 8] = uint16_t(m);
+    base[size_t(2) * lanes * 8] = uint16_t(l);
   };
   if (idx < n1) {
     const int e = idx % 8, lane = (idx / 8) % 64;
     if constexpr (S::kWideIn) {
       const int sl = (idx / 512) % KS1, mw = idx / (512 * KS1);
       const int k = 32 * sl + 8 * (lane / 16) + e;
-      put3(Pk::OFF_W1A, mw * KS1 + sl, 64, lane, e, k < KIN ? kPreExact * W1[size_t(k) * kH + 16 * mw + lane % 16] : 0.0);
+      put3(Pk::OFF_W1A, mw * KS1 + sl, 64, lane, e, k < KIN ? kPre * W1[size_t(k) * kH + 16 * mw + lane % 16] : 0.0f);
       return;
     }
     const int m = idx / 512;
     const int gq = lane / 16, k = 8 * (gq & 1) + e, o = 16 * m + lane % 16;
-    uint32_t t[3];
-    split_weight(k < KIN ? kPreExact * W1[size_t(k) * kH + o] : 0.0, t);
+    uint32_t h, mm, l;
+    split3(k < KIN ? kPre * W1[size_t(k) * kH + o] : 0.0f, h, mm, l);
     uint16_t* base = reinterpret_cast<uint16_t*>(out + Pk::OFF_W1A) + size_t(m) * 2 * 64 * 8 + lane * 8 + e;
-    base[0] = uint16_t(gq < 2 ? t[0] : t[1]);        // combo 0 = (h | m)
-    base[64 * 8] = uint16_t(gq < 2 ? t[0] : t[2]);   // combo 1 = (h | l)
+    base[0] = uint16_t(gq < 2 ? h : mm);        // combo 0 = (h | m)
+    base[64 * 8] = uint16_t(gq < 2 ? h : l);    // combo 1 = (h | l)
     return;
   }
   idx -= n1;
   if (idx < n2) {
     const int e = idx % 8, lane = (idx / 8) % 64, s = (idx / 512) % 2, m = idx / 1024;
     const int k = hidden_k(s, lane / 16, e), o = 16 * m + lane % 16;
-    uint32_t t[2];
-    split_weight(kPreExact * W2[size_t(k) * kH + o], t);
+    uint32_t ph, pm;
+    split2_pair(kPre * W2[size_t(k) * kH + o], 0.0f, ph, pm);
     uint16_t* base = reinterpret_cast<uint16_t*>(out + Pk::OFF_W2A) + size_t(m * 2 + s) * 2 * 64 * 8 + lane * 8 + e;
-    base[0] = uint16_t(t[0]);
-    base[64 * 8] = uint16_t(t[1]);
+    base[0] = uint16_t(ph & 0xFFFFu);
+    base[64 * 8] = uint16_t(pm & 0xFFFFu);
     return;
   }
   idx -= n2;
@@ -217,10 +206,10 @@ __global__ void pack_split_kernel(uint8_t* __restrict__ packed, const float* __r
     if constexpr (S::kRowTerms) {
       const int out_o = l3_row_output(o), term = l3_row_term(o);
       uint32_t t3[3] = {0u, 0u, 0u};
-      if (out_o >= 0 && out_o < nout) split_weight(W3[size_t(k) * nout + out_o], t3);
+      if (out_o >= 0 && out_o < nout) split3(W3[size_t(k) * nout + out_o], t3[0], t3[1], t3[2]);
       reinterpret_cast<uint16_t*>(out + Pk::OFF_W3A)[(size_t(s) * 64 + lane) * 8 + e] = uint16_t(t3[term]);
     } else {
-      put3(Pk::OFF_W3A, s, 64, lane, e, o < nout ? W3[size_t(k) * nout + o] : 0.0);
+      put3(Pk::OFF_W3A, s, 64, lane, e, o < nout ? W3[size_t(k) * nout + o] : 0.0f);
     }
     return;
   }
@@ -281,29 +270,29 @@ __device__ __forceinline__ Terms split_activation(const float (&v)[8]) {
 #define MPE_MFMA_SPLIT(A, B, C) \
   __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, A), __builtin_bit_cast(f16x8, B), C, 0, 0, 0)
 
-// The product of the two middle terms is left out everywhere but in the 16-input layer 1, where it rides along: the
-// weights' terms are rounded to nearest, so their middle term is at most 2^-12 of the weight with a random sign, and m m
-// at most 2^-23 (three-term inputs, truncated) or 2^-24 of a product (activations), a fraction of one rounding of the fp32
-// accumulator it would be added to.
-// acc += A * B, three-term weights a against three-term inputs b: the five cross terms that matter, smallest first.
+// acc += A * B from the six cross terms of weight >= 2^-22 (terms h, m, l weigh 1, 2^-11, 2^-22; the
+// dropped m l, l m, l l are below 2^-33 of the product), smallest first.
 __device__ __forceinline__ f32x4 mma_split(const Terms& a, const Terms& b, f32x4 acc) {
   acc = MPE_MFMA_SPLIT(a.l, b.h, acc);
   acc = MPE_MFMA_SPLIT(a.h, b.l, acc);
+  acc = MPE_MFMA_SPLIT(a.m, b.m, acc);
   acc = MPE_MFMA_SPLIT(a.m, b.h, acc);
   acc = MPE_MFMA_SPLIT(a.h, b.m, acc);
   acc = MPE_MFMA_SPLIT(a.h, b.h, acc);
   return acc;
 }
 
-// Two-term operands on both sides (terms h, m of a and b): three cross terms, smallest first.
+// Two-term operands on both sides (terms h, m of a and b): the four cross terms, smallest first.
 __device__ __forceinline__ f32x4 mma_split22(const Terms& a, const Terms& b, f32x4 acc) {
+  acc = MPE_MFMA_SPLIT(a.m, b.m, acc);
   acc = MPE_MFMA_SPLIT(a.m, b.h, acc);
   acc = MPE_MFMA_SPLIT(a.h, b.m, acc);
   acc = MPE_MFMA_SPLIT(a.h, b.h, acc);
   return acc;
 }
 
-// Three-term weights a against a two-term activation operand b (split_activation), smallest first.
+// Three-term weights a against a two-term activation operand b (split_activation): the five cross terms of
+// weight >= 2^-23, smallest first.
 __device__ __forceinline__ f32x4 mma_split_act(const Terms& a, const Terms& b, f32x4 acc) {
   acc = MPE_MFMA_SPLIT(a.l, b.h, acc);
   return mma_split22(a, b, acc);
@@ -367,10 +356,10 @@ __device__ __forceinline__ void policy_core(const uint8_t* __restrict__ wsm, con
   }
   const bf16x8* w1 = reinterpret_cast<const bf16x8*>(wsm + Pk::OFF_W1A);  // [m][combo][lane64]; kWideIn: [m][term][lane64]
   const bf16x8* w2 = reinterpret_cast<const bf16x8*>(wsm + Pk::OFF_W2A);  // [m][s][term 2][lane64]
-  // Layer 1, one output tile: six cross terms in three instructions, smallest first:
+  // Layer 1, one output tile: the six cross terms in three instructions, smallest first:
   //   (Wh | Wl) x (Xl | Xh) = hl + lh,  (Wh | Wm) x (Xm | Xm) = hm + mm,  (Wh | Wm) x (Xh | Xh) = hh + mh
   auto layer1 = [&](int m, const Terms (&b)[KS1], const bf16x8& b_lh, f32x4 acc) {
-    if constexpr (S::kWideIn) {   // 17..64 inputs fill one or two K slices: five cross terms, one instruction each
+    if constexpr (S::kWideIn) {   // 17..64 inputs fill one or two K slices: the six cross terms, one instruction each
 #pragma unroll
       for (int s = 0; s < KS1; ++s) {
         Terms a;
@@ -395,7 +384,7 @@ __device__ __forceinline__ void policy_core(const uint8_t* __restrict__ wsm, con
     return a;
   };
   // Layer 3, one K slice.  Row-term layout: the one A operand against the three activation terms
-  // (smallest first); otherwise the four significant ones.
+  // (all nine cross terms, smallest first); otherwise the six significant ones.
   auto layer3 = [&](const Terms& a, const Terms& b, f32x4 acc) {
     if constexpr (S::kRowTerms) {
       acc = MPE_MFMA_SPLIT(a.h, b.m, acc);

@@ -116,16 +116,16 @@ struct TileNet {
         acc2[m] = *reinterpret_cast<const f32x4*>(b + kH + 16 * m);
       }
       if constexpr (S::kWideIn) {
-        // the five cross terms, smallest first, the four tiles in turn (see mma_split)
+        // the six cross terms, smallest first, the four tiles in turn (see mma_split)
 #pragma unroll
         for (int s = 0; s < KS1; ++s)
 #pragma unroll
-          for (int x = 0; x < 5; ++x)
+          for (int x = 0; x < 6; ++x)
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-              constexpr int ta[5] = {2, 0, 1, 0, 0};             // l h m h h of the weights
+              constexpr int ta[6] = {2, 0, 1, 1, 0, 0};          // l h m m h h of the weights
               const bf16x8 a = w1((m * KS1 + s) * 3 + ta[x], zero);
-              const bf16x8 c = (x == 0 || x == 2 || x == 4) ? in[s].h : (x == 1 ? in[s].l : in[s].m);
+              const bf16x8 c = (x == 0 || x == 3 || x == 5) ? in[s].h : (x == 1 ? in[s].l : in[s].m);
               acc[m] = MPE_MFMA_SPLIT(a, c, acc[m]);
             }
       } else {
@@ -140,10 +140,10 @@ struct TileNet {
       for (int s = 0; s < 2; ++s) {
         const Terms h = tanh_split(acc[2 * s], acc[2 * s + 1]);
 #pragma unroll
-        for (int x = 0; x < 3; ++x)     // m h, h m, h h (see mma_split22)
+        for (int x = 0; x < 4; ++x)
 #pragma unroll
           for (int m = 0; m < 4; ++m)
-            acc2[m] = MPE_MFMA_SPLIT(w2((m * 2 + s) * 2 + (x == 0 ? 1 : 0), zero), x == 1 ? h.m : h.h, acc2[m]);
+            acc2[m] = MPE_MFMA_SPLIT(w2((m * 2 + s) * 2 + (x < 2 ? 1 : 0), zero), (x == 0 || x == 2) ? h.m : h.h, acc2[m]);
       }
       f32x4 z = *reinterpret_cast<const f32x4*>(b + 2 * kH);
 #pragma unroll

@@ -252,32 +252,3 @@ def test_fp32_network_outputs_are_as_close_to_float64_as_a_plain_float32_evaluat
     assert ev.mean() < 2.5e-7 and el.mean() < 2.5e-7 and ev.max() < 3e-6 and el.max() < 3e-6
     assert ev.mean() <= 3.0 * plain.mean()
     env.close()
-
-
-@pytest.mark.parametrize("N", [1, 3, 6, 10])
-def test_weights_beyond_the_range_of_fp16(mods, N):
-    """The fp32 networks hold a weight as fp16 terms: values (times 2 log2 e, as they are stored) beyond fp16's largest finite
-    one spill into the next term.  With such weights nearly every hidden unit is saturated, where tanh is exactly +-1 on both
-    sides, and the last layer adds 64 of them in fp32 (64 roundings of 2^-24 of at most 64 * 0.5).  Such a weight is held to
-    one unit of fp16 at 32,768, 32 as stored and 11 as given: a sum over 64 inputs is off by about 50 and has the wrong sign where
-    it lies that close to zero, a chance of 50 / (8 * 3e4) or 2e-4 for each of 128 units, 3 % of the rows."""
-    MpeEnv, Oracle = mods
-    E = 500
-    env, orc = MpeEnv(Hp.gpu_config(E, N, 1, 64, 0)), Oracle(Hp.oracle_config(E, N, 1, 64, 0), threads=8)
-    rng = np.random.default_rng(N)
-    w = synth.policy_weights_with_bias(3, 1, 6 * N, 64)
-    c = [np.array(a, np.float32) for a in synth.critic_weights(3, 1, 6 * N, 64)]
-    c[0] = (rng.choice([-1, 1], c[0].shape) * rng.uniform(4e4, 6e4, c[0].shape)).astype(np.float32)    # 1.7e5 as stored: three terms
-    c[2] = (rng.choice([-1, 1], c[2].shape) * rng.uniform(2e4, 4e4, c[2].shape)).astype(np.float32)    # 1.1e5 as stored: two terms
-    c[4] = rng.uniform(-0.5, 0.5, c[4].shape).astype(np.float32)
-    env.set_policy(*Hp.to_dev(w))
-    env.set_critic(*Hp.to_dev(c))
-    orc.set_critic(*c)
-    env.reset(5)
-    out = env.rollout_ac(4, *env.empty_traj_ac(4))
-    obs, val = out[0].cpu().numpy(), out[3].cpu().numpy()
-    ref = orc.value(obs.reshape(-1, 6 * N).astype(np.float64))
-    close = np.abs(val.reshape(-1) - ref) <= 64 * 32 * 2.0 ** -24
-    say("  N=%d: %.4f of %d values equal to the rounding of the last layer" % (N, close.mean(), close.size))
-    assert np.isfinite(val).all() and close.mean() >= 0.9
-    env.close()
