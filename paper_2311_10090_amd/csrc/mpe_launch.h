@@ -166,7 +166,7 @@ hipError_t launch_rollout_policy_f32(int N, bool bf16, const RolloutArgs& A, con
                                      const char** why);
 hipError_t ensure_policy_bytes(PolicyBuffers& pb, size_t bytes);
 
-// Recurrent policy (hidden 128, bf16): simple spread with 1..3 agents.
+// Recurrent policy (hidden 128, bf16): simple spread with 1..10 agents.
 // tag: the predator-prey scenario with (N, L, G) agents, landmarks, good agents; otherwise simple spread (L, G unused)
 bool gru_supported(bool tag, int N, int L, int G, int H, int weight_dtype);
 // D = observation width of the scenario, TE, E = all envs, envs per run

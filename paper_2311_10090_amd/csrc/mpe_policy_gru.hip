@@ -9,7 +9,7 @@
 // Design.  The network has 240 KB of bf16 weights, more than the 160 KB of LDS, and 236 matrix
 // instructions per 16 rows: re-reading the weights per wavefront from L2 would cost ~90 GB per
 // rollout.  So the weights are STATIONARY and the activations move: a block is 8 wavefronts around
-// 64 envs (64 N agent rows; 32 or 16 envs for small batches); wavefront u owns hidden units 16u..16u+15 of every layer and keeps
+// 64 envs (64 N agent rows; fewer, down to one 16-row tile, for small batches); wavefront u owns hidden units 16u..16u+15 of every layer and keeps
 // its 24 GRU A-operands (r, z, n gates x input/recurrent x 4 K slices) and its embedding operand
 // in registers for the whole rollout (100 of its 256 registers); the small layers' operands
 // (second fully-connected layer, logits) sit in LDS.  Activations of all rows go through LDS as
@@ -51,18 +51,36 @@ inline uint32_t gru_block_envs(int N, int D, uint32_t envs) {
   return kmax == 32 || (envs + 31) / 32 <= cus ? 32 : 64;
 }
 
+// Envs in a block of one, two or four row tiles where those lie beside 16 and 32 envs: for a batch of one run, the fewest tiles
+// for which each block gets a CU to itself; 0: blocks of 16, 32 or 64 envs.  A step's time follows the tiles of a block, every
+// phase being a loop over them.  Measured, 64 steps, plain / critic, us, blocks of 16 (32) envs -> these: 3 agents, 1 tile
+// (1,280 envs) 272 / 366 -> 162 / 219, 2 (2,560) 274 / 367 -> 216 / 289, 4 (5,376) 469 / 641 -> 341 / 468; 2 agents, 1 (2,048) 197 / 272 ->
+// 150 / 211; 6 agents, 1 (512) 517 / 724 -> 198 / 265, 2 (1,280) 519 / 728 -> 263 / 360, 4 (2,560) 524 / 729 -> 376 / 525; 10 agents, plain, 1 (256)
+// 945 -> 258, 2 (768) 952 -> 313, 4 (1,536) 957 -> 470.
+inline uint32_t gru_tile_envs(int N, int D, uint32_t envs) {
+  const uint32_t cus = compute_units();
+  for (uint32_t tiles = 1; tiles <= 4; tiles *= 2) {
+    const uint32_t eb = 16 * tiles / uint32_t(N);
+    const bool small = eb < 16, between = eb > 16 && eb < 32 && gru_max_envs(N, D) >= 32 && (envs + 15) / 16 > cus;
+    if ((small || between) && (envs + eb - 1) / eb <= cus) return eb;
+  }
+  return 0;
+}
+
 // Envs of a batch, from the first on, that run in independent wavefronts (mpe_gru_waves.hip); the rest runs in blocks.
 // Three choices: all in blocks, whole rounds of independent wavefronts (a block of them per CU) and the rest in blocks, or
 // everything in independent wavefronts; the shortest by this estimate, in units of such a round, which takes the same
 // time whatever its last block holds.  A round of blocks costs what its envs are of that round, times 1.1 to 1.2 (1.17 to 1.37,
 // and 1.65 for 8 and more agents of simple spread, with a critic) by the block's size.  Measured, 64 steps, plain / critic, us: 3 agents, a round of
 // 20,480 envs 1,066 / 1,298, blocks for 4,096, 8,192 and 16,384 envs 272 / 367, 469 / 641, 920 / 1,200; 6 agents, a round of 10,240
-// envs 1,137 / 1,373, blocks for 4,096 522 / 733; 10 agents, 6,144 envs 1,258 / 1,499, blocks for 4,096 1,040 / 1,808; 1 agent, 65,536 envs
+// envs 1,137 / 1,373, blocks for 4,096 522 / 733 (a round of smaller blocks is a small fixed time and its tiles: gru_tile_envs); 10 agents, 6,144 envs 1,258 / 1,499, blocks for 4,096 1,040 / 1,808; 1 agent, 65,536 envs
 // 1,034 / 1,250, blocks for 16,384 306 / 413.  Several runs stay in blocks, which stage a run's weights once for all their steps.
 uint32_t gru_waves_envs(int N, int D, bool ac, uint32_t TE, uint32_t E) {
   if (TE != E) return 0;
   const uint32_t cus = compute_units(), round = cus * gru_waves_block_envs(N), full = TE / round, rest = TE % round;
   auto blocks = [&](uint32_t envs) {
+    if (envs == 0) return 0.0f;
+    if (const uint32_t eb = gru_tile_envs(N, D, envs)) return 0.1f + 0.07f * float((eb * uint32_t(N) + 15) / 16);
     const uint32_t eb = gru_block_envs(N, D, envs), n = cus * eb;
     const float each = ac ? (eb == 16 ? (N >= 8 && D > 32 ? 1.65f : 1.37f) : (eb == 32 ? 1.24f : 1.17f)) : (eb == 16 ? 1.2f : (eb == 32 ? 1.12f : 1.1f));
     return float((envs + n - 1) / n) * float(n) / float(round) * each;
@@ -248,9 +266,9 @@ constexpr size_t up16(size_t x) { return (x + 15) & ~size_t(15); }
 template <typename Scn, int EB = 64, bool AC = false>
 struct GruSmem {
   static constexpr int N = Scn::N;
-  static constexpr int B = EB * N, D = Scn::D, NT = B / 16;     // rows, obs width, 16-row tiles
+  static constexpr int ROWS = EB * N, D = Scn::D, NT = (ROWS + 15) / 16, B = 16 * NT;   // agent rows, obs width, 16-row tiles, their rows
   static constexpr int KS = D <= 32 ? 1 : 2;                    // K slices of the embedding
-  static_assert(B % 16 == 0 && EB <= 64 && D <= 64 && D % 2 == 0, "whole row tiles; at most two K slices");
+  static_assert(EB <= 64 && B / N <= 64 && D <= 64 && D % 2 == 0, "a done flag per env (spare rows too); at most two K slices");
   // bf16 observation tile, 32 KS columns per row (zero beyond D); after the embedding it is dead, and the
   // logits of the same step, [5][B] floats (action-major: the agent lanes read consecutive words), are
   // stored in its place
@@ -286,9 +304,10 @@ __device__ __forceinline__ uint2 pack4_bf16(float a, float b, float c, float d) 
   return make_uint2(pack_bf16_rne(a, b), pack_bf16_rne(c, d));
 }
 
-// EB = envs per block: 64, or 32 / 16 for small batches (every phase of a step is a loop over the block's
+// EB = envs per block: 64, or fewer for small batches (every phase of a step is a loop over the block's
 // 16-row tiles, so the step latency of a block, which is the time of a rollout while every block has a CU
-// to itself, falls with its rows) and for the shapes whose activations would not fit the LDS otherwise.
+// to itself, falls with its rows) and for the shapes whose activations would not fit the LDS otherwise.  Rows of the
+// last tile that belong to no env are computed with the others and stored nowhere.
 // AC = the actor-critic rollout (packed_critic = the head of pack_gru_critic): per step also the critic's second
 // layer on the new carried state and the log-probability of the sampled action, and, when a bootstrap value
 // is asked for, one more pass of the network phases after the last step that writes nothing else.
@@ -300,7 +319,7 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   using M = GruSmem<Scn, EB, AC>;
   using TS = typename Scn::Shape;                      // predator-prey only
   constexpr bool kTag = Scn::kTag;
-  constexpr int N = Scn::N, L = Scn::L, B = M::B, D = M::D, NT = M::NT, KS = M::KS;
+  constexpr int N = Scn::N, L = Scn::L, B = M::B, ROWS = M::ROWS, D = M::D, NT = M::NT, KS = M::KS;
   constexpr int G = kTag ? TS::G : 1, NA = kTag ? TS::A : 0;   // good agents, adversaries
   const RolloutArgs& A = TA.r;
   [[maybe_unused]] const TagPhys& tg = TA.tg;
@@ -387,9 +406,10 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   static_assert(B <= 256, "a row per thread of half the block");
   const bool agent = tid < B;
   const int srow = tid & 255;                        // this lane's row as an agent or service lane
-  const int el = srow / N, i = srow - el * N;        // env within block, agent (agent and service lanes only)
+  const int erow = srow < ROWS ? srow : 0;           // spare rows of the last tile look at the block's first env and store nothing
+  const int el = erow / N, i = erow - el * N;        // env within block, agent (agent and service lanes only)
   const size_t g = g0 + el;
-  const bool in_range = srow < B && g < TE;
+  const bool in_range = srow < ROWS && g < TE;
   const bool valid = agent && in_range;
   const bool service = M::kAhead ? tid >= 256 && srow < B : agent;
   const uint32_t gc = in_range ? uint32_t(g) : uint32_t(g0);
@@ -735,7 +755,7 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
       ep += 1;
       const bool done = ep >= max_ep;
       if (done_base && env_writer) done_base[gc] = done ? 1 : 0;
-      if (i == 0) donef[el] = done ? 1 : 0;     // read by the gate phase of the next step
+      if (i == 0 && srow < ROWS) donef[el] = done ? 1 : 0;     // read by the gate phase of the next step
       if (done) {
         // new episode keyed by step + 1; every lane regenerates its whole env (1 step in max_ep)
         uint32_t env_r = env;
@@ -816,9 +836,18 @@ hipError_t rollout_gru_sized(const TagArgs& A, const PolicyBuffers& pb, const vo
     hipError_t e = launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, A, pb.packed, critic, hidden, first, s);
     if (e != hipSuccess || rest == 0) return e;
   }
-  // Smaller blocks while each still gets a CU to itself (measured per 128-step rollout, 3 agents: 16-env
-  // blocks 0.57-0.60 ms up to 4,096 envs and 32-env blocks 0.96-1.01 ms up to 8,192 envs against 1.9 ms with
-  // 64-env blocks; with more blocks than CUs the largest blocks are the fastest).
+  constexpr int kOne = 16 / Scn::N, kTwo = 32 / Scn::N, kFour = 64 / Scn::N;
+  if (const uint32_t te = runs ? 0 : gru_tile_envs(Scn::N, Scn::D, rest)) {
+    if constexpr (kOne < 16) {
+      if (te == kOne) return rollout_gru_blocks<Scn, kOne, AC>(A, pb, critic, hidden, first, s);
+    }
+    if constexpr (kTwo < 16) {
+      if (te == kTwo) return rollout_gru_blocks<Scn, kTwo, AC>(A, pb, critic, hidden, first, s);
+    }
+    if constexpr (kFour < 16 || (kFour > 16 && kFour < 32 && kMax >= 32)) {
+      if (te == kFour) return rollout_gru_blocks<Scn, kFour, AC>(A, pb, critic, hidden, first, s);
+    }
+  }
   // With one set of weights per run a block must lie inside a run: the largest of 64, 32, 16 that divides
   // the run size bounds the choice.
   const uint32_t eb = gru_block_envs(Scn::N, Scn::D, rest);
