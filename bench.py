@@ -359,7 +359,7 @@ def main():
         g_tf = g_flop * agent_steps / (ms7 * 1e-3) / 1e12
         gru = {"agent_steps_per_s": agent_steps / (w7 / k), "kernel_ms_avg": ms7, "flop_per_agent_step": g_flop,
                "roofline": {"bound": "mfma", "achieved": g_tf, "peak": 2500.0, "unit": "TFLOP/s", "frac": g_tf / 2500.0},
-               "dtype": "bf16xbf16->f32", "kernel": "rollout_gru_kernel<3> (weight-stationary, 8 wavefronts per 64 envs)",
+               "dtype": "bf16xbf16->f32", "kernel": "rollout_gru_waves_kernel<3> (independent wavefronts of 32 agent rows), remainder of whole rounds in rollout_gru_kernel",
                "note": "mpe_set_gru_policy: 18 -> 128 tanh -> GRU 128 -> 128 tanh -> 5; carried state fp32"}
         # the recurrent actor-critic on the same shape: critic head on the new carried state, bootstrap pass
         env7.set_gru_critic(*to_dev(synth.gru_critic_weights(0, 1)))

@@ -315,7 +315,8 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
     auto blend = [&](auto C, auto X) {
       constexpr int c = decltype(C)::value, rt = decltype(X)::value / 4, x = decltype(X)::value % 4;
       // (1 - z) n + z h.  In plain C++ the compiler copies n to h's register and accumulates there, two instructions; the
-      // s_nop is the wait state between the reciprocal and its use, which the compiler does not put in front of asm.
+      // s_nop is the wait state between the reciprocal and its use, which the compiler does not put in front of asm.  Of matrix
+      // instructions it needs none: in every instance the last one that touches its registers is 15 or more instructions earlier.
       const float nv = nn.t[rt][x], z = gate_sigmoid(zz.t[rt][x]), d = h[c][rt][x] - nv;
       asm("s_nop 0\n\tv_fma_f32 %0, %1, %2, %3" : "=v"(h[c][rt][x]) : "v"(z), "v"(d), "v"(nv));
     };
