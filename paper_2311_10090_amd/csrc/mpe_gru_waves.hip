@@ -314,11 +314,11 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
     Acc nn, zz;         // of the tile whose new state comes next: tanh gate, update gate before its sigmoid
     auto blend = [&](auto C, auto X) {
       constexpr int c = decltype(C)::value, rt = decltype(X)::value / 4, x = decltype(X)::value % 4;
-      // (1 - z) n + z h.  In plain C++ the compiler copies n to h's register and accumulates there, two instructions; the
-      // s_nop is the wait state between the reciprocal and its use, which the compiler does not put in front of asm.  Of matrix
-      // instructions it needs none: in every instance the last one that touches its registers is 15 or more instructions earlier.
+      // (1 - z) n + z h.  n is kept past the sum: where it ends there the compiler adds into its register and copies the sum to
+      // h's, two instructions.
       const float nv = nn.t[rt][x], z = gate_sigmoid(zz.t[rt][x]), d = h[c][rt][x] - nv;
-      asm("s_nop 0\n\tv_fma_f32 %0, %1, %2, %3" : "=v"(h[c][rt][x]) : "v"(z), "v"(d), "v"(nv));
+      h[c][rt][x] = __builtin_fmaf(z, d, nv);
+      asm volatile("" : : "v"(nv));
     };
     static_for<8>([&](auto C) {
       constexpr int c = decltype(C)::value;

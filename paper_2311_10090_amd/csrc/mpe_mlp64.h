@@ -55,14 +55,14 @@ typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
 typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
 
 // c - a, where a is the low (HI = false) or high half of a packed fp16 pair: one v_fma_mix_f32, which
-// widens the half in place.  (Written as a * -1 + c in plain C++ the compiler folds it into a conversion
-// and a subtraction, two instructions.)
+// widens the half in place.  (With a plain -1 the compiler folds the product into a conversion and a subtraction, two
+// instructions: the empty asm hides its value.  The instruction itself is the compiler's, which alone knows the
+// wait states that a register needs after a matrix instruction that still reads or writes it.)
 template <bool HI>
 __device__ __forceinline__ float sub_half(uint32_t pair, float c) {
-  float d;
-  if constexpr (HI) asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(d) : "v"(pair), "v"(c));
-  else asm("v_fma_mix_f32 %0, %1, -1.0, %2 op_sel_hi:[1,0,0]" : "=v"(d) : "v"(pair), "v"(c));
-  return d;
+  float minus_one = -1.0f;
+  asm("" : "+s"(minus_one));
+  return __builtin_fmaf(float(__builtin_bit_cast(f16x2, pair)[HI ? 1 : 0]), minus_one, c);
 }
 
 // Two values at once: the packed pairs (low half <- x0) of the three terms.
