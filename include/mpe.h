@@ -179,7 +179,9 @@ int mpe_set_policy(mpe_env* env, const float* W1, const float* b1, const float* 
  * 1 <= T <= MPE_MAX_ROLLOUT_STEPS.  Advances the absolute step counter by T.  MPE_ESTATE and the counter's
  * limit as for mpe_step.  MPE_EHIP, on this and every later stepping call of the handle, if a kernel of an
  * earlier call gave up one of its bounded waits (it then ran to its end with invalid results; that takes a
- * defect in the library, and the handle is to be destroyed).  With a policy and several runs (one set of weights per run) num_envs must be a multiple
+ * defect in the library, and the handle is to be destroyed).  Where a large batch with a recurrent policy takes two launches and
+ * the runtime refuses the second, MPE_EHIP with a part of the batch stepped: the handle then asks for mpe_reset or mpe_set_state
+ * again (and, with the latter, mpe_set_hidden).  With a policy and several runs (one set of weights per run) num_envs must be a multiple
  * of 16 (the policies for 4 and more agents: of 64; of 32 with 8 agents), MPE_EINVAL otherwise;
  * multiples of 64 run fastest. */
 int mpe_rollout(mpe_env* env, int32_t T, float* obs_traj, uint8_t* act_traj, float* rew_traj,

@@ -186,6 +186,23 @@ RolloutArgs rollout_args(const mpe_env* e, int32_t T, float* obs_traj, uint8_t* 
   return A;
 }
 
+// The rollout with the recurrent policy; critic: packed head of the actor-critic rollout, or null.
+int gru_rollout(mpe_env* e, const RolloutArgs& A, const void* critic, hipStream_t s, const char* who) {
+  TagArgs TA{};
+  TA.r = A;
+  TA.tg = e->tg;
+  TA.actions_in = nullptr;
+  const char* why = nullptr;
+  bool partial = false;
+  const hipError_t err = launch_rollout_gru(e->tag, e->N, e->L, e->G, TA, e->gru, critic, e->hidden, s, &partial, &why);
+  if (why) return fail(MPE_EINVAL, "%s: %s", who, why);
+  if (err == hipSuccess) return MPE_OK;
+  if (!partial) return fail(MPE_EHIP, "%s: %s", who, hipGetErrorString(err));
+  e->ready = false;
+  return fail(MPE_EHIP, "%s: %s, with a part of the batch stepped: call mpe_reset, or mpe_set_state and mpe_set_hidden", who,
+              hipGetErrorString(err));
+}
+
 }  // namespace
 
 extern "C" {
@@ -330,15 +347,7 @@ int mpe_rollout(mpe_env* e, int32_t T, float* obs_traj, uint8_t* act_traj, float
     return fail(MPE_EINVAL, "mpe_rollout: absolute step counter would overflow 32 bits");
   const RolloutArgs A = rollout_args(e, T, obs_traj, act_traj, rew_traj, done_traj, last_obs);
   if (e->has_gru) {
-    TagArgs TA{};
-    TA.r = A;
-    TA.tg = e->tg;
-    TA.actions_in = nullptr;
-    const char* why = nullptr;
-    hipError_t err = launch_rollout_gru(e->tag, e->N, e->L, e->G, TA, e->gru, nullptr, e->hidden,
-                                        static_cast<hipStream_t>(stream), &why);
-    if (why) return fail(MPE_EINVAL, "mpe_rollout: %s", why);
-    if (err != hipSuccess) return fail(MPE_EHIP, "mpe_rollout: %s", hipGetErrorString(err));
+    if (int rc = gru_rollout(e, A, nullptr, static_cast<hipStream_t>(stream), "mpe_rollout")) return rc;
   } else if (e->tag) {
     TagArgs TA{};
     TA.r = A;
@@ -496,14 +505,9 @@ int mpe_rollout_ac(mpe_env* e, int32_t T, float* obs_traj, uint8_t* act_traj, fl
   A.value_traj = value_traj;
   A.last_value = last_value;
   const char* why = nullptr;
-  hipError_t err;
+  hipError_t err = hipSuccess;
   if (e->has_gru) {
-    TagArgs TA{};
-    TA.r = A;
-    TA.tg = e->tg;
-    TA.actions_in = nullptr;
-    err = launch_rollout_gru(e->tag, e->N, e->L, e->G, TA, e->gru, e->gru_critic.packed, e->hidden,
-                             static_cast<hipStream_t>(stream), &why);
+    if (int rc = gru_rollout(e, A, e->gru_critic.packed, static_cast<hipStream_t>(stream), "mpe_rollout_ac")) return rc;
   } else if (e->tag) {
     TagArgs TA{};
     TA.r = A;

@@ -18,6 +18,7 @@ inline hipError_t allow_lds(const void* kern, size_t bytes, std::atomic<uint64_t
   if (done.load(std::memory_order_acquire) & bit) return hipSuccess;
   e = hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes));
   if (e == hipSuccess) done.fetch_or(bit, std::memory_order_release);
+  else (void)hipGetLastError();   // reported here, not by a later launch's check
   return e;
 }
 
@@ -177,8 +178,9 @@ hipError_t pack_policy_gru(PolicyBuffers& pb, bool tag, int N, int D, uint32_t T
 // predator-prey shapes only
 // critic: the packed critic head (pack_gru_critic) for the actor-critic rollout (A.r.logp_traj, value_traj,
 // last_value), or null for the plain one
+// *partial: the launch of a part of the batch failed after that of another, which runs (state and hidden are then no step's)
 hipError_t launch_rollout_gru(bool tag, int N, int L, int G, const TagArgs& A, const PolicyBuffers& pb, const void* critic,
-                              float* hidden, hipStream_t s, const char** why);
+                              float* hidden, hipStream_t s, bool* partial, const char** why);
 // Critic head of the recurrent actor-critic: Wc [R][128][128], bc [R][128], wv [R][128], bv [R]
 hipError_t pack_gru_critic(PolicyBuffers& pb, int N, int D, uint32_t TE, uint32_t E, const float* Wc, const float* bc, const float* wv,
                            const float* bv, hipStream_t s);

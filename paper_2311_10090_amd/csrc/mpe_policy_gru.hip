@@ -813,63 +813,69 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   }
 }
 
-// The envs from `first` on.
+// The envs from `first` on in blocks, the ones before them in independent wavefronts.  Whatever can be refused ahead of a launch
+// comes ahead of both; *partial: the second launch failed all the same, after the first.
 template <typename Scn, int EB, bool AC>
-hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, uint32_t first, hipStream_t s) {
+hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, uint32_t first, hipStream_t s,
+                              bool* partial) {
   using M = GruSmem<Scn, EB, AC>;
   auto kern = rollout_gru_kernel<Scn, EB, AC>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed); e != hipSuccess) return e;
+  if (first) {
+    hipError_t e = launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, A, pb.packed, critic, hidden, first, s);
+    if (e != hipSuccess) return e;
+  }
   const uint32_t groups = (A.r.TE - first + EB - 1) / EB;
   const uint32_t per_xcd = (groups + 7) / 8;
   hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(512), M::TOTAL, s, A, static_cast<const uint8_t*>(pb.packed),
                      static_cast<const uint8_t*>(critic), hidden, int(A.r.TE != A.r.E), first, groups, per_xcd);
-  return hipGetLastError();
+  const hipError_t e = hipGetLastError();
+  *partial = e != hipSuccess && first != 0;
+  return e;
 }
 
 template <typename Scn, bool AC>
-hipError_t rollout_gru_sized(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, hipStream_t s) {
+hipError_t rollout_gru_sized(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, hipStream_t s, bool* partial) {
   constexpr int kMax = gru_max_envs(Scn::N, Scn::D);
   const bool runs = A.r.TE != A.r.E;
   const uint32_t first = gru_waves_envs(Scn::N, Scn::D, AC, A.r.TE, A.r.E), rest = A.r.TE - first;
-  if (first) {
-    hipError_t e = launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, A, pb.packed, critic, hidden, first, s);
-    if (e != hipSuccess || rest == 0) return e;
-  }
+  if (rest == 0)
+    return launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, A, pb.packed, critic, hidden, first, s);
   constexpr int kOne = 16 / Scn::N, kTwo = 32 / Scn::N, kFour = 64 / Scn::N;
   if (const uint32_t te = runs ? 0 : gru_tile_envs(Scn::N, Scn::D, rest)) {
     if constexpr (kOne < 16) {
-      if (te == kOne) return rollout_gru_blocks<Scn, kOne, AC>(A, pb, critic, hidden, first, s);
+      if (te == kOne) return rollout_gru_blocks<Scn, kOne, AC>(A, pb, critic, hidden, first, s, partial);
     }
     if constexpr (kTwo < 16) {
-      if (te == kTwo) return rollout_gru_blocks<Scn, kTwo, AC>(A, pb, critic, hidden, first, s);
+      if (te == kTwo) return rollout_gru_blocks<Scn, kTwo, AC>(A, pb, critic, hidden, first, s, partial);
     }
     if constexpr (kFour < 16 || (kFour > 16 && kFour < 32 && kMax >= 32)) {
-      if (te == kFour) return rollout_gru_blocks<Scn, kFour, AC>(A, pb, critic, hidden, first, s);
+      if (te == kFour) return rollout_gru_blocks<Scn, kFour, AC>(A, pb, critic, hidden, first, s, partial);
     }
   }
   // With one set of weights per run a block must lie inside a run: the largest of 64, 32, 16 that divides
   // the run size bounds the choice.
   const uint32_t eb = gru_block_envs(Scn::N, Scn::D, rest);
-  if (eb == 16 || (runs && A.r.E % 32 != 0)) return rollout_gru_blocks<Scn, 16, AC>(A, pb, critic, hidden, first, s);
+  if (eb == 16 || (runs && A.r.E % 32 != 0)) return rollout_gru_blocks<Scn, 16, AC>(A, pb, critic, hidden, first, s, partial);
   if constexpr (kMax >= 32) {
-    if (eb == 32 || (runs && A.r.E % 64 != 0)) return rollout_gru_blocks<Scn, 32, AC>(A, pb, critic, hidden, first, s);
+    if (eb == 32 || (runs && A.r.E % 64 != 0)) return rollout_gru_blocks<Scn, 32, AC>(A, pb, critic, hidden, first, s, partial);
   }
-  if constexpr (kMax >= 64) return rollout_gru_blocks<Scn, 64, AC>(A, pb, critic, hidden, first, s);
+  if constexpr (kMax >= 64) return rollout_gru_blocks<Scn, 64, AC>(A, pb, critic, hidden, first, s, partial);
   return hipErrorInvalidValue;
 }
 
 template <typename Scn>
 hipError_t rollout_gru_impl(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, hipStream_t s,
-                            const char** why) {
+                            bool* partial, const char** why) {
   if (A.r.TE != A.r.E && A.r.E % 16 != 0) {
     *why = "with several runs, num_envs per run must be a multiple of 16";
     return hipSuccess;
   }
   // critic: the packed head of the actor-critic rollout (same block shapes: its partial values live in LDS
   // that is dead at that point of the step)
-  return critic ? rollout_gru_sized<Scn, true>(A, pb, critic, hidden, s)
-                : rollout_gru_sized<Scn, false>(A, pb, nullptr, hidden, s);
+  return critic ? rollout_gru_sized<Scn, true>(A, pb, critic, hidden, s, partial)
+                : rollout_gru_sized<Scn, false>(A, pb, nullptr, hidden, s, partial);
 }
 
 __global__ void fill_zero_kernel(float* __restrict__ p, size_t n) {
@@ -929,25 +935,26 @@ hipError_t pack_gru_critic(PolicyBuffers& pb, int N, int D, uint32_t TE, uint32_
 }
 
 hipError_t launch_rollout_gru(bool tag, int N, int L, int G, const TagArgs& A, const PolicyBuffers& pb, const void* critic,
-                              float* hidden, hipStream_t s, const char** why) {
+                              float* hidden, hipStream_t s, bool* partial, const char** why) {
+  *partial = false;
   if (tag) {
 #define X(n, l, g) \
-    if (N == n && L == l && G == g) return rollout_gru_impl<GruTag<n, l, g>>(A, pb, critic, hidden, s, why);
+    if (N == n && L == l && G == g) return rollout_gru_impl<GruTag<n, l, g>>(A, pb, critic, hidden, s, partial, why);
     MPE_TAG_SHAPES(X)
 #undef X
     return hipErrorInvalidValue;
   }
   switch (N) {
-    case 1: return rollout_gru_impl<GruSpread<1>>(A, pb, critic, hidden, s, why);
-    case 2: return rollout_gru_impl<GruSpread<2>>(A, pb, critic, hidden, s, why);
-    case 3: return rollout_gru_impl<GruSpread<3>>(A, pb, critic, hidden, s, why);
-    case 4: return rollout_gru_impl<GruSpread<4>>(A, pb, critic, hidden, s, why);
-    case 5: return rollout_gru_impl<GruSpread<5>>(A, pb, critic, hidden, s, why);
-    case 6: return rollout_gru_impl<GruSpread<6>>(A, pb, critic, hidden, s, why);
-    case 7: return rollout_gru_impl<GruSpread<7>>(A, pb, critic, hidden, s, why);
-    case 8: return rollout_gru_impl<GruSpread<8>>(A, pb, critic, hidden, s, why);
-    case 9: return rollout_gru_impl<GruSpread<9>>(A, pb, critic, hidden, s, why);
-    case 10: return rollout_gru_impl<GruSpread<10>>(A, pb, critic, hidden, s, why);
+    case 1: return rollout_gru_impl<GruSpread<1>>(A, pb, critic, hidden, s, partial, why);
+    case 2: return rollout_gru_impl<GruSpread<2>>(A, pb, critic, hidden, s, partial, why);
+    case 3: return rollout_gru_impl<GruSpread<3>>(A, pb, critic, hidden, s, partial, why);
+    case 4: return rollout_gru_impl<GruSpread<4>>(A, pb, critic, hidden, s, partial, why);
+    case 5: return rollout_gru_impl<GruSpread<5>>(A, pb, critic, hidden, s, partial, why);
+    case 6: return rollout_gru_impl<GruSpread<6>>(A, pb, critic, hidden, s, partial, why);
+    case 7: return rollout_gru_impl<GruSpread<7>>(A, pb, critic, hidden, s, partial, why);
+    case 8: return rollout_gru_impl<GruSpread<8>>(A, pb, critic, hidden, s, partial, why);
+    case 9: return rollout_gru_impl<GruSpread<9>>(A, pb, critic, hidden, s, partial, why);
+    case 10: return rollout_gru_impl<GruSpread<10>>(A, pb, critic, hidden, s, partial, why);
     default: return hipErrorInvalidValue;
   }
 }

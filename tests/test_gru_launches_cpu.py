@@ -1,0 +1,39 @@
+"""Launches of the recurrent rollout, recorded without a device: a call that the runtime refuses leaves the handle as it was or
+makes it ask for a new state."""
+import pytest
+
+from paper_2311_10090_amd.binding import MPE_EHIP, MPE_ESTATE, MPE_OK
+from tests.launch_record import build_recorder, launches, record
+
+SPLIT = ["0 3 3 0 65536 1", "0 6 6 0 10500 1", "0 10 10 0 6300 1", "1 4 2 3 20500 1"]    # independent wavefronts, then blocks
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    return build_recorder(tmp_path_factory.mktemp("recorder"))
+
+
+def _setup(shape):
+    return ["create " + shape, "gru", "critic", "reset"]
+
+
+@pytest.mark.parametrize("call", ["rollout 4", "rollout_ac 4"])
+@pytest.mark.parametrize("shape", SPLIT)
+def test_refused_preparation_launches_nothing(recorder, shape, call):
+    for k in (1, 2):                                       # either kernel's LDS
+        *_, (rc, lines), (_, step), (again, then) = record(recorder, _setup(shape) + ["fail attribute %d" % k, call, "abs_step", call])
+        assert rc == MPE_EHIP and not launches(lines) and "FAILS" in lines[-1]
+        assert step == ["abs_step 0"] and again == MPE_OK and len(launches(then)) == 2
+
+
+@pytest.mark.parametrize("call", ["rollout 4", "rollout_ac 4"])
+@pytest.mark.parametrize("shape", SPLIT)
+def test_refused_launch(recorder, shape, call):
+    # the first of the two: nothing has run
+    *_, (rc, _), (again, then) = record(recorder, _setup(shape) + ["fail launch 1", call, call])
+    assert rc == MPE_EHIP and again == MPE_OK and len(launches(then)) == 2
+    # the second: part of the batch has been stepped
+    rcs = [rc for rc, _ in record(recorder, _setup(shape) + ["fail launch 2", call, call, "reset", call])]
+    assert rcs[-4:] == [MPE_EHIP, MPE_ESTATE, MPE_OK, MPE_OK]
+    rcs = [rc for rc, _ in record(recorder, _setup(shape) + ["fail launch 2", call, "set_state", call])]
+    assert rcs[-3:] == [MPE_EHIP, MPE_OK, MPE_OK]
