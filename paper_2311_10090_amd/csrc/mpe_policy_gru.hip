@@ -267,6 +267,9 @@ template <typename Scn, int EB = 64, bool AC = false>
 struct GruSmem {
   static constexpr int N = Scn::N;
   static constexpr int ROWS = EB * N, D = Scn::D, NT = (ROWS + 15) / 16, B = 16 * NT;   // agent rows, obs width, 16-row tiles, their rows
+  // Rows of the last tile that belong to no env.  Blocks without them count the first env in blocks and test no row: otherwise they
+  // take 1 to 4 % longer, in instructions and spilled registers.
+  static constexpr bool kSpare = ROWS != B;
   static constexpr int KS = D <= 32 ? 1 : 2;                    // K slices of the embedding
   static_assert(EB <= 64 && B / N <= 64 && D <= 64 && D % 2 == 0, "a done flag per env (spare rows too); at most two K slices");
   // bf16 observation tile, 32 KS columns per row (zero beyond D); after the embedding it is dead, and the
@@ -315,7 +318,8 @@ template <typename Scn, int EB, bool AC>
 __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint8_t* __restrict__ packed,
                                                           const uint8_t* __restrict__ packed_critic,
                                                           float* __restrict__ hidden, int per_run_weights,
-                                                          uint32_t first_env, uint32_t groups, uint32_t groups_per_xcd) {
+                                                          uint32_t first, uint32_t groups, uint32_t groups_per_xcd) {
+  // first: the first env, in envs (M::kSpare) or in blocks
   using M = GruSmem<Scn, EB, AC>;
   using TS = typename Scn::Shape;                      // predator-prey only
   constexpr bool kTag = Scn::kTag;
@@ -352,7 +356,7 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   const size_t TE = A.TE;
   const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
   if (grp >= groups) return;  // whole block, before any barrier
-  const size_t g0 = first_env + size_t(grp) * EB;
+  const size_t g0 = M::kSpare ? first + size_t(grp) * EB : size_t(first + grp) * EB;
   const size_t left = TE - g0;
   const int nvalid = left < size_t(EB) ? int(left) : EB;   // valid envs of this block
   const int vrows = nvalid * N;                            // valid agent rows
@@ -406,7 +410,7 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   static_assert(B <= 256, "a row per thread of half the block");
   const bool agent = tid < B;
   const int srow = tid & 255;                        // this lane's row as an agent or service lane
-  const int erow = srow < ROWS ? srow : 0;           // spare rows of the last tile look at the block's first env and store nothing
+  const int erow = M::kSpare && srow >= ROWS ? 0 : srow;   // spare rows look at the block's first env and store nothing
   const int el = erow / N, i = erow - el * N;        // env within block, agent (agent and service lanes only)
   const size_t g = g0 + el;
   const bool in_range = srow < ROWS && g < TE;
@@ -755,7 +759,7 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
       ep += 1;
       const bool done = ep >= max_ep;
       if (done_base && env_writer) done_base[gc] = done ? 1 : 0;
-      if (i == 0 && srow < ROWS) donef[el] = done ? 1 : 0;     // read by the gate phase of the next step
+      if (i == 0 && (!M::kSpare || srow < ROWS)) donef[el] = done ? 1 : 0;     // read by the gate phase of the next step
       if (done) {
         // new episode keyed by step + 1; every lane regenerates its whole env (1 step in max_ep)
         uint32_t env_r = env;
@@ -822,6 +826,7 @@ hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const v
   auto kern = rollout_gru_kernel<Scn, EB, AC>;
   static std::atomic<uint64_t> lds_allowed{0};
   if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed); e != hipSuccess) return e;
+  if (!M::kSpare) first -= first % EB;    // whole blocks before them (they are with any multiple of 8 compute units)
   if (first) {
     hipError_t e = launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, A, pb.packed, critic, hidden, first, s);
     if (e != hipSuccess) return e;
@@ -829,7 +834,7 @@ hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const v
   const uint32_t groups = (A.r.TE - first + EB - 1) / EB;
   const uint32_t per_xcd = (groups + 7) / 8;
   hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(512), M::TOTAL, s, A, static_cast<const uint8_t*>(pb.packed),
-                     static_cast<const uint8_t*>(critic), hidden, int(A.r.TE != A.r.E), first, groups, per_xcd);
+                     static_cast<const uint8_t*>(critic), hidden, int(A.r.TE != A.r.E), M::kSpare ? first : first / EB, groups, per_xcd);
   const hipError_t e = hipGetLastError();
   *partial = e != hipSuccess && first != 0;
   return e;

@@ -1,4 +1,4 @@
-"""The library's calls of the HIP runtime, recorded on the CPU by tests/launch_recorder.cpp (256 compute units, kernels do not run)."""
+"""The library's calls of the HIP runtime, recorded on the CPU by tests/launch_recorder.cpp (kernels do not run)."""
 import os
 import re
 import subprocess
@@ -17,9 +17,9 @@ def build_recorder(folder):
     return exe
 
 
-def record(exe, commands):
+def record(exe, commands, units=256):
     """Per command (return code, lines it printed)."""
-    r = subprocess.run([exe], input="\n".join(commands) + "\n", capture_output=True, text=True, timeout=300)
+    r = subprocess.run([exe, str(units)], input="\n".join(commands) + "\n", capture_output=True, text=True, timeout=300)
     assert r.returncode == 0, r.stderr
     out, lines = [], []
     for line in r.stdout.splitlines():

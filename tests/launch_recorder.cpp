@@ -1,6 +1,6 @@
 // What libmpe asks of the HIP runtime, without a device: this program defines the runtime's functions that the library calls,
 // so its own take their place (the executable comes first in symbol lookup), and prints every launch and every LDS
-// attribute.  Memory is host memory, kernels do not run.  Commands on stdin, one a line; after each one line "rc <n>":
+// attribute.  Memory is host memory, kernels do not run.  argv[1]: compute units (256).  Commands on stdin, one a line; after each one line "rc <n>":
 //   create <scenario> <agents> <landmarks> <adversaries> <envs> <runs>   hidden 128, bf16 weights
 //   destroy | reset | set_state | gru | critic | rollout <T> | rollout_ac <T> | abs_step
 //   fail <attribute|launch> <k>                                          the k-th such call from here on fails, once
@@ -25,6 +25,7 @@ std::map<const void*, std::string>& kernels() {
 }
 struct Config { uint32_t grid[3], block[3]; size_t lds; void* stream; } pushed;
 int last_error = 0;
+int units = 256;           // compute units
 int fail_in[2] = {0, 0};   // attribute, launch: calls until the one that fails
 int outcome(int kind) { return fail_in[kind] && --fail_in[kind] == 0 ? (last_error = 1) : 0; }
 struct Dim3 { uint32_t x, y, z; };
@@ -54,9 +55,14 @@ int __hipPopCallConfiguration(Dim3* grid, Dim3* block, size_t* lds, void** strea
   *stream = pushed.stream;
   return 0;
 }
-int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void**, size_t lds, void*) {
+int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void** args, size_t lds, void*) {
   const int rc = outcome(1);
-  std::printf("launch %s grid %u %u block %u lds %zu%s\n", kernels()[host].c_str(), grid.x, grid.y, block.x, lds, rc ? " FAILS" : "");
+  const std::string& name = kernels()[host];
+  auto word = [&](int k) { return *static_cast<const uint32_t*>(args[k]); };
+  std::printf("launch %s grid %u %u block %u lds %zu", name.c_str(), grid.x, grid.y, block.x, lds);
+  if (name.rfind("rollout_gru_kernel<", 0) == 0) std::printf(" first %u groups %u", word(5), word(6));
+  if (name.rfind("rollout_gru_waves_kernel<", 0) == 0) std::printf(" envs %u", word(4));
+  std::printf("%s\n", rc ? " FAILS" : "");
   return rc;
 }
 int hipFuncSetAttribute(const void* host, int, int bytes) {
@@ -67,7 +73,7 @@ int hipFuncSetAttribute(const void* host, int, int bytes) {
 int hipGetLastError() { const int e = last_error; last_error = 0; return e; }
 const char* hipGetErrorString(int) { return "planned failure"; }
 int hipGetDevice(int* dev) { *dev = 0; return 0; }
-int hipDeviceGetAttribute(int* value, int, int) { *value = 256; return 0; }   // compute units
+int hipDeviceGetAttribute(int* value, int, int) { *value = units; return 0; }
 int hipDeviceSynchronize() { return 0; }
 int hipMalloc(void** p, size_t n) { std::printf("malloc %zu\n", n); return (*p = std::calloc(n ? n : 1, 1)) ? 0 : 2; }
 int hipFree(void* p) { std::free(p); return 0; }
@@ -78,7 +84,8 @@ int hipMemcpyAsync(void*, const void*, size_t, int, void*) { return 0; }
 int hipGetSymbolAddress(void** p, const void*) { *p = nullptr; return 1; }
 }
 
-int main() {
+int main(int argc, char** argv) {
+  if (argc > 1) units = std::atoi(argv[1]);
   mpe_env* env = nullptr;
   alignas(16) static float w[4];                // never read: kernels do not run
   const float* p = w;
