@@ -70,10 +70,13 @@ inline uint32_t gru_tile_envs(int N, int D, uint32_t envs) {
 // Envs of a batch, from the first on, that run in independent wavefronts (mpe_gru_waves.hip); the rest runs in blocks.
 // Three choices: all in blocks, whole rounds of independent wavefronts (a block of them per CU) and the rest in blocks, or
 // everything in independent wavefronts; the shortest by this estimate, in units of such a round, which takes the same
-// time whatever its last block holds.  A round of blocks costs what its envs are of that round, times 1.1 to 1.2 (1.17 to 1.37,
-// and 1.65 for 8 and more agents of simple spread, with a critic) by the block's size.  Measured, 64 steps, plain / critic, us: 3 agents, a round of
+// time whatever its last block holds.  A round of blocks costs what its envs are of that round, times 1.1 to 1.2 (1.17 to 1.37 with a
+// critic) by the block's size; with a critic and 8 and more agents of simple spread, times 1.2 to 2 by the agents and the share of CUs that
+// have a block.  Measured, 64 steps, plain / critic, us: 3 agents, a round of
 // 20,480 envs 1,066 / 1,298, blocks for 4,096, 8,192 and 16,384 envs 272 / 367, 469 / 641, 920 / 1,200; 6 agents, a round of 10,240
-// envs 1,137 / 1,373, blocks for 4,096 522 / 733 (a round of smaller blocks is a small fixed time and its tiles: gru_tile_envs); 10 agents, 6,144 envs 1,258 / 1,499, blocks for 4,096 1,040 / 1,808; 1 agent, 65,536 envs
+// envs 1,137 / 1,373, blocks for 4,096 522 / 733 (a round of smaller blocks is a small fixed time and its tiles: gru_tile_envs); 10 agents, 6,144 envs
+// 1,258 / 1,499, blocks for 4,096 1,040 / 1,808; with a critic, a round against blocks for 1,928, 2,411, 3,015 and 3,992 envs, 9 agents 1,344
+// against 1,242, 1,286, 1,427 and 1,539, 10 agents 1,375 against 1,536, 1,650, 1,750 and 1,813; 1 agent, 65,536 envs
 // 1,034 / 1,250, blocks for 16,384 306 / 413.  Several runs stay in blocks, which stage a run's weights once for all their steps.
 uint32_t gru_waves_envs(int N, int D, bool ac, uint32_t TE, uint32_t E) {
   if (TE != E) return 0;
@@ -82,8 +85,11 @@ uint32_t gru_waves_envs(int N, int D, bool ac, uint32_t TE, uint32_t E) {
     if (envs == 0) return 0.0f;
     if (const uint32_t eb = gru_tile_envs(N, D, envs)) return 0.1f + 0.07f * float((eb * uint32_t(N) + 15) / 16);
     const uint32_t eb = gru_block_envs(N, D, envs), n = cus * eb;
-    const float each = ac ? (eb == 16 ? (N >= 8 && D > 32 ? 1.65f : 1.37f) : (eb == 32 ? 1.24f : 1.17f)) : (eb == 16 ? 1.2f : (eb == 32 ? 1.12f : 1.1f));
-    return float((envs + n - 1) / n) * float(n) / float(round) * each;
+    const float each = ac ? (eb == 16 ? 1.37f : (eb == 32 ? 1.24f : 1.17f)) : (eb == 16 ? 1.2f : (eb == 32 ? 1.12f : 1.1f));
+    if (!(ac && N >= 8 && D > 32)) return float((envs + n - 1) / n) * float(n) / float(round) * each;
+    // the shapes with the most spilled registers: a round takes the longer the more of its blocks there are
+    const float tiles = N == 8 ? 0.85f : 0.22f * float(N) - 1.0f, last = float(envs % n) / float(n);
+    return (float(envs / n) * (tiles + 0.8f) + (last > 0.0f ? tiles + 0.8f * last : 0.0f)) * float(n) / float(round);
   };
   const float all = blocks(TE), some = float(full) + blocks(rest), none = float(full + (rest != 0));
   if (all <= some && all <= none) return 0;

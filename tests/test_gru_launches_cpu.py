@@ -68,3 +68,14 @@ def test_kernels_cover_the_batch(recorder, units, call):
                 assert done + (groups - 1) * eb < envs <= done + groups * eb
                 done = envs
         assert done == envs, (shape, envs, lines)
+
+
+def test_batches_between_blocks_and_wavefronts_with_a_critic(recorder):
+    """Where a round of blocks costs about a round of independent wavefronts: 9 agents, blocks while at most two thirds of the
+    compute units have one; 10 agents, wavefronts from the first batch on that small blocks leave."""
+    def kernel(agents, envs):
+        out = record(recorder, ["create 0 %d %d 0 %d 1" % (agents, agents, envs), "gru", "critic", "reset", "rollout_ac 4"])
+        return [name.split("<")[0] for name, _ in launches(out[-1][1])]
+    for agents, envs, waves in ((8, 2000, False), (8, 4000, False), (9, 1800, False), (9, 2400, False), (9, 3000, True), (9, 4096, True),
+                                (10, 1600, True), (10, 4096, True)):
+        assert kernel(agents, envs) == ["rollout_gru_waves_kernel" if waves else "rollout_gru_kernel"], (agents, envs)
