@@ -1,4 +1,5 @@
-// Weight image of the recurrent rollout's independent wavefronts (mpe_gru_waves.hip) and the host-side interface to them.
+// Weight image of the recurrent rollout's independent wavefronts (mpe_gru_waves.hip; packed by mpe_policy_gru.hip with the other one)
+// and the host-side interface to them.
 #pragma once
 
 #include "mpe_launch.h"
@@ -48,10 +49,6 @@ struct GruWaveCriticPk {
 // Envs in a block: 8 wavefronts of 32 rows.
 constexpr uint32_t gru_waves_block_envs(int N) { return 8u * (32u / uint32_t(N)); }
 
-hipError_t pack_gru_waves(uint8_t* image, int D, int live, const float* We, const float* be, const float* Wi, const float* bi,
-                          const float* Wh, const float* bh, const float* Wf, const float* bf, const float* Wo, const float* bo,
-                          hipStream_t s);
-hipError_t pack_gru_waves_critic(uint8_t* image, const float* Wc, const float* bc, const float* wv, const float* bv, hipStream_t s);
 // The first `envs` envs of the batch.
 hipError_t launch_gru_waves(bool tag, int N, int L, int G, const TagArgs& A, const void* packed, const void* critic, float* hidden,
                             uint32_t envs, hipStream_t s);

@@ -647,81 +647,7 @@ hipError_t launch_impl(const TagArgs& A, const void* packed, const void* critic,
   });
 }
 
-// One thread per packed bf16 weight or fp32 bias.
-__global__ void pack_kernel(uint8_t* __restrict__ image, int D, int kse, const float* __restrict__ We, const float* __restrict__ be,
-                            const float* __restrict__ Wi, const float* __restrict__ bi, const float* __restrict__ Wh,
-                            const float* __restrict__ bh, const float* __restrict__ Wf, const float* __restrict__ bf,
-                            const float* __restrict__ Wo, const float* __restrict__ bo) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int e = idx % 8, lane = idx / 8 % 64, gq = lane / 16, row = lane % 16;
-  int f = idx / 512;                                     // operand
-  const int frags = GruWavePk::frags(kse), k8 = 8 * gq + e;
-  if (f < frags) {
-    float v = 0.0f;
-    int gate = -1;                                       // gate operands by position in the stream
-    if (f < GruWavePk::RESIDENT) gate = f / 3 * 4 + f % 3;
-    else if (f >= GruWavePk::RESIDENT + 8 * kse && f < GruWavePk::RESIDENT + 8 * kse + 48) gate = (f - GruWavePk::RESIDENT - 8 * kse) * 4 + 3;
-    if (gate >= 0) {
-      const auto part = GruWavePk::gate_part(gate % 24);
-      const float* W = part.recurrent ? Wh : Wi;
-      v = W[size_t(32 * part.s + k8) * 3 * kG + part.gate * kG + GruWavePk::unit(gate / 24, row)];
-    } else if (f < GruWavePk::RESIDENT + 8 * kse) {
-      const int k2 = f - GruWavePk::RESIDENT, k = 32 * (k2 % kse) + k8;
-      v = k < D ? We[size_t(k) * kG + GruWavePk::unit(k2 / kse, row)] : 0.0f;
-    } else {
-      const int k2 = f - (GruWavePk::RESIDENT + 8 * kse + 48);
-      if (k2 < 32) v = Wf[size_t(32 * (k2 % 4) + k8) * kG + GruWavePk::unit(k2 / 4, row)];
-      else if (const int out = GruWavePk::out_row(row); out >= 0) v = Wo[size_t(32 * (k2 - 32) + k8) * kNumActions + out];
-    }
-    reinterpret_cast<uint16_t*>(image)[idx] = f32_to_bf16_rne(v);
-    return;
-  }
-  idx -= frags * 512;
-  if (idx < GruWavePk::BIAS_FLOATS) {
-    float v = 0.0f;
-    if (idx < kG) v = be[idx];
-    else if (idx < 3 * kG) v = bi[idx - kG] + bh[idx - kG];
-    else if (idx < 4 * kG) v = bi[idx - kG];
-    else if (idx < 5 * kG) v = bh[idx - 2 * kG];
-    else if (idx < 6 * kG) v = bf[idx - 5 * kG];
-    else if (const int out = GruWavePk::out_row(idx - 6 * kG); out >= 0) v = bo[out];
-    reinterpret_cast<float*>(image + size_t(frags) * kFrag)[idx] = v;
-  }
-}
-
-__global__ void pack_critic_kernel(uint8_t* __restrict__ image, const float* __restrict__ Wc, const float* __restrict__ bc,
-                                   const float* __restrict__ wv, const float* __restrict__ bv) {
-  int idx = blockIdx.x * blockDim.x + threadIdx.x;
-  const int e = idx % 8, lane = idx / 8 % 64, f = idx / 512;
-  if (f < GruWaveCriticPk::FRAGS) {
-    reinterpret_cast<uint16_t*>(image)[idx] =
-        f32_to_bf16_rne(Wc[size_t(32 * (f % 4) + 8 * (lane / 16) + e) * kG + GruWavePk::unit(f / 4, lane % 16)]);
-    return;
-  }
-  idx -= GruWaveCriticPk::FRAGS * 512;
-  if (idx < GruWaveCriticPk::BIAS_FLOATS) {
-    float v = 0.0f;
-    if (idx < kG) v = bc[idx];
-    else if (idx < 2 * kG) v = __uint_as_float(uint32_t(f32_to_bf16_rne(wv[idx - kG])) << 16);
-    else if (idx == 2 * kG) v = bv[0];
-    reinterpret_cast<float*>(image + size_t(GruWaveCriticPk::FRAGS) * kFrag)[idx] = v;
-  }
-}
-
 }  // namespace
-
-hipError_t pack_gru_waves(uint8_t* image, int D, int live, const float* We, const float* be, const float* Wi, const float* bi,
-                          const float* Wh, const float* bh, const float* Wf, const float* bf, const float* Wo, const float* bo,
-                          hipStream_t s) {
-  const int kse = (live + 31) / 32, threads = GruWavePk::frags(kse) * 512 + GruWavePk::BIAS_FLOATS;
-  hipLaunchKernelGGL(pack_kernel, dim3((threads + 255) / 256), dim3(256), 0, s, image, D, kse, We, be, Wi, bi, Wh, bh, Wf, bf, Wo, bo);
-  return hipGetLastError();
-}
-hipError_t pack_gru_waves_critic(uint8_t* image, const float* Wc, const float* bc, const float* wv, const float* bv, hipStream_t s) {
-  constexpr int threads = GruWaveCriticPk::FRAGS * 512 + GruWaveCriticPk::BIAS_FLOATS;
-  hipLaunchKernelGGL(pack_critic_kernel, dim3((threads + 255) / 256), dim3(256), 0, s, image, Wc, bc, wv, bv);
-  return hipGetLastError();
-}
 
 hipError_t launch_gru_waves(bool tag, int N, int L, int G, const TagArgs& A, const void* packed, const void* critic, float* hidden,
                             uint32_t envs, hipStream_t s) {

@@ -159,13 +159,78 @@ struct GruPk {
   static constexpr int THREADS = N_EMB + N_GRU + N_FC + N_OUT + BIAS_FLOATS;
 };
 
-// One thread per packed bf16 weight or fp32 bias of one run (blockIdx.y).  D = observation width (<= 64).
-__global__ void pack_gru_kernel(uint8_t* __restrict__ out, int D, const float* __restrict__ We,
+// Packed weight or bias idx of the independent wavefronts' image.
+__device__ void pack_waves(int idx, uint8_t* __restrict__ image, int D, int kse, const float* __restrict__ We, const float* __restrict__ be,
+                           const float* __restrict__ Wi, const float* __restrict__ bi, const float* __restrict__ Wh,
+                           const float* __restrict__ bh, const float* __restrict__ Wf, const float* __restrict__ bf,
+                           const float* __restrict__ Wo, const float* __restrict__ bo) {
+  using W = GruWavePk;
+  const int e = idx % 8, lane = idx / 8 % 64, row = lane % 16, f = idx / 512;   // f: operand
+  const int frags = W::frags(kse), k8 = 8 * (lane / 16) + e;
+  if (f < frags) {
+    float v = 0.0f;
+    int gate = -1;                                       // gate operands by position in the stream
+    if (f < W::RESIDENT) gate = f / 3 * 4 + f % 3;
+    else if (f >= W::RESIDENT + 8 * kse && f < W::RESIDENT + 8 * kse + 48) gate = (f - W::RESIDENT - 8 * kse) * 4 + 3;
+    if (gate >= 0) {
+      const auto part = W::gate_part(gate % 24);
+      v = (part.recurrent ? Wh : Wi)[size_t(32 * part.s + k8) * 3 * kG + part.gate * kG + W::unit(gate / 24, row)];
+    } else if (f < W::RESIDENT + 8 * kse) {
+      const int k2 = f - W::RESIDENT, k = 32 * (k2 % kse) + k8;
+      v = k < D ? We[size_t(k) * kG + W::unit(k2 / kse, row)] : 0.0f;
+    } else {
+      const int k2 = f - (W::RESIDENT + 8 * kse + 48);
+      if (k2 < 32) v = Wf[size_t(32 * (k2 % 4) + k8) * kG + W::unit(k2 / 4, row)];
+      else if (const int out = W::out_row(row); out >= 0) v = Wo[size_t(32 * (k2 - 32) + k8) * kNumActions + out];
+    }
+    reinterpret_cast<uint16_t*>(image)[idx] = f32_to_bf16_rne(v);
+    return;
+  }
+  idx -= frags * 512;
+  if (idx < W::BIAS_FLOATS) {
+    float v = 0.0f;
+    if (idx < kG) v = be[idx];
+    else if (idx < 3 * kG) v = bi[idx - kG] + bh[idx - kG];
+    else if (idx < 4 * kG) v = bi[idx - kG];
+    else if (idx < 5 * kG) v = bh[idx - 2 * kG];
+    else if (idx < 6 * kG) v = bf[idx - 5 * kG];
+    else if (const int out = W::out_row(idx - 6 * kG); out >= 0) v = bo[out];
+    reinterpret_cast<float*>(image + size_t(frags) * W::kFrag)[idx] = v;
+  }
+}
+__device__ void pack_waves_critic(int idx, uint8_t* __restrict__ image, const float* __restrict__ Wc, const float* __restrict__ bc,
+                                  const float* __restrict__ wv, const float* __restrict__ bv) {
+  using W = GruWaveCriticPk;
+  const int e = idx % 8, lane = idx / 8 % 64, f = idx / 512;
+  if (f < W::FRAGS) {
+    reinterpret_cast<uint16_t*>(image)[idx] =
+        f32_to_bf16_rne(Wc[size_t(32 * (f % 4) + 8 * (lane / 16) + e) * kG + GruWavePk::unit(f / 4, lane % 16)]);
+    return;
+  }
+  idx -= W::FRAGS * 512;
+  if (idx < W::BIAS_FLOATS) {
+    float v = 0.0f;
+    if (idx < kG) v = bc[idx];
+    else if (idx < 2 * kG) v = __uint_as_float(uint32_t(f32_to_bf16_rne(wv[idx - kG])) << 16);
+    else if (idx == 2 * kG) v = bv[0];
+    reinterpret_cast<float*>(image + size_t(W::FRAGS) * GruWavePk::kFrag)[idx] = v;
+  }
+}
+
+// One thread per packed bf16 weight or fp32 bias of one run (blockIdx.y).  D = observation width (<= 64).  The blocks past the
+// image's own pack that of the independent wavefronts behind it (one run only; kse = its K slices of the embedding).  A loop of
+// calls is bound by their launches: 4.7 us a call in one, with either image or both, 8.5 in two.
+constexpr int pack_blocks(int threads) { return (threads + 255) / 256; }
+__global__ void pack_gru_kernel(uint8_t* __restrict__ out, int D, int kse, const float* __restrict__ We,
                                 const float* __restrict__ be, const float* __restrict__ Wi,
                                 const float* __restrict__ bi, const float* __restrict__ Wh,
                                 const float* __restrict__ bh, const float* __restrict__ Wf,
                                 const float* __restrict__ bf, const float* __restrict__ Wo,
                                 const float* __restrict__ bo) {
+  if (blockIdx.x >= pack_blocks(GruPk::THREADS)) {
+    const int idx = (blockIdx.x - pack_blocks(GruPk::THREADS)) * blockDim.x + threadIdx.x;
+    return pack_waves(idx, out + GruWavePk::base(), D, kse, We, be, Wi, bi, Wh, bh, Wf, bf, Wo, bo);
+  }
   const size_t run = blockIdx.y;
   out += run * GruPk::BYTES;
   We += run * size_t(D) * kG;
@@ -242,6 +307,10 @@ struct GruCriticPk {
 
 __global__ void pack_gru_critic_kernel(uint8_t* __restrict__ out, const float* __restrict__ Wc, const float* __restrict__ bc,
                                        const float* __restrict__ wv, const float* __restrict__ bv) {
+  if (blockIdx.x >= pack_blocks(GruCriticPk::THREADS)) {
+    const int idx = (blockIdx.x - pack_blocks(GruCriticPk::THREADS)) * blockDim.x + threadIdx.x;
+    return pack_waves_critic(idx, out + GruWaveCriticPk::base(), Wc, bc, wv, bv);
+  }
   const size_t run = blockIdx.y;
   out += run * GruCriticPk::BYTES;
   Wc += run * size_t(kG) * kG;
@@ -917,16 +986,13 @@ hipError_t pack_policy_gru(PolicyBuffers& pb, bool tag, int N, int D, uint32_t T
                            const float* Wo, const float* bo, hipStream_t s) {
   if (D < 1 || D > 64) return hipErrorInvalidValue;
   const uint32_t R = TE / E;
-  const int live = tag ? D : 4 * N + 2;
+  // the independent wavefronts' image wherever a rollout of this batch may read it, with or without a critic, which may come later
   const bool waves = gru_waves_envs(N, D, false, TE, E) || gru_waves_envs(N, D, true, TE, E);
-  const size_t bytes = size_t(R) * GruPk::BYTES + (waves ? GruWavePk::bytes((live + 31) / 32) : 0);
-  if (hipError_t e = ensure_policy_bytes(pb, bytes); e != hipSuccess) return e;
-  if (waves) {
-    hipError_t e = pack_gru_waves(static_cast<uint8_t*>(pb.packed) + GruWavePk::base(), D, live, We, be, Wi, bi, Wh, bh, Wf, bf, Wo, bo, s);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(pack_gru_kernel, dim3((GruPk::THREADS + 255) / 256, R), dim3(256), 0, s,
-                     static_cast<uint8_t*>(pb.packed), D, We, be, Wi, bi, Wh, bh, Wf, bf, Wo, bo);
+  const int kse = waves ? ((tag ? D : 4 * N + 2) + 31) / 32 : 0;
+  if (hipError_t e = ensure_policy_bytes(pb, size_t(R) * GruPk::BYTES + (waves ? GruWavePk::bytes(kse) : 0)); e != hipSuccess) return e;
+  const int blocks = pack_blocks(GruPk::THREADS) + (waves ? pack_blocks(GruWavePk::frags(kse) * 512 + GruWavePk::BIAS_FLOATS) : 0);
+  hipLaunchKernelGGL(pack_gru_kernel, dim3(blocks, R), dim3(256), 0, s, static_cast<uint8_t*>(pb.packed), D, kse, We, be, Wi, bi, Wh, bh, Wf,
+                     bf, Wo, bo);
   return hipGetLastError();
 }
 
@@ -934,14 +1000,9 @@ hipError_t pack_gru_critic(PolicyBuffers& pb, int N, int D, uint32_t TE, uint32_
                            const float* bv, hipStream_t s) {
   const uint32_t R = TE / E;
   const bool waves = gru_waves_envs(N, D, true, TE, E);
-  const size_t bytes = size_t(R) * GruCriticPk::BYTES + (waves ? GruWaveCriticPk::BYTES : 0);
-  if (hipError_t e = ensure_policy_bytes(pb, bytes); e != hipSuccess) return e;
-  if (waves) {
-    hipError_t e = pack_gru_waves_critic(static_cast<uint8_t*>(pb.packed) + GruWaveCriticPk::base(), Wc, bc, wv, bv, s);
-    if (e != hipSuccess) return e;
-  }
-  hipLaunchKernelGGL(pack_gru_critic_kernel, dim3((GruCriticPk::THREADS + 255) / 256, R), dim3(256), 0, s,
-                     static_cast<uint8_t*>(pb.packed), Wc, bc, wv, bv);
+  if (hipError_t e = ensure_policy_bytes(pb, size_t(R) * GruCriticPk::BYTES + (waves ? GruWaveCriticPk::BYTES : 0)); e != hipSuccess) return e;
+  const int blocks = pack_blocks(GruCriticPk::THREADS) + (waves ? pack_blocks(GruWaveCriticPk::FRAGS * 512 + GruWaveCriticPk::BIAS_FLOATS) : 0);
+  hipLaunchKernelGGL(pack_gru_critic_kernel, dim3(blocks, R), dim3(256), 0, s, static_cast<uint8_t*>(pb.packed), Wc, bc, wv, bv);
   return hipGetLastError();
 }
 

@@ -79,3 +79,11 @@ def test_batches_between_blocks_and_wavefronts_with_a_critic(recorder):
     for agents, envs, waves in ((8, 2000, False), (8, 4000, False), (9, 1800, False), (9, 2400, False), (9, 3000, True), (9, 4096, True),
                                 (10, 1600, True), (10, 4096, True)):
         assert kernel(agents, envs) == ["rollout_gru_waves_kernel" if waves else "rollout_gru_kernel"], (agents, envs)
+
+
+@pytest.mark.parametrize("shape", ["0 3 3 0 256 1", "0 6 6 0 6000 1", "0 10 10 0 2000 1", "0 3 3 0 65536 1", "1 4 2 3 20500 1", "0 3 3 0 64 8"])
+def test_weights_are_packed_in_one_launch(recorder, shape):
+    """Also where a batch may run in both kernels, which read images of their own."""
+    out = record(recorder, _setup(shape) + ["gru", "critic"])
+    assert [name for name, _ in launches(out[4][1])] == ["pack_gru_kernel"]
+    assert [name for name, _ in launches(out[5][1])] == ["pack_gru_critic_kernel"]
