@@ -5,6 +5,7 @@ import re
 import pytest
 
 from paper_2311_10090_amd.binding import MPE_EHIP, MPE_ESTATE, MPE_OK
+from tests.gru_batches import SHAPES, batches, whole_rounds
 from tests.launch_record import build_recorder, launches, record
 
 SPLIT = ["0 3 3 0 65536 1", "0 6 6 0 10500 1", "0 10 10 0 6300 1", "1 4 2 3 20500 1"]    # independent wavefronts, then blocks
@@ -87,3 +88,16 @@ def test_weights_are_packed_in_one_launch(recorder, shape):
     out = record(recorder, _setup(shape) + ["gru", "critic"])
     assert [name for name, _ in launches(out[4][1])] == ["pack_gru_kernel"]
     assert [name for name, _ in launches(out[5][1])] == ["pack_gru_critic_kernel"]
+
+
+@pytest.mark.parametrize("ac", [False, True], ids=["plain", "actor_critic"])
+def test_batches_of_the_gpu_tests_reach_their_kernels(recorder, ac):
+    cases = [(s, kernels, envs) for s in SHAPES for kernels, envs in batches(*s, ac) + [("waves", whole_rounds(s[1]))]]
+    out = record(recorder, [c for s, _, envs in cases for c in ["create %d %d %d %d" % (s[0] == "tag", *s[1:]) + " %d 1" % envs, "gru", "critic",
+                                                               "reset", "rollout_ac 1" if ac else "rollout 1", "destroy"]])
+    for (shape, kernels, envs), (rc, lines) in zip(cases, out[4::6]):
+        found = []
+        for line in (x for x in lines if x.startswith("launch ")):
+            block = BLOCK.match(line)
+            found.append("blocks" + block[2] if block else "waves")
+        assert rc == MPE_OK and "+".join(found) == kernels, (shape, envs)
