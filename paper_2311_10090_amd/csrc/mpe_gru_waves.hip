@@ -13,8 +13,9 @@
 // agent rows in the environment's part; each draws one of the two blocks of sampling noise.
 //
 // What bounds it: issue and power.  A step of a wavefront issues 16,100 SIMD cycles with the critic (4,300 of them for 536
-// matrix instructions, 8 of each one's 16 cycles; 6,300 for 790 exp and rcp), and the counters find the SIMDs busy for 95 %
-// of the cycles, at 2.0 GHz: matrix instructions on real data run against the power limit (alone, at 1.7 GHz).  The same
+// matrix instructions, 8 of each one's 16 cycles; 6,300 for 790 exp and rcp), and the two wavefronts of a SIMD take 42,900 cycles a step:
+// an instruction is issued in 86 % of them, the vector unit active in 73 %, the matrix cores busy in 40 %, a third of that at the same
+// time.  The clock is 1.8 to 2.0 GHz: matrix instructions on real data run against the power limit (alone, at 1.7 GHz).  The same
 // network with v_mfma_f32_32x32x16_bf16, half the issue cycles, ran at 1.8 GHz and no faster; rings of other depths neither.
 // Measured, 61,440 envs x 3 agents x 64 steps, us: 3,670 -> 3,210, with the critic 4,775 -> 3,880; 10,240 envs x 6 agents 1,558 ->
 // 1,126 and 2,188 -> 1,351; 6,144 x 10 1,997 -> 1,251 and 3,358 -> 1,482.  Results are those of the block kernel, bit for bit.
