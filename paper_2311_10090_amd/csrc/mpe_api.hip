@@ -220,7 +220,9 @@ int mpe_create(const mpe_config* cfg, mpe_env** out) {
   hipError_t err = hipMalloc(&e->st.pos_a, nf);
   if (err == hipSuccess) err = hipMalloc(&e->st.vel_a, nf);
   if (err == hipSuccess) err = hipMalloc(&e->st.pos_l, landmark_floats(e) * sizeof(float) + 16);
-  if (err == hipSuccess) err = hipMalloc(&e->st.ep_step, size_t(e->TE) * sizeof(int32_t));
+  // the episode counters, and behind them the tickets
+  if (err == hipSuccess) err = hipMalloc(&e->st.ep_step, size_t(e->TE) * 2 * sizeof(int32_t));
+  if (err == hipSuccess) e->st.tickets = reinterpret_cast<uint32_t*>(e->st.ep_step + e->TE);
   if (err == hipSuccess) err = hipHostMalloc(reinterpret_cast<void**>(&e->fault_host), sizeof(uint32_t), hipHostMallocMapped);
   if (err == hipSuccess) {
     *e->fault_host = 0u;
@@ -554,6 +556,8 @@ int mpe_set_state(mpe_env* e, const float* pos_a, const float* vel_a, const floa
   const size_t nl = landmark_floats(e) * sizeof(float);
   if (nl) MPE_HIP(hipMemcpyAsync(e->st.pos_l, pos_l, nl, hipMemcpyDeviceToDevice, s));
   MPE_HIP(hipMemcpyAsync(e->st.ep_step, ep_step, size_t(e->TE) * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
+  // a rollout leaves the tickets at zero, as mpe_reset does
+  if (!e->ready) MPE_HIP(launch_fill_zero(reinterpret_cast<float*>(e->st.tickets), e->TE, s));
   e->seed = seed;
   e->abs_step = abs_step;
   e->ready = true;
@@ -618,7 +622,7 @@ int mpe_rollout_noalloc(const mpe_config* cfg, uint32_t seed, const float* W1, c
     if (!packed_bytes)
       return fail(MPE_EINVAL, "mpe_rollout_noalloc: unsupported policy shape (see mpe_set_policy)");
   }
-  // ---- layout inside the scratch array: fault word | pos_a | vel_a | pos_l | ep_step | packed policy
+  // ---- layout inside the scratch array: fault word | pos_a | vel_a | pos_l | ep_step | packed policy | tickets, where they fit
   const size_t nf = agent_floats(&e) * sizeof(float);
   const size_t off_pos = 256;
   const size_t off_vel = align_up(off_pos + nf, 256);
@@ -637,6 +641,8 @@ int mpe_rollout_noalloc(const mpe_config* cfg, uint32_t seed, const float* W1, c
   e.st.vel_a = reinterpret_cast<float*>(base + off_vel);
   e.st.pos_l = reinterpret_cast<float*>(base + off_lm);
   e.st.ep_step = reinterpret_cast<int32_t*>(base + off_ep);
+  if (const size_t off_tk = align_up(need, 256); off_tk + size_t(e.TE) * sizeof(uint32_t) <= size_t(MPE_NOALLOC_SCRATCH_BYTES))
+    e.st.tickets = reinterpret_cast<uint32_t*>(base + off_tk);
   e.fault_dev = reinterpret_cast<uint32_t*>(base);
   // The array keeps the last call's contents.  Cleared here: the fault word (a fill kernel, not a memset node, so
   // that the call can be captured into a graph).  Overwritten in full before use: the state (reset kernel) and

@@ -220,6 +220,7 @@ struct StatePtrs {
   float* vel_a;
   float* pos_l;
   int32_t* ep_step;
+  uint32_t* tickets;   // [TE], zero between launches (mpe_slots.h); null: rollouts in one slot
 };
 
 template <int N>
@@ -237,7 +238,7 @@ __device__ __forceinline__ void load_state(Env<N>& s, const StatePtrs& st, size_
 }
 
 template <int N>
-__device__ __forceinline__ void store_state(const Env<N>& s, const StatePtrs& st, size_t TE, size_t g) {
+__device__ __forceinline__ void store_state(const Env<N>& s, const StatePtrs& st, size_t TE, size_t g, bool counter = true) {
 #pragma unroll
   for (int i = 0; i < N; ++i) {
     st.pos_a[(0 * N + i) * TE + g] = s.px[i];
@@ -247,7 +248,7 @@ __device__ __forceinline__ void store_state(const Env<N>& s, const StatePtrs& st
     st.pos_l[(0 * N + i) * TE + g] = s.lx[i];
     st.pos_l[(1 * N + i) * TE + g] = s.ly[i];
   }
-  st.ep_step[g] = s.ep;
+  if (counter) st.ep_step[g] = s.ep;
 }
 
 template <int N>

@@ -11,6 +11,7 @@
 // What bounds it: small batches by the latency of a step, which is why the generator, the rewards and the stores are
 // off wave 0's path and a lane carries one agent instead of a whole env; large ones by the trajectory writes.
 #include "mpe_scenario.h"
+#include "mpe_slots.h"
 
 namespace mpe {
 
@@ -88,7 +89,7 @@ template <typename Scn, typename Piece>
 __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece piece) {
   using M = AgentsSmem<Scn>;
   using TS = typename Scn::Shape;
-  constexpr bool kTag = Scn::kTag;
+  constexpr bool kTag = Scn::kTag, SLOTS = kSlots<Piece>;
   constexpr int N = Scn::N, L = Scn::L, D = Scn::D, EB = M::EB, B = M::B, ENT = N + L, LIVE = Scn::LIVE;
   constexpr int G = kTag ? TS::G : 1, NA = kTag ? TS::A : 0;
   __shared__ __attribute__((aligned(16))) M sm;
@@ -97,8 +98,9 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const size_t TE = A.TE;
-  const uint32_t grp = xcd_group(piece);
-  if (grp >= piece.end) return;
+  int k_slot;
+  uint32_t grp;
+  if (!take_slot(A, piece, k_slot, grp)) return;
   const size_t g0 = size_t(grp) * EB;
   const int nvalid = TE - g0 < size_t(EB) ? int(TE - g0) : EB;
   const bool has_row = B == 64 || lane < B;                 // spare lanes shadow row 0 and store nothing
@@ -107,6 +109,9 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
   const bool in_range = g < TE, valid = has_row && in_range;
   const int32_t max_ep = kTag ? tg.max_ep : A.ph.max_ep;
   int32_t ep = in_range ? A.st.ep_step[g] : 0;
+  const TimeSlot slot = group_slot<SLOTS>(A, k_slot, max_ep, g0, nvalid, lane);
+  const bool head = k_slot == 0;                         // the slot that reads and writes the envs' state
+  if (SLOTS) counter_read(ep);
 
   // the rows' trailing zeros are written once
   for (int k = threadIdx.x; k < int(sizeof(sm.obs) / 4); k += 128) (&sm.obs[0][0])[k] = 0.0f;
@@ -119,16 +124,37 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
     [[maybe_unused]] float gvx[G], gvy[G];
     lx[L] = ly[L] = 0.0f;
     gvx[0] = gvy[0] = 0.0f;
-    if (in_range) {
-      px = A.st.pos_a[(0 * N + i) * TE + g];
-      py = A.st.pos_a[(1 * N + i) * TE + g];
-      vx = A.st.vel_a[(0 * N + i) * TE + g];
-      vy = A.st.vel_a[(1 * N + i) * TE + g];
-    }
+    // a new episode's positions, drawn by the other wavefront
+    auto take_fresh = [&](int parity) {
+      const float2* f = &sm.fresh[parity][el * ENT];
 #pragma unroll
-    for (int k = 0; k < L; ++k) {
-      lx[k] = in_range ? A.st.pos_l[(0 * L + k) * TE + g] : 0.0f;
-      ly[k] = in_range ? A.st.pos_l[(1 * L + k) * TE + g] : 0.0f;
+      for (int a = 0; a < N; ++a) {
+        qx[a] = f[a].x;
+        qy[a] = f[a].y;
+        if (a == i) { px = qx[a]; py = qy[a]; }
+      }
+#pragma unroll
+      for (int k = 0; k < L; ++k) {
+        lx[k] = f[N + k].x;
+        ly[k] = f[N + k].y;
+      }
+    };
+    if (!head) {
+      __syncthreads();
+      take_fresh(1);
+      ep = 0;
+    } else {
+      if (in_range) {
+        px = A.st.pos_a[(0 * N + i) * TE + g];
+        py = A.st.pos_a[(1 * N + i) * TE + g];
+        vx = A.st.vel_a[(0 * N + i) * TE + g];
+        vy = A.st.vel_a[(1 * N + i) * TE + g];
+      }
+#pragma unroll
+      for (int k = 0; k < L; ++k) {
+        lx[k] = in_range ? A.st.pos_l[(0 * L + k) * TE + g] : 0.0f;
+        ly[k] = in_range ? A.st.pos_l[(1 * L + k) * TE + g] : 0.0f;
+      }
     }
     [[maybe_unused]] TagRole me{};
     if constexpr (kTag) me = tag_role<TS>(i, tg);
@@ -162,7 +188,7 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
     exchange(1);
     write_row(0);
     __syncthreads();
-    for (int t = 0; t < A.T; ++t) {
+    for (int t = 0; t < slot.len; ++t) {
       const int par = t & 1;
       const uint32_t act = sm.act[par][row];
       if constexpr (kTag) tag_move<TS>(act, i, me, tg, px, py, vx, vy, qx, qy, lx, ly);
@@ -170,18 +196,7 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
       exchange(par);
       ep += 1;
       if (ep >= max_ep) {
-        const float2* f = &sm.fresh[par][el * ENT];
-#pragma unroll
-        for (int a = 0; a < N; ++a) {
-          qx[a] = f[a].x;
-          qy[a] = f[a].y;
-          if (a == i) { px = qx[a]; py = qy[a]; }
-        }
-#pragma unroll
-        for (int k = 0; k < L; ++k) {
-          lx[k] = f[N + k].x;
-          ly[k] = f[N + k].y;
-        }
+        take_fresh(par);
         if constexpr (kTag) {
 #pragma unroll
           for (int k = 0; k < G; ++k) gvx[k] = gvy[k] = 0.0f;
@@ -192,7 +207,7 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
       write_row(par ^ 1);
       __syncthreads();
     }
-    if (valid) {
+    if (valid && head) {
       A.st.pos_a[(0 * N + i) * TE + g] = px;
       A.st.pos_a[(1 * N + i) * TE + g] = py;
       A.st.vel_a[(0 * N + i) * TE + g] = vx;
@@ -204,7 +219,7 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
           A.st.pos_l[(1 * L + l) * TE + g] = ly[l];
         }
       }
-      if (i == 0) A.st.ep_step[g] = ep;
+      if (i == 0 && !SLOTS) A.st.ep_step[g] = ep;
     }
   } else {
     // ================================================================ generator and stores
@@ -222,8 +237,8 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
 #pragma unroll
       for (int k = 0; k < RL; ++k) {
         const int l = kByLanes ? i : k;
-        lx[k] = in_range ? A.st.pos_l[(0 * L + l) * TE + g] : 0.0f;
-        ly[k] = in_range ? A.st.pos_l[(1 * L + l) * TE + g] : 0.0f;
+        lx[k] = head && in_range ? A.st.pos_l[(0 * L + l) * TE + g] : 0.0f;
+        ly[k] = head && in_range ? A.st.pos_l[(1 * L + l) * TE + g] : 0.0f;
       }
     }
     [[maybe_unused]] TagRole me{};
@@ -232,8 +247,23 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
     float* rew_p = A.rew_traj;
     uint8_t* done_p = A.done_traj;
     float* obs_p = A.obs_traj;
-    uint32_t step = A.abs_step;      // of the next draw
+    int t_draw = 0;                                          // local and absolute step of the next draw
+    uint32_t step = A.abs_step + uint32_t(slot.t0);
 
+    auto new_episode = [&](int parity) {                     // that starts at `step`
+      uint32_t env_r = env;
+      asm volatile("" : "+v"(env_r));
+      draw_fresh<Scn>(sm.fresh[parity], el, i, has_row, env_r, step, A.seed, run);
+    };
+    auto take_landmarks = [&](int parity) {
+      const float2* f = &sm.fresh[parity][el * ENT + N];
+#pragma unroll
+      for (int k = 0; k < RL; ++k) {
+        const float2 p = f[kByLanes ? i : k];
+        lx[k] = p.x;
+        ly[k] = p.y;
+      }
+    };
     // action of step `step` and, if the env's episode ends with it, the next episode's positions; returns the latter
     auto draw = [&](int parity) {
       const uint32_t act = word_to_action(philox4x32_10(env, step, uint32_t(i), kTagUniformAction, A.seed, run).x);
@@ -242,14 +272,11 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
         if (valid) act_p[row_off] = uint8_t(act);
         act_p += TE * N;
       }
-      const bool done = ep + 1 >= max_ep;
-      if (done) {
-        uint32_t env_r = env;
-        asm volatile("" : "+v"(env_r));
-        draw_fresh<Scn>(sm.fresh[parity], el, i, has_row, env_r, step + 1u, A.seed, run);
-      }
+      const bool done = ep + 1 >= max_ep, turn = ++t_draw == slot.turn;
+      step += turn ? 1u + uint32_t(slot.jump) : 1u;
+      if (turn && act_p) act_p += size_t(slot.jump) * TE * N;
+      if (done) new_episode(parity);
       ep = done ? 0 : ep + 1;
-      ++step;
       return done;
     };
     // reward and done flag of the step whose positions are in xch[parity]
@@ -284,15 +311,7 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
         done_p += TE;
       }
       if constexpr (!kTag) {
-        if (done) {
-          const float2* f = &sm.fresh[parity][el * ENT + N];
-#pragma unroll
-          for (int k = 0; k < RL; ++k) {
-            const float2 p = f[kByLanes ? i : k];
-            lx[k] = p.x;
-            ly[k] = p.y;
-          }
-        }
+        if (done) take_landmarks(parity);
       }
     };
     auto flush = [&](int parity, float* slice) {
@@ -301,21 +320,43 @@ __global__ __launch_bounds__(128) void rollout_agents_kernel(TagArgs TA, Piece p
       if (vec4 && nvalid == EB) stream_out_full<B * D / 4>(sm.obs[parity], dst, lane);
       else stream_out(sm.obs[parity], dst, nvalid * N * D, vec4, lane);
     };
-    bool done_now = draw(0), done_before = false;   // of steps t and t - 1
+    // time goes on: rewards and done flags are a step behind the rows, the actions a step ahead of them
+    auto skip = [&](int steps) {
+      if (rew_p) rew_p += size_t(steps) * TE * (per_agent ? N : 1);
+      if (done_p) done_p += size_t(steps) * TE;
+    };
+    [[maybe_unused]] const int32_t ep0 = ep;
+    if (!head) {
+      skip(slot.t0);
+      if (obs_p) obs_p += size_t(slot.t0) * TE * (N * D);
+      if (act_p) act_p += size_t(slot.t0) * TE * N;
+      ep = 0;
+      new_episode(1);
+      __syncthreads();
+      if constexpr (!kTag) take_landmarks(1);
+    }
+    bool done_now = (!SLOTS || slot.len > 0) && draw(0), done_before = false;   // of steps t and t - 1
     __syncthreads();
-    for (int t = 0; t < A.T; ++t) {
+    [[maybe_unused]] uint32_t ticket = 0;
+    if (SLOTS && env_writer) ticket = take_ticket(A, g);
+    for (int t = 0; t < slot.len; ++t) {
       const int par = t & 1;
       if (obs_p) {
         flush(par, obs_p);
         obs_p += TE * (N * D);
+        if (t + 1 == slot.turn) obs_p += size_t(slot.jump) * TE * (N * D);
       }
-      if (t > 0) finish(par ^ 1, done_before);
+      if (t > 0) {
+        finish(par ^ 1, done_before);
+        if (t == slot.turn) skip(slot.jump);
+      }
       done_before = done_now;
-      if (t + 1 < A.T) done_now = draw(par ^ 1);
+      if (t + 1 < slot.len) done_now = draw(par ^ 1);
       __syncthreads();
     }
-    finish((A.T - 1) & 1, done_before);
-    if (A.last_obs) flush(A.T & 1, A.last_obs);
+    if (!SLOTS || slot.len > 0) finish((slot.len - 1) & 1, done_before);
+    if (A.last_obs && head) flush(slot.len & 1, A.last_obs);
+    if (SLOTS && env_writer) settle_ticket(A, max_ep, g, ticket, ep0);
   }
 }
 
@@ -501,6 +542,10 @@ hipError_t launch_agents(const TagArgs& A, hipStream_t s) {
       return hipErrorInvalidValue;
     }
   }
+  if (A.r.slots > 1) {
+    hipLaunchKernelGGL((rollout_agents_kernel<Scn, SlotGrid>), slots_grid(A.r, waves), dim3(128), 0, s, A, SlotGrid{waves});
+    return hipGetLastError();
+  }
   return launch_groups<128>(waves, [&](dim3 grid, const GridPiece& p) {
     if (p.first == 0 && p.end == waves) hipLaunchKernelGGL((rollout_agents_kernel<Scn, WholeGrid>), grid, dim3(128), 0, s, A, WholeGrid{p.end, p.per_xcd});
     else hipLaunchKernelGGL((rollout_agents_kernel<Scn, GridPiece>), grid, dim3(128), 0, s, A, p);
@@ -536,6 +581,21 @@ bool env_agents_faster(bool tag, int N, uint32_t TE) {
   if (N == 3) return per_cu <= 64;
   if (N == 4) return per_cu <= 128;
   return per_cu <= (N <= 7 ? 96 : 52);
+}
+
+// Slots of time for a rollout without a policy.  They pay while the latency of a step keeps the writes below what the
+// trajectory's address pattern takes (5 to 5.5 TB/s), and cost up to 10 % beyond: TE envs write `bytes` a step, which takes
+// about 0.26 N us with a lane per env (up to 3 agents of simple spread), 0.45 + 0.05 N us with a lane per agent.  Measured,
+// 128 steps, us, 1 / 2 / 5 slots: 1 agent 1,000 envs 44 / 28 / 12, 32,768 40 / 26 / 23; 2 agents 16,384 65 / 43 / 43 (3.2
+// TB/s with one slot), 24,576 71 / 59 / 60 (4.9), 32,768 72 / 78 / 79 (6.5); 3 agents 1,000 85 / 54 / 24, 12,288 96 / 71 / 66
+// (3.5), 16,384 99 / 88 / 91 (4.7), 24,576 118 / 127 / 135 (7.1); 4 agents 4,096 76 / 49 / 41 (2.5), 8,192 77 / 78 / 83 (5.0);
+// 5 agents 4,096 100 / 69 / 74 (3.5); 10 agents 1,000 145 / 91 / 67 (2.5), 2,048 120 / 132 / 135 (5.2); predator-prey of 4
+// agents 1,000 85 / 54 / 22, 8,192 75 / 53 / 57 (3.5), 16,384 105 / 104 / 107 (7.0).
+uint32_t env_slots(bool tag, int N, int D, uint32_t TE) {
+  const bool per_env = !tag && N <= 3;
+  const float rate = float(TE) * float(N * (4 * D + 1) + 5) / (per_env ? 0.26f * float(N) : 0.45f + 0.05f * float(N));   // bytes/us
+  const float all = per_env ? 3.9e6f : 2.7e6f, two = per_env ? 4.95e6f : 4.8e6f, chip = float(compute_units()) / 256.0f;
+  return rate <= all * chip ? ~0u : (rate <= two * chip ? 2u : 1u);
 }
 
 hipError_t launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s) {

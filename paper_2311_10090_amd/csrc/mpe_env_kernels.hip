@@ -2,7 +2,7 @@
 // T-step rollout with seeded uniform actions (small batches of 3 agents, and more agents: mpe_env_agents.hip).  One
 // lane owns one environment; the whole state of that env stays
 // in registers for the T steps of a rollout and only the trajectory leaves the chip.
-#include "mpe_launch.h"
+#include "mpe_slots.h"
 
 namespace mpe {
 
@@ -39,7 +39,10 @@ __global__ __launch_bounds__(kWave) void reset_kernel(StatePtrs st, uint32_t TE,
   const Lane L = lane_info(TE, E);
   Env<N> s;
   reset_env<N>(s, seed, L.run, L.env, 0u);
-  if (L.valid) store_state<N>(s, st, TE, L.g);
+  if (L.valid) {
+    store_state<N>(s, st, TE, L.g);
+    if (st.tickets) st.tickets[L.g] = 0u;
+  }
   if (obs) emit_obs<N>(s, tile, obs + L.g0 * (N * 6 * N), L.nvalid, L.lane);
 }
 
@@ -121,7 +124,8 @@ struct SliceBuf {
 // GENERAL: env counts that are no multiple of 64, or outputs whose time slices do not all start on 16 bytes: rows still
 // leave in 16-byte pieces (a slice starts on 8 bytes), the small outputs element by element.  (128 steps of 1,000 envs x 1 agent 70 -> 45 us, 1,000 x 2 104 -> 72 us, 32,760
 // x 3 206 -> 173 us against the one-wavefront kernel that such batches took before.)
-template <int N, bool GENERAL, bool PER_AGENT>
+// SLOTS: a launch of several slots of time (mpe_slots.h).
+template <int N, bool GENERAL, bool PER_AGENT, bool SLOTS>
 __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutArgs A, uint32_t groups,
                                                                        uint32_t groups_per_xcd) {
   using SB = SliceBuf<N, PER_AGENT>;
@@ -130,10 +134,13 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
   __shared__ __attribute__((aligned(16))) uint8_t buf[2][SB::BYTES];
   const int lane = threadIdx.x & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
-  if (grp >= groups) return;  // whole block, before any barrier
+  int k_slot = 0;
+  uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
+  if (SLOTS ? !take_slot(A, SlotGrid{groups}, k_slot, grp) : grp >= groups) return;  // whole block, before any barrier
   const size_t TE = A.TE;
   const size_t g0 = size_t(grp) * kWave;
+  const TimeSlot slot = group_slot<SLOTS>(A, k_slot, A.ph.max_ep, g0, int(min(TE - g0, size_t(kWave))), lane);
+  const bool head = k_slot == 0;              // the slot that reads and writes the envs' state
 
   if (wave == 0) {
     // ------------------------------------------------------------------ compute wave
@@ -141,25 +148,35 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
     const size_t g = valid ? g0 + lane : g0;      // lanes past the last env shadow the group's first and store nothing
     const uint32_t run = uint32_t(g) / A.E;
     const uint32_t env = uint32_t(g) - run * A.E;
+    uint32_t step = A.abs_step + uint32_t(slot.t0);
     Env<N> s;
-    load_state<N>(s, A.st, TE, g);
+    [[maybe_unused]] int32_t ep0 = 0;
+    [[maybe_unused]] uint32_t ticket = 0;
+    if (head) load_state<N>(s, A.st, TE, g);
+    else reset_env<N>(s, A.seed, run, env, step);
+    if constexpr (SLOTS) {
+      ep0 = head ? s.ep : A.st.ep_step[g];
+      counter_read(ep0);
+      __syncthreads();                           // the writer has read the counters
+      if (valid) ticket = take_ticket(A, g);
+    }
     auto write_obs = [&](uint8_t* b) {
       float2* row = reinterpret_cast<float2*>(b) + lane * (N * D / 2);
 #pragma unroll
       for (int i = 0; i < N; ++i) build_agent_obs<N>(s, i, row + i * (D / 2));
     };
     write_obs(buf[0]);
-    uint32_t step = A.abs_step;
-    for (int t = 0; t < A.T; ++t, ++step) {
+    for (int t = 0; t < slot.len; ++t) {
       uint32_t a[N];
 #pragma unroll
       for (int i = 0; i < N; ++i) {
         const uint4 w = philox4x32_10(env, step, uint32_t(i), kTagUniformAction, A.seed, run);
         a[i] = word_to_action(w.x);
       }
+      step += t + 1 == slot.turn ? 1u + uint32_t(slot.jump) : 1u;
       float r[RW];
       bool d;
-      transition<N, PER_AGENT>(s, a, A.ph, A.seed, run, env, step, r, d);
+      transition<N, PER_AGENT>(s, a, A.ph, A.seed, run, env, step - 1u, r, d);
       __syncthreads();  // X_t
       uint8_t* cur = buf[t & 1];
 #pragma unroll
@@ -170,53 +187,57 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
       write_obs(buf[(t + 1) & 1]);
       __syncthreads();  // Y_t
     }
-    if (A.last_obs) {
-      const float* last = reinterpret_cast<const float*>(buf[A.T & 1]);
+    if (A.last_obs && head) {
+      const float* last = reinterpret_cast<const float*>(buf[slot.len & 1]);
       if constexpr (GENERAL) stream_out(last, A.last_obs + g0 * (N * D), int(min(TE - g0, size_t(kWave))) * N * D, false, lane);
       else stream_out_full<SB::OBS_F4>(last, A.last_obs + g0 * (N * D), lane);
     }
-    if (valid) store_state<N>(s, A.st, TE, g);
+    if (valid && head) store_state<N>(s, A.st, TE, g, !SLOTS);
+    if (SLOTS && valid) settle_ticket(A, A.ph.max_ep, g, ticket, ep0);
   } else if constexpr (GENERAL) {
     // ------------------------------------------------------------------ writer wave, any size and alignment
     typedef float v4f_a8 __attribute__((ext_vector_type(4), aligned(8)));
     const int n = int(min(TE - g0, size_t(kWave)));          // envs of this group
     const int n4 = n * N * D / 4;                            // whole 16-byte pieces of their rows
     constexpr int kRounds = (SB::OBS_F4 + kWave - 1) / kWave;
-    uint8_t* obs_g = A.obs_traj ? reinterpret_cast<uint8_t*>(A.obs_traj + g0 * (N * D)) : nullptr;
-    uint8_t* act_g = A.act_traj ? A.act_traj + g0 * N : nullptr;
-    float* rew_g = A.rew_traj ? A.rew_traj + g0 * RW : nullptr;
-    uint8_t* done_g = A.done_traj ? A.done_traj + g0 : nullptr;
+    const size_t e0 = size_t(slot.t0) * TE + g0;             // the group's first env in its first time slice
+    uint8_t* obs_g = A.obs_traj ? reinterpret_cast<uint8_t*>(A.obs_traj + e0 * (N * D)) : nullptr;
+    uint8_t* act_g = A.act_traj ? A.act_traj + e0 * N : nullptr;
+    float* rew_g = A.rew_traj ? A.rew_traj + e0 * RW : nullptr;
+    uint8_t* done_g = A.done_traj ? A.done_traj + e0 : nullptr;
     v4f v[kRounds];
     v2f tail = {0.0f, 0.0f};
     float rew[RW];
     uint8_t act[N], done = 0;
-    for (int t = 0; t <= A.T; ++t) {
+    if (SLOTS) __syncthreads();
+    for (int t = 0; t <= slot.len; ++t) {
       if (t > 0) {
+        const size_t on = TE * (t == slot.turn ? 1u + size_t(slot.jump) : 1u);   // envs to the next time slice
         if (obs_g) {
 #pragma unroll
           for (int k = 0; k < kRounds; ++k)
             if (k * kWave + lane < n4) __builtin_nontemporal_store(v[k], reinterpret_cast<v4f_a8*>(obs_g) + (k * kWave + lane));
           if ((n * N * D) % 4 && lane == 0) *reinterpret_cast<v2f*>(obs_g + size_t(n4) * 16) = tail;
-          obs_g += TE * (N * D) * 4;
+          obs_g += on * (N * D) * 4;
         }
         if (rew_g) {
 #pragma unroll
           for (int i = 0; i < RW; ++i)
             if (i * kWave + lane < n * RW) rew_g[i * kWave + lane] = rew[i];
-          rew_g += TE * RW;
+          rew_g += on * RW;
         }
         if (act_g) {
 #pragma unroll
           for (int i = 0; i < N; ++i)
             if (i * kWave + lane < n * N) act_g[i * kWave + lane] = act[i];
-          act_g += TE * N;
+          act_g += on * N;
         }
         if (done_g) {
           if (lane < n) done_g[lane] = done;
-          done_g += TE;
+          done_g += on;
         }
       }
-      if (t == A.T) break;
+      if (t == slot.len) break;
       __syncthreads();  // X_t
       __syncthreads();  // Y_t
       const uint8_t* cur = buf[t & 1];
@@ -236,7 +257,8 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
     // ------------------------------------------------------------------ writer wave
     // Full rounds: lane l moves obs float4 number k*64 + l.  Mixed round: the obs tail, then
     // reward (16 lanes), actions (4N lanes) and done (4 lanes), one float4 each.
-    uint8_t* obs_g = A.obs_traj ? reinterpret_cast<uint8_t*>(A.obs_traj + g0 * (N * D)) + lane * 16 : nullptr;
+    const size_t e0 = size_t(slot.t0) * TE + g0;             // the group's first env in its first time slice
+    uint8_t* obs_g = A.obs_traj ? reinterpret_cast<uint8_t*>(A.obs_traj + e0 * (N * D)) + lane * 16 : nullptr;
     const size_t obs_stride = TE * (N * D) * 4;
     int mix_lds = -1;          // byte offset inside a slice buffer, -1: lane idle in the mixed round
     uint8_t* mix_g = nullptr;
@@ -244,25 +266,25 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
     if (lane < SB::TAIL) {
       if (A.obs_traj) {
         mix_lds = (SB::FULL * kWave + lane) * 16;
-        mix_g = reinterpret_cast<uint8_t*>(A.obs_traj + g0 * (N * D)) + mix_lds;
+        mix_g = reinterpret_cast<uint8_t*>(A.obs_traj + e0 * (N * D)) + mix_lds;
         mix_stride = obs_stride;
       }
     } else if (lane < SB::ACT_L) {
       if (A.rew_traj) {
         mix_lds = SB::REW_OFF + (lane - SB::REW_L) * 16;
-        mix_g = reinterpret_cast<uint8_t*>(A.rew_traj + g0) + (lane - SB::REW_L) * 16;
+        mix_g = reinterpret_cast<uint8_t*>(A.rew_traj + e0) + (lane - SB::REW_L) * 16;
         mix_stride = TE * 4;
       }
     } else if (lane < SB::DONE_L) {
       if (A.act_traj) {
         mix_lds = SB::ACT_OFF + (lane - SB::ACT_L) * 16;
-        mix_g = A.act_traj + g0 * N + (lane - SB::ACT_L) * 16;
+        mix_g = A.act_traj + e0 * N + (lane - SB::ACT_L) * 16;
         mix_stride = TE * N;
       }
     } else if (lane < SB::END_L) {
       if (A.done_traj) {
         mix_lds = SB::DONE_OFF + (lane - SB::DONE_L) * 16;
-        mix_g = A.done_traj + g0 + (lane - SB::DONE_L) * 16;
+        mix_g = A.done_traj + e0 + (lane - SB::DONE_L) * 16;
         mix_stride = TE;
       }
     }
@@ -270,8 +292,9 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
     v4f vm = {0.0f, 0.0f, 0.0f, 0.0f};
     [[maybe_unused]] v4f vr = {0.0f, 0.0f, 0.0f, 0.0f};
     // the per-agent rewards' own round
-    [[maybe_unused]] uint8_t* rew_g = PER_AGENT && A.rew_traj && lane < 16 * RW ? reinterpret_cast<uint8_t*>(A.rew_traj + g0 * RW) + lane * 16 : nullptr;
-    for (int t = 0; t <= A.T; ++t) {
+    [[maybe_unused]] uint8_t* rew_g = PER_AGENT && A.rew_traj && lane < 16 * RW ? reinterpret_cast<uint8_t*>(A.rew_traj + e0 * RW) + lane * 16 : nullptr;
+    if (SLOTS) __syncthreads();
+    for (int t = 0; t <= slot.len; ++t) {
       if (t > 0) {
         if (obs_g) {
 #pragma unroll
@@ -288,8 +311,13 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
             rew_g += TE * RW * 4;
           }
         }
+        if (t == slot.turn) {
+          if (obs_g) obs_g += size_t(slot.jump) * obs_stride;
+          if (mix_lds >= 0) mix_g += size_t(slot.jump) * mix_stride;
+          if (PER_AGENT && rew_g) rew_g += size_t(slot.jump) * TE * RW * 4;
+        }
       }
-      if (t == A.T) break;
+      if (t == slot.len) break;
       __syncthreads();  // X_t
       __syncthreads();  // Y_t
       const uint8_t* cur = buf[t & 1];
@@ -332,16 +360,20 @@ struct EnvLaunch {
     return hipGetLastError();
   }
   static hipError_t rollout(const RolloutArgs& A, hipStream_t s) {
+    return A.slots > 1 ? rollout_slots<true>(A, s) : rollout_slots<false>(A, s);
+  }
+  template <bool SLOTS>
+  static hipError_t rollout_slots(const RolloutArgs& A, hipStream_t s) {
     const uint32_t groups = (A.TE + kWave - 1) / kWave;
     const uint32_t per_xcd = (groups + 7) / 8;
-    const dim3 grid(per_xcd * 8), block(2 * kWave);
+    const dim3 grid = SLOTS ? slots_grid(A, groups) : dim3(per_xcd * 8), block(2 * kWave);
     const bool mixed = A.ph.reward_mode == 1;
     if (ws_aligned<N>(A)) {
-      if (mixed) hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, false, true>), grid, block, 0, s, A, groups, per_xcd);
-      else hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, false, false>), grid, block, 0, s, A, groups, per_xcd);
+      if (mixed) hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, false, true, SLOTS>), grid, block, 0, s, A, groups, per_xcd);
+      else hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, false, false, SLOTS>), grid, block, 0, s, A, groups, per_xcd);
     } else {
-      if (mixed) hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, true, true>), grid, block, 0, s, A, groups, per_xcd);
-      else hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, true, false>), grid, block, 0, s, A, groups, per_xcd);
+      if (mixed) hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, true, true, SLOTS>), grid, block, 0, s, A, groups, per_xcd);
+      else hipLaunchKernelGGL((rollout_uniform_ws_kernel<N, true, false, SLOTS>), grid, block, 0, s, A, groups, per_xcd);
     }
     return hipGetLastError();
   }
@@ -388,15 +420,17 @@ hipError_t launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, 
 }
 
 hipError_t launch_rollout_uniform(int N, const RolloutArgs& A, hipStream_t s) {
-  if (env_agents_faster(false, N, A.TE)) {
+  RolloutArgs B = A;
+  choose_slots(B, A.ph.max_ep, env_slots(false, N, 6 * N, A.TE));
+  if (env_agents_faster(false, N, B.work()) || (N > 3 && B.slots > 1)) {
     TagArgs TA{};
-    TA.r = A;
+    TA.r = B;
     return launch_env_agents(false, N, N, 0, TA, s);
   }
   // many agents: one lane per agent (the wide fused kernel without its policy) writes contiguous pieces of the
   // trajectory
   if (N > 3) return launch_rollout_uniform_wide(N, A, s);
-  MPE_DISPATCH_FEW(N, EnvLaunch<kN>::rollout(A, s));
+  MPE_DISPATCH_FEW(N, EnvLaunch<kN>::rollout(B, s));
 }
 
 }  // namespace mpe

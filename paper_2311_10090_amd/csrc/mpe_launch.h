@@ -79,6 +79,9 @@ struct RolloutArgs {
   uint32_t* fault = nullptr;
   // Polls after which a wait at a sync-group barrier gives up (kBarrierSpinLimit unless a test lowers it).
   uint32_t barrier_polls = 1u << 24;
+  // Slots of time that run side by side, steps of one (mpe_slots.h).
+  int32_t slots = 1, span = 0;
+  uint32_t work() const { return TE * uint32_t(slots); }   // envs that the launch steps side by side
 };
 
 // Predator-prey scenario: constants by role (index 0 adversary, 1 good agent), combined on the
@@ -188,6 +191,8 @@ hipError_t pack_gru_critic(PolicyBuffers& pb, int N, int D, uint32_t TE, uint32_
 // step through A.r.rew_traj, done_traj, last_obs), or, with A.actions_in null, a rollout with uniform actions.
 // Whether its rollout is the faster one for this batch.
 bool env_agents_faster(bool tag, int N, uint32_t TE);
+// The most slots of time (mpe_slots.h) that its rollout, or for up to 3 agents of simple spread that of mpe_env_kernels.hip, is to use.
+uint32_t env_slots(bool tag, int N, int D, uint32_t TE);
 hipError_t launch_env_agents(bool tag, int N, int L, int G, const TagArgs& A, hipStream_t s);
 // Blocks of half-filled wavefronts are up to 16 threads per env and launched whole: for up to this many envs, 2^31 threads.
 constexpr uint32_t kWholeLaunchEnvs = 1u << 27;

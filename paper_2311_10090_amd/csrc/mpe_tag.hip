@@ -10,6 +10,7 @@
 // 64 rows are one contiguous piece of the trajectory and leave with 16-byte stores over whole
 // cache lines.  Rewards are per agent, so every lane stores its own.
 #include "mpe_mlp64.h"
+#include "mpe_slots.h"
 #include "mpe_tag_device.h"
 
 namespace mpe {
@@ -74,6 +75,7 @@ __global__ __launch_bounds__(64 * S::N) void tag_reset_kernel(StatePtrs st, uint
       st.pos_l[(1 * L + k) * size_t(TE) + g] = ly[k];
     }
     st.ep_step[g] = 0;
+    if (st.tickets) st.tickets[g] = 0u;
   }
   if (obs) {
     float2 row[D / 2];
@@ -477,10 +479,12 @@ template <typename S>
 hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void* packed_critic, hipStream_t s,
                       const char** why) {
   if (mode == kUniform) {
+    TagArgs B = A;
+    choose_slots(B.r, A.tg.max_ep, env_slots(true, S::N, S::D, A.r.TE));
     if constexpr (S::N != 4 && S::N != 10) {
-      if (!env_agents_faster(true, S::N, A.r.TE)) return tag_rollout_impl<S, kUniform>(A, nullptr, nullptr, s);
+      if (B.r.slots == 1 && !env_agents_faster(true, S::N, A.r.TE)) return tag_rollout_impl<S, kUniform>(A, nullptr, nullptr, s);
     }
-    return launch_env_agents(true, S::N, S::L, S::G, A, s);
+    return launch_env_agents(true, S::N, S::L, S::G, B, s);
   }
   if (A.r.TE != A.r.E && A.r.E % 16 != 0) {
     *why = "with several runs, num_envs per run must be a multiple of 16";

@@ -1,0 +1,34 @@
+"""Which rollouts run in slots of time (mpe_slots.h), from recorded launches: the blocks of all slots, eight XCDs at a time."""
+import pytest
+
+from tests.launch_record import build_recorder, launches, record
+
+
+@pytest.fixture(scope="module")
+def recorder(tmp_path_factory):
+    return build_recorder(tmp_path_factory.mktemp("recorder"))
+
+
+def blocks(recorder, shape, T):
+    out = record(recorder, ["create " + shape, "reset", "rollout %d" % T])
+    (name, grid), = launches(out[-1][1])
+    return name.split("<")[0], grid
+
+
+def padded(n):
+    return (n + 7) // 8 * 8
+
+
+@pytest.mark.parametrize("shape,T,kernel,groups,slots", [
+    ("0 3 3 0 1000 1", 128, "rollout_agents_kernel", 50, 5),              # 20 envs to a block; 28 + 4 x 25 steps
+    ("0 3 3 0 1000 1", 74, "rollout_agents_kernel", 50, 2),
+    ("0 3 3 0 1000 1", 49, "rollout_agents_kernel", 50, 1),               # no two episodes
+    ("0 3 3 0 1000 8", 128, "rollout_uniform_ws_kernel", 125, 5),         # runs side by side are one batch
+    ("0 3 3 0 16384 1", 128, "rollout_uniform_ws_kernel", 256, 2),        # near the rate of the writes: two
+    ("0 3 3 0 65536 1", 128, "rollout_uniform_ws_kernel", 1024, 1),
+    ("0 1 1 0 32768 1", 100, "rollout_uniform_ws_kernel", 512, 4),
+    ("0 10 10 0 1000 1", 128, "rollout_agents_kernel", 167, 5),
+    ("1 4 2 3 1000 1", 2048, "rollout_agents_kernel", 63, 81),
+])
+def test_environment_only(recorder, shape, T, kernel, groups, slots):
+    assert blocks(recorder, shape, T) == (kernel, padded(groups * slots))

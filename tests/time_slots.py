@@ -1,0 +1,65 @@
+"""Rollouts whose time runs in slots side by side, against the same steps in calls that are too short for slots: an
+environment's trajectory does not depend on how its steps are divided among calls, bit for bit."""
+import torch
+
+from paper_2311_10090_amd import synth
+from paper_2311_10090_amd.binding import MpeConfig, MpeEnv
+
+SHORT = 30           # two slots are at least 32 steps
+
+
+def counters(kind, envs, max_ep):
+    """Episode counters at the start: all alike; alike in stretches of 500 envs; each its own, also beyond the episode's end
+    and below zero."""
+    if kind == "alike":
+        return torch.full((envs,), 7 % max_ep, dtype=torch.int32)
+    if kind == "stretches":
+        return (torch.arange(envs) // 500 % max_ep).to(torch.int32)
+    return torch.randint(-3, max_ep + 4, (envs,), generator=torch.Generator().manual_seed(5), dtype=torch.int32)
+
+
+def outputs(cfg, T, start, pieces, policy=(), critic=(), gru=False, left_out=()):
+    """Everything that two rollouts of T steps write, each in calls of the given lengths."""
+    assert sum(pieces) == T
+    env = MpeEnv(MpeConfig(**cfg))
+    if policy:
+        (env.set_gru_policy if gru else env.set_policy)(*policy)
+    if critic:
+        (env.set_gru_critic if gru else env.set_critic)(*critic)
+    env.reset(11)
+    pa, va, pl, _, step = env.get_state()
+    env.set_state(pa, va, pl, start.cuda(), 11, int(step))
+    kept = []
+    for _ in range(2):
+        parts = []
+        for n in pieces:
+            bufs = list(env.empty_traj_ac(n) if critic else env.empty_traj(n))
+            for k in left_out:
+                bufs[k] = None
+            out = env.rollout_ac(n, *bufs) if critic else env.rollout(n, *bufs)
+            parts.append([None if o is None else o.clone() for o in out])
+        last = 2 if critic else 1
+        for k in range(len(parts[0])):
+            if parts[0][k] is not None:
+                kept.append(parts[-1][k] if k >= len(parts[0]) - last else torch.cat([p[k] for p in parts]))
+        kept += [s.clone() for s in env.get_state()[:4]]
+        if gru:
+            kept.append(env.get_hidden().clone())
+    env.close()
+    return kept
+
+
+def assert_slots_change_nothing(cfg, T, kind, max_ep, **more):
+    envs = cfg["num_envs"] * cfg["num_runs"]
+    print("slots: %d envs, %d agents, %d steps, episodes of %d, counters %s" % (envs, cfg["num_agents"], T, max_ep, kind), flush=True)
+    start = counters(kind, envs, max_ep)
+    short = [SHORT] * (T // SHORT) + ([T % SHORT] if T % SHORT else [])
+    for k, (a, b) in enumerate(zip(outputs(cfg, T, start, [T], **more), outputs(cfg, T, start, short, **more))):
+        assert torch.equal(a, b), ("output", k)
+
+
+def config(scenario, agents, envs, max_ep, runs=1, hidden=0, wd=0):
+    if scenario == "tag":
+        landmarks, adversaries = {2: (1, 1), 3: (0, 2), 4: (2, 3), 5: (2, 4), 6: (2, 4), 8: (2, 6), 10: (3, 8)}[agents]
+        return synth.tag_config(envs, agents, landmarks, adversaries, runs, hidden, wd, max_episode_steps=max_ep)
+    return synth.spread_config(envs, agents, runs, hidden, wd, max_episode_steps=max_ep, reward_mode=agents % 2)
