@@ -203,6 +203,11 @@ inline bool half_empty_waves(const RolloutArgs& A, uint32_t N) { return A.TE != 
 // Full batches, independent wavefronts (mpe_waves.h).  critic: the packed critic of the actor-critic rollout, or null.
 hipError_t launch_waves_spread(int N, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s);
 hipError_t launch_waves_tag(int N, int L, int G, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s);
+// The same in the slots of A (mpe_slots.h): *taken = true and launched where that pays.
+hipError_t launch_waves_spread_slots(int N, bool bf16, const TagArgs& A, const void* packed, const void* critic, hipStream_t s, bool* taken);
+// against: this kernel would also run the batch in one slot
+hipError_t launch_waves_tag_slots(int N, int L, int G, bool bf16, const TagArgs& A, bool against, const void* packed, const void* critic,
+                                  hipStream_t s, bool* taken);
 // Small batches and small runs (mpe_small.h): *taken = true and the rollout launched where that kernel is the faster
 // one for the batch, else nothing done.  A.tg is read by the predator-prey shapes only.
 // unfit: the runs suit no block of the other kernels.

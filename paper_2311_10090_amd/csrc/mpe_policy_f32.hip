@@ -33,6 +33,7 @@
 // to bf16, nearest even, fp32 accumulation -- one matrix instruction per product instead of
 // six, no operand split; policy_pair_bf).
 #include "mpe_mlp64.h"
+#include "mpe_slots.h"
 
 namespace mpe {
 
@@ -684,6 +685,33 @@ TagArgs small_args(const RolloutArgs& A) {
   return t;
 }
 
+// In several slots of time (mpe_slots.h), where the rollout is long enough for them: small batches in the small-batch
+// kernel, others in independent wavefronts, which slots keep full at every size.  What stays in one slot are batches that
+// fill the chip in (nearly) whole rounds of this file's 256-env blocks, whose arithmetic shares more, with 3 agents (65,536
+// envs 1,470 us, in slots 1,510; 57,344 envs in slots 1,325) and with 2 agents in the plain rollout, and runs that suit no
+// wavefront.  128 steps, us, one slot / several: 1 agent 65,536 envs 590 / 484, critic 1,167 / 890; 2 agents, critic, 49,152 1,785
+// / 1,340; 3 agents, 20,011 envs 622 / 507, critic, 32,768 1,707 / 1,478; 3 agents bf16, critic, 32,768 1,829 / 927; 1,024
+// runs x 16 envs x 3 agents 475 / 412, critic 884 / 760; 1,024 runs x 64, critic 3,543 / 3,000.
+template <int N, bool BF>
+hipError_t launch_slots(const RolloutArgs& A, const PolicyBuffers& pb, const void* critic, hipStream_t s, bool* taken) {
+  TagArgs B = small_args(A);
+  choose_slots(B.r, A.ph.max_ep, ~0u);
+  const bool runs = A.TE != A.E;
+  if (B.r.slots == 1 || (runs && A.E % 16 != 0)) return hipSuccess;
+  // with a critic and 6 or 8 agents, where 8-env blocks of one slot are about one per CU (2,048 envs x 8 agents 453 us, 512 in slots)
+  const uint32_t cus = compute_units();
+  constexpr uint32_t kTenths = N == 8 ? 64 : (N == 6 ? 75 : 80);
+  if (critic && A.TE * 10 > kTenths * cus && A.TE <= 8 * cus) return hipSuccess;
+  const hipError_t e = critic ? launch_small_spread_ac(N, BF, B, false, pb.packed, critic, s, taken) : launch_small_spread(N, BF, B, false, pb.packed, s, taken);
+  if (*taken || e != hipSuccess) return e;
+  if constexpr (N == 3 || N == 2) {
+    const uint32_t blocks = (A.TE + 255) / 256, rounds = (blocks + cus - 1) / cus;
+    const bool full = uint64_t(blocks) * 25 >= uint64_t(rounds) * cus * 24;
+    if (full && (N == 3 || !critic) && (!runs || (critic ? A.E % 256 == 0 : !BF && A.E % 64 == 0))) return hipSuccess;
+  }
+  return launch_waves_spread_slots(N, BF, B, pb.packed, critic, s, taken);
+}
+
 // Envs per block.  64 (N wavefronts, one block barrier per step) is the general shape: three
 // blocks are resident per CU, and with several runs every block must lie inside one run.  When
 // one run has at least one 256-env block per CU, blocks of 256 envs = four independent 64-env
@@ -702,9 +730,12 @@ hipError_t launch_n(const RolloutArgs& A, const PolicyBuffers& pb, hipStream_t s
       return hipSuccess;
     }
     bool taken = false;
+    if (const hipError_t e = launch_slots<N, BF>(A, pb, nullptr, s, &taken); taken || e != hipSuccess) return e;
     const hipError_t e = launch_small_spread(N, BF, small_args(A), half_empty_waves(A, N), pb.packed, s, &taken);
     return taken || e != hipSuccess ? e : launch_waves_spread(N, BF, small_args(A), pb.packed, nullptr, s);
   } else {
+  bool slots = false;
+  if (const hipError_t e = launch_slots<N, BF>(A, pb, nullptr, s, &slots); slots || e != hipSuccess) return e;
   const uint32_t cus = compute_units();
   // Runs that are a multiple of 16 envs but not of 32 suit the small-batch kernel only, but for bf16 weights and 2 agents
   // beyond 6 blocks of 16 envs per CU: such blocks here (2,048 / 4,096 runs x 16 envs x 64 steps 207 / 441 us against 306 / 527).
@@ -771,9 +802,12 @@ hipError_t launch_ac_n(const RolloutArgs& A, const PolicyBuffers& pb, const Poli
       return hipSuccess;
     }
     bool taken = false;
+    if (const hipError_t e = launch_slots<N, BF>(A, pb, critic.packed, s, &taken); taken || e != hipSuccess) return e;
     const hipError_t e = launch_small_spread_ac(N, BF, small_args(A), half_empty_waves(A, N), pb.packed, critic.packed, s, &taken);
     return taken || e != hipSuccess ? e : launch_waves_spread(N, BF, small_args(A), pb.packed, critic.packed, s);
   } else {
+  bool slots = false;
+  if (const hipError_t e = launch_slots<N, BF>(A, pb, critic.packed, s, &slots); slots || e != hipSuccess) return e;
   // Runs that are no multiple of 64 envs suit the small-batch kernel only, but for bf16 weights and runs of a multiple of
   // 32: blocks of 32 envs here with 2 agents between 5 and 8 16-env blocks per CU (24,576 envs 703 against 743 us; 65,536
   // envs 1,830 against 1,770) and with 3 agents between 6 and 8, one full round of them, and beyond 12 (24,576 envs 984

@@ -57,6 +57,12 @@ __device__ __forceinline__ bool take_slot(const RolloutArgs& A, const Piece& p, 
   }
 }
 
+// Blocks that have lanes of several slots: an XCD has every eighth piece of four neighbouring ones.
+__device__ __forceinline__ uint32_t spread_group() {
+  const uint32_t at = blockIdx.x >> 3;
+  return (at >> 2) * 32u + (blockIdx.x & 7u) * 4u + (at & 3u);
+}
+
 // ep: the env's episode counter; alike: whether it is that of every env that shares the slot (else slot 0 runs all steps)
 __device__ __forceinline__ TimeSlot time_slot(const RolloutArgs& A, int k, int32_t ep, int32_t max_ep, bool alike) {
   if (!alike || ep < 0) return {0, k == 0 ? A.T : 0, 0, 0};
@@ -97,6 +103,7 @@ constexpr int32_t kSlotSteps = 16;
 inline void choose_slots(RolloutArgs& A, int32_t max_ep, uint32_t want) {
   A.slots = 1;
   if (!A.st.tickets || want < 2 || max_ep > A.T / 2) return;
+  if (uint64_t(A.TE) * uint64_t(A.T) > (1u << 30)) return;   // envs of all slots are counted in 32 bits
   for (int64_t span = int64_t((kSlotSteps + max_ep - 1) / max_ep) * max_ep; 2 * span <= A.T; span += max_ep) {
     if (A.T / span > int64_t(want)) continue;
     A.slots = int32_t(A.T / span);
@@ -105,6 +112,7 @@ inline void choose_slots(RolloutArgs& A, int32_t max_ep, uint32_t want) {
   }
 }
 
+inline dim3 spread_grid(uint32_t blocks) { return dim3((blocks + 31) / 32 * 32); }   // see spread_group
 // Blocks of a launch of several slots.
 inline dim3 slots_grid(const RolloutArgs& A, uint32_t groups) { return dim3((groups * uint32_t(A.slots) + 7) / 8 * 8); }
 

@@ -21,6 +21,7 @@
 
 #include "mpe_mlp64.h"
 #include "mpe_scenario.h"
+#include "mpe_slots.h"
 
 namespace mpe {
 
@@ -227,14 +228,14 @@ struct SmallSmem {
 };
 
 // MINW: wavefronts per SIMD the register budget is set for.
-template <typename Scn, int EB, bool AC, bool BF, bool REGW, int MINW>
+template <typename Scn, int EB, bool AC, bool BF, bool REGW, int MINW, typename Piece>
 __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MINW) void rollout_small_kernel(
-    TagArgs TA, const uint8_t* __restrict__ packed, const uint8_t* __restrict__ packed_critic, int per_run_weights, GridPiece piece) {
+    TagArgs TA, const uint8_t* __restrict__ packed, const uint8_t* __restrict__ packed_critic, int per_run_weights, Piece piece) {
   using M = SmallSmem<Scn, EB, AC, BF, REGW>;
   using P = typename M::P;
   using S = typename Scn::Net;
   using TS = typename Scn::Shape;                      // predator-prey only
-  constexpr bool kTag = Scn::kTag;
+  constexpr bool kTag = Scn::kTag, SLOTS = kSlots<Piece>;
   constexpr int N = Scn::N, L = Scn::L, D = Scn::D, B = M::B, TILES = M::TILES, KS1 = S::kSlices1;
   constexpr int G = kTag ? TS::G : 1, NA = kTag ? TS::A : 0;
   const RolloutArgs& A = TA.r;
@@ -250,12 +251,15 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   const size_t TE = A.TE;
-  const uint32_t grp = xcd_group(piece);
-  if (grp >= piece.end) return;                           // whole block, before any barrier
+  int k_slot;
+  uint32_t grp;
+  if (!take_slot(A, piece, k_slot, grp)) return;                           // whole block, before any barrier
   const size_t g0 = size_t(grp) * EB;
   const int nvalid = TE - g0 < size_t(EB) ? int(TE - g0) : EB;
   const size_t run_off = per_run_weights ? size_t(uint32_t(g0) / A.E) * P::RUN_BYTES : 0;
   const int32_t max_ep = kTag ? tg.max_ep : A.ph.max_ep;
+  const TimeSlot slot = group_slot<SLOTS>(A, k_slot, max_ep, g0, nvalid, lane);
+  const bool head = k_slot == 0;                       // the slot that reads and writes the envs' state
 
   // ---- biases (and, unless the operands stay in registers, the staged weights)
   {
@@ -296,7 +300,25 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
     for (int k = 0; k < L + 1; ++k) lx[k] = ly[k] = 0.0f;
 #pragma unroll
     for (int k = 0; k < G; ++k) gvx[k] = gvy[k] = 0.0f;
-    if (valid) {
+    // a new episode's positions, drawn by the service wavefronts
+    auto take_fresh = [&](int parity) {
+      const float2* f = fresh + (size_t(parity) * EB + el) * M::ENT;
+#pragma unroll
+      for (int a = 0; a < N; ++a) {
+        qx[a] = f[a].x;
+        qy[a] = f[a].y;
+        if (a == i) { px = qx[a]; py = qy[a]; }
+      }
+#pragma unroll
+      for (int k = 0; k < L; ++k) {
+        lx[k] = f[N + k].x;
+        ly[k] = f[N + k].y;
+      }
+    };
+    if (!head) {
+      __syncthreads();
+      take_fresh(1);
+    } else if (valid) {
 #pragma unroll
       for (int a = 0; a < N; ++a) {
         qx[a] = A.st.pos_a[(0 * N + a) * TE + g];
@@ -354,8 +376,9 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
       }
     };
     next_obs(0);
+    if (SLOTS) counter_read(ep);
     __syncthreads();   // first observations and the noise of step 0
-    for (int t = 0; t < A.T; ++t) {
+    for (int t = 0; t < slot.len; ++t) {
       const int par = t & 1;
       float nz[kNumActions], z[kNumActions];
 #pragma unroll
@@ -393,19 +416,8 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
           }
         }
       }
-      if (done) {   // the new episode's positions were drawn by the service wavefronts
-        const float2* f = fresh + (size_t(par) * EB + el) * M::ENT;
-#pragma unroll
-        for (int a = 0; a < N; ++a) {
-          qx[a] = f[a].x;
-          qy[a] = f[a].y;
-          if (a == i) { px = qx[a]; py = qy[a]; }
-        }
-#pragma unroll
-        for (int k = 0; k < L; ++k) {
-          lx[k] = f[N + k].x;
-          ly[k] = f[N + k].y;
-        }
+      if (done) {
+        take_fresh(par);
         if constexpr (kTag) {
 #pragma unroll
           for (int k = 0; k < G; ++k) gvx[k] = gvy[k] = 0.0f;
@@ -416,7 +428,7 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
       next_obs(par ^ 1);
     }
     __syncthreads();   // last observations
-    if (valid && gq == 0) {
+    if (valid && gq == 0 && head) {
       A.st.pos_a[(0 * N + i) * TE + g] = px;
       A.st.pos_a[(1 * N + i) * TE + g] = py;
       A.st.vel_a[(0 * N + i) * TE + g] = vx;
@@ -428,7 +440,7 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
           A.st.pos_l[(1 * L + l) * TE + g] = ly[l];
         }
       }
-      if (i == 0) A.st.ep_step[g] = ep;
+      if (i == 0 && !SLOTS) A.st.ep_step[g] = ep;
     }
   } else if (AC && wave < TILES + M::CRITICS) {
     // ================================================================ critic wavefront: tiles wave - TILES, + CRITICS, ...
@@ -446,17 +458,19 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
           if (gq == 0 && c0 + j < nvalid * N) dst[g0 * N + c0 + j] = (!BF && S::kRowTerms) ? (z[0] + z[1]) + z[2] : z[0];
         }
       };
+      if (!head) __syncthreads();
       __syncthreads();
-      float* value_p = A.value_traj;
-      for (int t = 0; t < A.T; ++t) {
+      float* value_p = A.value_traj ? A.value_traj + size_t(slot.t0) * TE * N : nullptr;
+      for (int t = 0; t < slot.len; ++t) {
         __syncthreads();
         if (value_p) {   // of the observation that step t acted on
           values(t & 1, value_p);
           value_p += TE * N;
+          if (t + 1 == slot.turn) value_p += size_t(slot.jump) * TE * N;
         }
       }
       __syncthreads();
-      if (A.last_value) values(A.T & 1, A.last_value);
+      if (A.last_value && head) values(slot.len & 1, A.last_value);
     }
   } else {
     // ================================================================ service wavefront: rows 64 w .. of the block
@@ -478,17 +492,21 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
     int32_t ep = 0;
     if (g < TE) {
       if constexpr (!kTag) {
+        if (head) {
 #pragma unroll
-        for (int k = 0; k < L; ++k) {
-          lx[k] = A.st.pos_l[(0 * L + k) * TE + g];
-          ly[k] = A.st.pos_l[(1 * L + k) * TE + g];
+          for (int k = 0; k < L; ++k) {
+            lx[k] = A.st.pos_l[(0 * L + k) * TE + g];
+            ly[k] = A.st.pos_l[(1 * L + k) * TE + g];
+          }
         }
       }
       ep = A.st.ep_step[g];
     }
+    if (SLOTS) counter_read(ep);
+    [[maybe_unused]] const int32_t ep0 = ep;
     [[maybe_unused]] TagRole me{};
     if constexpr (kTag) me = tag_role<TS>(i, tg);
-    uint32_t step = A.abs_step;
+    uint32_t step = A.abs_step + uint32_t(slot.t0);
 
     // sampling noise of step `step` into the buffer of its parity
     auto draw_noise = [&](int parity, uint32_t at) {
@@ -507,36 +525,65 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
       else if (vec4 && my_rows == kLastRows) stream_out_full<kLastRows * D / 4>(src, dst, lane);
       else stream_out(src, dst, my_rows * D, vec4, lane);
     };
+    // the positions of an episode that starts at step `at` into the buffer of a parity
+    auto draw_fresh = [&](int parity, uint32_t at) {
+      uint32_t env_r = env;
+      asm volatile("" : "+v"(env_r));
+      float2* f = fresh + (size_t(parity) * EB + el) * M::ENT;
+      // entities i, i + N, ... of the env (agents first, then landmarks)
+#pragma unroll
+      for (int e = 0; e < (M::ENT + N - 1) / N; ++e) {
+        const int ent = i + e * N;
+        if (ent < M::ENT) {
+          const uint4 d = philox4x32_10(env_r, at, uint32_t(ent), kTagResetPos, A.seed, run);
+          float2 p = make_float2(word_to_position(d.x), word_to_position(d.y));
+          if (kTag && e > 0) { p.x *= 0.9f; p.y *= 0.9f; }   // obstacles start inside [-0.9, 0.9)
+          if (has_row) f[ent] = p;
+        }
+      }
+    };
+    auto take_landmarks = [&](int parity) {
+      const float2* f = fresh + (size_t(parity) * EB + el) * M::ENT;
+#pragma unroll
+      for (int k = 0; k < L; ++k) {
+        lx[k] = f[N + k].x;
+        ly[k] = f[N + k].y;
+      }
+    };
+    const bool per_agent = kTag || A.ph.reward_mode == 1;
     float* obs_p = A.obs_traj;
     uint8_t* act_p = A.act_traj;
     float* rew_p = A.rew_traj;
     uint8_t* done_p = A.done_traj;
     [[maybe_unused]] float* logp_p = A.logp_traj;
-    const bool per_agent = kTag || A.ph.reward_mode == 1;
+    auto advance = [&](int steps) {
+      const size_t envs = size_t(steps) * TE;
+      if (obs_p) obs_p += envs * (N * D);
+      if (act_p) act_p += envs * N;
+      if (rew_p) rew_p += per_agent ? envs * N : envs;
+      if (done_p) done_p += envs;
+      if (AC && logp_p) logp_p += envs * N;
+    };
 
     draw_noise(0, step);
+    if (!head) {
+      advance(slot.t0);
+      draw_fresh(1, step);
+      ep = 0;
+      __syncthreads();
+      if constexpr (!kTag) take_landmarks(1);
+    }
     __syncthreads();
-    for (int t = 0; t < A.T; ++t, ++step) {
+    [[maybe_unused]] uint32_t ticket = 0;
+    if (SLOTS && env_writer) ticket = take_ticket(A, g);
+    for (int t = 0; t < slot.len; ++t) {
       const int par = t & 1;
+      const bool turn = t + 1 == slot.turn;
+      const uint32_t next = step + 1u + (turn ? uint32_t(slot.jump) : 0u);
       // ---- ahead: noise of step t + 1, and the new episode's draw if this env's ends with step t
-      draw_noise(par ^ 1, step + 1u);
+      draw_noise(par ^ 1, next);
       const bool done = ep + 1 >= max_ep;
-      if (done) {
-        uint32_t env_r = env;
-        asm volatile("" : "+v"(env_r));
-        float2* f = fresh + (size_t(par) * EB + el) * M::ENT;
-        // entities i, i + N, ... of the env (agents first, then landmarks)
-#pragma unroll
-        for (int e = 0; e < (M::ENT + N - 1) / N; ++e) {
-          const int ent = i + e * N;
-          if (ent < M::ENT) {
-            const uint4 d = philox4x32_10(env_r, step + 1u, uint32_t(ent), kTagResetPos, A.seed, run);
-            float2 p = make_float2(word_to_position(d.x), word_to_position(d.y));
-            if (kTag && e > 0) { p.x *= 0.9f; p.y *= 0.9f; }   // obstacles start inside [-0.9, 0.9)
-            if (has_row) f[ent] = p;
-          }
-        }
-      }
+      if (done) draw_fresh(par, next);
       __syncthreads();
       // ---- behind: everything that leaves the chip for step t
       if (obs_p) {
@@ -600,31 +647,35 @@ __global__ __launch_bounds__((SmallSmem<Scn, EB, AC, BF, REGW>::WAVES * 64), MIN
       }
       ep = done ? 0 : ep + 1;
       if constexpr (!kTag) {
-        if (done) {
-          const float2* f = fresh + (size_t(par) * EB + el) * M::ENT;
-#pragma unroll
-          for (int k = 0; k < L; ++k) {
-            lx[k] = f[N + k].x;
-            ly[k] = f[N + k].y;
-          }
-        }
+        if (done) take_landmarks(par);
       }
+      step = next;
+      if (turn) advance(slot.jump);
     }
     __syncthreads();
-    if (A.last_obs) flush(A.T & 1, A.last_obs);
+    if (A.last_obs && head) flush(slot.len & 1, A.last_obs);
+    if (SLOTS && env_writer) settle_ticket(A, max_ep, g, ticket, ep0);
   }
 }
 
 template <typename Scn, int EB, bool AC, bool BF, bool REGW, int MINW>
 hipError_t launch_small_impl(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
   using M = SmallSmem<Scn, EB, AC, BF, REGW>;
-  auto kern = rollout_small_kernel<Scn, EB, AC, BF, REGW, MINW>;
-  static std::atomic<uint64_t> lds_allowed{0};
-  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed); e != hipSuccess) return e;
-  return launch_groups<M::WAVES * 64>((A.r.TE + EB - 1) / EB, [&](dim3 grid, const GridPiece& p) {
+  static std::atomic<uint64_t> lds_allowed[2];
+  const uint32_t groups = (A.r.TE + EB - 1) / EB;
+  auto launch = [&](auto kern, dim3 grid, auto piece) {
     hipLaunchKernelGGL(kern, grid, dim3(M::WAVES * 64), M::TOTAL, s, A, static_cast<const uint8_t*>(packed),
-                       static_cast<const uint8_t*>(critic), int(A.r.TE != A.r.E), p);
-  });
+                       static_cast<const uint8_t*>(critic), int(A.r.TE != A.r.E), piece);
+  };
+  if (A.r.slots > 1) {
+    auto kern = rollout_small_kernel<Scn, EB, AC, BF, REGW, MINW, SlotGrid>;
+    if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[1]); e != hipSuccess) return e;
+    launch(kern, slots_grid(A.r, groups), SlotGrid{groups});
+    return hipGetLastError();
+  }
+  auto kern = rollout_small_kernel<Scn, EB, AC, BF, REGW, MINW, GridPiece>;
+  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[0]); e != hipSuccess) return e;
+  return launch_groups<M::WAVES * 64>(groups, [&](dim3 grid, const GridPiece& p) { launch(kern, grid, p); });
 }
 
 // Up to how many envs this kernel is the faster one for a batch of whole runs (or of runs whose size suits the kernels
@@ -663,13 +714,44 @@ constexpr SmallRange small_range() {
   }
 }
 
+// The same for a rollout in several slots of time (mpe_slots.h), whose envs are those of all slots; what it is measured
+// against are the independent wavefronts (mpe_waves.h), of which a block per CU takes the same time whatever it holds.  128
+// steps in five slots, us, this kernel against them, at 5 x {1,000, 2,048, 4,096, 8,192} envs (fp32 unless stated):
+//   1 agent          43/133 44/133 63/135 133/136            critic 58/231 64/230 128/231 219/236     (bf16 31/92 31/93 44/93 83/94)
+//   2 agents         60/129 63/128 91/129 186/188            critic 69/231 102/235 172/234 361/344    (bf16 45/93 48/94 72/94 151/132)
+//   3 agents         65/137 88/138 135/143 239/222           critic 97/259 143/260 228/274 492/405    (bf16 51/96 68/96 100/98 193/142)
+//   4 agents         75/151 114/152 189/215 400/323          critic 128/275 190/276 323/406 641/579
+//   6 agents         134/160 188/178 314/257 607/515         critic 202/286 307/314 523/461 1044/883
+//   10 agents        307/238 452/315 773/631                 critic 366/365 631/533 1253/1025
+//   tag (4,2,1)      75/135 -/- 188/209 402/302              critic 124/247 -/- 322/376 639/542       (bf16 64/100 116/101 175/148 342/211)
+//   tag (8,2,2)      180/164 270/229 458/340                 critic 282/288 423/407 719/619           (bf16 146/111 217/164 368/239)
+template <typename Scn, bool AC, bool BF>
+constexpr SmallRange small_range_slots() {
+  constexpr int N = Scn::N;
+  if constexpr (!Scn::kTag) {
+    constexpr SmallRange plain[10] = {{105, 0}, {100, 0}, {85, 0}, {32, 52}, {22, 0}, {22, 30}, {15, 0}, {10, 0}, {10, 0}, {10, 0}};
+    constexpr SmallRange critic[10] = {{110, 0}, {66, 0}, {75, 0}, {37, 52}, {26, 40}, {26, 38}, {20, 32}, {18, 27}, {11, 0}, {12, 0}};
+    constexpr SmallRange plain_bf[3] = {{115, 0}, {63, 0}, {49, 0}}, critic_bf[3] = {{115, 0}, {61, 0}, {60, 0}};
+    if constexpr (BF) return AC ? critic_bf[N - 1] : plain_bf[N - 1];
+    else return AC ? critic[N - 1] : plain[N - 1];
+  } else {
+    // 2, 3, 4, 5, 6, 8, 10 agents
+    constexpr SmallRange plain[7] = {{85, 0}, {72, 0}, {32, 52}, {22, 0}, {18, 0}, {10, 0}, {10, 0}};
+    constexpr SmallRange critic[7] = {{61, 0}, {66, 0}, {37, 52}, {26, 0}, {24, 0}, {13, 0}, {10, 0}};
+    constexpr SmallRange plain_bf[7] = {{62, 0}, {60, 0}, {21, 0}, {14, 0}, {11, 0}, {9, 0}, {10, 0}};
+    constexpr SmallRange critic_bf[7] = {{58, 0}, {49, 0}, {27, 0}, {23, 0}, {16, 0}, {11, 0}, {10, 0}};
+    constexpr int k = N <= 6 ? N - 2 : (N == 8 ? 5 : 6);
+    return BF ? (AC ? critic_bf[k] : plain_bf[k]) : (AC ? critic[k] : plain[k]);
+  }
+}
+
 template <typename Scn, int EB, bool AC, bool BF>
 hipError_t launch_small_eb(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
   // Stationary operands while a block has a CU to itself (6-10 % faster there); they take 100 to 170 registers per
   // wavefront, so beyond that, and with more than 8 wavefronts per block, the operands are read from LDS.
   constexpr int W = SmallSmem<Scn, EB, AC, BF, true>::WAVES, kMin = (W + 3) / 4;
   if constexpr (kMin <= 2) {
-    if ((A.r.TE + EB - 1) / EB <= compute_units()) return launch_small_impl<Scn, EB, AC, BF, true, 2>(A, packed, critic, s);
+    if ((A.r.TE + EB - 1) / EB * uint32_t(A.r.slots) <= compute_units()) return launch_small_impl<Scn, EB, AC, BF, true, 2>(A, packed, critic, s);
   }
   return launch_small_impl<Scn, EB, AC, BF, false, (kMin < 4 ? 4 : kMin)>(A, packed, critic, s);
 }
@@ -687,10 +769,11 @@ hipError_t launch_small(const TagArgs& A, bool unfit, const void* packed, const 
   constexpr bool kEight = N == 6 || N == 8 || N == 10, kOnlyEight = AC && N == 10 && Scn::D > 32;
   const bool runs = A.r.TE != A.r.E;
   if (runs && A.r.E % 16 != 0) return hipSuccess;
-  const uint32_t cus = compute_units(), blocks16 = (A.r.TE + 15) / 16;
+  const uint32_t cus = compute_units(), blocks16 = (A.r.TE + 15) / 16 * uint32_t(A.r.slots);
   if (!(runs && unfit)) {
-    constexpr SmallRange range = small_range<Scn, AC, BF>();
-    const bool first_round_full = A.r.TE > kWavesBlock * cus;
+    constexpr SmallRange one = small_range<Scn, AC, BF>(), several = small_range_slots<Scn, AC, BF>();
+    const SmallRange range = A.r.slots > 1 ? several : one;
+    const bool first_round_full = A.r.work() > kWavesBlock * cus;
     // One agent's blocks are two or three wavefronts around 33 KB of weights per network: in a rollout of one step the
     // staging of a full range of them is what counts (32,768 envs 11.4 us, 64-env blocks 8.3; actor-critic 22.1 against 17.3).
     const uint32_t upto = N == 1 && A.r.T == 1 ? 70 : range.upto;
@@ -698,7 +781,7 @@ hipError_t launch_small(const TagArgs& A, bool unfit, const void* packed, const 
   }
   *taken = true;
   if constexpr (kEight) {
-    if (kOnlyEight || (A.r.TE + 7) / 8 <= cus) return launch_small_eb<Scn, 8, AC, BF>(A, packed, critic, s);
+    if (kOnlyEight || (A.r.TE + 7) / 8 * uint32_t(A.r.slots) <= cus) return launch_small_eb<Scn, 8, AC, BF>(A, packed, critic, s);
   }
   if constexpr (!kOnlyEight) return launch_small_eb<Scn, 16, AC, BF>(A, packed, critic, s);
 }

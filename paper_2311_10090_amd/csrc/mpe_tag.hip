@@ -501,6 +501,25 @@ hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void
   const uint32_t cus = compute_units();
   const bool runs = A.r.TE != A.r.E;
   const bool rows = ac ? kRowsAc : kRows && (S::N != 4 || A.r.TE > 128 * cus);
+  // Slots of time, where the rollout is long enough (see launch_slots in mpe_policy_f32.hip).  In one slot stay, with fp32
+  // weights and a critic, the batches of 8 agents whose 8-env blocks are about one per CU (2,048 envs 393 us, 407 in slots), and
+  // with bf16 ones, plain, 8 agents in (nearly) whole rounds of 64-env blocks (16,384 envs 776 us, 813 in slots).  128 steps,
+  // us, one slot / several: 2 agents, critic, 32,768 envs 1,002 / 885; 3 agents, critic, 65,536 3,332 / 2,737; 4 agents 16,384 626 /
+  // 547; 5 agents bf16, critic, 8,192 672 / 513; 6 agents, critic, 32,768 4,104 / 3,328; 10 agents 1,000 445 / 176.
+  const uint32_t blocks64 = (A.r.TE + 63) / 64;
+  const bool full64 = blocks64 <= cus ? blocks64 * 10 >= cus * 9 : (blocks64 - 1) % cus * 10 >= cus * 9;
+  if (!(S::N == 8 && (ac ? !bf && A.r.TE * 10 > 64 * cus && A.r.TE <= 8 * cus : bf && full64 && (!runs || A.r.E % 64 == 0)))) {
+    TagArgs B = A;
+    choose_slots(B.r, A.tg.max_ep, ~0u);
+    if (B.r.slots > 1) {
+      bool taken = false;
+      hipError_t e = ac ? launch_small_tag_ac(S::N, S::L, S::G, bf, B, false, packed, packed_critic, s, &taken)
+                        : launch_small_tag(S::N, S::L, S::G, bf, B, false, packed, s, &taken);
+      if (!taken && e == hipSuccess)
+        e = launch_waves_tag_slots(S::N, S::L, S::G, bf, B, !rows && !(S::N == 4 && ac && bf), packed, ac ? packed_critic : nullptr, s, &taken);
+      if (taken || e != hipSuccess) return e;
+    }
+  }
   const bool unfit = runs && unfit_runs<S>(ac, rows, rows ? (ac ? uint32_t(kAcEnvs) : 64u) : 0u, A.r);
   if (unfit && A.r.TE <= kWholeLaunchEnvs) {
     const uint32_t blocks = A.r.TE / 16, line = blocks > 4 * cus ? run_blocks16<S>(mode).past : run_blocks16<S>(mode).from;

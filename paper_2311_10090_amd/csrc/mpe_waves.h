@@ -20,6 +20,7 @@
 
 #include "mpe_mlp64.h"
 #include "mpe_scenario.h"
+#include "mpe_slots.h"
 
 namespace mpe {
 
@@ -56,14 +57,17 @@ struct WavesSmem {
   static_assert(IMAGE % 16 == 0 && TOTAL <= 160 * 1024, "LDS");
 };
 
-template <typename Scn, int W, bool AC, bool BF, int MINW>
+// Piece: SlotGrid for a launch of several slots of time (mpe_slots.h).  A run's envs are then E * slots, one slot's after the
+// other's, and a lane has a slot of its own: wavefronts are full whatever the run size (runs of 16 envs x 3 agents in five
+// slots take four wavefronts of 21 envs), and no two envs of a wavefront need their episodes end together.
+template <typename Scn, int W, bool AC, bool BF, int MINW, typename Piece>
 __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA, const uint8_t* __restrict__ packed,
-                                                                     const uint8_t* __restrict__ packed_critic, GridPiece piece) {
+                                                                     const uint8_t* __restrict__ packed_critic, Piece piece) {
   using M = WavesSmem<Scn, W, AC, BF>;
   using P = typename M::P;
   using Net = typename Scn::Net;
   using TS = typename Scn::Shape;
-  constexpr bool kTag = Scn::kTag;
+  constexpr bool kTag = Scn::kTag, SLOTS = kSlots<Piece>;
   constexpr int N = Scn::N, L = Scn::L, D = Scn::D, KIN = Net::KIN, KS1 = Net::kSlices1;
   constexpr int EW = 64 / N, EB = W * EW, ROWS = EW * N;
   constexpr int G = kTag ? TS::G : 1, NA = kTag ? TS::A : 0;
@@ -75,16 +79,29 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
   const int wave = __builtin_amdgcn_readfirstlane(int(threadIdx.x) >> 6);
   WaveLds<Scn>& sm = *reinterpret_cast<WaveLds<Scn>*>(smem + M::OFF_WAVE + size_t(wave) * M::WAVE);
   const size_t TE = A.TE;
-  const uint32_t blk = xcd_group(piece);
-  if (blk >= piece.end) return;                          // whole block, before any barrier
+  uint32_t blk;
+  if constexpr (SLOTS) {
+    blk = spread_group();
+    if (blk >= piece.groups) return;
+  } else {
+    blk = xcd_group(piece);
+    if (blk >= piece.end) return;                        // whole block, before any barrier
+  }
   // the blocks of a run are its own; its last one may be partly filled
-  const uint32_t per_run = (A.E + EB - 1) / EB, run = blk / per_run;
+  const uint32_t run_envs = SLOTS ? A.E * uint32_t(A.slots) : A.E;
+  const uint32_t per_run = (run_envs + EB - 1) / EB, run = blk / per_run;
   const uint32_t env0 = (blk - run * per_run) * EB + wave * EW;        // first env of this wavefront inside its run
-  const int nvalid = env0 < A.E ? min(int(A.E - env0), EW) : 0;
+  const int nvalid = env0 < run_envs ? min(int(run_envs - env0), EW) : 0;
   const bool active = !kSpare || lane < ROWS;         // spare lanes shadow the wavefront's first row and store nothing
   const int row = active ? lane : 0, el = row / N, i = row - el * N;
   const bool in_range = el < nvalid, valid = active && in_range;
-  const uint32_t env = env0 + (in_range ? el : 0);
+  uint32_t env = env0 + (in_range ? el : 0);
+  uint32_t k_slot = 0;
+  if constexpr (SLOTS) {
+    k_slot = env / A.E;
+    env -= k_slot * A.E;
+  }
+  const bool head = k_slot == 0;                      // the slot that reads and writes its env's state
   const size_t g = size_t(run) * A.E + (nvalid ? env : 0u);
   const int32_t max_ep = kTag ? tg.max_ep : A.ph.max_ep;
 
@@ -106,12 +123,46 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
   // ---- this lane's agent; everything about the others is read from LDS where it is needed
   float px = 0.0f, py = 0.0f, vx = 0.0f, vy = 0.0f;
   int32_t ep = 0;
+  uint32_t step = A.abs_step;
+  // a new episode, keyed by the step that it starts at: every lane draws its own agent and landmarks i, i + N, ... of its env
+  auto new_episode = [&](uint32_t start) {
+    uint32_t env_r = env;
+    asm volatile("" : "+v"(env_r));
+    const uint4 d = philox4x32_10(env_r, start, uint32_t(i), kTagResetPos, A.seed, run);
+    px = word_to_position(d.x);
+    py = word_to_position(d.y);
+    vx = vy = 0.0f;
+    ep = 0;
+#pragma unroll
+    for (int k = 0; k < (L + N - 1) / N; ++k) {
+      const int l = i + k * N;
+      if (l < L) {
+        const uint4 w = philox4x32_10(env_r, start, uint32_t(N + l), kTagResetPos, A.seed, run);
+        float2 p = make_float2(word_to_position(w.x), word_to_position(w.y));
+        if (kTag) { p.x *= 0.9f; p.y *= 0.9f; }        // obstacles start inside [-0.9, 0.9)
+        if (active) sm.lm[el * (L + 1) + l] = p;
+      }
+    }
+  };
   if (in_range) {
     px = A.st.pos_a[(0 * N + i) * TE + g];
     py = A.st.pos_a[(1 * N + i) * TE + g];
     vx = A.st.vel_a[(0 * N + i) * TE + g];
     vy = A.st.vel_a[(1 * N + i) * TE + g];
     ep = A.st.ep_step[g];
+  }
+  [[maybe_unused]] int32_t ep0 = ep;
+  [[maybe_unused]] TimeSlot slot = {0, A.T, 0, 0};
+  int len = A.T;                                      // of the wavefront
+  if constexpr (SLOTS) {
+    counter_read(ep0);
+    slot = time_slot(A, int(k_slot), ep0, max_ep, true);
+    if (!in_range) slot.len = 0;
+    step += uint32_t(slot.t0);
+    len = slot.len;
+#pragma unroll
+    for (int o = 32; o; o >>= 1) len = max(len, __shfl_xor(len, o));
+    len = __builtin_amdgcn_readfirstlane(len);
   }
 #pragma unroll
   for (int k = 0; k < (L + N - 1) / N; ++k) {         // landmarks i, i + N, ...
@@ -134,6 +185,7 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
       return reinterpret_cast<const float2*>(sm.xch[parity])[el * N + a];
     }
   };
+  if (!head) new_episode(step);
   put(1);
   __syncthreads();   // weights staged; the only block-wide barrier
   // A wavefront past its run's last env ends here.  In this form, and not as a return, the rest of the kernel compiles as it
@@ -171,8 +223,8 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
     }
     agent_obs<Scn>(o, i, px, py, vx, vy, qx, qy, lx, ly, gvx, gvy);
   };
-  auto store_row = [&](const float (&o)[KIN], float* dst) {
-    if (!valid) return;
+  auto store_row = [&](const float (&o)[KIN], float* dst, bool stores) {
+    if (!stores) return;
     constexpr int CW = D % 4 == 0 ? 4 : 2;            // rows start on 16 bytes, or on 8
     typedef float vC __attribute__((ext_vector_type(CW)));
 #pragma unroll
@@ -281,26 +333,63 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
   uint8_t* done_p = A.done_traj;
   [[maybe_unused]] float* logp_p = A.logp_traj;
   [[maybe_unused]] float* value_p = A.value_traj;
-  const size_t row_off = g * N + i;
-  const bool env_writer = valid && i == 0;
+  // this lane's row and env in the time slices at the bases above, which go on a slice a step: in several slots with the
+  // steps that it is ahead of the launch's first
+  size_t row_off = g * N + i, env_off = g;
   const bool per_agent = kTag || A.ph.reward_mode == 1;
-  uint32_t step = A.abs_step;
+  [[maybe_unused]] uint32_t ticket = 0;
+  auto ahead = [&](int32_t steps) {
+    row_off += size_t(steps) * TE * N;
+    env_off += size_t(steps) * TE;
+  };
+  if constexpr (SLOTS) {
+    ahead(slot.t0);
+    if (valid && i == 0) ticket = take_ticket(A, g);
+  }
   float o[KIN];
 #pragma unroll
   for (int c = 0; c < KIN; ++c) o[c] = 0.0f;
   wave_sync();
   build(o, 1);
-  for (int t = 0; t < A.T; ++t, ++step) {
+  // state and last observation of the lanes that have run all their steps
+  auto finish = [&]() {
+    if (A.last_obs) store_row(o, A.last_obs + (g * N + i) * D, valid);
+    if (valid) {
+      A.st.pos_a[(0 * N + i) * TE + g] = px;
+      A.st.pos_a[(1 * N + i) * TE + g] = py;
+      A.st.vel_a[(0 * N + i) * TE + g] = vx;
+      A.st.vel_a[(1 * N + i) * TE + g] = vy;
+#pragma unroll
+      for (int k = 0; k < (L + N - 1) / N; ++k) {
+        const int l = i + k * N;
+        if (l < L) {
+          const float2 p = sm.lm[el * (L + 1) + l];
+          A.st.pos_l[(0 * L + l) * TE + g] = p.x;
+          A.st.pos_l[(1 * L + l) * TE + g] = p.y;
+        }
+      }
+      if (i == 0 && !SLOTS) A.st.ep_step[g] = ep;
+    }
+  };
+  for (int t = 0; t < len; ++t) {
     const int par = t & 1;
+    const bool running = !SLOTS || t < slot.len, stores = valid && running, env_writer = stores && i == 0;
+    const bool ended = SLOTS && head && t == slot.len;       // before the wavefront's other lanes
+    if constexpr (SLOTS) {
+      if (ended) finish();
+    }
     if (obs_p) {
-      store_row(o, obs_p + row_off * D);
+      store_row(o, obs_p + row_off * D, stores);
       obs_p += TE * (N * D);
     }
     float z[kNumActions], value = 0.0f;
     forward(o, z, value, std::true_type{});
+    if constexpr (AC && SLOTS) {
+      if (ended && valid && A.last_value) A.last_value[g * N + i] = value;
+    }
     const uint32_t act = gumbel_argmax(z, A.seed, run, env, step, uint32_t(i));
     if (act_p) {
-      if (valid) act_p[row_off] = uint8_t(act);
+      if (stores) act_p[row_off] = uint8_t(act);
       act_p += TE * N;
     }
     if constexpr (AC) {
@@ -315,11 +404,11 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
 #pragma unroll
       for (int k = 0; k < kNumActions; ++k) sum += hw_exp2((z[k] - zmax) * kLog2e);
       if (logp_p) {
-        if (valid) logp_p[row_off] = (zact - zmax) - kLn2 * hw_log2(sum);
+        if (stores) logp_p[row_off] = (zact - zmax) - kLn2 * hw_log2(sum);
         logp_p += TE * N;
       }
       if (value_p) {
-        if (valid) value_p[row_off] = value;
+        if (stores) value_p[row_off] = value;
         value_p += TE * N;
       }
     }
@@ -356,7 +445,7 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
       }
       if constexpr (kTag) {
         const float r = tag_reward<TS>(i, me, tg, px, py, qx, qy);
-        if (valid) rew_p[row_off] = r;
+        if (stores) rew_p[row_off] = r;
       } else {
         // coverage: this lane finds the distance of landmark i to the nearest agent; summed in landmark order
         const float2 mine = sm.lm[el * (L + 1) + i];
@@ -373,9 +462,9 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
         for (int a = 0; a < N; ++a) r -= sm.dmin[el * N + a];
         if (per_agent) {
           const float m = mixed_reward(r, overlap_count<N>(i, px, py, qx, qy, A.ph), A.ph);
-          if (valid) rew_p[row_off] = m;
+          if (stores) rew_p[row_off] = m;
         } else if (env_writer) {
-          rew_p[g] = r;
+          rew_p[env_off] = r;
         }
       }
       rew_p += per_agent ? TE * N : TE;
@@ -383,57 +472,33 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
     ep += 1;
     const bool done = ep >= max_ep;
     if (done_p) {
-      if (env_writer) done_p[g] = done ? 1 : 0;
+      if (env_writer) done_p[env_off] = done ? 1 : 0;
       done_p += TE;
     }
-    if (done) {
-      // new episode keyed by step + 1: every lane draws its own agent and landmarks i, i + N, ... of its env
-      uint32_t env_r = env;
-      asm volatile("" : "+v"(env_r));
-      const uint4 d = philox4x32_10(env_r, step + 1u, uint32_t(i), kTagResetPos, A.seed, run);
-      px = word_to_position(d.x);
-      py = word_to_position(d.y);
-      vx = vy = 0.0f;
-      ep = 0;
-#pragma unroll
-      for (int k = 0; k < (L + N - 1) / N; ++k) {
-        const int l = i + k * N;
-        if (l < L) {
-          const uint4 w = philox4x32_10(env_r, step + 1u, uint32_t(N + l), kTagResetPos, A.seed, run);
-          float2 p = make_float2(word_to_position(w.x), word_to_position(w.y));
-          if (kTag) { p.x *= 0.9f; p.y *= 0.9f; }      // obstacles start inside [-0.9, 0.9)
-          if (active) sm.lm[el * (L + 1) + l] = p;
-        }
+    ++step;
+    if constexpr (SLOTS) {
+      if (t + 1 == slot.turn) {
+        step += uint32_t(slot.jump);
+        ahead(slot.jump);
       }
     }
+    if (done) new_episode(step);
     wave_sync();               // the positions before a reset have been read
     if (done) put(par);
     wave_sync();
     build(o, par);
   }
-  if (A.last_obs) store_row(o, A.last_obs + row_off * D);
+  if constexpr (SLOTS) {
+    if (valid && i == 0) settle_ticket(A, max_ep, g, ticket, ep0);
+  }
+  const bool ended = !SLOTS || (head && slot.len == len);
+  if (ended) finish();
   if constexpr (AC) {
     if (A.last_value) {        // value of the observation after the last step
       float z[kNumActions], value = 0.0f;
       forward(o, z, value, std::false_type{});
-      if (valid) A.last_value[row_off] = value;
+      if (valid && ended) A.last_value[g * N + i] = value;
     }
-  }
-  if (valid) {
-    A.st.pos_a[(0 * N + i) * TE + g] = px;
-    A.st.pos_a[(1 * N + i) * TE + g] = py;
-    A.st.vel_a[(0 * N + i) * TE + g] = vx;
-    A.st.vel_a[(1 * N + i) * TE + g] = vy;
-#pragma unroll
-    for (int k = 0; k < (L + N - 1) / N; ++k) {
-      const int l = i + k * N;
-      if (l < L) {
-        const float2 p = sm.lm[el * (L + 1) + l];
-        A.st.pos_l[(0 * L + l) * TE + g] = p.x;
-        A.st.pos_l[(1 * L + l) * TE + g] = p.y;
-      }
-    }
-    if (i == 0) A.st.ep_step[g] = ep;
   }
 }
 
@@ -444,43 +509,89 @@ struct WavesBlocks {
   static constexpr size_t LDS = WavesSmem<Scn, W, AC, BF>::TOTAL;
   static constexpr int kResident = W != 4 || 2 * LDS > 160 * 1024 ? 1 : (3 * LDS > 160 * 1024 ? 2 : 3);
   static constexpr int kMinWaves = W * kResident > 8 ? 3 : 2;      // per SIMD, for the register budget
-  static uint32_t count(const RolloutArgs& A) { return A.TE / A.E * ((A.E + EB - 1) / EB); }
+  static uint32_t count(const RolloutArgs& A) { return A.TE / A.E * ((A.E * uint32_t(A.slots) + EB - 1) / EB); }
 };
 
 template <typename Scn, int W, bool AC, bool BF>
 hipError_t launch_waves_impl(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
   using B = WavesBlocks<Scn, W, AC, BF>;
-  auto kern = rollout_waves_kernel<Scn, W, AC, BF, B::kMinWaves>;
-  static std::atomic<uint64_t> lds_allowed{0};
-  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), B::LDS, lds_allowed); e != hipSuccess) return e;
-  return launch_groups<W * 64>(B::count(A.r), [&](dim3 grid, const GridPiece& p) {
-    hipLaunchKernelGGL(kern, grid, dim3(W * 64), B::LDS, s, A, static_cast<const uint8_t*>(packed),
-                       static_cast<const uint8_t*>(critic), p);
-  });
+  static std::atomic<uint64_t> lds_allowed[2];
+  const uint32_t blocks = B::count(A.r);
+  auto launch = [&](auto kern, dim3 grid, auto piece) {
+    hipLaunchKernelGGL(kern, grid, dim3(W * 64), B::LDS, s, A, static_cast<const uint8_t*>(packed), static_cast<const uint8_t*>(critic), piece);
+  };
+  if (A.r.slots > 1) {
+    auto kern = rollout_waves_kernel<Scn, W, AC, BF, B::kMinWaves, SlotGrid>;
+    if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), B::LDS, lds_allowed[1]); e != hipSuccess) return e;
+    launch(kern, spread_grid(blocks), SlotGrid{blocks});
+    return hipGetLastError();
+  }
+  auto kern = rollout_waves_kernel<Scn, W, AC, BF, B::kMinWaves, GridPiece>;
+  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), B::LDS, lds_allowed[0]); e != hipSuccess) return e;
+  return launch_groups<W * 64>(blocks, [&](dim3 grid, const GridPiece& p) { launch(kern, grid, p); });
 }
 
-// Estimated time of a batch in blocks of W wavefronts, in units of a CU's time with 12 resident wavefronts: full rounds
-// of resident blocks, then a last one with as many blocks per CU as are left.  4, 8 and 12 wavefronts per CU take 0.42,
-// 0.75 and 1 (measured with 6 agents, fp32, 128 steps: 661-698, 1,030-1,210 and 1,412-1,660 us).  Where blocks of 4 and of
-// 8 come out the same, 8 are faster by up to 14 % with fp32 weights: half the copies of them to stage, and no CU with one
-// block of 4 beside one with two (8,192 / 24,576 envs x 10 agents 1,374 / 3,426 us against 1,580 / 3,820); with bf16 ones, a
-// third of the bytes, 4 are (predator-prey, actor-critic, 12,288 envs x 6 agents 1,242 us against 1,280).
+// Estimated time of a batch in blocks of W wavefronts, in steps of a CU with 12 resident wavefronts: full rounds of resident
+// blocks, then a last one with as many blocks per CU as are left.  4, 8 and 12 wavefronts per CU take 0.42,
+// 0.75 and 1 (measured with 6 agents, fp32, 128 steps: 661-698, 1,030-1,210 and 1,412-1,660 us; 12 with a critic or of 8 and more agents,
+// with spilled registers, 4 to 9 % more).  A block takes its steps and about one and a half more to stage the weights; in
+// several slots slot 0, whose blocks come first, takes the longest.
 template <typename Scn, int W, bool AC, bool BF>
 float waves_cost(const RolloutArgs& A) {
   using B = WavesBlocks<Scn, W, AC, BF>;
+  constexpr float kTwelve = !Scn::kTag && Scn::N > 8 ? 1.09f : (AC ? 1.07f : (!Scn::kTag && Scn::N == 8 ? 1.04f : 1.0f));
   const uint32_t cus = compute_units(), blocks = B::count(A), round = cus * B::kResident, rest = blocks % round;
-  auto time_of = [](uint32_t waves) { return waves == 0 ? 0.0f : (waves <= 4 ? 0.42f : (waves <= 8 ? 0.75f : 1.0f)); };
-  return float(blocks / round) * time_of(W * B::kResident) + time_of(W * ((rest + cus - 1) / cus));
+  auto time_of = [](uint32_t waves) { return waves == 0 ? 0.0f : (waves <= 4 ? 0.42f : (waves <= 8 ? 0.75f : kTwelve)); };
+  const float mean = float(A.T) / float(A.slots) + 1.5f, tail = blocks >= round ? float(A.slots > 1 ? A.span : A.T) + 1.5f : float(A.T - (A.slots - 1) * A.span) + 1.5f;
+  return float(blocks / round) * time_of(W * B::kResident) * mean + time_of(W * ((rest + cus - 1) / cus)) * tail;
+}
+
+// The fewest steps of that estimate, and the W that takes them.  Where blocks of 4 and of
+// 8 come out the same, 8 are faster by up to 14 % with fp32 weights: half the copies of them to stage, and no CU with one
+// block of 4 beside one with two (8,192 / 24,576 envs x 10 agents 1,374 / 3,426 us against 1,580 / 3,820); with bf16 ones, a
+// third of the bytes, 4 are (predator-prey, actor-critic, 12,288 envs x 6 agents 1,242 us against 1,280), and in several slots
+// where the last round of 8 would be less than nine tenths full (16,384 envs x 1 agent 193 us against 209).
+struct WavesPlan {
+  int W;
+  float cost;
+};
+template <typename Scn, bool AC, bool BF>
+WavesPlan waves_plan(const RolloutArgs& A) {
+  // One run of 3 agents of simple spread in one slot comes here up to 168 envs per CU: one block of 8 always
+  if constexpr (!Scn::kTag && Scn::N == 3 && !BF) {
+    if (A.slots == 1) return {8, waves_cost<Scn, 8, AC, BF>(A)};
+  }
+  const float c4 = waves_cost<Scn, 4, AC, BF>(A), c8 = waves_cost<Scn, 8, AC, BF>(A), c12 = waves_cost<Scn, 12, AC, BF>(A);
+  const uint32_t cus = compute_units(), last8 = WavesBlocks<Scn, 8, AC, BF>::count(A) % cus;
+  const bool four = BF || (A.slots > 1 && last8 && last8 * 10 < cus * 9);
+  if ((four ? c4 <= c8 : c4 < c8) && c4 <= c12) return {4, c4};
+  return c8 <= c12 ? WavesPlan{8, c8} : WavesPlan{12, c12};
 }
 
 template <typename Scn, bool AC, bool BF>
 hipError_t launch_waves(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
-  // 3 agents of simple spread come here up to 168 envs per CU: one block of 8 always (see waves_cost)
-  if constexpr (!Scn::kTag && Scn::N == 3) return launch_waves_impl<Scn, 8, AC, BF>(A, packed, critic, s);
-  const float c4 = waves_cost<Scn, 4, AC, BF>(A.r), c8 = waves_cost<Scn, 8, AC, BF>(A.r), c12 = waves_cost<Scn, 12, AC, BF>(A.r);
-  if ((BF ? c4 <= c8 : c4 < c8) && c4 <= c12) return launch_waves_impl<Scn, 4, AC, BF>(A, packed, critic, s);
-  if (c8 <= c12) return launch_waves_impl<Scn, 8, AC, BF>(A, packed, critic, s);
-  return launch_waves_impl<Scn, 12, AC, BF>(A, packed, critic, s);
+  switch (waves_plan<Scn, AC, BF>(A.r).W) {
+    case 4: return launch_waves_impl<Scn, 4, AC, BF>(A, packed, critic, s);
+    case 8: return launch_waves_impl<Scn, 8, AC, BF>(A, packed, critic, s);
+    default: return launch_waves_impl<Scn, 12, AC, BF>(A, packed, critic, s);
+  }
+}
+
+// In the slots of A, where that pays: *taken.  With several runs, where a run's wavefronts and blocks are mostly full.
+// `against`: that without slots this kernel would run, which has the same time for the same wavefronts per CU: by the
+// estimate then (8 agents, critic, 20,011 envs 3,628 us in one slot, 3,737 in five; 6 agents, 20,011 envs 1,218 and 1,176).
+template <typename Scn, bool AC, bool BF>
+hipError_t launch_waves_slots(const TagArgs& A, bool against, const void* packed, const void* critic, hipStream_t s, bool* taken) {
+  constexpr uint32_t EW = 64 / Scn::N;
+  const uint32_t envs = A.r.E * uint32_t(A.r.slots), waves = (envs + EW - 1) / EW;
+  if (A.r.TE != A.r.E && (envs * 4 < waves * EW * 3 || waves * 4 < (waves + 3) / 4 * 4 * 3)) return hipSuccess;
+  if (against) {
+    RolloutArgs one = A.r;
+    one.slots = 1;
+    if (waves_plan<Scn, AC, BF>(A.r).cost > 0.98f * waves_plan<Scn, AC, BF>(one).cost) return hipSuccess;
+  }
+  *taken = true;
+  return launch_waves<Scn, AC, BF>(A, packed, critic, s);
 }
 
 }  // namespace
