@@ -415,7 +415,7 @@ int mpe_set_gru_critic(mpe_env* e, const float* Wc, const float* bc, const float
   if (!gru_supported(e->tag, e->N, e->L, e->G, e->H, e->cfg.weight_dtype))
     return fail(MPE_EINVAL, "mpe_set_gru_critic: the recurrent actor-critic needs hidden 128 and MPE_WEIGHTS_BF16");
   e->has_gru_critic = false;   // as in mpe_set_gru_policy
-  hipError_t err = pack_gru_critic(e->gru_critic, e->N, e->D, e->TE, e->E, Wc, bc, wv, bv, static_cast<hipStream_t>(stream));
+  hipError_t err = pack_gru_critic(e->gru_critic, e->TE, e->E, Wc, bc, wv, bv, static_cast<hipStream_t>(stream));
   if (err != hipSuccess) return fail(MPE_EHIP, "mpe_set_gru_critic: %s", hipGetErrorString(err));
   e->has_gru_critic = true;
   return MPE_OK;

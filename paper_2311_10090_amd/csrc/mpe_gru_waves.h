@@ -49,7 +49,7 @@ struct GruWaveCriticPk {
 // Envs in a block: 8 wavefronts of 32 rows.
 constexpr uint32_t gru_waves_block_envs(int N) { return 8u * (32u / uint32_t(N)); }
 
-// The first `envs` envs of the batch.
+// The first `envs` envs of the batch; in several slots of time (A.r.slots) the envs of all slots, which is the whole batch.
 hipError_t launch_gru_waves(bool tag, int N, int L, int G, const TagArgs& A, const void* packed, const void* critic, float* hidden,
                             uint32_t envs, hipStream_t s);
 

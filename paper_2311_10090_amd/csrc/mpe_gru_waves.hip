@@ -24,6 +24,7 @@
 
 #include "mpe_mlp64.h"
 #include "mpe_scenario.h"
+#include "mpe_slots.h"
 #include "mpe_gru_waves.h"
 
 namespace mpe {
@@ -63,13 +64,16 @@ struct GruWaveSmem {
 
 __device__ __forceinline__ float gate_sigmoid(float x) { return hw_rcp(1.0f + hw_exp2(-kLog2e * x)); }
 
-template <typename Scn, bool AC>
+// Piece: SlotGrid for a launch of several slots of time (mpe_slots.h).  The envs of the launch are then TE * slots, one slot's after
+// the other's, and a lane has a slot of its own (as in mpe_waves.h): wavefronts are full, and a batch of any size is many rounds of
+// short blocks, of which the last one weighs little.
+template <typename Scn, bool AC, typename Piece>
 __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, const uint8_t* __restrict__ packed,
                                                                    const uint8_t* __restrict__ packed_critic,
-                                                                   float* __restrict__ hidden, uint32_t end_env, GridPiece piece) {
+                                                                   float* __restrict__ hidden, uint32_t end_env, Piece piece) {
   using M = GruWaveSmem<Scn, AC>;
   using TS = typename Scn::Shape;
-  constexpr bool kTag = Scn::kTag;
+  constexpr bool kTag = Scn::kTag, SLOTS = kSlots<Piece>;
   constexpr int N = Scn::N, L = Scn::L, D = Scn::D, KIN = Scn::LIVE, KSE = (KIN + 31) / 32;
   constexpr int EW = 32 / N, EB = 8 * EW, ROWS = EW * N;
   constexpr int G = kTag ? TS::G : 1, NA = kTag ? TS::A : 0;
@@ -83,14 +87,27 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
   const int j = lane & 15, gq = lane >> 4;     // matrix layout: rows j and 16 + j, lane group gq
   GruWaveLds<Scn>& sm = *reinterpret_cast<GruWaveLds<Scn>*>(smem + M::OFF_WAVE + size_t(wave) * M::WAVE);
   const size_t TE = A.TE;
-  const uint32_t blk = xcd_group(piece);
-  if (blk >= piece.end) return;                          // whole block, before any barrier
+  uint32_t blk;
+  if constexpr (SLOTS) {
+    blk = spread_group();
+    if (blk >= piece.groups) return;
+  } else {
+    blk = xcd_group(piece);
+    if (blk >= piece.end) return;                        // whole block, before any barrier
+  }
   const uint32_t env0 = blk * EB + wave * EW;   // uniform
   const int nvalid = env0 < end_env ? min(int(end_env - env0), EW) : 0;
   const bool active = ROWS == 32 || n < ROWS;            // spare rows shadow the wavefront's first one and store nothing
   const int row = active ? n : 0, el = row / N, i = row - el * N;
   const bool in_range = el < nvalid, valid = active && in_range && lane < 32;
-  const uint32_t env = env0 + (in_range ? el : 0);
+  // the wavefront's first envs, those of the slot that reads and writes the state
+  const int nhead = !SLOTS ? nvalid : (env0 < A.TE ? min(int(A.TE - env0), nvalid) : 0);
+  const bool head = !SLOTS || el < nhead;
+  uint32_t env = env0 + (in_range ? el : 0), k_slot = 0;
+  if constexpr (SLOTS) {
+    k_slot = env / A.TE;
+    env -= k_slot * A.TE;
+  }
   const size_t g = nvalid ? env : 0u;
   const int32_t max_ep = kTag ? tg.max_ep : A.ph.max_ep;
 
@@ -112,12 +129,47 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
   // ---- this lane's agent; everything about the others is read from LDS where it is needed
   float px = 0.0f, py = 0.0f, vx = 0.0f, vy = 0.0f;
   int32_t ep = 0;
+  uint32_t step = A.abs_step;
+  // a new episode, keyed by the step that it starts at: every lane draws its own agent and landmarks i, i + N, ... of its env
+  auto new_episode = [&](uint32_t start) {
+    uint32_t env_r = env;
+    asm volatile("" : "+v"(env_r));
+    const uint4 d = philox4x32_10(env_r, start, uint32_t(i), kTagResetPos, A.seed, 0u);
+    px = word_to_position(d.x);
+    py = word_to_position(d.y);
+    vx = vy = 0.0f;
+    ep = 0;
+#pragma unroll
+    for (int k = 0; k < (L + N - 1) / N; ++k) {
+      const int l = i + k * N;
+      if (l < L) {
+        const uint4 w = philox4x32_10(env_r, start, uint32_t(N + l), kTagResetPos, A.seed, 0u);
+        float2 p = make_float2(word_to_position(w.x), word_to_position(w.y));
+        if (kTag) { p.x *= 0.9f; p.y *= 0.9f; }
+        if (active) sm.lm[el * (L + 1) + l] = p;
+      }
+    }
+  };
   if (in_range) {
     px = A.st.pos_a[(0 * N + i) * TE + g];
     py = A.st.pos_a[(1 * N + i) * TE + g];
     vx = A.st.vel_a[(0 * N + i) * TE + g];
     vy = A.st.vel_a[(1 * N + i) * TE + g];
     ep = A.st.ep_step[g];
+  }
+  // Several slots: number of steps of this lane's env, or, until the jump of slot 0, minus the steps before it
+  [[maybe_unused]] int32_t event = 0, ep0 = ep, t0 = 0;
+  int len = A.T;                                         // of the wavefront
+  if constexpr (SLOTS) {
+    counter_read(ep0);
+    const TimeSlot slot = time_slot(A, int(k_slot), ep0, max_ep, true);
+    t0 = slot.t0;
+    step += uint32_t(t0);
+    event = in_range ? (slot.turn ? -slot.turn : slot.len) : 0;
+    len = in_range ? slot.len : 0;
+#pragma unroll
+    for (int o = 32; o; o >>= 1) len = max(len, __shfl_xor(len, o));
+    len = __builtin_amdgcn_readfirstlane(len);
   }
 #pragma unroll
   for (int k = 0; k < (L + N - 1) / N; ++k) {
@@ -139,6 +191,7 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
       return reinterpret_cast<const float2*>(sm.xch[parity])[el * N + a];
     }
   };
+  if (!head) new_episode(step);
   put(1);
   __syncthreads();   // weights staged; the only block-wide barrier
   if (nvalid == 0) return;
@@ -173,8 +226,8 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
     }
     agent_obs<Scn>(o, i, px, py, vx, vy, qx, qy, lx, ly, gvx, gvy);
   };
-  auto store_row = [&](const float (&o)[KIN], float* dst) {
-    if (!valid) return;
+  auto store_row = [&](const float (&o)[KIN], float* dst, bool stores) {
+    if (!stores) return;
     constexpr int CW = D % 4 == 0 ? 4 : 2;
     typedef float vC __attribute__((ext_vector_type(CW)));
 #pragma unroll
@@ -191,7 +244,7 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
   float h[8][2][4];
   bf16x8 hb[4][2];      // the same rounded to bf16: B operand of K slice s, row tile rt
   float* hrow = hidden + (size_t(env0) * N + j) * kG + 8 * gq;
-  const int vrows = nvalid * N;
+  const int vrows = nhead * N;
 #pragma unroll
   for (int rt = 0; rt < 2; ++rt) {
 #pragma unroll
@@ -212,17 +265,23 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
       for (int rt = 0; rt < 2; ++rt) hb[s][rt] = pack8(h[2 * s][rt], h[2 * s + 1][rt]);
   };
   pack_state();
-  // outputs of this wavefront's first row (env): uniform, the lane adds its row
-  const size_t row0 = size_t(env0) * N;
+  // outputs of this wavefront's first row (env), uniform, to which the lane adds its row; several slots: of the first time slice, to
+  // which it adds the row and env in the slice of its own step
+  const size_t row0 = SLOTS ? 0 : size_t(env0) * N;
   const bool per_agent = kTag || A.ph.reward_mode == 1;
   float* obs_p = A.obs_traj ? A.obs_traj + row0 * D : nullptr;
   uint8_t* act_p = A.act_traj ? A.act_traj + row0 : nullptr;
-  float* rew_p = A.rew_traj ? A.rew_traj + (per_agent ? row0 : env0) : nullptr;
-  uint8_t* done_p = A.done_traj ? A.done_traj + env0 : nullptr;
+  float* rew_p = A.rew_traj ? A.rew_traj + (per_agent || SLOTS ? row0 : env0) : nullptr;
+  uint8_t* done_p = A.done_traj ? A.done_traj + (SLOTS ? 0 : env0) : nullptr;
   [[maybe_unused]] float* logp_p = AC && A.logp_traj ? A.logp_traj + row0 : nullptr;
   [[maybe_unused]] float* value_p = AC && A.value_traj ? A.value_traj + row0 : nullptr;
-  const bool env_writer = valid && i == 0;
-  uint32_t step = A.abs_step;
+  using Off = std::conditional_t<SLOTS, size_t, int>;
+  Off env_at = el;
+  if constexpr (SLOTS) {
+    env_at = g + size_t(t0) * TE;
+    if (valid && i == 0) settle_ticket(A, max_ep, g, take_ticket(A, g), ep0);
+  }
+  auto row_at = [&]() { return SLOTS ? Off(env_at * N + i) : Off(row); };
   float o[KIN];
 #pragma unroll
   for (int c = 0; c < KIN; ++c) o[c] = 0.0f;
@@ -459,13 +518,58 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
     }
   };
 
-  for (int t = 0; t < A.T; ++t, ++step) {
+  // state and last observation of the lanes that have run all their steps
+  auto finish = [&](bool ended) {
+    const bool stores = valid && ended;
+    // opaque: addresses computed from it stay here instead of in 20 to 30 registers over the loop of steps
+    uint32_t env_f = uint32_t(g), j_f = uint32_t(j), i_f = uint32_t(i), gq_f = uint32_t(gq);
+    if constexpr (SLOTS) asm volatile("" : "+v"(env_f), "+v"(j_f), "+v"(i_f), "+v"(gq_f));
+    const size_t g = env_f;
+    const int i = int(i_f), j = int(j_f);
+    float* hrow = hidden + (size_t(env0) * N + j_f) * kG + 8 * gq_f;
+    if (A.last_obs) store_row(o, A.last_obs + (g * N + i) * D, stores);
+    const uint64_t rows = SLOTS ? __ballot(ended) : ~0ull;
+#pragma unroll
+    for (int rt = 0; rt < 2; ++rt) {
+      if (16 * rt + j < vrows && (rows >> (16 * rt + j) & 1)) {
+#pragma unroll
+        for (int c = 0; c < 8; ++c)
+          *reinterpret_cast<f32x4*>(hrow + rt * 16 * kG + 32 * (c / 2) + 4 * (c % 2)) = f32x4{h[c][rt][0], h[c][rt][1], h[c][rt][2], h[c][rt][3]};
+      }
+    }
+    if (stores) {
+      A.st.pos_a[(0 * N + i) * TE + g] = px;
+      A.st.pos_a[(1 * N + i) * TE + g] = py;
+      A.st.vel_a[(0 * N + i) * TE + g] = vx;
+      A.st.vel_a[(1 * N + i) * TE + g] = vy;
+#pragma unroll
+      for (int k = 0; k < (L + N - 1) / N; ++k) {
+        const int l = i + k * N;
+        if (l < L) {
+          const float2 p = sm.lm[el * (L + 1) + l];
+          A.st.pos_l[(0 * L + l) * TE + g] = p.x;
+          A.st.pos_l[(1 * L + l) * TE + g] = p.y;
+        }
+      }
+      if (i == 0 && !SLOTS) A.st.ep_step[g] = ep;
+    }
+  };
+
+  for (int t = 0; t < len; ++t) {
+    const bool ended = SLOTS && head && t == event;      // before the wavefront's other lanes
+    if constexpr (SLOTS) {
+      if (__ballot(ended)) finish(ended);
+    }
+    const bool stores = valid && (!SLOTS || event < 0 || t < event), env_writer = stores && i == 0;
     if (obs_p) {
-      store_row(o, obs_p + row * D);
+      store_row(o, obs_p + row_at() * D, stores);
       obs_p += TE * (N * D);
     }
     float z[kNumActions], value = 0.0f;
     network(z, value);
+    if constexpr (AC && SLOTS) {
+      if (ended && valid && A.last_value) A.last_value[g * N + i] = value;
+    }
     const int par = t & 1;
     // Sampling noise as in gumbel_noise: the lower half of the wavefront draws the block of the first four actions, the
     // upper half that of the fifth; the lower half picks.
@@ -482,7 +586,7 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
       act = __builtin_amdgcn_permlane32_swap(act, act, false, false)[0];
     }
     if (act_p) {
-      if (valid) act_p[row] = uint8_t(act);
+      if (stores) act_p[row_at()] = uint8_t(act);
       act_p += TE * N;
     }
     if constexpr (AC) {
@@ -497,11 +601,11 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
 #pragma unroll
       for (int k = 0; k < kNumActions; ++k) sum += hw_exp2((z[k] - zmax) * kLog2e);
       if (logp_p) {
-        if (valid) logp_p[row] = (zact - zmax) - kLn2 * hw_log2(sum);
+        if (stores) logp_p[row_at()] = (zact - zmax) - kLn2 * hw_log2(sum);
         logp_p += TE * N;
       }
       if (value_p) {
-        if (valid) value_p[row] = value;
+        if (stores) value_p[row_at()] = value;
         value_p += TE * N;
       }
     }
@@ -536,7 +640,7 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
       }
       if constexpr (kTag) {
         const float r = tag_reward<TS>(i, me, tg, px, py, qx, qy);
-        if (valid) rew_p[row] = r;
+        if (stores) rew_p[row_at()] = r;
       } else {
         const float2 mine = sm.lm[el * (L + 1) + i];
         float best2 = INFINITY;
@@ -552,9 +656,9 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
         for (int a = 0; a < N; ++a) r -= sm.dmin[el * N + a];
         if (per_agent) {
           const float mr = mixed_reward(r, overlap_count<N>(i, px, py, qx, qy, A.ph), A.ph);
-          if (valid) rew_p[row] = mr;
+          if (stores) rew_p[row_at()] = mr;
         } else if (env_writer) {
-          rew_p[el] = r;
+          rew_p[env_at] = r;
         }
       }
       rew_p += per_agent ? TE * N : TE;
@@ -562,29 +666,19 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
     ep += 1;
     const bool done = ep >= max_ep;
     if (done_p) {
-      if (env_writer) done_p[el] = done ? 1 : 0;
+      if (env_writer) done_p[env_at] = done ? 1 : 0;
       done_p += TE;
     }
-    if (done) {
-      // new episode keyed by step + 1: every lane draws its own agent and landmarks i, i + N, ... of its env
-      uint32_t env_r = env;
-      asm volatile("" : "+v"(env_r));
-      const uint4 d = philox4x32_10(env_r, step + 1u, uint32_t(i), kTagResetPos, A.seed, 0u);
-      px = word_to_position(d.x);
-      py = word_to_position(d.y);
-      vx = vy = 0.0f;
-      ep = 0;
-#pragma unroll
-      for (int k = 0; k < (L + N - 1) / N; ++k) {
-        const int l = i + k * N;
-        if (l < L) {
-          const uint4 w = philox4x32_10(env_r, step + 1u, uint32_t(N + l), kTagResetPos, A.seed, 0u);
-          float2 p = make_float2(word_to_position(w.x), word_to_position(w.y));
-          if (kTag) { p.x *= 0.9f; p.y *= 0.9f; }
-          if (active) sm.lm[el * (L + 1) + l] = p;
-        }
+    ++step;
+    if constexpr (SLOTS) {
+      if (t + 1 == -event) {                           // slot 0's current episode ends
+        const int32_t jump = (A.slots - 1) * A.span;
+        event = A.T - jump;
+        step += uint32_t(jump);
+        env_at += size_t(jump) * TE;
       }
     }
+    if (done) new_episode(step);
     if (const uint64_t fresh = __ballot(done)) {       // the carried state of a new episode is zero
 #pragma unroll
       for (int rt = 0; rt < 2; ++rt) {
@@ -601,51 +695,35 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
     wave_sync();
     build(o, par);
   }
-  if (A.last_obs) store_row(o, A.last_obs + (row0 + row) * D);
-#pragma unroll
-  for (int rt = 0; rt < 2; ++rt) {
-    if (16 * rt + j < vrows) {
-#pragma unroll
-      for (int c = 0; c < 8; ++c)
-        *reinterpret_cast<f32x4*>(hrow + rt * 16 * kG + 32 * (c / 2) + 4 * (c % 2)) = f32x4{h[c][rt][0], h[c][rt][1], h[c][rt][2], h[c][rt][3]};
-    }
-  }
+  const bool ended = !SLOTS || (head && event == len);
+  if (nhead) finish(ended);
   if constexpr (AC) {
-    if (A.last_value) {        // one more evaluation on the last observation; the state it leaves is dropped
+    if (A.last_value && nhead) {   // one more evaluation on the last observation; the state it leaves is dropped
       float z[kNumActions], value = 0.0f;
       network(z, value);
-      if (valid) A.last_value[row0 + row] = value;
+      if (valid && ended) A.last_value[g * N + i] = value;
     }
-  }
-  if (valid) {
-    A.st.pos_a[(0 * N + i) * TE + g] = px;
-    A.st.pos_a[(1 * N + i) * TE + g] = py;
-    A.st.vel_a[(0 * N + i) * TE + g] = vx;
-    A.st.vel_a[(1 * N + i) * TE + g] = vy;
-#pragma unroll
-    for (int k = 0; k < (L + N - 1) / N; ++k) {
-      const int l = i + k * N;
-      if (l < L) {
-        const float2 p = sm.lm[el * (L + 1) + l];
-        A.st.pos_l[(0 * L + l) * TE + g] = p.x;
-        A.st.pos_l[(1 * L + l) * TE + g] = p.y;
-      }
-    }
-    if (i == 0) A.st.ep_step[g] = ep;
   }
 }
 
 template <typename Scn, bool AC>
 hipError_t launch_impl(const TagArgs& A, const void* packed, const void* critic, float* hidden, uint32_t envs, hipStream_t s) {
   using M = GruWaveSmem<Scn, AC>;
-  auto kern = rollout_gru_waves_kernel<Scn, AC>;
-  static std::atomic<uint64_t> lds_allowed{0};
-  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed); e != hipSuccess) return e;
+  static std::atomic<uint64_t> lds_allowed[2];
   constexpr uint32_t EB = gru_waves_block_envs(Scn::N);
-  return launch_groups<512>((envs + EB - 1) / EB, [&](dim3 grid, const GridPiece& p) {
-    hipLaunchKernelGGL(kern, grid, dim3(512), M::TOTAL, s, A, static_cast<const uint8_t*>(packed),
-                       static_cast<const uint8_t*>(critic), hidden, envs, p);
-  });
+  auto launch = [&](auto kern, dim3 grid, auto piece) {
+    hipLaunchKernelGGL(kern, grid, dim3(512), M::TOTAL, s, A, static_cast<const uint8_t*>(packed), static_cast<const uint8_t*>(critic), hidden, envs, piece);
+  };
+  if (A.r.slots > 1) {
+    auto kern = rollout_gru_waves_kernel<Scn, AC, SlotGrid>;
+    if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[1]); e != hipSuccess) return e;
+    const uint32_t blocks = (envs + EB - 1) / EB;
+    launch(kern, spread_grid(blocks), SlotGrid{blocks});
+    return hipGetLastError();
+  }
+  auto kern = rollout_gru_waves_kernel<Scn, AC, GridPiece>;
+  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[0]); e != hipSuccess) return e;
+  return launch_groups<512>((envs + EB - 1) / EB, [&](dim3 grid, const GridPiece& p) { launch(kern, grid, p); });
 }
 
 }  // namespace

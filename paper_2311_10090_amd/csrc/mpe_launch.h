@@ -185,7 +185,7 @@ hipError_t pack_policy_gru(PolicyBuffers& pb, bool tag, int N, int D, uint32_t T
 hipError_t launch_rollout_gru(bool tag, int N, int L, int G, const TagArgs& A, const PolicyBuffers& pb, const void* critic,
                               float* hidden, hipStream_t s, bool* partial, const char** why);
 // Critic head of the recurrent actor-critic: Wc [R][128][128], bc [R][128], wv [R][128], bv [R]
-hipError_t pack_gru_critic(PolicyBuffers& pb, int N, int D, uint32_t TE, uint32_t E, const float* Wc, const float* bc, const float* wv,
+hipError_t pack_gru_critic(PolicyBuffers& pb, uint32_t TE, uint32_t E, const float* Wc, const float* bc, const float* wv,
                            const float* bv, hipStream_t s);
 // One lane per agent (mpe_env_agents.hip), both scenarios: one step under A.actions_in (reward, done and obs after the
 // step through A.r.rew_traj, done_traj, last_obs), or, with A.actions_in null, a rollout with uniform actions.

@@ -34,6 +34,7 @@
 // simple spread) enter the embedding as two K slices.
 #include "mpe_gru_waves.h"
 #include "mpe_mlp64.h"
+#include "mpe_slots.h"
 #include "mpe_tag_device.h"
 
 namespace mpe {
@@ -94,6 +95,85 @@ uint32_t gru_waves_envs(int N, int D, bool ac, uint32_t TE, uint32_t E) {
   const float all = blocks(TE), some = float(full) + blocks(rest), none = float(full + (rest != 0));
   if (all <= some && all <= none) return 0;
   return some <= none ? TE - rest : TE;
+}
+
+// When the last of `longs` blocks of a steps and then `shorts` of b steps ends, each taken by the compute unit that is free first.
+inline float gru_makespan(uint32_t longs, float a, uint32_t shorts, float b) {
+  const uint32_t cus = compute_units(), busy = longs % cus;
+  uint32_t n[2] = {cus - busy, busy};                       // compute units that are free at free[0], free[1]
+  float free[2] = {float(longs / cus) * a, float(longs / cus + 1) * a}, end = busy ? free[1] : free[0];
+  if (const uint32_t rounds = shorts / cus; rounds > 2) {
+    for (float& f : free) f += float(rounds - 2) * b;
+    shorts -= (rounds - 2) * cus;
+  }
+  while (shorts) {
+    const int k = n[1] && free[1] < free[0] ? 1 : 0;
+    shorts -= shorts < n[k] ? shorts : n[k];
+    free[k] += b;
+    end = fmaxf(end, free[k]);
+  }
+  return end;
+}
+
+// How a batch runs: in one slot of time, or, where that is shorter by the estimate, in as many as the rollout holds (mpe_slots.h): in
+// independent wavefronts or in blocks of any of the sizes.  In several slots the blocks of a batch are many and short: with few
+// envs the smallest blocks for which each slot's still get CUs of their own, and no round of independent wavefronts is mostly
+// empty.  The estimate counts steps of a block of independent wavefronts, one more for the staging of its weights; a step of a block of
+// `tiles` row tiles is a + b tiles of those (measured: 1 agent 1 / 4 tiles 0.16 / 0.34, 3 agents 1 / 4 / 12 tiles 0.15 / 0.34 / 0.85, 6 agents 1 / 6 0.20 /
+// 0.51, 10 agents 1 / 10 0.22 / 0.81; with a critic 3 agents 0.18 / 0.38 / 0.92, 6 agents 0.22 / 0.59, 10 agents 0.26 / 1.05).  Measured, 128 steps,
+// one slot / five, plain, us: 3 agents 64 envs 303 / 73 (5-env blocks), 512 300 / 132 (16), 2,000 423 / 301 (21), 3,000 542 / 416 (64), 4,096 540 / 512
+// (wavefronts, and from here on), 12,000 1,841 / 1,357, 32,768 3,703 / 3,500; with a critic 64 441 / 104, 4,096 724 / 630, 12,000 2,366 / 1,668,
+// 32,768 4,767 / 4,221; 6 agents 200 373 / 125, 5,000 2,065 / 1,299; 10 agents 200 482 / 214, 3,000 1,925 / 1,491, 5,000 (one round of wavefronts four fifths full
+// against 4.07), with a critic, 2,905 / 2,994.
+struct GruPlan {
+  uint32_t waves;          // envs, from the first on, in independent wavefronts: none, whole rounds, all
+  uint32_t block;          // envs in a block of the others
+  int32_t slots, span;     // slots of time
+};
+GruPlan gru_plan(int N, int D, bool ac, const RolloutArgs& A, int32_t max_ep) {
+  const bool runs = A.TE != A.E;
+  const uint32_t cus = compute_units(), kmax = uint32_t(gru_max_envs(N, D));
+  GruPlan plan{gru_waves_envs(N, D, ac, A.TE, A.E), 0, 1, 0};
+  const uint32_t rest = A.TE - plan.waves;
+  if (!runs) plan.block = gru_tile_envs(N, D, rest);
+  if (!plan.block) {
+    // With one set of weights per run a block must lie inside a run: the largest of 64, 32, 16 that divides
+    // the run size bounds the choice.
+    plan.block = gru_block_envs(N, D, rest);
+    while (runs && A.E % plan.block != 0) plan.block /= 2;
+  }
+  RolloutArgs B = A;
+  choose_slots(B, max_ep, ~0u);
+  if (B.slots == 1) return plan;
+
+  const float a = ac ? 0.08f + 0.0095f * float(N) : 0.07f + 0.009f * float(N), b = ac ? 0.06f + 0.003f * float(N) : 0.063f;
+  auto block_step = [&](uint32_t eb) { return a + b * float((eb * uint32_t(N) + 15) / 16); };
+  // one slot: rounds of wavefronts, then of blocks, which wait for the last of those
+  const uint32_t round = cus * gru_waves_block_envs(N);
+  const float steps = float(A.T) + 1.0f;
+  float one = float((plan.waves + round - 1) / round) * steps;
+  if (rest) one += block_step(plan.block) * float(((rest + plan.block - 1) / plan.block + cus - 1) / cus) * steps + (plan.waves ? 4.0f : 0.0f);
+  float best = (plan.waves ? 0.97f : 0.92f) * one;     // blocks in one slot have smaller instances, 3 to 8 % faster
+  const float longest = float(A.T - (B.slots - 1) * B.span), span = float(B.span);
+  auto offer = [&](float time, uint32_t waves, uint32_t block) {
+    if (time >= best) return;
+    best = time;
+    plan = {waves, block, B.slots, B.span};
+  };
+  auto offer_block = [&](uint32_t eb) {
+    const uint32_t groups = (A.TE + eb - 1) / eb;
+    if (!runs || A.E % eb == 0) offer(block_step(eb) * gru_makespan(groups, longest + 0.5f, groups * uint32_t(B.slots - 1), span + 0.5f), 0, eb);
+  };
+  if (!runs) {
+    for (uint32_t tiles = 1; tiles <= 4; tiles *= 2) {
+      const uint32_t eb = 16 * tiles / uint32_t(N);
+      if (eb < 16 || (eb > 16 && eb < 32 && kmax >= 32)) offer_block(eb);
+    }
+    const uint32_t eb = gru_waves_block_envs(N), longs = (A.TE + eb - 1) / eb, blocks = (A.TE * uint32_t(B.slots) + eb - 1) / eb;
+    offer(gru_makespan(longs, longest + 1.0f, blocks - longs, span + 1.0f), A.TE, 0);
+  }
+  for (uint32_t eb = 16; eb <= kmax; eb *= 2) offer_block(eb);
+  return plan;
 }
 
 constexpr int kG = 128;    // hidden width of every layer
@@ -389,15 +469,19 @@ __device__ __forceinline__ uint2 pack4_bf16(float a, float b, float c, float d) 
 // AC = the actor-critic rollout (packed_critic = the head of pack_gru_critic): per step also the critic's second
 // layer on the new carried state and the log-probability of the sampled action, and, when a bootstrap value
 // is asked for, one more pass of the network phases after the last step that writes nothing else.
-template <typename Scn, int EB, bool AC>
+// Piece: GruGrid, or SlotGrid for a launch of several slots of time (mpe_slots.h), whose blocks are of one slot each.
+// first: the first env, in envs (M::kSpare) or in blocks; groups: blocks (of one slot).
+struct GruGrid {
+  uint32_t groups_per_xcd;
+};
+template <typename Scn, int EB, bool AC, typename Piece>
 __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint8_t* __restrict__ packed,
                                                           const uint8_t* __restrict__ packed_critic,
-                                                          float* __restrict__ hidden, int per_run_weights,
-                                                          uint32_t first, uint32_t groups, uint32_t groups_per_xcd) {
-  // first: the first env, in envs (M::kSpare) or in blocks
+                                                          float* __restrict__ hidden, int per_run_weights, uint32_t first,
+                                                          uint32_t groups, Piece piece) {
   using M = GruSmem<Scn, EB, AC>;
   using TS = typename Scn::Shape;                      // predator-prey only
-  constexpr bool kTag = Scn::kTag;
+  constexpr bool kTag = Scn::kTag, SLOTS = kSlots<Piece>;
   constexpr int N = Scn::N, L = Scn::L, B = M::B, ROWS = M::ROWS, D = M::D, NT = M::NT, KS = M::KS;
   constexpr int G = kTag ? TS::G : 1, NA = kTag ? TS::A : 0;   // good agents, adversaries
   const RolloutArgs& A = TA.r;
@@ -429,12 +513,23 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   const int rd_off = j * kAS + 16 * act_piece(gq, j);
   constexpr int kTile = 16 * kAS;   // bytes of one tile of 16 activation rows
   const size_t TE = A.TE;
-  const uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
-  if (grp >= groups) return;  // whole block, before any barrier
-  const size_t g0 = M::kSpare ? first + size_t(grp) * EB : size_t(first + grp) * EB;
+  int k_slot = 0;
+  size_t g0;
+  if constexpr (SLOTS) {
+    uint32_t grp;
+    if (!take_slot(A, piece, k_slot, grp)) return;
+    g0 = size_t(grp) * EB;
+  } else {
+    const uint32_t grp = (blockIdx.x & 7u) * piece.groups_per_xcd + (blockIdx.x >> 3);
+    if (grp >= groups) return;  // whole block, before any barrier
+    g0 = M::kSpare ? first + size_t(grp) * EB : size_t(first + grp) * EB;
+  }
   const size_t left = TE - g0;
   const int nvalid = left < size_t(EB) ? int(left) : EB;   // valid envs of this block
   const int vrows = nvalid * N;                            // valid agent rows
+  const int32_t max_ep = kTag ? tg.max_ep : A.ph.max_ep;
+  const TimeSlot slot = group_slot<SLOTS>(A, k_slot, max_ep, g0, nvalid, lane);
+  const bool head = k_slot == 0;                           // the slot that reads and writes the envs' state
   if (per_run_weights) packed += size_t(uint32_t(g0) / A.E) * GruPk::BYTES;   // the run of this block's envs
   if constexpr (AC) {
     if (per_run_weights) packed_critic += size_t(uint32_t(g0) / A.E) * GruCriticPk::BYTES;
@@ -474,7 +569,7 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   for (int rt = 0; rt < NT; ++rt) {
     const int row = 16 * rt + j;
     f32x4 v = {0.0f, 0.0f, 0.0f, 0.0f};
-    if (row < vrows) v = *reinterpret_cast<const f32x4*>(hidden + (g0 * N + row) * kG + 16 * u + 4 * gq);
+    if (row < vrows && head) v = *reinterpret_cast<const f32x4*>(hidden + (g0 * N + row) * kG + 16 * u + 4 * gq);
 #pragma unroll
     for (int r = 0; r < 4; ++r) hreg[rt][r] = v[r];
     *reinterpret_cast<uint2*>(hbuf + rt * kTile + wr_off) = pack4_bf16(v[0], v[1], v[2], v[3]);
@@ -505,7 +600,36 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   for (int k = 0; k < L + 1; ++k) lx[k] = ly[k] = 0.0f;
 #pragma unroll
   for (int k = 0; k < G; ++k) gvx[k] = gvy[k] = 0.0f;
-  if (valid) {
+  uint32_t step = A.abs_step + uint32_t(slot.t0);
+  // A new episode, keyed by the step that it starts at; every lane draws its whole env (1 step in max_ep).
+  auto new_episode = [&](uint32_t start) {
+    uint32_t env_r = env;
+    asm volatile("" : "+v"(env_r));
+    if constexpr (kTag) {
+      tag_draw_positions<TS>(qx, qy, lx, ly, env_r, start, A.seed, run);
+#pragma unroll
+      for (int k = 0; k < G; ++k) gvx[k] = gvy[k] = 0.0f;
+    } else {
+#pragma unroll
+      for (int a = 0; a < N; ++a) {
+        const uint4 w = philox4x32_10(env_r, start, uint32_t(a), kTagResetPos, A.seed, run);
+        qx[a] = word_to_position(w.x);
+        qy[a] = word_to_position(w.y);
+        const uint4 wl = philox4x32_10(env_r, start, uint32_t(N + a), kTagResetPos, A.seed, run);
+        lx[a] = word_to_position(wl.x);
+        ly[a] = word_to_position(wl.y);
+      }
+    }
+#pragma unroll
+    for (int a = 0; a < N; ++a) {
+      if (a == i) { px = qx[a]; py = qy[a]; }
+    }
+    vx = vy = 0.0f;
+    ep = 0;
+  };
+  if (SLOTS && !head) {
+    if (agent) new_episode(step);
+  } else if (valid) {
 #pragma unroll
     for (int a = 0; a < N; ++a) {
       qx[a] = A.st.pos_a[(0 * N + a) * TE + g];
@@ -526,10 +650,10 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
     vx = A.st.vel_a[(0 * N + i) * TE + g];
     vy = A.st.vel_a[(1 * N + i) * TE + g];
     ep = A.st.ep_step[g];
-  }
 #pragma unroll
-  for (int a = 0; a < N; ++a) {
-    if (a == i) { px = qx[a]; py = qy[a]; }
+    for (int a = 0; a < N; ++a) {
+      if (a == i) { px = qx[a]; py = qy[a]; }
+    }
   }
   // predator-prey: the constants of this lane's role
   [[maybe_unused]] TagRole me{};
@@ -569,8 +693,9 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
     }
   };
   const size_t slice = TE * size_t(N * D);                               // floats per time slice
-  float* obs_row = A.obs_traj ? A.obs_traj + (size_t(gc) * N + i) * D : nullptr;   // this lane's row, slot 0
-  float* last_row = A.last_obs ? A.last_obs + (size_t(gc) * N + i) * D : nullptr;
+  // this lane's row of the first time slice
+  float* obs_row = A.obs_traj ? A.obs_traj + size_t(slot.t0) * slice + (size_t(gc) * N + i) * D : nullptr;
+  float* last_row = A.last_obs && head ? A.last_obs + (size_t(gc) * N + i) * D : nullptr;
   // Sampling noise of this lane's row for step `at`.
   [[maybe_unused]] auto draw_noise = [&](uint32_t at) {
     float nz[kNumActions];
@@ -578,9 +703,14 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
 #pragma unroll
     for (int k = 0; k < kNumActions; ++k) noise[k * B + srow] = nz[k];
   };
-  if (agent) write_obs_row(obs_row);
+  if (agent) write_obs_row(!SLOTS || slot.len ? obs_row : nullptr);
   if constexpr (M::kAhead) {
-    if (service) draw_noise(A.abs_step);
+    if (service) draw_noise(step);
+  }
+  [[maybe_unused]] int32_t ep0 = 0;
+  if constexpr (SLOTS) {
+    if (valid) ep0 = A.st.ep_step[g];
+    counter_read(ep0);
   }
   __syncthreads();   // staged weights, biases, HB, first observation and noise
 
@@ -590,9 +720,22 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
   const size_t row_off = size_t(gc) * N + i;
   const bool env_writer = valid && i == 0;
   const bool per_agent_reward = kTag || A.ph.reward_mode == 1;
-  uint32_t step = A.abs_step;
   [[maybe_unused]] float* logp_base = A.logp_traj;
   [[maybe_unused]] float* value_base = A.value_traj;
+
+  // The bases above, `steps` time slices further
+  [[maybe_unused]] auto ahead = [&](int32_t steps) {
+    const size_t k = size_t(steps);
+    if (act_base) act_base += k * TE * N;
+    if (rew_base) rew_base += k * (per_agent_reward ? TE * N : TE);
+    if (done_base) done_base += k * TE;
+    if (AC && logp_base) logp_base += k * TE * N;
+    if (AC && value_base) value_base += k * TE * N;
+  };
+  if constexpr (SLOTS) {
+    ahead(slot.t0);
+    if (env_writer) settle_ticket(A, max_ep, g, take_ticket(A, g), ep0);
+  }
 
   // The carried state back to HBM (cleared where the last step ended an episode).
   auto store_hidden = [&]() {
@@ -618,10 +761,10 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
 
   // Actor-critic with a bootstrap value: one more pass of the network over the observation after the last
   // step, on the carried state as it stands; that pass writes nothing back (the state has been stored by then).
-  const bool bootstrap = AC && A.last_value != nullptr;
-  const int passes = A.T + (bootstrap ? 1 : 0);
+  const bool bootstrap = AC && head && A.last_value != nullptr;
+  const int passes = slot.len + (bootstrap ? 1 : 0);
   for (int t = 0; t < passes; ++t, ++step) {
-    const bool extra = AC && t == A.T;
+    const bool extra = AC && t == slot.len;
     if (extra) store_hidden();   // the registers of the carried state are free from here on
     // Opaque zero: keeps the step-invariant LDS reads (biases, small-layer operands) inside the step
     // loop; hoisted out of it they would pin ~40 registers for the whole rollout.
@@ -796,12 +939,13 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
     }
     __syncthreads();   // new positions visible; L has been read
 
+    const bool turn = SLOTS && t + 1 == slot.turn;       // an episode's end, after which time goes on elsewhere
+    if (turn) step += uint32_t(slot.jump);
     // ---- agents: reward, done, auto-reset, next observation (written over L); service lanes: the next step's noise
     if constexpr (M::kAhead) {
       if (service) draw_noise(step + 1u);
     }
     if (agent) {
-      int32_t max_ep;
       if constexpr (kTag) {
 #pragma unroll
         for (int a = 0; a < N; ++a) {
@@ -814,7 +958,6 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
           }
         }
         if (rew_base && valid) rew_base[row_off] = tag_reward<TS>(i, me, tg, px, py, qx, qy);
-        max_ep = tg.max_ep;
       } else {
 #pragma unroll
         for (int a = 0; a < N; ++a) {
@@ -829,53 +972,32 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
         } else if (rew_base && env_writer) {
           rew_base[gc] = r;
         }
-        max_ep = A.ph.max_ep;
       }
       ep += 1;
       const bool done = ep >= max_ep;
       if (done_base && env_writer) done_base[gc] = done ? 1 : 0;
       if (i == 0 && (!M::kSpare || srow < ROWS)) donef[el] = done ? 1 : 0;     // read by the gate phase of the next step
       if (done) {
-        // new episode keyed by step + 1; every lane regenerates its whole env (1 step in max_ep)
-        uint32_t env_r = env;
-        asm volatile("" : "+v"(env_r));
-        if constexpr (kTag) {
-          tag_draw_positions<TS>(qx, qy, lx, ly, env_r, step + 1u, A.seed, run);
-#pragma unroll
-          for (int k = 0; k < G; ++k) gvx[k] = gvy[k] = 0.0f;
-        } else {
-#pragma unroll
-          for (int a = 0; a < N; ++a) {
-            const uint4 w = philox4x32_10(env_r, step + 1u, uint32_t(a), kTagResetPos, A.seed, run);
-            qx[a] = word_to_position(w.x);
-            qy[a] = word_to_position(w.y);
-            const uint4 wl = philox4x32_10(env_r, step + 1u, uint32_t(N + a), kTagResetPos, A.seed, run);
-            lx[a] = word_to_position(wl.x);
-            ly[a] = word_to_position(wl.y);
-          }
-        }
-#pragma unroll
-        for (int a = 0; a < N; ++a) {
-          if (a == i) { px = qx[a]; py = qy[a]; }
-        }
-        vx = vy = 0.0f;
-        ep = 0;
+        new_episode(step + 1u);
         // the carried state of the new episode is zero: clear this row's bf16 copy (the fp32
         // registers of the owning wavefronts follow the done flag)
 #pragma unroll
         for (int q = 0; q < 16; ++q) reinterpret_cast<u32x4*>(hbuf + tid * kAS)[q] = u32x4{0u, 0u, 0u, 0u};
       }
-      if (obs_row) obs_row += slice;
-      write_obs_row(t + 1 < A.T ? obs_row : last_row);
+      if (obs_row) obs_row += turn ? size_t(slot.jump + 1) * slice : slice;
+      write_obs_row(t + 1 < slot.len ? obs_row : last_row);
     }
     if (rew_base) rew_base += per_agent_reward ? TE * N : TE;
     if (done_base) done_base += TE;
+    if constexpr (SLOTS) {
+      if (turn) ahead(slot.jump);
+    }
     __syncthreads();   // next observation and the done flags complete
   }
 
   // ---- state back to HBM: the carried state (unless the bootstrap pass has stored it), agents
-  if (!bootstrap) store_hidden();
-  if (valid) {
+  if (!bootstrap && head) store_hidden();
+  if (valid && head) {
     A.st.pos_a[(0 * N + i) * TE + g] = px;
     A.st.pos_a[(1 * N + i) * TE + g] = py;
     A.st.vel_a[(0 * N + i) * TE + g] = vx;
@@ -888,7 +1010,7 @@ __global__ __launch_bounds__(512) void rollout_gru_kernel(TagArgs TA, const uint
         A.st.pos_l[(1 * L + l) * TE + g] = ly[l];
       }
     }
-    if (i == 0) A.st.ep_step[g] = ep;
+    if (i == 0 && !SLOTS) A.st.ep_step[g] = ep;
   }
 }
 
@@ -898,9 +1020,20 @@ template <typename Scn, int EB, bool AC>
 hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, uint32_t first, hipStream_t s,
                               bool* partial) {
   using M = GruSmem<Scn, EB, AC>;
-  auto kern = rollout_gru_kernel<Scn, EB, AC>;
-  static std::atomic<uint64_t> lds_allowed{0};
-  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed); e != hipSuccess) return e;
+  static std::atomic<uint64_t> lds_allowed[2];
+  auto launch = [&](auto kern, dim3 grid, uint32_t start, uint32_t groups, auto piece) {
+    hipLaunchKernelGGL(kern, grid, dim3(512), M::TOTAL, s, A, static_cast<const uint8_t*>(pb.packed), static_cast<const uint8_t*>(critic), hidden,
+                       int(A.r.TE != A.r.E), start, groups, piece);
+    return hipGetLastError();
+  };
+  if (A.r.slots > 1) {
+    auto kern = rollout_gru_kernel<Scn, EB, AC, SlotGrid>;
+    if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[1]); e != hipSuccess) return e;
+    const uint32_t groups = (A.r.TE + EB - 1) / EB;
+    return launch(kern, slots_grid(A.r, groups), 0u, groups, SlotGrid{groups});
+  }
+  auto kern = rollout_gru_kernel<Scn, EB, AC, GruGrid>;
+  if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[0]); e != hipSuccess) return e;
   if (!M::kSpare) first -= first % EB;    // whole blocks before them (they are with any multiple of 8 compute units)
   if (first) {
     hipError_t e = launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, A, pb.packed, critic, hidden, first, s);
@@ -908,9 +1041,7 @@ hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const v
   }
   const uint32_t groups = (A.r.TE - first + EB - 1) / EB;
   const uint32_t per_xcd = (groups + 7) / 8;
-  hipLaunchKernelGGL(kern, dim3(per_xcd * 8), dim3(512), M::TOTAL, s, A, static_cast<const uint8_t*>(pb.packed),
-                     static_cast<const uint8_t*>(critic), hidden, int(A.r.TE != A.r.E), M::kSpare ? first : first / EB, groups, per_xcd);
-  const hipError_t e = hipGetLastError();
+  const hipError_t e = launch(kern, dim3(per_xcd * 8), M::kSpare ? first : first / EB, groups, GruGrid{per_xcd});
   *partial = e != hipSuccess && first != 0;
   return e;
 }
@@ -918,30 +1049,32 @@ hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const v
 template <typename Scn, bool AC>
 hipError_t rollout_gru_sized(const TagArgs& A, const PolicyBuffers& pb, const void* critic, float* hidden, hipStream_t s, bool* partial) {
   constexpr int kMax = gru_max_envs(Scn::N, Scn::D);
-  const bool runs = A.r.TE != A.r.E;
-  const uint32_t first = gru_waves_envs(Scn::N, Scn::D, AC, A.r.TE, A.r.E), rest = A.r.TE - first;
-  if (rest == 0)
-    return launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, A, pb.packed, critic, hidden, first, s);
+  GruPlan plan = gru_plan(Scn::N, Scn::D, AC, A.r, Scn::kTag ? A.tg.max_ep : A.r.ph.max_ep);
+  TagArgs B = A;
+  B.r.slots = plan.slots;
+  B.r.span = plan.span;
+  if (plan.waves == A.r.TE)
+    return launch_gru_waves(Scn::kTag, Scn::N, Scn::L, Scn::kTag ? Scn::Shape::G : 0, B, pb.packed, critic, hidden, B.r.work(), s);
   constexpr int kOne = 16 / Scn::N, kTwo = 32 / Scn::N, kFour = 64 / Scn::N;
-  if (const uint32_t te = runs ? 0 : gru_tile_envs(Scn::N, Scn::D, rest)) {
-    if constexpr (kOne < 16) {
-      if (te == kOne) return rollout_gru_blocks<Scn, kOne, AC>(A, pb, critic, hidden, first, s, partial);
-    }
-    if constexpr (kTwo < 16) {
-      if (te == kTwo) return rollout_gru_blocks<Scn, kTwo, AC>(A, pb, critic, hidden, first, s, partial);
-    }
-    if constexpr (kFour < 16 || (kFour > 16 && kFour < 32 && kMax >= 32)) {
-      if (te == kFour) return rollout_gru_blocks<Scn, kFour, AC>(A, pb, critic, hidden, first, s, partial);
-    }
+  switch (plan.block) {
+#define MPE_GO(eb) return rollout_gru_blocks<Scn, eb, AC>(B, pb, critic, hidden, plan.waves, s, partial)
+    case 16: MPE_GO(16);
+    case 32: if constexpr (kMax >= 32) MPE_GO(32);
+      break;
+    case 64: if constexpr (kMax >= 64) MPE_GO(64);
+      break;
+    default:
+      if constexpr (kOne < 16) {
+        if (plan.block == kOne) MPE_GO(kOne);
+      }
+      if constexpr (kTwo < 16) {
+        if (plan.block == kTwo) MPE_GO(kTwo);
+      }
+      if constexpr (kFour < 16 || (kFour > 16 && kFour < 32 && kMax >= 32)) {
+        if (plan.block == kFour) MPE_GO(kFour);
+      }
+#undef MPE_GO
   }
-  // With one set of weights per run a block must lie inside a run: the largest of 64, 32, 16 that divides
-  // the run size bounds the choice.
-  const uint32_t eb = gru_block_envs(Scn::N, Scn::D, rest);
-  if (eb == 16 || (runs && A.r.E % 32 != 0)) return rollout_gru_blocks<Scn, 16, AC>(A, pb, critic, hidden, first, s, partial);
-  if constexpr (kMax >= 32) {
-    if (eb == 32 || (runs && A.r.E % 64 != 0)) return rollout_gru_blocks<Scn, 32, AC>(A, pb, critic, hidden, first, s, partial);
-  }
-  if constexpr (kMax >= 64) return rollout_gru_blocks<Scn, 64, AC>(A, pb, critic, hidden, first, s, partial);
   return hipErrorInvalidValue;
 }
 
@@ -986,8 +1119,8 @@ hipError_t pack_policy_gru(PolicyBuffers& pb, bool tag, int N, int D, uint32_t T
                            const float* Wo, const float* bo, hipStream_t s) {
   if (D < 1 || D > 64) return hipErrorInvalidValue;
   const uint32_t R = TE / E;
-  // the independent wavefronts' image wherever a rollout of this batch may read it, with or without a critic, which may come later
-  const bool waves = gru_waves_envs(N, D, false, TE, E) || gru_waves_envs(N, D, true, TE, E);
+  // one run: also the independent wavefronts' image, which a rollout long enough for many slots of time reads at any batch size
+  const bool waves = TE == E;
   const int kse = waves ? ((tag ? D : 4 * N + 2) + 31) / 32 : 0;
   if (hipError_t e = ensure_policy_bytes(pb, size_t(R) * GruPk::BYTES + (waves ? GruWavePk::bytes(kse) : 0)); e != hipSuccess) return e;
   const int blocks = pack_blocks(GruPk::THREADS) + (waves ? pack_blocks(GruWavePk::frags(kse) * 512 + GruWavePk::BIAS_FLOATS) : 0);
@@ -996,10 +1129,10 @@ hipError_t pack_policy_gru(PolicyBuffers& pb, bool tag, int N, int D, uint32_t T
   return hipGetLastError();
 }
 
-hipError_t pack_gru_critic(PolicyBuffers& pb, int N, int D, uint32_t TE, uint32_t E, const float* Wc, const float* bc, const float* wv,
+hipError_t pack_gru_critic(PolicyBuffers& pb, uint32_t TE, uint32_t E, const float* Wc, const float* bc, const float* wv,
                            const float* bv, hipStream_t s) {
   const uint32_t R = TE / E;
-  const bool waves = gru_waves_envs(N, D, true, TE, E);
+  const bool waves = TE == E;
   if (hipError_t e = ensure_policy_bytes(pb, size_t(R) * GruCriticPk::BYTES + (waves ? GruWaveCriticPk::BYTES : 0)); e != hipSuccess) return e;
   const int blocks = pack_blocks(GruCriticPk::THREADS) + (waves ? pack_blocks(GruWaveCriticPk::FRAGS * 512 + GruWaveCriticPk::BIAS_FLOATS) : 0);
   hipLaunchKernelGGL(pack_gru_critic_kernel, dim3(blocks, R), dim3(256), 0, s, static_cast<uint8_t*>(pb.packed), Wc, bc, wv, bv);

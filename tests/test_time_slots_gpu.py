@@ -78,3 +78,29 @@ def test_runs_in_wavefronts(agents, runs, envs, ac):
 def test_actor_critic_without_some_outputs(envs, left_out):
     from tests.time_slots import assert_slots_change_nothing, config
     assert_slots_change_nothing(config("spread", 3, envs, 25, 1, 64, 0), 128, "alike", 25, left_out=left_out, **networks("spread", 3, 1, True))
+
+
+# recurrent policy: blocks of every number of row tiles (spare rows too), partly filled; runs; wavefronts whose first rows are the end
+# of a slot and whose last ones the start of the next.  Counters of its own also leave envs that run all steps in slot 0.
+RECURRENT = [("spread", 1, 1, 1), ("spread", 1, 5000, 1), ("spread", 2, 903, 1), ("spread", 3, 3, 1), ("spread", 3, 251, 1), ("spread", 3, 509, 1),
+             ("spread", 3, 1030, 1), ("spread", 3, 1500, 1), ("spread", 3, 3100, 1), ("spread", 3, 6007, 1), ("spread", 3, 16, 12), ("spread", 3, 32, 90),
+             ("spread", 3, 64, 60), ("spread", 4, 2501, 1), ("spread", 6, 333, 1), ("spread", 6, 2222, 1), ("spread", 10, 130, 1),
+             ("spread", 10, 1601, 1), ("tag", 2, 1003, 1), ("tag", 3, 4001, 1), ("tag", 4, 200, 1), ("tag", 4, 16, 33), ("tag", 6, 1999, 1),
+             ("tag", 8, 777, 1), ("tag", 10, 601, 1)]
+
+
+@pytest.mark.parametrize("ac", [False, True], ids=["plain", "actor_critic"])
+@pytest.mark.parametrize("max_ep,T", [(25, 128), (5, 75), (40, 81)])
+@pytest.mark.parametrize("scenario,agents,envs,runs", RECURRENT)
+def test_recurrent_policies(scenario, agents, envs, runs, max_ep, T, ac):
+    import torch
+    from paper_2311_10090_amd import synth
+    from tests.time_slots import assert_slots_change_nothing, config
+    cfg = config(scenario, agents, envs, max_ep, runs, synth.GRU_HIDDEN, 1)
+    D = synth.tag_obs_dim(agents, cfg["num_landmarks"], cfg["num_adversaries"]) if scenario == "tag" else 6 * agents
+    dev = lambda arrs: [torch.from_numpy(a).cuda() for a in arrs]
+    nets = dict(policy=dev(synth.gru_weights(5, runs, D)), critic=dev(synth.gru_critic_weights(5, runs)) if ac else (), gru=True)
+    for kind in ("alike", "own"):
+        assert_slots_change_nothing(cfg, T, kind, max_ep, **nets)
+    if envs == 6007 or envs == 509:
+        assert_slots_change_nothing(cfg, T, "stretches", max_ep, left_out=(0, 4) if not ac else (0, 1, 5, 7), **nets)
