@@ -173,10 +173,11 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
         const uint4 w = philox4x32_10(env, step, uint32_t(i), kTagUniformAction, A.seed, run);
         a[i] = word_to_action(w.x);
       }
-      step += t + 1 == slot.turn ? 1u + uint32_t(slot.jump) : 1u;
+      if (SLOTS && t + 1 == slot.turn) step += uint32_t(slot.jump);
       float r[RW];
       bool d;
-      transition<N, PER_AGENT>(s, a, A.ph, A.seed, run, env, step - 1u, r, d);
+      transition<N, PER_AGENT>(s, a, A.ph, A.seed, run, env, step, r, d);
+      ++step;
       __syncthreads();  // X_t
       uint8_t* cur = buf[t & 1];
 #pragma unroll

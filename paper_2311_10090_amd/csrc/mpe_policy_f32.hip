@@ -688,7 +688,7 @@ TagArgs small_args(const RolloutArgs& A) {
 // In several slots of time (mpe_slots.h), where the rollout is long enough for them: small batches in the small-batch
 // kernel, others in independent wavefronts, which slots keep full at every size.  What stays in one slot are batches that
 // fill the chip in (nearly) whole rounds of this file's 256-env blocks, whose arithmetic shares more, with 3 agents (65,536
-// envs 1,470 us, in slots 1,510; 57,344 envs in slots 1,325) and with 2 agents in the plain rollout, and runs that suit no
+// envs 1,470 us, in slots 1,510; 57,344 envs in slots 1,325; 1,024 runs x 64 envs bf16 1,018, in slots 1,097) and with 2 agents in the plain rollout, and runs that suit no
 // wavefront.  128 steps, us, one slot / several: 1 agent 65,536 envs 590 / 484, critic 1,167 / 890; 2 agents, critic, 49,152 1,785
 // / 1,340; 3 agents, 20,011 envs 622 / 507, critic, 32,768 1,707 / 1,478; 3 agents bf16, critic, 32,768 1,829 / 927; 1,024
 // runs x 16 envs x 3 agents 475 / 412, critic 884 / 760; 1,024 runs x 64, critic 3,543 / 3,000.
@@ -707,7 +707,7 @@ hipError_t launch_slots(const RolloutArgs& A, const PolicyBuffers& pb, const voi
   if constexpr (N == 3 || N == 2) {
     const uint32_t blocks = (A.TE + 255) / 256, rounds = (blocks + cus - 1) / cus;
     const bool full = uint64_t(blocks) * 25 >= uint64_t(rounds) * cus * 24;
-    if (full && (N == 3 || !critic) && (!runs || (critic ? A.E % 256 == 0 : !BF && A.E % 64 == 0))) return hipSuccess;
+    if (full && (N == 3 || !critic) && (!runs || A.E % (critic ? 256 : 64) == 0)) return hipSuccess;
   }
   return launch_waves_spread_slots(N, BF, B, pb.packed, critic, s, taken);
 }

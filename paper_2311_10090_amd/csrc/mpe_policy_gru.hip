@@ -97,24 +97,6 @@ uint32_t gru_waves_envs(int N, int D, bool ac, uint32_t TE, uint32_t E) {
   return some <= none ? TE - rest : TE;
 }
 
-// When the last of `longs` blocks of a steps and then `shorts` of b steps ends, each taken by the compute unit that is free first.
-inline float gru_makespan(uint32_t longs, float a, uint32_t shorts, float b) {
-  const uint32_t cus = compute_units(), busy = longs % cus;
-  uint32_t n[2] = {cus - busy, busy};                       // compute units that are free at free[0], free[1]
-  float free[2] = {float(longs / cus) * a, float(longs / cus + 1) * a}, end = busy ? free[1] : free[0];
-  if (const uint32_t rounds = shorts / cus; rounds > 2) {
-    for (float& f : free) f += float(rounds - 2) * b;
-    shorts -= (rounds - 2) * cus;
-  }
-  while (shorts) {
-    const int k = n[1] && free[1] < free[0] ? 1 : 0;
-    shorts -= shorts < n[k] ? shorts : n[k];
-    free[k] += b;
-    end = fmaxf(end, free[k]);
-  }
-  return end;
-}
-
 // How a batch runs: in one slot of time, or, where that is shorter by the estimate, in as many as the rollout holds (mpe_slots.h): in
 // independent wavefronts or in blocks of any of the sizes.  In several slots the blocks of a batch are many and short: with few
 // envs the smallest blocks for which each slot's still get CUs of their own, and no round of independent wavefronts is mostly
@@ -162,7 +144,7 @@ GruPlan gru_plan(int N, int D, bool ac, const RolloutArgs& A, int32_t max_ep) {
   };
   auto offer_block = [&](uint32_t eb) {
     const uint32_t groups = (A.TE + eb - 1) / eb;
-    if (!runs || A.E % eb == 0) offer(block_step(eb) * gru_makespan(groups, longest + 0.5f, groups * uint32_t(B.slots - 1), span + 0.5f), 0, eb);
+    if (!runs || A.E % eb == 0) offer(block_step(eb) * makespan(cus, groups, longest + 0.5f, groups * uint32_t(B.slots - 1), span + 0.5f), 0, eb);
   };
   if (!runs) {
     for (uint32_t tiles = 1; tiles <= 4; tiles *= 2) {
@@ -170,7 +152,7 @@ GruPlan gru_plan(int N, int D, bool ac, const RolloutArgs& A, int32_t max_ep) {
       if (eb < 16 || (eb > 16 && eb < 32 && kmax >= 32)) offer_block(eb);
     }
     const uint32_t eb = gru_waves_block_envs(N), longs = (A.TE + eb - 1) / eb, blocks = (A.TE * uint32_t(B.slots) + eb - 1) / eb;
-    offer(gru_makespan(longs, longest + 1.0f, blocks - longs, span + 1.0f), A.TE, 0);
+    offer(makespan(cus, longs, longest + 1.0f, blocks - longs, span + 1.0f), A.TE, 0);
   }
   for (uint32_t eb = 16; eb <= kmax; eb *= 2) offer_block(eb);
   return plan;

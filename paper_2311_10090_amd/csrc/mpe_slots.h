@@ -14,6 +14,8 @@
 // puts the tickets back to zero.  No slot waits for another.
 #pragma once
 
+#include <cmath>
+
 #include "mpe_launch.h"
 
 namespace mpe {
@@ -110,6 +112,24 @@ inline void choose_slots(RolloutArgs& A, int32_t max_ep, uint32_t want) {
     A.span = int32_t(span);
     return;
   }
+}
+
+// Host: when the last of `longs` blocks of a steps and then `shorts` of b steps ends, each taken by the place for a block, of
+// `places` on the chip, that is free first.
+inline float makespan(uint32_t places, uint32_t longs, float a, uint32_t shorts, float b) {
+  const uint32_t busy = longs % places, n[2] = {places - busy, busy};       // places that are free at free[0], free[1]
+  float free[2] = {float(longs / places) * a, float(longs / places + 1) * a}, end = busy ? free[1] : free[0];
+  if (const uint32_t rounds = shorts / places; rounds > 2) {
+    for (float& f : free) f += float(rounds - 2) * b;
+    shorts -= (rounds - 2) * places;
+  }
+  while (shorts) {
+    const int k = n[1] && free[1] < free[0] ? 1 : 0;
+    shorts -= shorts < n[k] ? shorts : n[k];
+    free[k] += b;
+    end = fmaxf(end, free[k]);
+  }
+  return end;
 }
 
 inline dim3 spread_grid(uint32_t blocks) { return dim3((blocks + 31) / 32 * 32); }   // see spread_group

@@ -21,7 +21,7 @@
 
 #include "mpe_mlp64.h"
 #include "mpe_scenario.h"
-#include "mpe_slots.h"
+#include "mpe_slot_cost.h"
 
 namespace mpe {
 
@@ -678,73 +678,6 @@ hipError_t launch_small_impl(const TagArgs& A, const void* packed, const void* c
   return launch_groups<M::WAVES * 64>(groups, [&](dim3 grid, const GridPiece& p) { launch(kern, grid, p); });
 }
 
-// Up to how many envs this kernel is the faster one for a batch of whole runs (or of runs whose size suits the kernels
-// for full batches), in tenths of 16-env blocks per CU.  Its time grows with every round of resident blocks, that of the
-// others in steps; the lines are where the two measured curves cross, per shape.  128-step rollouts, us, this kernel
-// against the others, at 16 x 256 x {1, 2, 3, 4, 6, 8, 12} envs (fp32 unless stated):
-//   3 agents         193/418 295/419 411/531 493/537 727/958 953/945 1438/1339     (bf16 148/314 .. 537/675 744/681)
-//   3 agents, critic 274/699 466/706 690/961 907/965 1549/1803 1975/1717 2812/2522
-//   2 agents         176/390 281/388 296/393 322/394 543/527                       (critic 218/689 324/692 487/697 753/696)
-//   1 agent          170/383 188/385 190/383 196/382 404/532 494/533 699/548
-//   6 agents         364/661 674/670 942/1032 1248/1107                            (critic 537/1136 1039/1153 1523/1830 2011/1910)
-//   tag (4,2,1)      221/626 356/644 545/640 852/638                               (critic 324/1109 604/1112 888/1119 1178/1124)
-//   tag (10,3,2)     719/769 1381/1164
-// `past`: where those kernels' first round of blocks (4 wavefronts of whole envs per CU) is just full, a second range.
-struct SmallRange {
-  uint32_t upto, past;
-};
-template <typename Scn, bool AC, bool BF>
-constexpr SmallRange small_range() {
-  constexpr int N = Scn::N;
-  if constexpr (!Scn::kTag) {
-    if constexpr (N == 1) return {80, 0};
-    if constexpr (N == 2) return {AC ? 30 : 40, 0};
-    if constexpr (N == 3) return {AC || BF ? 60 : 80, 0};
-    constexpr SmallRange plain[7] = {{32, 0}, {23, 0}, {20, 30}, {17, 0}, {15, 0}, {12, 0}, {10, 0}};
-    constexpr SmallRange critic[7] = {{35, 0}, {26, 40}, {22, 35}, {20, 32}, {16, 0}, {14, 21}, {12, 0}};
-    return AC ? critic[N - 4] : plain[N - 4];
-  } else {
-    if constexpr (N == 2) return {AC ? 30 : 40, 0};
-    if constexpr (N == 3) return {60, 0};
-    if constexpr (N == 4) return {AC && BF ? 20 : 31, 0};
-    if constexpr (N == 5) return AC && !BF ? SmallRange{24, 40} : SmallRange{22, 0};
-    if constexpr (N == 6) return AC && !BF ? SmallRange{22, 35} : SmallRange{19, 30};
-    if constexpr (N == 8) return {15, 0};
-    return {AC ? 11 : 10, 0};
-  }
-}
-
-// The same for a rollout in several slots of time (mpe_slots.h), whose envs are those of all slots; what it is measured
-// against are the independent wavefronts (mpe_waves.h), of which a block per CU takes the same time whatever it holds.  128
-// steps in five slots, us, this kernel against them, at 5 x {1,000, 2,048, 4,096, 8,192} envs (fp32 unless stated):
-//   1 agent          43/133 44/133 63/135 133/136            critic 58/231 64/230 128/231 219/236     (bf16 31/92 31/93 44/93 83/94)
-//   2 agents         60/129 63/128 91/129 186/188            critic 69/231 102/235 172/234 361/344    (bf16 45/93 48/94 72/94 151/132)
-//   3 agents         65/137 88/138 135/143 239/222           critic 97/259 143/260 228/274 492/405    (bf16 51/96 68/96 100/98 193/142)
-//   4 agents         75/151 114/152 189/215 400/323          critic 128/275 190/276 323/406 641/579
-//   6 agents         134/160 188/178 314/257 607/515         critic 202/286 307/314 523/461 1044/883
-//   10 agents        307/238 452/315 773/631                 critic 366/365 631/533 1253/1025
-//   tag (4,2,1)      75/135 -/- 188/209 402/302              critic 124/247 -/- 322/376 639/542       (bf16 64/100 116/101 175/148 342/211)
-//   tag (8,2,2)      180/164 270/229 458/340                 critic 282/288 423/407 719/619           (bf16 146/111 217/164 368/239)
-template <typename Scn, bool AC, bool BF>
-constexpr SmallRange small_range_slots() {
-  constexpr int N = Scn::N;
-  if constexpr (!Scn::kTag) {
-    constexpr SmallRange plain[10] = {{105, 0}, {100, 0}, {85, 0}, {32, 52}, {22, 0}, {22, 30}, {15, 0}, {10, 0}, {10, 0}, {10, 0}};
-    constexpr SmallRange critic[10] = {{110, 0}, {66, 0}, {75, 0}, {37, 52}, {26, 40}, {26, 38}, {20, 32}, {18, 27}, {11, 0}, {12, 0}};
-    constexpr SmallRange plain_bf[3] = {{115, 0}, {63, 0}, {49, 0}}, critic_bf[3] = {{115, 0}, {61, 0}, {60, 0}};
-    if constexpr (BF) return AC ? critic_bf[N - 1] : plain_bf[N - 1];
-    else return AC ? critic[N - 1] : plain[N - 1];
-  } else {
-    // 2, 3, 4, 5, 6, 8, 10 agents
-    constexpr SmallRange plain[7] = {{85, 0}, {72, 0}, {32, 52}, {22, 0}, {18, 0}, {10, 0}, {10, 0}};
-    constexpr SmallRange critic[7] = {{61, 0}, {66, 0}, {37, 52}, {26, 0}, {24, 0}, {13, 0}, {10, 0}};
-    constexpr SmallRange plain_bf[7] = {{62, 0}, {60, 0}, {21, 0}, {14, 0}, {11, 0}, {9, 0}, {10, 0}};
-    constexpr SmallRange critic_bf[7] = {{58, 0}, {49, 0}, {27, 0}, {23, 0}, {16, 0}, {11, 0}, {10, 0}};
-    constexpr int k = N <= 6 ? N - 2 : (N == 8 ? 5 : 6);
-    return BF ? (AC ? critic_bf[k] : plain_bf[k]) : (AC ? critic[k] : plain[k]);
-  }
-}
-
 template <typename Scn, int EB, bool AC, bool BF>
 hipError_t launch_small_eb(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
   // Stationary operands while a block has a CU to itself (6-10 % faster there); they take 100 to 170 registers per
@@ -771,13 +704,15 @@ hipError_t launch_small(const TagArgs& A, bool unfit, const void* packed, const 
   if (runs && A.r.E % 16 != 0) return hipSuccess;
   const uint32_t cus = compute_units(), blocks16 = (A.r.TE + 15) / 16 * uint32_t(A.r.slots);
   if (!(runs && unfit)) {
-    constexpr SmallRange one = small_range<Scn, AC, BF>(), several = small_range_slots<Scn, AC, BF>();
+    constexpr SmallRange one = small_range<Scn::kTag, N, AC, BF>(), several = small_range_slots<Scn::kTag, N, AC, BF>();
     const SmallRange range = A.r.slots > 1 ? several : one;
     const bool first_round_full = A.r.work() > kWavesBlock * cus;
     // One agent's blocks are two or three wavefronts around 33 KB of weights per network: in a rollout of one step the
     // staging of a full range of them is what counts (32,768 envs 11.4 us, 64-env blocks 8.3; actor-critic 22.1 against 17.3).
     const uint32_t upto = N == 1 && A.r.T == 1 ? 70 : range.upto;
     if (blocks16 * 10 > cus * (first_round_full && range.past ? range.past : upto)) return hipSuccess;
+    constexpr BatchKind kind{N, Scn::kTag, BF, AC};
+    if (A.r.slots > 1 && !slots_pay(A.r, small_time(kind, A.r), one_slot_time(kind, A.r, one.upto))) return hipSuccess;
   }
   *taken = true;
   if constexpr (kEight) {

@@ -20,7 +20,7 @@
 
 #include "mpe_mlp64.h"
 #include "mpe_scenario.h"
-#include "mpe_slots.h"
+#include "mpe_slot_cost.h"
 
 namespace mpe {
 
@@ -561,6 +561,12 @@ WavesPlan waves_plan(const RolloutArgs& A) {
   if constexpr (!Scn::kTag && Scn::N == 3 && !BF) {
     if (A.slots == 1) return {8, waves_cost<Scn, 8, AC, BF>(A)};
   }
+  // slots of unequal length, which the estimate of whole rounds does not see
+  if (A.slots > 1 && !equal_slots(A)) {
+    const float t4 = waves_time(Scn::N, 4, WavesBlocks<Scn, 4, AC, BF>::kResident, A), t8 = waves_time(Scn::N, 8, 1, A), t12 = waves_time(Scn::N, 12, 1, A);
+    if ((BF ? t4 <= t8 : t4 < t8) && t4 <= t12) return {4, t4};
+    return t8 <= t12 ? WavesPlan{8, t8} : WavesPlan{12, t12};
+  }
   const float c4 = waves_cost<Scn, 4, AC, BF>(A), c8 = waves_cost<Scn, 8, AC, BF>(A), c12 = waves_cost<Scn, 12, AC, BF>(A);
   const uint32_t cus = compute_units(), last8 = WavesBlocks<Scn, 8, AC, BF>::count(A) % cus;
   const bool four = BF || (A.slots > 1 && last8 && last8 * 10 < cus * 9);
@@ -578,17 +584,22 @@ hipError_t launch_waves(const TagArgs& A, const void* packed, const void* critic
 }
 
 // In the slots of A, where that pays: *taken.  With several runs, where a run's wavefronts and blocks are mostly full.
-// `against`: that without slots this kernel would run, which has the same time for the same wavefronts per CU: by the
-// estimate then (8 agents, critic, 20,011 envs 3,628 us in one slot, 3,737 in five; 6 agents, 20,011 envs 1,218 and 1,176).
+// `against`: that without slots this kernel would run, if not the small-batch kernel; slots of equal length are then compared in whole
+// rounds (8 agents, critic, 20,011 envs 3,628 us in one slot, 3,737 in five; 6 agents, 20,011 envs 1,218 and 1,176), all else by mpe_slot_cost.h.
 template <typename Scn, bool AC, bool BF>
 hipError_t launch_waves_slots(const TagArgs& A, bool against, const void* packed, const void* critic, hipStream_t s, bool* taken) {
-  constexpr uint32_t EW = 64 / Scn::N;
+  constexpr uint32_t EW = 64 / Scn::N, kUpto = small_range<Scn::kTag, Scn::N, AC, BF>().upto;
+  constexpr BatchKind kind{Scn::N, Scn::kTag, BF, AC};
   const uint32_t envs = A.r.E * uint32_t(A.r.slots), waves = (envs + EW - 1) / EW;
   if (A.r.TE != A.r.E && (envs * 4 < waves * EW * 3 || waves * 4 < (waves + 3) / 4 * 4 * 3)) return hipSuccess;
-  if (against) {
-    RolloutArgs one = A.r;
-    one.slots = 1;
-    if (waves_plan<Scn, AC, BF>(A.r).cost > 0.98f * waves_plan<Scn, AC, BF>(one).cost) return hipSuccess;
+  const WavesPlan plan = waves_plan<Scn, AC, BF>(A.r);
+  RolloutArgs one = A.r;
+  one.slots = 1;
+  if (against && equal_slots(A.r) && !small_in_one_slot(kind, one, kUpto)) {
+    if (plan.cost > 0.98f * waves_plan<Scn, AC, BF>(one).cost) return hipSuccess;
+  } else {
+    const float several = waves_time(Scn::N, plan.W, plan.W == 4 ? WavesBlocks<Scn, 4, AC, BF>::kResident : 1, A.r);
+    if (!slots_pay(A.r, several, one_slot_time(kind, one, kUpto))) return hipSuccess;
   }
   *taken = true;
   return launch_waves<Scn, AC, BF>(A, packed, critic, s);

@@ -9,8 +9,8 @@ def recorder(tmp_path_factory):
     return build_recorder(tmp_path_factory.mktemp("recorder"))
 
 
-def blocks(recorder, shape, T):
-    out = record(recorder, ["create " + shape, "reset", "rollout %d" % T])
+def blocks(recorder, shape, T, call="rollout", policy=()):
+    out = record(recorder, ["create " + shape, *policy, "reset", "%s %d" % (call, T)])
     (name, grid), = launches(out[-1][1])
     return name.split("<")[0], grid
 
@@ -32,3 +32,21 @@ def padded(n):
 ])
 def test_environment_only(recorder, shape, T, kernel, groups, slots):
     assert blocks(recorder, shape, T) == (kernel, padded(groups * slots))
+
+
+def spread(n):
+    return (n + 31) // 32 * 32
+
+
+@pytest.mark.parametrize("shape,T,call,kernel,grid", [
+    ("0 3 3 0 64 1", 128, "rollout", "rollout_gru_kernel", padded(13 * 5)),               # 5-env blocks, one slot each
+    ("0 3 3 0 64 1", 49, "rollout", "rollout_gru_kernel", padded(13)),                    # no two episodes
+    ("0 3 3 0 1000 1", 128, "rollout_ac", "rollout_gru_kernel", padded(48 * 5)),          # 21 envs
+    ("0 3 3 0 16 12", 128, "rollout", "rollout_gru_kernel", padded(12 * 5)),              # runs: blocks inside one
+    ("0 3 3 0 4096 1", 128, "rollout", "rollout_gru_waves_kernel", spread(256)),          # wavefronts with lanes of several slots
+    ("0 3 3 0 12000 1", 128, "rollout_ac", "rollout_gru_waves_kernel", spread(750)),
+    ("0 10 10 0 3000 1", 64, "rollout", "rollout_gru_waves_kernel", spread(250)),
+    ("0 3 3 0 20480 1", 128, "rollout_ac", "rollout_gru_waves_kernel", 256),              # a whole round in one slot
+])
+def test_recurrent_policies(recorder, shape, T, call, kernel, grid):
+    assert blocks(recorder, shape, T, call, ("gru", "critic")) == (kernel, grid)
