@@ -1,10 +1,10 @@
 // Host: whether a feed-forward rollout is faster in the slots of time that it holds (mpe_slots.h) than in one.  The unit of time is a
 // step of the independent wavefronts (mpe_waves.h) with every SIMD at its full rate: 4, 8 and 12 wavefronts of a CU take 0.36, 0.56 and
 // 0.81 of it (all shapes within 5 %).  The small-batch kernel's step is a table by 16-env blocks per CU, the kernels of up to 3 agents
-// for full batches take 0.085 for every wavefront of 64 rows that their 64-env blocks put on a CU.  Of 4,542 measured batches (1 to 10 agents and
-// every predator-prey shape, 64 to 65,536 envs, 16 to 1,024 runs, both types, with and without critic, 50 to 128 steps) the choice by this estimate leaves 35 that are 3
-// to 13 % slower than in one slot, almost all of them where a round of blocks is just full; slots everywhere left 397, up to half as fast, above
-// all where two or three slots of unequal length meet a chip that one slot fills.
+// for full batches take 0.085 for every wavefront of 64 rows that their 64-env blocks put on a CU.  Measured on 4,542 batches (1 to 10
+// agents and every predator-prey shape, 64 to 65,536 envs, 16 to 1,024 runs, both types, with and without critic, 50 to 128 steps), slots where
+// this says so against one slot everywhere: 1.36 times as fast in the mean, 30 batches 2.5 to 9 % slower.  Slots wherever the size of
+// the batch allows them: 397 slower, up to twice, above all where two or three slots of unequal length meet a chip that one slot fills.
 #pragma once
 
 #include "mpe_slots.h"
@@ -83,7 +83,7 @@ struct BatchKind {
   bool tag, bf, ac;
 };
 
-// A step of the small-batch kernel with `slots` slots in flight.
+// A step of the small-batch kernel with `slots` of A's slots in flight.
 inline float small_step(const BatchKind& k, const RolloutArgs& A, uint32_t slots) {
   struct Line { float at[4], more; };                  // 1, 2, 3, 4 blocks per CU, each one more
   static constexpr Line few[7] = {{{0.09f, 0.10f, 0.10f, 0.10f}, 0.055f}, {{0.12f, 0.195f, 0.195f, 0.21f}, 0.075f}, {{0.12f, 0.20f, 0.27f, 0.31f}, 0.095f},
@@ -98,11 +98,11 @@ inline float small_step(const BatchKind& k, const RolloutArgs& A, uint32_t slots
     return per_cu <= 4 ? l.at[per_cu - 1] : l.at[3] + l.more * float(per_cu - 4);
   }
   if (k.N == 6 || k.N == 8 || k.N == 10) {             // 8-env blocks while each has a CU
-    const uint32_t eight = (A.TE + 7) / 8 * slots;
+    const uint32_t eight = (A.TE + 7) / 8 * uint32_t(A.slots);
     static constexpr float alone[3][2] = {{0.11f, 0.09f}, {0.14f, 0.11f}, {0.18f, 0.13f}};
     const float one = alone[(k.N - 6) / 2][k.ac];
     if (eight <= cus) return one;
-    if (k.N == 10 && k.ac) return one * float((eight + cus - 1) / cus);
+    if (k.N == 10 && k.ac) return one * float(((A.TE + 7) / 8 * slots + cus - 1) / cus);
   }
   const float* l = (k.ac ? critic : plain)[k.N - 4];
   return l[0] + l[1] * float(per_cu - 1);

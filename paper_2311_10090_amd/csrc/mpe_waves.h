@@ -584,8 +584,9 @@ hipError_t launch_waves(const TagArgs& A, const void* packed, const void* critic
 }
 
 // In the slots of A, where that pays: *taken.  With several runs, where a run's wavefronts and blocks are mostly full.
-// `against`: that without slots this kernel would run, if not the small-batch kernel; slots of equal length are then compared in whole
-// rounds (8 agents, critic, 20,011 envs 3,628 us in one slot, 3,737 in five; 6 agents, 20,011 envs 1,218 and 1,176), all else by mpe_slot_cost.h.
+// `against`: that without slots this kernel would run, if not the small-batch kernel.  The same kernel either way: slots of equal length are compared in
+// whole rounds (8 agents, critic, 20,011 envs 3,628 us in one slot, 3,737 in five; 6 agents, 20,011 envs 1,218 and 1,176), unequal ones taken from
+// an estimated gain of 3 % on (10,000 envs x 5 agents x 74 steps 402 / 330 us); another kernel: from one of 5 and 10 % on.
 template <typename Scn, bool AC, bool BF>
 hipError_t launch_waves_slots(const TagArgs& A, bool against, const void* packed, const void* critic, hipStream_t s, bool* taken) {
   constexpr uint32_t EW = 64 / Scn::N, kUpto = small_range<Scn::kTag, Scn::N, AC, BF>().upto;
@@ -595,11 +596,13 @@ hipError_t launch_waves_slots(const TagArgs& A, bool against, const void* packed
   const WavesPlan plan = waves_plan<Scn, AC, BF>(A.r);
   RolloutArgs one = A.r;
   one.slots = 1;
-  if (against && equal_slots(A.r) && !small_in_one_slot(kind, one, kUpto)) {
+  const bool same = against && !small_in_one_slot(kind, one, kUpto);
+  if (same && equal_slots(A.r)) {
     if (plan.cost > 0.98f * waves_plan<Scn, AC, BF>(one).cost) return hipSuccess;
   } else {
     const float several = waves_time(Scn::N, plan.W, plan.W == 4 ? WavesBlocks<Scn, 4, AC, BF>::kResident : 1, A.r);
-    if (!slots_pay(A.r, several, one_slot_time(kind, one, kUpto))) return hipSuccess;
+    const float single = one_slot_time(kind, one, kUpto);
+    if (same ? several > 0.97f * single : !slots_pay(A.r, several, single)) return hipSuccess;
   }
   *taken = true;
   return launch_waves<Scn, AC, BF>(A, packed, critic, s);
