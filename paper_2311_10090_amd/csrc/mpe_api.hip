@@ -556,8 +556,8 @@ int mpe_set_state(mpe_env* e, const float* pos_a, const float* vel_a, const floa
   const size_t nl = landmark_floats(e) * sizeof(float);
   if (nl) MPE_HIP(hipMemcpyAsync(e->st.pos_l, pos_l, nl, hipMemcpyDeviceToDevice, s));
   MPE_HIP(hipMemcpyAsync(e->st.ep_step, ep_step, size_t(e->TE) * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-  // a rollout leaves the tickets at zero, as mpe_reset does
-  if (!e->ready) MPE_HIP(launch_fill_zero(reinterpret_cast<float*>(e->st.tickets), e->TE, s));
+  // Rollouts and mpe_reset leave the tickets at zero, but a reset that a capture has recorded does so only once its graph runs.
+  MPE_HIP(launch_fill_zero(reinterpret_cast<float*>(e->st.tickets), e->TE, s));
   e->seed = seed;
   e->abs_step = abs_step;
   e->ready = true;

@@ -50,3 +50,10 @@ def spread(n):
 ])
 def test_recurrent_policies(recorder, shape, T, call, kernel, grid):
     assert blocks(recorder, shape, T, call, ("gru", "critic")) == (kernel, grid)
+
+
+def test_set_state_clears_the_tickets(recorder):
+    """With and without a reset before: one that a capture has recorded has not run."""
+    for first in ([], ["reset"]):
+        out = record(recorder, ["create 0 3 3 0 1000 1", *first, "set_state"])
+        assert [name for name, _ in launches(out[-1][1])] == ["fill_zero_kernel"]
