@@ -150,12 +150,12 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
       }
     }
   };
-  if (in_range) {
+  if (in_range) ep = A.st.ep_step[g];
+  if (in_range && head) {      // the other slots of the env draw theirs; slot 0 may be writing these
     px = A.st.pos_a[(0 * N + i) * TE + g];
     py = A.st.pos_a[(1 * N + i) * TE + g];
     vx = A.st.vel_a[(0 * N + i) * TE + g];
     vy = A.st.vel_a[(1 * N + i) * TE + g];
-    ep = A.st.ep_step[g];
   }
   // Several slots: number of steps of this lane's env, or, until the jump of slot 0, minus the steps before it
   [[maybe_unused]] int32_t event = 0, ep0 = ep, t0 = 0;
@@ -175,7 +175,7 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
   for (int k = 0; k < (L + N - 1) / N; ++k) {
     const int l = i + k * N;
     if (l < L && active)
-      sm.lm[el * (L + 1) + l] = in_range ? make_float2(A.st.pos_l[(0 * L + l) * TE + g], A.st.pos_l[(1 * L + l) * TE + g]) : make_float2(0.0f, 0.0f);
+      sm.lm[el * (L + 1) + l] = in_range && head ? make_float2(A.st.pos_l[(0 * L + l) * TE + g], A.st.pos_l[(1 * L + l) * TE + g]) : make_float2(0.0f, 0.0f);
   }
   auto put = [&](int parity) {
     if (active) {

@@ -144,12 +144,12 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
       }
     }
   };
-  if (in_range) {
+  if (in_range) ep = A.st.ep_step[g];
+  if (in_range && head) {      // the other slots of the env draw theirs; slot 0 may be writing these
     px = A.st.pos_a[(0 * N + i) * TE + g];
     py = A.st.pos_a[(1 * N + i) * TE + g];
     vx = A.st.vel_a[(0 * N + i) * TE + g];
     vy = A.st.vel_a[(1 * N + i) * TE + g];
-    ep = A.st.ep_step[g];
   }
   [[maybe_unused]] int32_t ep0 = ep;
   [[maybe_unused]] TimeSlot slot = {0, A.T, 0, 0};
@@ -168,7 +168,7 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
   for (int k = 0; k < (L + N - 1) / N; ++k) {         // landmarks i, i + N, ...
     const int l = i + k * N;
     if (l < L && active)
-      sm.lm[el * (L + 1) + l] = in_range ? make_float2(A.st.pos_l[(0 * L + l) * TE + g], A.st.pos_l[(1 * L + l) * TE + g]) : make_float2(0.0f, 0.0f);
+      sm.lm[el * (L + 1) + l] = in_range && head ? make_float2(A.st.pos_l[(0 * L + l) * TE + g], A.st.pos_l[(1 * L + l) * TE + g]) : make_float2(0.0f, 0.0f);
   }
   // what the lanes of an env read of each other, by step parity
   auto put = [&](int parity) {
