@@ -89,7 +89,7 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
   const size_t TE = A.TE;
   uint32_t blk;
   if constexpr (SLOTS) {
-    blk = spread_group();
+    blk = spread_group(blockIdx.x);
     if (blk >= piece.groups) return;
   } else {
     blk = xcd_group(piece);
@@ -162,7 +162,7 @@ __global__ __launch_bounds__(512, 2) void rollout_gru_waves_kernel(TagArgs TA, c
   int len = A.T;                                         // of the wavefront
   if constexpr (SLOTS) {
     counter_read(ep0);
-    const TimeSlot slot = time_slot(A, int(k_slot), ep0, max_ep, true);
+    const TimeSlot slot = time_slot(A.T, A.slots, A.span, int(k_slot), ep0, max_ep, true);
     t0 = slot.t0;
     step += uint32_t(t0);
     event = in_range ? (slot.turn ? -slot.turn : slot.len) : 0;

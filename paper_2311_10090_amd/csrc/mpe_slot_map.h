@@ -1,0 +1,46 @@
+// Which blocks and which steps the slots of time of a rollout take (mpe_slots.h).  Whole-number arithmetic, the same for host and device.
+#pragma once
+
+#include <cstdint>
+
+namespace mpe {
+
+// Blocks of one slot each.  One slot's groups come after the other's, slot 0, the longest, first.  Every XCD has an eighth of
+// each slot's groups, in one piece (see xcd_group), the next eighth in the next slot: the XCDs' totals then differ by one, and
+// 245 blocks that want a CU each are at most 31 on the 32 CUs of an XCD (in whole pieces 35 or none; with left-over
+// blocks between them CUs stay idle beside others with two: 8,192 envs x 3 agents 353 against 215 us).
+struct SlotGroup {
+  uint32_t slot, group;    // slot not below the number of slots: a block that is left over
+};
+constexpr SlotGroup slot_group(uint32_t block, uint32_t groups) {
+  // Piece m of an endless row of eighths starts at m groups / 8, rounded down; XCD x has the pieces from x on, one a slot.
+  const uint32_t x = block & 7u, at = (block >> 3) + x * groups / 8u, piece = (8u * at + 7u) / groups;
+  return {piece - x, at - piece / 8u * groups};
+}
+
+// Blocks that have lanes of several slots: an XCD has every eighth piece of four neighbouring ones.
+constexpr uint32_t spread_group(uint32_t block) {
+  const uint32_t at = block >> 3;
+  return (at >> 2) * 32u + (block & 7u) * 4u + (at & 3u);
+}
+
+struct TimeSlot {
+  int32_t t0, len;     // first step, number of steps
+  int32_t turn, jump;  // after `turn` steps time goes on `jump` steps later (turn 0: never)
+};
+// Slot k of `slots` of `span` steps, T >= slots * span.  ep: the env's episode counter; alike: whether it is that of every env that shares
+// the slot (else slot 0 runs all steps).
+constexpr TimeSlot time_slot(int32_t T, int32_t slots, int32_t span, int32_t k, int32_t ep, int32_t max_ep, bool alike) {
+  if (!alike || ep < 0) return {0, k == 0 ? T : 0, 0, 0};
+  const int32_t first = max_ep - ep > 1 ? max_ep - ep : 1, jump = (slots - 1) * span;
+  if (k == 0) return {0, T - jump, first, jump};
+  return {first + (k - 1) * span, span, 0, 0};
+}
+
+// The episode counter T steps later
+constexpr int32_t counter_after(int32_t T, int32_t ep, int32_t max_ep) {
+  const int64_t left = int64_t(max_ep) - ep, first = left > 1 ? left : 1;
+  return T < first ? ep + T : int32_t((T - first) % max_ep);
+}
+
+}  // namespace mpe

@@ -17,15 +17,11 @@
 #include <cmath>
 
 #include "mpe_launch.h"
+#include "mpe_slot_map.h"
 
 namespace mpe {
 
 namespace {
-
-struct TimeSlot {
-  int32_t t0, len;     // first step, number of steps
-  int32_t turn, jump;  // after `turn` steps time goes on `jump` steps later (turn 0: never)
-};
 
 // The groups of one slot in a launch of several.  A kernel instance takes this in the place of its other grids and is then
 // one for slots: without them it has the code that it would have anyway (in one instance for both the step loops take up
@@ -36,11 +32,7 @@ struct SlotGrid {
 template <typename Piece> constexpr bool kSlots = false;
 template <> constexpr bool kSlots<SlotGrid> = true;
 
-// The slot and the group of this block; false: a block that is left over.  One slot's groups come after the other's, slot 0,
-// the longest, first.  Every XCD has an eighth of each slot's groups, in one piece (see xcd_group), the next eighth in the
-// next slot: the XCDs' totals then differ by one, and 245 blocks that want a CU each are at most 31 on the 32 CUs of an XCD (in
-// whole pieces 35 or none; with left-over blocks between them CUs stay idle beside others with two: 8,192 envs x 3 agents
-// 353 against 215 us).
+// The slot and the group of this block; false: a block that is left over.
 template <typename Piece>
 __device__ __forceinline__ bool take_slot(const RolloutArgs& A, const Piece& p, int& k, uint32_t& grp) {
   k = 0;
@@ -48,29 +40,11 @@ __device__ __forceinline__ bool take_slot(const RolloutArgs& A, const Piece& p, 
     grp = xcd_group(p);
     return grp < p.end;
   } else {
-    uint32_t at = blockIdx.x >> 3;
-    for (; k < A.slots; ++k) {
-      const uint32_t c = (blockIdx.x + uint32_t(k)) & 7u, first = c * p.groups / 8u, n = (c + 1u) * p.groups / 8u - first;
-      grp = first + at;
-      if (at < n) return true;
-      at -= n;
-    }
-    return false;
+    const SlotGroup s = slot_group(blockIdx.x, p.groups);
+    k = int(s.slot);
+    grp = s.group;
+    return s.slot < uint32_t(A.slots);
   }
-}
-
-// Blocks that have lanes of several slots: an XCD has every eighth piece of four neighbouring ones.
-__device__ __forceinline__ uint32_t spread_group() {
-  const uint32_t at = blockIdx.x >> 3;
-  return (at >> 2) * 32u + (blockIdx.x & 7u) * 4u + (at & 3u);
-}
-
-// ep: the env's episode counter; alike: whether it is that of every env that shares the slot (else slot 0 runs all steps)
-__device__ __forceinline__ TimeSlot time_slot(const RolloutArgs& A, int k, int32_t ep, int32_t max_ep, bool alike) {
-  if (!alike || ep < 0) return {0, k == 0 ? A.T : 0, 0, 0};
-  const int32_t first = max(max_ep - ep, 1), jump = (A.slots - 1) * A.span;
-  if (k == 0) return {0, A.T - jump, first, jump};
-  return {first + (k - 1) * A.span, A.span, 0, 0};
 }
 
 // The slot of a wavefront whose envs are [g0, g0 + n), n <= 64.
@@ -78,7 +52,7 @@ template <bool SLOTS>
 __device__ __forceinline__ TimeSlot group_slot(const RolloutArgs& A, int k, int32_t max_ep, size_t g0, int n, int lane) {
   if constexpr (!SLOTS) return {0, A.T, 0, 0};
   const int32_t ep = A.st.ep_step[g0 + min(lane, n - 1)], ep0 = __builtin_amdgcn_readfirstlane(ep);
-  TimeSlot s = time_slot(A, k, ep0, max_ep, __ballot(ep != ep0) == 0ull);
+  TimeSlot s = time_slot(A.T, A.slots, A.span, k, ep0, max_ep, __ballot(ep != ep0) == 0ull);
   asm volatile("" : "+s"(s.len));   // the counters have been read when the wavefront comes to its next barrier
   return s;
 }
@@ -92,8 +66,7 @@ __device__ __forceinline__ uint32_t take_ticket(const RolloutArgs& A, size_t g) 
 }
 __device__ __forceinline__ void settle_ticket(const RolloutArgs& A, int32_t max_ep, size_t g, uint32_t ticket, int32_t ep) {
   if (ticket != uint32_t(A.slots) - 1u) return;
-  const int64_t first = max(int64_t(max_ep) - ep, int64_t(1));
-  A.st.ep_step[g] = A.T < first ? ep + A.T : int32_t((A.T - first) % max_ep);
+  A.st.ep_step[g] = counter_after(A.T, ep, max_ep);
   A.st.tickets[g] = 0u;
 }
 

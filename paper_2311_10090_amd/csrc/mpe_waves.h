@@ -81,7 +81,7 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
   const size_t TE = A.TE;
   uint32_t blk;
   if constexpr (SLOTS) {
-    blk = spread_group();
+    blk = spread_group(blockIdx.x);
     if (blk >= piece.groups) return;
   } else {
     blk = xcd_group(piece);
@@ -156,7 +156,7 @@ __global__ __launch_bounds__(W * 64, MINW) void rollout_waves_kernel(TagArgs TA,
   int len = A.T;                                      // of the wavefront
   if constexpr (SLOTS) {
     counter_read(ep0);
-    slot = time_slot(A, int(k_slot), ep0, max_ep, true);
+    slot = time_slot(A.T, A.slots, A.span, int(k_slot), ep0, max_ep, true);
     if (!in_range) slot.len = 0;
     step += uint32_t(slot.t0);
     len = slot.len;

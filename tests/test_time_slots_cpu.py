@@ -1,7 +1,25 @@
-"""Which rollouts run in slots of time (mpe_slots.h), from recorded launches: the blocks of all slots, eight XCDs at a time."""
+"""Which rollouts run in slots of time (mpe_slots.h), from recorded launches: the blocks of all slots, eight XCDs at a time; and what the
+blocks and the slots cover (mpe_slot_map.h), by counting."""
+import os
+import subprocess
+
 import pytest
 
-from tests.launch_record import build_recorder, launches, record
+from tests.launch_record import ROOT, build_recorder, launches, record
+
+
+def test_blocks_and_slots_cover_everything_once(tmp_path):
+    exe = str(tmp_path / "slot_map")
+    subprocess.check_call(["g++", "-std=c++17", "-O2", "-Wall", "-Werror", "-o", exe, os.path.join(ROOT, "tests", "slot_map.cpp")])
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0 and r.stdout == "slots ok\n", r.stdout
+
+
+def test_a_block_finds_its_slot_without_a_walk():
+    """A rollout may have 671,088 slots of 25 steps: what a block does before its first step does not grow with them."""
+    text = open(os.path.join(ROOT, "paper_2311_10090_amd", "csrc", "mpe_slots.h")).read()
+    body = text[text.index("bool take_slot("):]
+    assert "for (" not in body[:body.index("\n}\n")]
 
 
 @pytest.fixture(scope="module")
