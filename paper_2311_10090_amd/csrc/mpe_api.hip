@@ -10,6 +10,7 @@
 #include <new>
 
 #include "mpe_launch.h"
+#include "mpe_slot_map.h"
 
 using namespace mpe;
 
@@ -39,6 +40,12 @@ struct mpe_env {
   uint32_t* fault_host = nullptr;
   uint32_t* fault_dev = nullptr;
   uint32_t barrier_polls = 1u << 24;   // see mpe_set_barrier_poll_limit
+  // Behind it, where the envs' episode counters differ (counter_unit), as mpe_set_state's kernel has found them; read like the
+  // fault word.  Until that kernel has run they hold what the call before it left, and a rollout that is enqueued meanwhile goes by
+  // that: which kernel runs depends on it, its results do not.  mpe_reset makes all counters alike, and no call makes them unlike again.
+  uint32_t* units_host = nullptr;
+  uint32_t* units_dev = nullptr;
+  bool counters_given = false;         // by mpe_set_state, since the last mpe_reset
 };
 
 namespace {
@@ -166,6 +173,14 @@ int check_fault(const mpe_env* e, const char* who) {
   return MPE_OK;
 }
 
+// The unit of the counters' stretches, for RolloutArgs::alike
+uint32_t counters_alike(const mpe_env* e) {
+  uint32_t unit = 0;
+  if (e->counters_given)
+    for (uint32_t b = 0; b < counter_blocks(e->TE); ++b) unit = common_unit(unit, static_cast<volatile const uint32_t*>(e->units_host)[b]);
+  return unit;
+}
+
 RolloutArgs rollout_args(const mpe_env* e, int32_t T, float* obs_traj, uint8_t* act_traj, float* rew_traj,
                          uint8_t* done_traj, float* last_obs) {
   RolloutArgs A;
@@ -183,6 +198,7 @@ RolloutArgs rollout_args(const mpe_env* e, int32_t T, float* obs_traj, uint8_t* 
   A.last_obs = last_obs;
   A.fault = e->fault_dev;
   A.barrier_polls = e->barrier_polls;
+  A.alike = counters_alike(e);
   return A;
 }
 
@@ -223,10 +239,13 @@ int mpe_create(const mpe_config* cfg, mpe_env** out) {
   // the episode counters, and behind them the tickets
   if (err == hipSuccess) err = hipMalloc(&e->st.ep_step, size_t(e->TE) * 2 * sizeof(int32_t));
   if (err == hipSuccess) e->st.tickets = reinterpret_cast<uint32_t*>(e->st.ep_step + e->TE);
-  if (err == hipSuccess) err = hipHostMalloc(reinterpret_cast<void**>(&e->fault_host), sizeof(uint32_t), hipHostMallocMapped);
+  constexpr size_t kWords = 1 + kCounterBlocks;
+  if (err == hipSuccess) err = hipHostMalloc(reinterpret_cast<void**>(&e->fault_host), kWords * sizeof(uint32_t), hipHostMallocMapped);
   if (err == hipSuccess) {
-    *e->fault_host = 0u;
+    std::memset(e->fault_host, 0, kWords * sizeof(uint32_t));
     err = hipHostGetDevicePointer(reinterpret_cast<void**>(&e->fault_dev), e->fault_host, 0);
+    e->units_host = e->fault_host + 1;
+    e->units_dev = e->fault_dev + 1;
   }
   if (err != hipSuccess) {
     int rc = fail(MPE_EHIP, "mpe_create: allocation failed: %s", hipGetErrorString(err));
@@ -271,6 +290,7 @@ int mpe_reset(mpe_env* e, uint32_t seed, float* obs, void* stream) {
   e->seed = seed;
   e->abs_step = 0;
   e->ready = true;
+  e->counters_given = false;
   return MPE_OK;
 }
 
@@ -557,7 +577,8 @@ int mpe_set_state(mpe_env* e, const float* pos_a, const float* vel_a, const floa
   if (nl) MPE_HIP(hipMemcpyAsync(e->st.pos_l, pos_l, nl, hipMemcpyDeviceToDevice, s));
   MPE_HIP(hipMemcpyAsync(e->st.ep_step, ep_step, size_t(e->TE) * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
   // Rollouts and mpe_reset leave the tickets at zero, but a reset that a capture has recorded does so only once its graph runs.
-  MPE_HIP(launch_fill_zero(reinterpret_cast<float*>(e->st.tickets), e->TE, s));
+  MPE_HIP(launch_read_counters(e->st, e->TE, e->units_dev, s));
+  e->counters_given = true;
   e->seed = seed;
   e->abs_step = abs_step;
   e->ready = true;

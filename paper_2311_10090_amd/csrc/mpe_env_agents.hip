@@ -19,7 +19,7 @@ namespace {
 
 // Envs per wavefront: the largest even number whose agents fit 64 lanes.
 template <typename Scn>
-constexpr int wave_envs() { return 64 / Scn::N / 2 * 2; }
+constexpr int wave_envs() { return int(env_agents_block(Scn::N)); }
 
 // What an agent passes to the others of its env: its new position, in predator-prey also its velocity.
 template <bool TAG> struct Slot { float x, y; };

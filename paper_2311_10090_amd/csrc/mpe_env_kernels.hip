@@ -46,6 +46,24 @@ __global__ __launch_bounds__(kWave) void reset_kernel(StatePtrs st, uint32_t TE,
   if (obs) emit_obs<N>(s, tile, obs + L.g0 * (N * 6 * N), L.nvalid, L.lane);
 }
 
+__global__ __launch_bounds__(256) void read_counters_kernel(StatePtrs st, uint32_t TE, uint32_t* __restrict__ unit) {
+  __shared__ uint32_t units[256];
+  const uint32_t each = (TE + gridDim.x - 1) / gridDim.x, first = blockIdx.x * each, end = min(first + each, TE);   // each * gridDim.x < 2^32
+  uint32_t q = 0;
+  for (uint32_t g = first + threadIdx.x; g < end; g += 256) {
+    const int32_t ep = st.ep_step[g];
+    q = counter_unit(q, g, st.ep_step[g ? g - 1 : 0], ep);
+    st.tickets[g] = 0u;
+  }
+  units[threadIdx.x] = q;
+  __syncthreads();
+  for (int n = 128; n; n >>= 1) {
+    if (int(threadIdx.x) < n) units[threadIdx.x] = common_unit(units[threadIdx.x], units[threadIdx.x + n]);
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) unit[blockIdx.x] = units[0];
+}
+
 template <int N>
 __global__ __launch_bounds__(kWave) void step_kernel(StatePtrs st, Phys ph, uint32_t TE, uint32_t E,
                                                      uint32_t seed, uint32_t abs_step,
@@ -399,6 +417,11 @@ hipError_t launch_reset(int N, const StatePtrs& st, uint32_t TE, uint32_t E, uin
   MPE_DISPATCH_N(N, EnvLaunch<kN>::reset(st, TE, E, seed, obs, s));
 }
 
+hipError_t launch_read_counters(const StatePtrs& st, uint32_t TE, uint32_t* unit, hipStream_t s) {
+  hipLaunchKernelGGL(read_counters_kernel, dim3(counter_blocks(TE)), dim3(256), 0, s, st, TE, unit);
+  return hipGetLastError();
+}
+
 hipError_t launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, uint32_t E, uint32_t seed,
                        uint32_t abs_step, const uint8_t* actions, float* obs, float* reward, uint8_t* done,
                        hipStream_t s) {
@@ -423,7 +446,9 @@ hipError_t launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, 
 hipError_t launch_rollout_uniform(int N, const RolloutArgs& A, hipStream_t s) {
   RolloutArgs B = A;
   choose_slots(B, A.ph.max_ep, env_slots(false, N, 6 * N, A.TE));
-  if (env_agents_faster(false, N, B.work()) || (N > 3 && B.slots > 1)) {
+  auto by_agents = [&]() { return env_agents_faster(false, N, B.work()) || (N > 3 && B.slots > 1); };
+  if (!slots_fit(B, by_agents() ? env_agents_block(N) : kWave)) B.slots = 1;
+  if (by_agents()) {
     TagArgs TA{};
     TA.r = B;
     return launch_env_agents(false, N, N, 0, TA, s);

@@ -79,6 +79,8 @@ struct RolloutArgs {
   uint32_t* fault = nullptr;
   // Polls after which a wait at a sync-group barrier gives up (kBarrierSpinLimit unless a test lowers it).
   uint32_t barrier_polls = 1u << 24;
+  // Blocks of which envs, from the first one on, have their episode counters alike: of this many, or a part of it (counter_unit); 0: any
+  uint32_t alike = 0;
   // Slots of time that run side by side, steps of one (mpe_slots.h).
   int32_t slots = 1, span = 0;
   uint32_t work() const { return TE * uint32_t(slots); }   // envs that the launch steps side by side
@@ -126,6 +128,10 @@ hipError_t pack_policy_tag(PolicyBuffers& pb, int N, int L, int G, int R, bool b
 
 hipError_t launch_reset(int N, const StatePtrs& st, uint32_t TE, uint32_t E, uint32_t seed, float* obs,
                         hipStream_t s);
+// For mpe_set_state: no ticket is taken, and unit[0 ..] = the units of the counters' stretches (counter_unit), one per block.
+constexpr uint32_t kCounterBlocks = 256;
+inline uint32_t counter_blocks(uint32_t TE) { return TE / 1024 < kCounterBlocks ? TE / 1024 + 1 : kCounterBlocks; }
+hipError_t launch_read_counters(const StatePtrs& st, uint32_t TE, uint32_t* unit, hipStream_t s);
 hipError_t launch_step(int N, const StatePtrs& st, const Phys& ph, uint32_t TE, uint32_t E, uint32_t seed,
                        uint32_t abs_step, const uint8_t* actions, float* obs, float* reward, uint8_t* done,
                        hipStream_t s);
@@ -189,6 +195,8 @@ hipError_t pack_gru_critic(PolicyBuffers& pb, uint32_t TE, uint32_t E, const flo
                            const float* bv, hipStream_t s);
 // One lane per agent (mpe_env_agents.hip), both scenarios: one step under A.actions_in (reward, done and obs after the
 // step through A.r.rew_traj, done_traj, last_obs), or, with A.actions_in null, a rollout with uniform actions.
+// Envs in a block of it.
+constexpr uint32_t env_agents_block(int N) { return uint32_t(64 / N / 2 * 2); }
 // Whether its rollout is the faster one for this batch.
 bool env_agents_faster(bool tag, int N, uint32_t TE);
 // The most slots of time (mpe_slots.h) that its rollout, or for up to 3 agents of simple spread that of mpe_env_kernels.hip, is to use.

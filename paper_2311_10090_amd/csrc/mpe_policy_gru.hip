@@ -144,7 +144,7 @@ GruPlan gru_plan(int N, int D, bool ac, const RolloutArgs& A, int32_t max_ep) {
   };
   auto offer_block = [&](uint32_t eb) {
     const uint32_t groups = (A.TE + eb - 1) / eb;
-    if (!runs || A.E % eb == 0) offer(block_step(eb) * makespan(cus, groups, longest + 0.5f, groups * uint32_t(B.slots - 1), span + 0.5f), 0, eb);
+    if (slots_fit(B, eb) && (!runs || A.E % eb == 0)) offer(block_step(eb) * makespan(cus, groups, longest + 0.5f, groups * uint32_t(B.slots - 1), span + 0.5f), 0, eb);
   };
   if (!runs) {
     for (uint32_t tiles = 1; tiles <= 4; tiles *= 2) {

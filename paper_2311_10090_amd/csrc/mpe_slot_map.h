@@ -37,6 +37,21 @@ constexpr TimeSlot time_slot(int32_t T, int32_t slots, int32_t span, int32_t k, 
   return {first + (k - 1) * span, span, 0, 0};
 }
 
+// In which blocks all envs have the same episode counter.  The counter changes from one env to the next at some envs, counted from the
+// batch's first: blocks of b envs, from the first one on, are alike throughout exactly if b divides all of these, and so
+// if it divides their greatest common divisor (0: they are all alike).  A counter below zero has all steps run in slot 0, as a change at 1 would.
+constexpr uint32_t common_unit(uint32_t a, uint32_t b) {
+  while (b) {
+    const uint32_t rest = a % b;
+    a = b;
+    b = rest;
+  }
+  return a;
+}
+constexpr uint32_t counter_unit(uint32_t unit, uint32_t env, int32_t before, int32_t ep) {   // before: of the env before, or ep
+  return unit == 1u ? 1u : (ep < 0 ? 1u : (before != ep ? common_unit(unit, env) : unit));
+}
+
 // The episode counter T steps later
 constexpr int32_t counter_after(int32_t T, int32_t ep, int32_t max_ep) {
   const int64_t left = int64_t(max_ep) - ep, first = left > 1 ? left : 1;

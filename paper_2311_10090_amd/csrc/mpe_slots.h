@@ -87,6 +87,12 @@ inline void choose_slots(RolloutArgs& A, int32_t max_ep, uint32_t want) {
   }
 }
 
+// Host: whether blocks of this many envs can have slots: a block whose envs have unlike counters runs all its steps in slot 0, in a
+// block shape chosen for the shorter ones (128 steps, counters each its own, us, one slot against five: 3 agents 4,800 envs without a
+// policy 96 / 166; 6 agents 1,000 envs 214 / 359, critic 290 / 504; recurrent, 3 agents 1,000 envs 321 / 726).  The wavefronts, whose lanes
+// have a slot each, take any counters.
+inline bool slots_fit(const RolloutArgs& A, uint32_t envs) { return A.alike % envs == 0; }
+
 // Host: when the last of `longs` blocks of a steps and then `shorts` of b steps ends, each taken by the place for a block, of
 // `places` on the chip, that is free first.
 inline float makespan(uint32_t places, uint32_t longs, float a, uint32_t shorts, float b) {

@@ -702,6 +702,7 @@ hipError_t launch_small(const TagArgs& A, bool unfit, const void* packed, const 
   constexpr bool kEight = N == 6 || N == 8 || N == 10, kOnlyEight = AC && N == 10 && Scn::D > 32;
   const bool runs = A.r.TE != A.r.E;
   if (runs && A.r.E % 16 != 0) return hipSuccess;
+  if (A.r.slots > 1 && !slots_fit(A.r, kOnlyEight ? 8 : 16)) return hipSuccess;
   const uint32_t cus = compute_units(), blocks16 = (A.r.TE + 15) / 16 * uint32_t(A.r.slots);
   if (!(runs && unfit)) {
     constexpr SmallRange one = small_range<Scn::kTag, N, AC, BF>(), several = small_range_slots<Scn::kTag, N, AC, BF>();

@@ -481,6 +481,7 @@ hipError_t tag_launch(int mode, const TagArgs& A, const void* packed, const void
   if (mode == kUniform) {
     TagArgs B = A;
     choose_slots(B.r, A.tg.max_ep, env_slots(true, S::N, S::D, A.r.TE));
+    if (!slots_fit(B.r, env_agents_block(S::N))) B.r.slots = 1;
     if constexpr (S::N != 4 && S::N != 10) {
       if (B.r.slots == 1 && !env_agents_faster(true, S::N, A.r.TE)) return tag_rollout_impl<S, kUniform>(A, nullptr, nullptr, s);
     }

@@ -1,8 +1,9 @@
 // What libmpe asks of the HIP runtime, without a device: this program defines the runtime's functions that the library calls,
 // so its own take their place (the executable comes first in symbol lookup), and prints every launch and every LDS
 // attribute.  Memory is host memory, kernels do not run.  argv[1]: compute units (256).  Commands on stdin, one a line; after each one line "rc <n>":
-//   create <scenario> <agents> <landmarks> <adversaries> <envs> <runs>   hidden 128, bf16 weights
-//   destroy | reset | set_state | gru | critic | rollout <T> | rollout_ac <T> | abs_step
+//   create <scenario> <agents> <landmarks> <adversaries> <envs> <runs> [<hidden> <weight type> <steps of an episode>]   128 1 25
+//   destroy | reset | set_state | gru | critic | mlp | mlp_critic | rollout <T> | rollout_ac <T> | abs_step
+//   counters <unit>                                                      what mpe_set_state's kernel finds from here on (0)
 //   fail <attribute|launch> <k>                                          the k-th such call from here on fails, once
 #include <cxxabi.h>
 
@@ -26,6 +27,7 @@ std::map<const void*, std::string>& kernels() {
 struct Config { uint32_t grid[3], block[3]; size_t lds; void* stream; } pushed;
 int last_error = 0;
 int units = 256;           // compute units
+uint32_t counters = 0;     // see the command
 int fail_in[2] = {0, 0};   // attribute, launch: calls until the one that fails
 int outcome(int kind) { return fail_in[kind] && --fail_in[kind] == 0 ? (last_error = 1) : 0; }
 struct Dim3 { uint32_t x, y, z; };
@@ -62,6 +64,7 @@ int hipLaunchKernel(const void* host, Dim3 grid, Dim3 block, void** args, size_t
   std::printf("launch %s grid %u %u block %u lds %zu", name.c_str(), grid.x, grid.y, block.x, lds);
   if (name.rfind("rollout_gru_kernel<", 0) == 0) std::printf(" first %u groups %u", word(5), word(6));
   if (name.rfind("rollout_gru_waves_kernel<", 0) == 0) std::printf(" envs %u", word(4));
+  if (name == "read_counters_kernel" && rc == 0) **static_cast<uint32_t**>(args[2]) = counters;
   std::printf("%s\n", rc ? " FAILS" : "");
   return rc;
 }
@@ -98,9 +101,16 @@ int main(int argc, char** argv) {
     if (what == "create") {
       mpe_config c{};
       in >> c.scenario >> c.num_agents >> c.num_landmarks >> c.num_adversaries >> c.num_envs >> c.num_runs;
+      c.hidden = 128;
+      c.weight_dtype = MPE_WEIGHTS_BF16;
       c.max_episode_steps = 25;
+      if (int32_t hidden, dtype, steps; in >> hidden >> dtype >> steps) {
+        c.hidden = hidden;
+        c.weight_dtype = dtype;
+        c.max_episode_steps = steps;
+      }
       c.dt = 0.1f; c.damping = 0.25f; c.mass = 1.0f; c.accel = 5.0f; c.agent_radius = 0.15f; c.landmark_radius = 0.05f;
-      c.contact_force = 100.0f; c.contact_margin = 1e-3f; c.hidden = 128; c.weight_dtype = MPE_WEIGHTS_BF16;
+      c.contact_force = 100.0f; c.contact_margin = 1e-3f;
       c.adv_radius = 0.075f; c.adv_accel = 3.0f; c.adv_max_speed = 1.0f; c.good_max_speed = 1.3f;
       rc = mpe_create(&c, &env);
     } else if (what == "destroy") {
@@ -114,6 +124,12 @@ int main(int argc, char** argv) {
       rc = mpe_set_gru_policy(env, p, p, p, p, p, p, p, p, p, p, nullptr);
     } else if (what == "critic") {
       rc = mpe_set_gru_critic(env, p, p, p, p, nullptr);
+    } else if (what == "mlp") {
+      rc = mpe_set_policy(env, p, p, p, p, p, p, nullptr);
+    } else if (what == "mlp_critic") {
+      rc = mpe_set_critic(env, p, p, p, p, p, p, nullptr);
+    } else if (what == "counters") {
+      in >> counters;
     } else if (what == "rollout" || what == "rollout_ac") {
       int T = 0;
       in >> T;

@@ -65,7 +65,34 @@ bool steps(int32_t T, int32_t slots, int32_t span, int32_t ep, int32_t max_ep, b
 
 }  // namespace
 
+bool alike(uint32_t seed) {
+  // stretches of a length each, with a break here and there that is none, a counter below zero in some
+  uint32_t state = seed * 2654435761u + 1u;
+  auto draw = [&](uint32_t n) { state = state * 1664525u + 1013904223u; return (state >> 8) % n; };
+  const uint32_t envs = 1 + draw(400), step = draw(3) ? 1 + draw(70) : envs;
+  std::vector<int32_t> ep(envs);
+  int32_t now = 3;
+  for (uint32_t g = 0; g < envs; ++g) {
+    if (g && g % step == 0) now = int32_t(draw(4));
+    ep[g] = now;
+  }
+  if (draw(8) == 0) ep[draw(envs)] = -1;
+  uint32_t unit = 0;
+  for (uint32_t part = 0; part < 7; ++part) {              // strided, as threads do
+    uint32_t mine = 0;
+    for (uint32_t g = part; g < envs; g += 7) mine = mpe::counter_unit(mine, g, ep[g ? g - 1 : 0], ep[g]);
+    unit = mpe::common_unit(unit, mine);
+  }
+  for (uint32_t block = 2; block <= 64; ++block) {
+    bool all = true;
+    for (uint32_t g = 0; g < envs; ++g) all = all && ep[g] >= 0 && ep[g] == ep[g / block * block];
+    if (all != (unit % block == 0)) return std::printf("seed %u block %u unit %u\n", seed, block, unit), false;
+  }
+  return true;
+}
+
 int main() {
+  for (uint32_t seed = 0; seed < 20000; ++seed) if (!alike(seed)) return 1;
   for (uint32_t groups = 1; groups <= 300; ++groups)
     for (uint32_t slots = 2; slots <= 41; ++slots) if (!blocks(groups, slots)) return 1;
   for (uint32_t groups : {1u, 7u, 8u, 41u, 1023u, 1024u, 40961u})

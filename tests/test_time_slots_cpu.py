@@ -74,4 +74,38 @@ def test_set_state_clears_the_tickets(recorder):
     """With and without a reset before: one that a capture has recorded has not run."""
     for first in ([], ["reset"]):
         out = record(recorder, ["create 0 3 3 0 1000 1", *first, "set_state"])
-        assert [name for name, _ in launches(out[-1][1])] == ["fill_zero_kernel"]
+        assert [name for name, _ in launches(out[-1][1])] == ["read_counters_kernel"]
+
+
+@pytest.mark.parametrize("shape,T,call,policy,alike,unlike", [
+    # in a block kernel, whose blocks have slots only where their envs' counters are alike
+    ("0 3 3 0 1000 1 0 0 25", 128, "rollout", (), "rollout_agents_kernel", "rollout_agents_kernel"),
+    ("0 3 3 0 4800 1 0 0 25", 128, "rollout", (), "rollout_uniform_ws_kernel", "rollout_agents_kernel"),
+    ("0 1 1 0 4800 1 0 0 25", 128, "rollout", (), "rollout_uniform_ws_kernel", "rollout_uniform_ws_kernel"),
+    ("1 4 2 3 1000 1 0 0 25", 128, "rollout", (), "rollout_agents_kernel", "rollout_agents_kernel"),
+    ("0 6 6 0 256 1 64 0 25", 50, "rollout", ("mlp",), "rollout_small_kernel", "rollout_small_kernel"),
+    ("1 8 2 6 200 1 64 0 25", 50, "rollout_ac", ("mlp", "mlp_critic"), "rollout_small_kernel", "rollout_small_kernel"),
+    ("0 3 3 0 1000 1 128 1 25", 128, "rollout", ("gru",), "rollout_gru_kernel", "rollout_gru_kernel"),
+    ("0 3 3 0 16 12 128 1 25", 128, "rollout_ac", ("gru", "critic"), "rollout_gru_kernel", "rollout_gru_kernel"),
+])
+def test_unlike_counters_in_blocks(recorder, shape, T, call, policy, alike, unlike):
+    """They run in one slot, as after no other call than mpe_set_state."""
+    def route(*before):
+        (name, _), = launches(record(recorder, ["create " + shape, *policy, *before, "%s %d" % (call, T)])[-1][1])
+        return name
+    several, fresh = route("reset"), route("counters 0", "set_state")
+    assert several == fresh and several.startswith(alike) and ("SlotGrid" in several or several.endswith("true>"))
+    one = route("counters 7", "set_state")
+    assert one.startswith(unlike) and "SlotGrid" not in one and (not one.startswith("rollout_uniform_ws") or one.endswith("false>"))
+    assert route("counters 7", "set_state", "reset") == several and route("counters 7", "set_state", "counters 0", "set_state") == several
+    # what was found last holds until the next state's kernel has run
+    assert route("counters 7", "set_state", "rollout 1") == one
+
+
+def test_unlike_counters_in_wavefronts(recorder):
+    """Lanes have a slot of their own: slots as ever, also of smaller batches, whose blocks can have none."""
+    for envs, alike in ((20011, "rollout_waves_kernel"), (1000, "rollout_small_kernel")):
+        for unit, kernel in ((0, alike), (7, "rollout_waves_kernel"), (48, alike)):
+            out = record(recorder, ["create 0 3 3 0 %d 1 64 0 25" % envs, "mlp", "counters %d" % unit, "set_state", "rollout 128"])
+            (name, _), = launches(out[-1][1])
+            assert name.startswith(kernel) and "SlotGrid" in name, (envs, unit, name)

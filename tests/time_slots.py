@@ -18,8 +18,9 @@ def counters(kind, envs, max_ep):
     return torch.randint(-3, max_ep + 4, (envs,), generator=torch.Generator().manual_seed(5), dtype=torch.int32)
 
 
-def outputs(cfg, T, start, pieces, policy=(), critic=(), gru=False, left_out=()):
-    """Everything that two rollouts of T steps write, each in calls of the given lengths."""
+def outputs(cfg, T, start, pieces, policy=(), critic=(), gru=False, left_out=(), captured=False):
+    """Everything that two rollouts of T steps write, each in calls of the given lengths.  captured: the state and the first rollout's
+    calls come from a graph, whose calls were chosen when the new counters were not known."""
     assert sum(pieces) == T
     env = MpeEnv(MpeConfig(**cfg))
     if policy:
@@ -28,16 +29,27 @@ def outputs(cfg, T, start, pieces, policy=(), critic=(), gru=False, left_out=())
         (env.set_gru_critic if gru else env.set_critic)(*critic)
     env.reset(11)
     pa, va, pl, _, step = env.get_state()
-    env.set_state(pa, va, pl, start.cuda(), 11, int(step))
+    start = start.cuda()
     kept = []
-    for _ in range(2):
-        parts = []
+    for first in (True, False):
+        sets = []
         for n in pieces:
-            bufs = list(env.empty_traj_ac(n) if critic else env.empty_traj(n))
+            sets.append(list(env.empty_traj_ac(n) if critic else env.empty_traj(n)))
             for k in left_out:
-                bufs[k] = None
-            out = env.rollout_ac(n, *bufs) if critic else env.rollout(n, *bufs)
-            parts.append([None if o is None else o.clone() for o in out])
+                sets[-1][k] = None
+
+        def calls():
+            if first:
+                env.set_state(pa, va, pl, start, 11, int(step))
+            return [(env.rollout_ac if critic else env.rollout)(n, *bufs) for n, bufs in zip(pieces, sets)]
+        if first and captured:
+            graph = torch.cuda.CUDAGraph()
+            with torch.cuda.graph(graph):
+                parts = calls()
+            graph.replay()
+        else:
+            parts = calls()
+        parts = [[None if o is None else o.clone() for o in out] for out in parts]
         last = 2 if critic else 1
         for k in range(len(parts[0])):
             if parts[0][k] is not None:
@@ -54,8 +66,10 @@ def assert_slots_change_nothing(cfg, T, kind, max_ep, **more):
     print("slots: %d envs, %d agents, %d steps, episodes of %d, counters %s" % (envs, cfg["num_agents"], T, max_ep, kind), flush=True)
     start = counters(kind, envs, max_ep)
     short = [SHORT] * (T // SHORT) + ([T % SHORT] if T % SHORT else [])
-    for k, (a, b) in enumerate(zip(outputs(cfg, T, start, [T], **more), outputs(cfg, T, start, short, **more))):
-        assert torch.equal(a, b), ("output", k)
+    expected = outputs(cfg, T, start, short, **more)
+    for captured in (False, True) if kind != "alike" else (False,):
+        for k, (a, b) in enumerate(zip(outputs(cfg, T, start, [T], captured=captured, **more), expected)):
+            assert torch.equal(a, b), ("output", k, captured)
 
 
 def config(scenario, agents, envs, max_ep, runs=1, hidden=0, wd=0):
