@@ -3,7 +3,7 @@
 // 0.81 of it (all shapes within 5 %).  The small-batch kernel's step is a table by 16-env blocks per CU, the kernels of up to 3 agents
 // for full batches take 0.085 for every wavefront of 64 rows that their 64-env blocks put on a CU.  Measured on 4,542 batches (1 to 10
 // agents and every predator-prey shape, 64 to 65,536 envs, 16 to 1,024 runs, both types, with and without critic, 50 to 128 steps), slots where
-// this says so against one slot everywhere: 1.36 times as fast in the mean, 30 batches 2.5 to 9 % slower.  Slots wherever the size of
+// this says so against one slot everywhere: 1.35 times as fast in the mean, 10 batches 2.5 to 6 % slower.  Slots wherever the size of
 // the batch allows them: 397 slower, up to twice, above all where two or three slots of unequal length meet a chip that one slot fills.
 #pragma once
 
@@ -83,11 +83,12 @@ struct BatchKind {
   bool tag, bf, ac;
 };
 
-// A step of the small-batch kernel with `slots` of A's slots in flight.
+// A step of the small-batch kernel with `slots` of A's slots in flight.  (With a critic and 2 or 3 agents, 450 runs x 48 envs x 86 steps, us,
+// 883 in one slot, 962 in three of the wavefronts.)
 inline float small_step(const BatchKind& k, const RolloutArgs& A, uint32_t slots) {
   struct Line { float at[4], more; };                  // 1, 2, 3, 4 blocks per CU, each one more
   static constexpr Line few[7] = {{{0.09f, 0.10f, 0.10f, 0.10f}, 0.055f}, {{0.12f, 0.195f, 0.195f, 0.21f}, 0.075f}, {{0.12f, 0.20f, 0.27f, 0.31f}, 0.095f},
-                                  {{0.05f, 0.07f, 0.085f, 0.12f}, 0.030f}, {{0.07f, 0.11f, 0.17f, 0.25f}, 0.08f}, {{0.09f, 0.17f, 0.25f, 0.32f}, 0.09f},
+                                  {{0.05f, 0.07f, 0.085f, 0.12f}, 0.030f}, {{0.065f, 0.10f, 0.155f, 0.23f}, 0.074f}, {{0.08f, 0.15f, 0.22f, 0.28f}, 0.079f},
                                   {{0.05f, 0.07f, 0.09f, 0.09f}, 0.04f}};
   static constexpr float plain[7][2] = {{0.12f, 0.08f}, {0.17f, 0.09f}, {0.19f, 0.14f}, {0.18f, 0.17f}, {0.22f, 0.21f}, {0.25f, 0.25f}, {0.28f, 0.12f}};
   static constexpr float critic[7][2] = {{0.095f, 0.095f}, {0.12f, 0.12f}, {0.16f, 0.15f}, {0.15f, 0.15f}, {0.20f, 0.20f}, {0.22f, 0.22f}, {0.26f, 0.26f}};
