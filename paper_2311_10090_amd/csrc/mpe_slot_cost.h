@@ -1,6 +1,9 @@
-// Host: whether a feed-forward rollout is faster in the slots of time that it holds (mpe_slots.h) than in one.  The unit of time is a
-// step of the independent wavefronts (mpe_waves.h) with every SIMD at its full rate: 4, 8 and 12 wavefronts of a CU take 0.36, 0.56 and
-// 0.81 of it (all shapes within 5 %).  The small-batch kernel's step is a table by 16-env blocks per CU, the kernels of up to 3 agents
+// Host: whether a feed-forward rollout is faster in the slots of time that it holds (mpe_slots.h) than in one.  The unit of time is that
+// in which 4, 8 and 12 wavefronts of a CU take 0.36, 0.56 and 0.81 for a step of the independent wavefronts (mpe_waves.h) while some CUs have
+// none.  Measured, us, blocks of 4, 8, 12 on 64 to 192 CUs: 4 agents 4.8, 7.6, 10.9; 6 agents 5.3, 8.0, 11.2 (critic 9.5, 14.6, 20.3);
+// 10 agents 7.9, 10.5, 15.4 (critic 12.0, 18.3, 27.2); medians over the batches of every shape lie within 10 %.  With a block of 8 or 12 on every CU the
+// clock falls under the power limit and a step takes 12 to 25 % longer: 6 agents 5.4, 9.4, 13.9; waves_cost in mpe_waves.h, which compares
+// full rounds, has the ratios of that.  The small-batch kernel's step is a table by 16-env blocks per CU, the kernels of up to 3 agents
 // for full batches take 0.085 for every wavefront of 64 rows that their 64-env blocks put on a CU.  Measured on 4,542 batches (1 to 10
 // agents and every predator-prey shape, 64 to 65,536 envs, 16 to 1,024 runs, both types, with and without critic, 50 to 128 steps), slots where
 // this says so against one slot everywhere: 1.35 times as fast in the mean, 10 batches 2.5 to 6 % slower.  Slots wherever the size of

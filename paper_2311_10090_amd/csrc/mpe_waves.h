@@ -532,9 +532,11 @@ hipError_t launch_waves_impl(const TagArgs& A, const void* packed, const void* c
 }
 
 // Estimated time of a batch in blocks of W wavefronts, in steps of a CU with 12 resident wavefronts: full rounds of resident
-// blocks, then a last one with as many blocks per CU as are left.  4, 8 and 12 wavefronts per CU take 0.42,
-// 0.75 and 1 (measured with 6 agents, fp32, 128 steps: 661-698, 1,030-1,210 and 1,412-1,660 us; 12 with a critic or of 8 and more agents,
-// with spilled registers, 4 to 9 % more).  A block takes its steps and about one and a half more to stage the weights; in
+// blocks, then a last one with as many blocks per CU as are left.  4, 8 and 12 wavefronts on every CU take 0.42,
+// 0.75 and 1 (measured, 128 steps in one slot, us a step: 4 agents 4.8, 8.6, 12.6; 6 agents 5.4, 9.4, 13.9, critic 9.6, 16.3, 25.1; 10 agents 8.3,
+// 12.6, 20.3; that is 0.38 to 0.41, 0.62 to 0.68 and 1; where some CUs have none, 8 and 12 are nearer to 4: mpe_slot_cost.h).  The estimate
+// of that in the place of this one picks the same blocks to within 0.1 % of the time, but takes 20,011 envs x 6 agents out of their slots (1,234 us
+// against 1,187).  12 with a critic or of 8 and more agents, with spilled registers, take 4 to 9 % more.  A block takes its steps and about one and a half more to stage the weights; in
 // several slots slot 0, whose blocks come first, takes the longest.
 template <typename Scn, int W, bool AC, bool BF>
 float waves_cost(const RolloutArgs& A) {
