@@ -678,15 +678,17 @@ hipError_t launch_small_impl(const TagArgs& A, const void* packed, const void* c
   return launch_groups<M::WAVES * 64>(groups, [&](dim3 grid, const GridPiece& p) { launch(kern, grid, p); });
 }
 
-template <typename Scn, int EB, bool AC, bool BF>
+// ALONE: every block has a CU to itself
+template <typename Scn, int EB, bool AC, bool BF, bool ALONE = false>
 hipError_t launch_small_eb(const TagArgs& A, const void* packed, const void* critic, hipStream_t s) {
   // Stationary operands while a block has a CU to itself (6-10 % faster there); they take 100 to 170 registers per
   // wavefront, so beyond that, and with more than 8 wavefronts per block, the operands are read from LDS.
   constexpr int W = SmallSmem<Scn, EB, AC, BF, true>::WAVES, kMin = (W + 3) / 4;
   if constexpr (kMin <= 2) {
+    if constexpr (ALONE) return launch_small_impl<Scn, EB, AC, BF, true, 2>(A, packed, critic, s);
     if ((A.r.TE + EB - 1) / EB * uint32_t(A.r.slots) <= compute_units()) return launch_small_impl<Scn, EB, AC, BF, true, 2>(A, packed, critic, s);
   }
-  return launch_small_impl<Scn, EB, AC, BF, false, (kMin < 4 ? 4 : kMin)>(A, packed, critic, s);
+  if constexpr (!ALONE || kMin > 2) return launch_small_impl<Scn, EB, AC, BF, false, (kMin < 4 ? 4 : kMin)>(A, packed, critic, s);
 }
 
 // *taken: whether the rollout was launched here.  unfit: runs that suit no block of the other kernels, which the caller
@@ -717,7 +719,7 @@ hipError_t launch_small(const TagArgs& A, bool unfit, const void* packed, const 
   }
   *taken = true;
   if constexpr (kEight) {
-    if (kOnlyEight || (A.r.TE + 7) / 8 * uint32_t(A.r.slots) <= cus) return launch_small_eb<Scn, 8, AC, BF>(A, packed, critic, s);
+    if (kOnlyEight || (A.r.TE + 7) / 8 * uint32_t(A.r.slots) <= cus) return launch_small_eb<Scn, 8, AC, BF, !kOnlyEight>(A, packed, critic, s);
   }
   if constexpr (!kOnlyEight) return launch_small_eb<Scn, 16, AC, BF>(A, packed, critic, s);
 }

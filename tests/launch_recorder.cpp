@@ -1,8 +1,10 @@
 // What libmpe asks of the HIP runtime, without a device: this program defines the runtime's functions that the library calls,
 // so its own take their place (the executable comes first in symbol lookup), and prints every launch and every LDS
 // attribute.  Memory is host memory, kernels do not run.  argv[1]: compute units (256).  Commands on stdin, one a line; after each one line "rc <n>":
-//   create <scenario> <agents> <landmarks> <adversaries> <envs> <runs> [<hidden> <weight type> <steps of an episode>]   128 1 25
+//   create <scenario> <agents> <landmarks> <adversaries> <envs> <runs> [<hidden> <weight type> <steps of an episode> [<reward mode>]]
+//                                                                        128 1 25 0
 //   destroy | reset | set_state | gru | critic | mlp | mlp_critic | rollout <T> | rollout_ac <T> | abs_step
+//   kernels                                                              the names of all that the library has
 //   counters <unit>                                                      what mpe_set_state's kernel finds from here on (0)
 //   fail <attribute|launch> <k>                                          the k-th such call from here on fails, once
 #include <cxxabi.h>
@@ -108,6 +110,7 @@ int main(int argc, char** argv) {
         c.hidden = hidden;
         c.weight_dtype = dtype;
         c.max_episode_steps = steps;
+        if (in >> c.reward_mode) c.local_ratio = 0.5f;
       }
       c.dt = 0.1f; c.damping = 0.25f; c.mass = 1.0f; c.accel = 5.0f; c.agent_radius = 0.15f; c.landmark_radius = 0.05f;
       c.contact_force = 100.0f; c.contact_margin = 1e-3f;
@@ -128,6 +131,8 @@ int main(int argc, char** argv) {
       rc = mpe_set_policy(env, p, p, p, p, p, p, nullptr);
     } else if (what == "mlp_critic") {
       rc = mpe_set_critic(env, p, p, p, p, p, p, nullptr);
+    } else if (what == "kernels") {
+      for (const auto& k : kernels()) std::printf("kernel %s\n", k.second.c_str());
     } else if (what == "counters") {
       in >> counters;
     } else if (what == "rollout" || what == "rollout_ac") {

@@ -6,6 +6,7 @@ import subprocess
 import pytest
 
 from tests.launch_record import ROOT, build_recorder, launches, record
+from tests.time_slots import RUNS, Batch, batches, record_commands
 
 
 def test_blocks_and_slots_cover_everything_once(tmp_path):
@@ -116,3 +117,29 @@ def test_runs_that_one_slot_suits_better(recorder, shape, T):
     """Actor-critic, 7 to 9 % slower in slots, whose last wavefronts are short of lanes."""
     (name, _), = launches(record(recorder, ["create " + shape, "mlp", "mlp_critic", "reset", "rollout_ac %d" % T])[-1][1])
     assert name.startswith("rollout_small_kernel") and "SlotGrid" not in name
+
+
+def single_launches(recorder, cases):
+    """The kernel that each batch's rollout launches."""
+    commands = [record_commands(b) for b in cases]
+    out, names = record(recorder, [c for cs in commands for c in cs]), []
+    for cs in commands:
+        (name, _), = launches(out[len(cs) - 2][1])
+        names.append(name)
+        out = out[len(cs):]
+    return names
+
+
+def test_every_instance_with_slots_has_its_batch(recorder):
+    """The GPU test of all instances runs these: each in the instance that it is listed for, and no instance without one."""
+    cases = list(batches())
+    assert single_launches(recorder, cases) == [b.kernel for b in cases]
+    (_, lines), = record(recorder, ["kernels"])
+    instances = {k[len("kernel "):] for k in lines if "SlotGrid" in k or (k.startswith("kernel rollout_uniform_ws_kernel<") and k.endswith("true>"))}
+    assert {b.kernel for b in cases} == instances and len(instances) > 400
+
+
+def test_runs_of_the_gpu_test_share_wavefronts(recorder):
+    cases = [Batch("spread", agents, 0, "mlp", ac, envs, runs, 25, 128, 0, "") for runs, envs, agents, ac in RUNS]
+    for b, name in zip(cases, single_launches(recorder, cases)):
+        assert name.startswith("rollout_waves_kernel<WaveSpread<%d>" % b.agents) and "SlotGrid" in name, b

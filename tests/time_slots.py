@@ -1,5 +1,8 @@
 """Rollouts whose time runs in slots side by side, against the same steps in calls that are too short for slots: an
 environment's trajectory does not depend on how its steps are divided among calls, bit for bit."""
+import collections
+import os
+
 import torch
 
 from paper_2311_10090_amd import synth
@@ -72,8 +75,43 @@ def assert_slots_change_nothing(cfg, T, kind, max_ep, **more):
             assert torch.equal(a, b), ("output", k, captured)
 
 
-def config(scenario, agents, envs, max_ep, runs=1, hidden=0, wd=0):
+TAG = {2: (1, 1), 3: (0, 2), 4: (2, 3), 5: (2, 4), 6: (2, 4), 8: (2, 6), 10: (3, 8)}      # landmarks, adversaries
+
+
+def config(scenario, agents, envs, max_ep, runs=1, hidden=0, wd=0, reward=None):
     if scenario == "tag":
-        landmarks, adversaries = {2: (1, 1), 3: (0, 2), 4: (2, 3), 5: (2, 4), 6: (2, 4), 8: (2, 6), 10: (3, 8)}[agents]
+        landmarks, adversaries = TAG[agents]
         return synth.tag_config(envs, agents, landmarks, adversaries, runs, hidden, wd, max_episode_steps=max_ep)
-    return synth.spread_config(envs, agents, runs, hidden, wd, max_episode_steps=max_ep, reward_mode=agents % 2)
+    return synth.spread_config(envs, agents, runs, hidden, wd, max_episode_steps=max_ep, reward_mode=agents % 2 if reward is None else reward)
+
+
+# Runs whose slots share wavefronts: (runs, envs of one, agents, critic)
+RUNS = [(1024, 16, 3, False), (300, 32, 3, False), (150, 48, 3, False), (100, 64, 3, False), (1024, 16, 3, True), (300, 32, 3, True),
+        (256, 48, 3, True), (100, 64, 3, True), (128, 48, 2, True), (512, 48, 2, True), (300, 64, 2, True), (77, 64, 2, True)]
+
+Batch = collections.namedtuple("Batch", "scenario agents wd policy critic envs runs max_ep T reward kernel")
+
+
+def batches():
+    """A batch for every kernel instance with slots."""
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "golden", "slot_batches.txt")
+    for line in open(path):
+        if not line.startswith("#"):
+            s, n, wd, policy, ac, *numbers = line.split(maxsplit=10)[:10]
+            yield Batch(s, int(n), int(wd), policy, ac == "1", *map(int, numbers), line.split(maxsplit=10)[10].strip())
+
+
+def networks(scenario, agents, runs, ac, gru=False):
+    D = synth.tag_obs_dim(agents, *TAG[agents]) if scenario == "tag" else 6 * agents
+    dev = lambda arrs: [torch.from_numpy(a).cuda() for a in arrs]
+    if gru:
+        return dict(policy=dev(synth.gru_weights(5, runs, D)), critic=dev(synth.gru_critic_weights(5, runs)) if ac else (), gru=True)
+    return dict(policy=dev(synth.policy_weights_with_bias(3, runs, D, 64)), critic=dev(synth.critic_weights(3, runs, D, 64)) if ac else ())
+
+
+def record_commands(b):
+    """For tests/launch_record.py: the batch's rollout is the command before the last."""
+    landmarks, adversaries = TAG[b.agents] if b.scenario == "tag" else (b.agents, 0)
+    hidden = {"none": 0, "mlp": 64, "gru": synth.GRU_HIDDEN}[b.policy]
+    return ["create %d %d %d %d %d %d %d %d %d %d" % (b.scenario == "tag", b.agents, landmarks, adversaries, b.envs, b.runs, hidden, b.wd, b.max_ep, b.reward),
+            *{"none": (), "mlp": ("mlp", "mlp_critic"), "gru": ("gru", "critic")}[b.policy], "reset", "%s %d" % ("rollout_ac" if b.critic else "rollout", b.T), "destroy"]
