@@ -2,6 +2,8 @@
 filled last groups, several blocks."""
 import pytest
 
+from tests.time_slots import RUNS, assert_slots_change_nothing, batches, config, networks
+
 pytestmark = pytest.mark.gpu
 
 EPISODES = [(25, 50), (25, 128), (5, 101), (1, 64), (40, 81)]        # steps of an episode, of a rollout
@@ -13,14 +15,12 @@ EPISODES = [(25, 50), (25, 128), (5, 101), (1, 64), (40, 81)]        # steps of 
                                                   ("spread", 3, 1024), ("spread", 3, 6000), ("spread", 4, 1001), ("spread", 10, 130),
                                                   ("tag", 2, 77), ("tag", 3, 1003), ("tag", 4, 1500), ("tag", 10, 100)])
 def test_environment_only(scenario, agents, envs, max_ep, T, kind):
-    from tests.time_slots import assert_slots_change_nothing, config
     assert_slots_change_nothing(config(scenario, agents, envs, max_ep), T, kind, max_ep)
 
 
 @pytest.mark.parametrize("scenario,agents", [("spread", 2), ("spread", 3), ("spread", 6), ("tag", 4)])
 @pytest.mark.parametrize("left_out", [(0, 4), (1, 2), (3,), (0, 1, 2, 3)])
 def test_environment_only_without_some_outputs(scenario, agents, left_out):
-    from tests.time_slots import assert_slots_change_nothing, config
     assert_slots_change_nothing(config(scenario, agents, 200, 25), 77, "alike", 25, left_out=left_out)
 
 
@@ -34,21 +34,10 @@ LARGE = [("spread", 1, 0, 9001), ("spread", 2, 1, 7001), ("spread", 3, 0, 5001),
          ("tag", 3, 0, 8001), ("tag", 4, 0, 7003), ("tag", 5, 1, 2501), ("tag", 6, 0, 3999), ("tag", 8, 0, 3001), ("tag", 10, 1, 3333)]
 
 
-def networks(scenario, agents, runs, ac):
-    import torch
-    from paper_2311_10090_amd import synth
-    from tests.time_slots import config
-    c = config(scenario, agents, 16, 25)
-    D = synth.tag_obs_dim(agents, c["num_landmarks"], c["num_adversaries"]) if scenario == "tag" else 6 * agents
-    dev = lambda arrs: [torch.from_numpy(a).cuda() for a in arrs]
-    return dict(policy=dev(synth.policy_weights_with_bias(3, runs, D, 64)), critic=dev(synth.critic_weights(3, runs, D, 64)) if ac else ())
-
-
 @pytest.mark.parametrize("ac", [False, True], ids=["plain", "actor_critic"])
 @pytest.mark.parametrize("envs,runs,max_ep,T", SIZES)
 @pytest.mark.parametrize("scenario,agents,wd", SHAPES)
 def test_policies(scenario, agents, wd, envs, runs, max_ep, T, ac):
-    from tests.time_slots import assert_slots_change_nothing, config
     if runs > 1 and scenario == "spread" and agents > 3:
         envs = 64
     cfg = config(scenario, agents, envs, max_ep, runs, 64, wd)
@@ -58,17 +47,14 @@ def test_policies(scenario, agents, wd, envs, runs, max_ep, T, ac):
 
 @pytest.mark.parametrize("ac", [False, True], ids=["plain", "actor_critic"])
 @pytest.mark.parametrize("scenario,agents,wd,envs", LARGE)
-def test_policies_in_wavefronts(scenario, agents, wd, envs, ac):
-    from tests.time_slots import assert_slots_change_nothing, config
+def test_larger_batches(scenario, agents, wd, envs, ac):
     cfg = config(scenario, agents, envs, 25, 1, 64, wd)
     for kind in ("stretches", "own"):
         assert_slots_change_nothing(cfg, 128, kind, 25, **networks(scenario, agents, 1, ac))
 
 
-@pytest.mark.parametrize("runs,envs", [(1024, 16), (300, 32), (77, 48), (100, 64)])
-@pytest.mark.parametrize("agents,ac", [(3, False), (3, True), (2, True)])
+@pytest.mark.parametrize("runs,envs,agents,ac", RUNS)
 def test_runs_in_wavefronts(agents, runs, envs, ac):
-    from tests.time_slots import assert_slots_change_nothing, config
     cfg = config("spread", agents, envs, 25, runs, 64, 0)
     assert_slots_change_nothing(cfg, 128, "own", 25, **networks("spread", agents, runs, ac))
 
@@ -76,7 +62,6 @@ def test_runs_in_wavefronts(agents, runs, envs, ac):
 @pytest.mark.parametrize("left_out", [(0, 6), (1, 2, 7), (3, 4), (5, 6, 7)])
 @pytest.mark.parametrize("envs", [500, 6000])
 def test_actor_critic_without_some_outputs(envs, left_out):
-    from tests.time_slots import assert_slots_change_nothing, config
     assert_slots_change_nothing(config("spread", 3, envs, 25, 1, 64, 0), 128, "alike", 25, left_out=left_out, **networks("spread", 3, 1, True))
 
 
@@ -93,14 +78,29 @@ RECURRENT = [("spread", 1, 1, 1), ("spread", 1, 5000, 1), ("spread", 2, 903, 1),
 @pytest.mark.parametrize("max_ep,T", [(25, 128), (5, 75), (40, 81)])
 @pytest.mark.parametrize("scenario,agents,envs,runs", RECURRENT)
 def test_recurrent_policies(scenario, agents, envs, runs, max_ep, T, ac):
-    import torch
-    from paper_2311_10090_amd import synth
-    from tests.time_slots import assert_slots_change_nothing, config
-    cfg = config(scenario, agents, envs, max_ep, runs, synth.GRU_HIDDEN, 1)
-    D = synth.tag_obs_dim(agents, cfg["num_landmarks"], cfg["num_adversaries"]) if scenario == "tag" else 6 * agents
-    dev = lambda arrs: [torch.from_numpy(a).cuda() for a in arrs]
-    nets = dict(policy=dev(synth.gru_weights(5, runs, D)), critic=dev(synth.gru_critic_weights(5, runs)) if ac else (), gru=True)
+    cfg = config(scenario, agents, envs, max_ep, runs, 128, 1)
+    nets = networks(scenario, agents, runs, ac, gru=True)
     for kind in ("alike", "own"):
         assert_slots_change_nothing(cfg, T, kind, max_ep, **nets)
     if envs == 6007 or envs == 509:
         assert_slots_change_nothing(cfg, T, "stretches", max_ep, left_out=(0, 4) if not ac else (0, 1, 5, 7), **nets)
+
+
+@pytest.mark.parametrize("batch", batches(), ids=lambda b: b.kernel.replace(" ", ""))
+def test_every_instance(batch):
+    """tests/test_time_slots_cpu.py: that the batch runs in this instance, and that none is missing."""
+    b = batch
+    nets = networks(b.scenario, b.agents, b.runs, b.critic, b.policy == "gru") if b.policy != "none" else {}
+    cfg = config(b.scenario, b.agents, b.envs, b.max_ep, b.runs, {"none": 0, "mlp": 64, "gru": 128}[b.policy], b.wd, b.reward)
+    for kind in ("alike", "own"):
+        assert_slots_change_nothing(cfg, b.T, kind, b.max_ep, **nets)
+
+
+@pytest.mark.parametrize("reward", [0, 1], ids=["shared", "mixed"])
+@pytest.mark.parametrize("agents", [1, 2, 3, 6])
+@pytest.mark.parametrize("policy,envs", [("none", 200), ("none", 8192), ("mlp", 500), ("mlp", 20011), ("gru", 300), ("gru", 6007)])
+def test_both_rewards(policy, envs, agents, reward):
+    nets = networks("spread", agents, 1, False, policy == "gru") if policy != "none" else {}
+    cfg = config("spread", agents, envs, 25, 1, {"none": 0, "mlp": 64, "gru": 128}[policy], int(policy == "gru"), reward)
+    for kind in ("alike", "own"):
+        assert_slots_change_nothing(cfg, 110, kind, 25, **nets)
