@@ -12,9 +12,13 @@ namespace mpe {
 struct SlotGroup {
   uint32_t slot, group;    // slot not below the number of slots: a block that is left over
 };
-constexpr SlotGroup slot_group(uint32_t block, uint32_t groups) {
+constexpr uint32_t slot_inverse(uint32_t groups) { return 0xFFFFFFFFu / groups; }
+constexpr SlotGroup slot_group(uint32_t block, uint32_t groups, uint32_t inverse) {
   // Piece m of an endless row of eighths starts at m groups / 8, rounded down; XCD x has the pieces from x on, one a slot.
-  const uint32_t x = block & 7u, at = (block >> 3) + x * groups / 8u, piece = (8u * at + 7u) / groups;
+  const uint32_t x = block & 7u, at = (block >> 3) + x * groups / 8u, n = 8u * at + 7u;
+  // n / groups: the product with the inverse is that or one less (n below 2^30, the inverse short by less than 1)
+  uint32_t piece = uint32_t(uint64_t(n) * inverse >> 32);
+  if (n - piece * groups >= groups) piece += 1u;
   return {piece - x, at - piece / 8u * groups};
 }
 
