@@ -45,6 +45,8 @@ PAIRS = [
     ((300, 5, 1, 0, 0, 30), (64, 1, 1, 64, 1, 30)),           # uniform actions, then a bf16 policy
     ((1024, 6, 1, 64, 0, 26), (100, 4, 1, 64, 0, 26)),        # fp32 weights with 4 and more agents
     ((512, 10, 1, 64, 0, 26), (70, 8, 1, 64, 0, 26)),         # ... with layer 1 over two K slices
+    ((107000, 3, 1, 64, 0, 60), (1000, 3, 1, 64, 0, 128)),    # no room for the tickets of slots of time, then room
+    ((107000, 3, 1, 0, 0, 60), (1000, 3, 1, 0, 0, 128)),
 ]
 
 
