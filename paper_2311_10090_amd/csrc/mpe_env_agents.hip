@@ -543,7 +543,7 @@ hipError_t launch_agents(const TagArgs& A, hipStream_t s) {
     }
   }
   if (A.r.slots > 1) {
-    hipLaunchKernelGGL((rollout_agents_kernel<Scn, SlotGrid>), slots_grid(A.r, waves), dim3(128), 0, s, A, slot_groups(waves));
+    hipLaunchKernelGGL((rollout_agents_kernel<Scn, SlotGrid>), slots_grid(A.r, waves), dim3(128), 0, s, A, SlotGrid{waves});
     return hipGetLastError();
   }
   return launch_groups<128>(waves, [&](dim3 grid, const GridPiece& p) {

@@ -142,7 +142,7 @@ struct SliceBuf {
 // GENERAL: env counts that are no multiple of 64, or outputs whose time slices do not all start on 16 bytes: rows still
 // leave in 16-byte pieces (a slice starts on 8 bytes), the small outputs element by element.  (128 steps of 1,000 envs x 1 agent 70 -> 45 us, 1,000 x 2 104 -> 72 us, 32,760
 // x 3 206 -> 173 us against the one-wavefront kernel that such batches took before.)
-// SLOTS: a launch of several slots of time (mpe_slots.h); groups_per_xcd is then slot_inverse(groups).
+// SLOTS: a launch of several slots of time (mpe_slots.h).
 template <int N, bool GENERAL, bool PER_AGENT, bool SLOTS>
 __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutArgs A, uint32_t groups,
                                                                        uint32_t groups_per_xcd) {
@@ -154,7 +154,7 @@ __global__ __launch_bounds__(2 * kWave) void rollout_uniform_ws_kernel(RolloutAr
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   int k_slot = 0;
   uint32_t grp = (blockIdx.x & 7u) * groups_per_xcd + (blockIdx.x >> 3);
-  if (SLOTS ? !take_slot(A, SlotGrid{groups, groups_per_xcd}, k_slot, grp) : grp >= groups) return;  // whole block, before any barrier
+  if (SLOTS ? !take_slot(A, SlotGrid{groups}, k_slot, grp) : grp >= groups) return;  // whole block, before any barrier
   const size_t TE = A.TE;
   const size_t g0 = size_t(grp) * kWave;
   const TimeSlot slot = group_slot<SLOTS>(A, k_slot, A.ph.max_ep, g0, int(min(TE - g0, size_t(kWave))), lane);
@@ -384,7 +384,7 @@ struct EnvLaunch {
   template <bool SLOTS>
   static hipError_t rollout_slots(const RolloutArgs& A, hipStream_t s) {
     const uint32_t groups = (A.TE + kWave - 1) / kWave;
-    const uint32_t per_xcd = SLOTS ? slot_inverse(groups) : (groups + 7) / 8;
+    const uint32_t per_xcd = (groups + 7) / 8;
     const dim3 grid = SLOTS ? slots_grid(A, groups) : dim3(per_xcd * 8), block(2 * kWave);
     const bool mixed = A.ph.reward_mode == 1;
     if (ws_aligned<N>(A)) {

@@ -718,7 +718,7 @@ hipError_t launch_impl(const TagArgs& A, const void* packed, const void* critic,
     auto kern = rollout_gru_waves_kernel<Scn, AC, SlotGrid>;
     if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[1]); e != hipSuccess) return e;
     const uint32_t blocks = (envs + EB - 1) / EB;
-    launch(kern, spread_grid(blocks), SlotGrid{blocks, 0});
+    launch(kern, spread_grid(blocks), SlotGrid{blocks});
     return hipGetLastError();
   }
   auto kern = rollout_gru_waves_kernel<Scn, AC, GridPiece>;

@@ -79,10 +79,11 @@ struct RolloutArgs {
   uint32_t* fault = nullptr;
   // Polls after which a wait at a sync-group barrier gives up (kBarrierSpinLimit unless a test lowers it).
   uint32_t barrier_polls = 1u << 24;
-  // Blocks of which envs, from the first one on, have their episode counters alike: of this many, or a part of it (counter_unit); 0: any
-  uint32_t alike = 0;
   // Slots of time that run side by side, steps of one (mpe_slots.h).
   int32_t slots = 1, span = 0;
+  // Blocks of which envs, from the first one on, have their episode counters alike: of this many, or a part of it (counter_unit); 0: any.  For the
+  // host alone, and where the struct had padding: the kernels' arguments, and so their code, are as without it.
+  uint32_t alike = 0;
   uint32_t work() const { return TE * uint32_t(slots); }   // envs that the launch steps side by side
 };
 

@@ -1012,7 +1012,7 @@ hipError_t rollout_gru_blocks(const TagArgs& A, const PolicyBuffers& pb, const v
     auto kern = rollout_gru_kernel<Scn, EB, AC, SlotGrid>;
     if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[1]); e != hipSuccess) return e;
     const uint32_t groups = (A.r.TE + EB - 1) / EB;
-    return launch(kern, slots_grid(A.r, groups), 0u, groups, slot_groups(groups));
+    return launch(kern, slots_grid(A.r, groups), 0u, groups, SlotGrid{groups});
   }
   auto kern = rollout_gru_kernel<Scn, EB, AC, GruGrid>;
   if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[0]); e != hipSuccess) return e;

@@ -91,7 +91,7 @@ struct BatchKind {
 inline float small_step(const BatchKind& k, const RolloutArgs& A, uint32_t slots) {
   struct Line { float at[4], more; };                  // 1, 2, 3, 4 blocks per CU, each one more
   static constexpr Line few[7] = {{{0.09f, 0.10f, 0.10f, 0.10f}, 0.055f}, {{0.12f, 0.195f, 0.195f, 0.21f}, 0.075f}, {{0.12f, 0.20f, 0.27f, 0.31f}, 0.095f},
-                                  {{0.05f, 0.07f, 0.085f, 0.12f}, 0.030f}, {{0.065f, 0.10f, 0.155f, 0.23f}, 0.074f}, {{0.08f, 0.15f, 0.22f, 0.28f}, 0.079f},
+                                  {{0.05f, 0.07f, 0.085f, 0.12f}, 0.030f}, {{0.07f, 0.11f, 0.17f, 0.25f}, 0.08f}, {{0.09f, 0.17f, 0.25f, 0.32f}, 0.09f},
                                   {{0.05f, 0.07f, 0.09f, 0.09f}, 0.04f}};
   static constexpr float plain[7][2] = {{0.12f, 0.08f}, {0.17f, 0.09f}, {0.19f, 0.14f}, {0.18f, 0.17f}, {0.22f, 0.21f}, {0.25f, 0.25f}, {0.28f, 0.12f}};
   static constexpr float critic[7][2] = {{0.095f, 0.095f}, {0.12f, 0.12f}, {0.16f, 0.15f}, {0.15f, 0.15f}, {0.20f, 0.20f}, {0.22f, 0.22f}, {0.26f, 0.26f}};
@@ -115,6 +115,8 @@ inline float small_step(const BatchKind& k, const RolloutArgs& A, uint32_t slots
 // Steps of the first slot, the longest.
 inline int32_t longest_slot(const RolloutArgs& A) { return A.slots > 1 ? A.T - (A.slots - 1) * A.span : A.T; }
 
+inline bool equal_slots(const RolloutArgs& A) { return longest_slot(A) * 4 <= A.span * 5; }
+
 // In the slots of A.  The blocks of slot 0 stay for its steps beyond a span, spread over the CUs.
 inline float small_time(const BatchKind& k, const RolloutArgs& A) {
   if (A.slots <= 1) return small_step(k, A, 1) * float(A.T + 1);
@@ -126,14 +128,19 @@ inline float waves_time(int N, int W, int resident, const RolloutArgs& A) {
   auto step = [](uint32_t waves) { return waves == 0 ? 0.0f : (waves <= 4 ? 0.36f : (waves <= 8 ? 0.56f : 0.81f)); };
   const uint32_t runs = A.TE / A.E, eb = uint32_t(W) * (64u / uint32_t(N)), w = uint32_t(W);
   uint32_t cus = compute_units(), longs = runs * ((A.E + eb - 1) / eb), blocks = longs;
+  bool stacked = false;
   if (A.slots > 1) {                                   // those of XCD 0, which has the most (spread_group)
     auto share = [](uint32_t n) { return n / 32u * 4u + (n % 32u < 4u ? n % 32u : 4u); };
-    blocks = share(runs * ((A.E * uint32_t(A.slots) + eb - 1) / eb));
+    const uint32_t per_run = (A.E * uint32_t(A.slots) + eb - 1) / eb;
+    // Blocks that share a CU are 32 apart on their XCD.  With 2, 4, .. blocks to a run, of which the first is long, they all have the same place
+    // in their runs, until a second round mixes them (450 runs x 48 envs x 3 agents x 86 steps, critic, us, 883 in one slot, 962 in three).
+    stacked = runs > 1 && !equal_slots(A) && 32 % per_run == 0 && runs * per_run < 2 * cus * uint32_t(resident);
+    blocks = share(runs * per_run);
     longs = share(longs);
     cus = (cus + 7) / 8;
   }
   const uint32_t round = cus * uint32_t(resident), rest = blocks % round;
-  const float a = float(longest_slot(A)) + 1.5f, b = float(A.slots > 1 ? A.span : A.T) + 1.5f;
+  const float a = float(longest_slot(A)) + 1.5f, b = stacked ? a : float(A.slots > 1 ? A.span : A.T) + 1.5f;
   if (blocks <= round) return step(w * ((blocks + cus - 1) / cus)) * b + step(w * ((longs + cus - 1) / cus)) * (a - b);
   const float full = step(w * uint32_t(resident)), all = makespan(round, longs, a, blocks - longs, b) * full;
   if (rest == 0) return all;
@@ -162,7 +169,6 @@ inline float one_slot_time(const BatchKind& k, RolloutArgs A, uint32_t upto) {
   return k.N == 3 && !k.bf && !k.tag && A.TE == A.E ? fminf(time, waves) : time;
 }
 
-inline bool equal_slots(const RolloutArgs& A) { return longest_slot(A) * 4 <= A.span * 5; }
 inline bool slots_pay(const RolloutArgs& A, float several, float one) { return several < (equal_slots(A) ? 0.95f : 0.90f) * one; }
 
 }  // namespace

@@ -670,7 +670,7 @@ hipError_t launch_small_impl(const TagArgs& A, const void* packed, const void* c
   if (A.r.slots > 1) {
     auto kern = rollout_small_kernel<Scn, EB, AC, BF, REGW, MINW, SlotGrid>;
     if (hipError_t e = allow_lds(reinterpret_cast<const void*>(kern), M::TOTAL, lds_allowed[1]); e != hipSuccess) return e;
-    launch(kern, slots_grid(A.r, groups), slot_groups(groups));
+    launch(kern, slots_grid(A.r, groups), SlotGrid{groups});
     return hipGetLastError();
   }
   auto kern = rollout_small_kernel<Scn, EB, AC, BF, REGW, MINW, GridPiece>;

@@ -524,7 +524,7 @@ hipError_t launch_waves_impl(const TagArgs& A, const void* packed, const void* c
     hipLaunchKernelGGL(kern, grid, dim3(W * 64), B::LDS, s, A, static_cast<const uint8_t*>(packed), static_cast<const uint8_t*>(critic), piece);
   };
   if constexpr (SLOTS) {
-    launch(spread_grid(blocks), SlotGrid{blocks, 0});
+    launch(spread_grid(blocks), SlotGrid{blocks});
     return hipGetLastError();
   } else {
     return launch_groups<W * 64>(blocks, launch);
