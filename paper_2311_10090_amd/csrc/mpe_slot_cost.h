@@ -6,7 +6,7 @@
 // full rounds, has the ratios of that.  The small-batch kernel's step is a table by 16-env blocks per CU, the kernels of up to 3 agents
 // for full batches take 0.085 for every wavefront of 64 rows that their 64-env blocks put on a CU.  Measured on 4,542 batches (1 to 10
 // agents and every predator-prey shape, 64 to 65,536 envs, 16 to 1,024 runs, both types, with and without critic, 50 to 128 steps), slots where
-// this says so against one slot everywhere: 1.35 times as fast in the mean, 10 batches 2.5 to 6 % slower.  Slots wherever the size of
+// this says so against one slot everywhere: 1.35 times as fast in the mean, 14 batches 2.5 to 7 % slower.  Slots wherever the size of
 // the batch allows them: 397 slower, up to twice, above all where two or three slots of unequal length meet a chip that one slot fills.
 #pragma once
 
@@ -86,8 +86,7 @@ struct BatchKind {
   bool tag, bf, ac;
 };
 
-// A step of the small-batch kernel with `slots` of A's slots in flight.  (With a critic and 2 or 3 agents, 450 runs x 48 envs x 86 steps, us,
-// 883 in one slot, 962 in three of the wavefronts.)
+// A step of the small-batch kernel with `slots` of A's slots in flight.
 inline float small_step(const BatchKind& k, const RolloutArgs& A, uint32_t slots) {
   struct Line { float at[4], more; };                  // 1, 2, 3, 4 blocks per CU, each one more
   static constexpr Line few[7] = {{{0.09f, 0.10f, 0.10f, 0.10f}, 0.055f}, {{0.12f, 0.195f, 0.195f, 0.21f}, 0.075f}, {{0.12f, 0.20f, 0.27f, 0.31f}, 0.095f},
